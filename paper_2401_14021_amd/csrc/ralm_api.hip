@@ -124,7 +124,7 @@ ralm_status make_plan(int64_t Q, const ralm_datastore_t *ds, int32_t k, int32_t 
     pl.off_flags = off;  off += FLAG_BLOCK_BYTES;   // always first: the counters of the last call (FLAG_*)
     pl.off_q = off;      off += up256((size_t)pl.Qpad * pl.dpad * 2);
     pl.off_tau = off;    off += up256((size_t)pl.Qpad * 8);
-    pl.off_cnt = off;    off += up256((size_t)pl.Qpad * 4);
+    pl.off_cnt = off;    off += up256((size_t)pl.Qpad * CNT_PITCH * 4);
     pl.off_lost = off;   off += up256((size_t)pl.Qpad * 4);   // directly behind cnt: cleared together
     pl.off_fb = off;     off += up256((size_t)pl.Qpad * 4);
     pl.off_cand = off;   off += up256((size_t)Q * pl.cap * 8);
@@ -338,7 +338,7 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
     const float u = mma_dt == RALM_F16 ? 1.f / 2048.f : 1.f / 256.f;   // 11 / 8 significant bits
     cert.u_query = u;
     cert.u_rows = (scan == ds->exact && scan_dt == ds->exact_dtype && scan_dt != RALM_F32) ? 0.f : u;
-    RALM_HIP(launch_rescore(cand, cnt, pl.cap, pl.k_prime, queries, Q, ds->exact, ds->exact_dtype, exact_ld, ds->d,
+    RALM_HIP(launch_rescore(cand, cnt, CNT_PITCH, pl.cap, pl.k_prime, queries, Q, ds->exact, ds->exact_dtype, exact_ld, ds->d,
                             ds->metric, k, out_ids, out_scores, out_margin, cert, stream));
     RALM_HIP(launch_exact_pass(queries, Q, ds->exact, ds->exact_dtype, exact_ld, ds->N, ds->d, ds->metric, k, fb_list,
                                flags, tau, cand, cnt, pl.cap, out_ids, out_scores, n_cu, stream));
@@ -686,7 +686,7 @@ ralm_status ralm_cache_lookup_topk(const int32_t *cache_ids, const int32_t *cach
     const int64_t ld = ds->exact_stride ? ds->exact_stride : ds->d;
     CertifyParams no_check;
     memset(&no_check, 0, sizeof(no_check));
-    RALM_HIP(launch_rescore(keys, cnt, (uint32_t)C, C, queries, Qt, ds->exact, ds->exact_dtype, ld, ds->d, ds->metric,
+    RALM_HIP(launch_rescore(keys, cnt, 1, (uint32_t)C, C, queries, Qt, ds->exact, ds->exact_dtype, ld, ds->d, ds->metric,
                             k, out_ids, out_scores, nullptr, no_check, stream));
     return RALM_OK;
 }

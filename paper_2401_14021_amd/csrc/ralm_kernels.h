@@ -11,6 +11,14 @@ typedef unsigned long long u64;
 constexpr int SCAN_BM = 256;       // datastore rows per tile of the stage ladder (a workgroup takes one, or half of one)
 constexpr int SCAN_BK = 64;        // reduction elements staged per pipeline step
 constexpr int SCAN_QPAD = 256;     // query matrix is zero-padded to a multiple of this
+// 32-bit words from one query's list length to the next: a 128-byte line each.  Every admitted score
+// moves its query's length by one atomic add, and adds to one line are served one after the
+// other (about 3 ns each, wherever they come from); packed lengths put 32 queries on a line, so a
+// stage that admits many scores was bound by a handful of lines and not by the scan: 100M-style keys,
+// 64 queries, k' = 512, the stage that admits 16.5 K scores per query: 3013 us packed, 895 us padded;
+// 256 queries, k' = 2048, 248 tiles that admit 524 K scores: 264 us -> 133 us; 81 queries over 1M x
+// 768, the stage behind the first: 72 us -> 43 us.
+constexpr int CNT_PITCH = 32;
 
 struct ScanParams {
     const void *X;          // scan copy [N, ldx]
@@ -23,7 +31,7 @@ struct ScanParams {
     int32_t Q;
     const u64 *tau;         // [Q] admission keys (0 = admit everything)
     u64 *cand;              // [Q, cap]
-    uint32_t *cnt;          // [Q]
+    uint32_t *cnt;          // [Q] list lengths, CNT_PITCH words apart
     uint32_t cap;
     int64_t n_row_tiles;    // tiles visited in this stage
     int64_t tile_stride;    // visited tile t is datastore tile (tile_begin + m(t)) * tile_stride, where m(t) = t
@@ -70,7 +78,7 @@ enum {
 struct CertifyParams {
     int32_t *flags;        // flag block
     const uint32_t *lost;  // [Q] != 0: the query's list lost entries during the scan
-    uint32_t *cnt_rw;      // [Q] list lengths, reset for queued queries
+    uint32_t *cnt_rw;      // [Q] list lengths (CNT_PITCH), reset for queued queries
     u64 *tau_exact;        // [Q] out: exact rank-k key of the queued query
     int32_t *fb_list;      // [Q] out: queued queries
     float u_query, u_rows; // unit roundoff applied by the scan to the query / to the rows (0: not rounded)
@@ -86,7 +94,7 @@ hipError_t launch_select(u64 *cand, uint32_t *cnt, uint32_t cap, int32_t k_prime
 
 // per query: exact scores of the (at most k') rows left in its list, final ranking, top k out;
 // with cert.flags: the result is checked and queries that fail are queued for launch_exact_pass
-hipError_t launch_rescore(const u64 *cand, const uint32_t *cnt, uint32_t cap, int32_t k_prime,
+hipError_t launch_rescore(const u64 *cand, const uint32_t *cnt, int cnt_pitch, uint32_t cap, int32_t k_prime,
                           const float *queries, int64_t Q, const void *exact, int32_t exact_dtype, int64_t ld,
                           int32_t d, int32_t metric, int32_t k, int32_t *out_ids, float *out_scores,
                           float *out_margin, const CertifyParams &cert, hipStream_t stream);

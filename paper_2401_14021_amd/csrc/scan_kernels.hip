@@ -139,7 +139,7 @@ __device__ __forceinline__ void select_epilogue_direct(const ScanParams &p, f32x
                     if (g < n_rows && make_key(acc[i][j][v], g) >= tkey) pass |= 1u << v;
                 }
                 if (pass) {
-                    uint32_t at = atomicAdd(p.cnt + q, (uint32_t)__popc(pass));
+                    uint32_t at = atomicAdd(p.cnt + (int64_t)q * CNT_PITCH, (uint32_t)__popc(pass));
                     u64 *dst = p.cand + (int64_t)q * p.cap;
 #pragma unroll
                     for (int v = 0; v < 16; ++v) {
@@ -167,7 +167,7 @@ struct PushList {
 
 __device__ __forceinline__ void push_global(const ScanParams &p, int q, u64 key)
 {
-    const uint32_t at = atomicAdd(p.cnt + q, 1u);
+    const uint32_t at = atomicAdd(p.cnt + (int64_t)q * CNT_PITCH, 1u);
     if (at < p.cap) p.cand[(int64_t)q * p.cap + at] = key;
 }
 
@@ -492,7 +492,7 @@ __global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams 
     if constexpr (ALL) {
         // every list ends up with one entry per row of the launch (all of its tiles are full: host check)
         if (blockIdx.x == 0)
-            for (int q = tid; q < p.Q; q += NT) p.cnt[q] = (uint32_t)n_tiles * BM;
+            for (int q = tid; q < p.Q; q += NT) p.cnt[(int64_t)q * CNT_PITCH] = (uint32_t)n_tiles * BM;
     }
     if (n_mine == 0) return;
     const unsigned char *Xb = static_cast<const unsigned char *>(p.X);

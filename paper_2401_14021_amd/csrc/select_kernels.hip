@@ -116,7 +116,7 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(u64 *__restrict__ c
 
     const int64_t q = blockIdx.x;
     const int tid = threadIdx.x;
-    uint32_t n = cnt[q];
+    uint32_t n = cnt[q * CNT_PITCH];
     u64 *c = cand + q * (int64_t)cap;
     // entries the scan sent to this list in the stage that just ended, plus the (at most k') kept before
     if (tid == 0 && stage >= 0 && stage < MAX_STAGE_SUMS) {
@@ -135,7 +135,7 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(u64 *__restrict__ c
     if (n < (uint32_t)k_prime) {    // fewer than k' candidates exist so far: keep admitting everything
         if (tid == 0) {
             tau[q] = 0ull;
-            cnt[q] = n;
+            cnt[q * CNT_PITCH] = n;
         }
         return;
     }
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(u64 *__restrict__ c
     for (int i = tid; i < k_prime; i += SEL_THREADS) c[i] = t[i];
     if (tid == 0) {
         tau[q] = kth;
-        cnt[q] = (uint32_t)k_prime;
+        cnt[q * CNT_PITCH] = (uint32_t)k_prime;
     }
 }
 
@@ -209,7 +209,7 @@ constexpr int RS_THREADS = 1024, RS_WAVES = RS_THREADS / 64;
 // compared.
 template <int EX, bool L2>
 __global__ __launch_bounds__(RS_THREADS) void rescore_kernel(const u64 *__restrict__ cand,
-                                                      const uint32_t *__restrict__ cnt, uint32_t cap,
+                                                      const uint32_t *__restrict__ cnt, int cnt_pitch, uint32_t cap,
                                                       int k_prime, int kp2, const float *__restrict__ queries,
                                                       const void *__restrict__ exact, int64_t ld, int d,
                                                       int k, int32_t *__restrict__ out_ids,
@@ -223,7 +223,7 @@ __global__ __launch_bounds__(RS_THREADS) void rescore_kernel(const u64 *__restri
 
     const int64_t q = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint32_t n_raw = cnt[q];
+    const uint32_t n_raw = cnt[q * cnt_pitch];
     const int n = (int)(n_raw < (uint32_t)k_prime ? n_raw : (uint32_t)k_prime);
     const u64 *mine = cand + q * (int64_t)cap;
     const float *qv = queries + q * (int64_t)d;
@@ -341,7 +341,7 @@ __global__ __launch_bounds__(RS_THREADS) void rescore_kernel(const u64 *__restri
                 const int at = atomicAdd(cert.flags + FLAG_FALLBACKS, 1);
                 cert.fb_list[at] = (int32_t)q;
                 cert.tau_exact[q] = keys[k - 1];
-                cert.cnt_rw[q] = 0u;
+                cert.cnt_rw[q * cnt_pitch] = 0u;
             }
         }
     }
@@ -415,7 +415,7 @@ __global__ __launch_bounds__(XS_THREADS) void exact_scan_kernel(const float *__r
                         const u64 key = make_key(sc, (int32_t)row);
                         if (key >= s_tau[qi]) {
                             const int32_t q = s_q[qi];
-                            const uint32_t at = atomicAdd(cnt + q, 1u);
+                            const uint32_t at = atomicAdd(cnt + (int64_t)q * CNT_PITCH, 1u);
                             if (at < cap) cand[(int64_t)q * cap + at] = key;
                         }
                     }
@@ -541,7 +541,7 @@ __global__ __launch_bounds__(XM_NW * 64) void exact_scan_mfma_kernel(const float
                     const int64_t rw = blk * 16 + 4 * v + kq;
                     const float sc = (float)acc[v];
                     if (rw < N && sc >= my_tsc) {
-                        const uint32_t at = atomicAdd(cnt + my_q, 1u);
+                        const uint32_t at = atomicAdd(cnt + my_q * CNT_PITCH, 1u);
                         if (at < cap) cand[my_q * cap + at] = make_key(sc, (int32_t)rw);
                     }
                 }
@@ -579,7 +579,7 @@ __global__ __launch_bounds__(SEL_THREADS) void exact_finish_kernel(const u64 *__
     const int tid = threadIdx.x;
     for (int i = blockIdx.x; i < F; i += gridDim.x) {
         const int64_t q = fb_list[i];
-        const uint32_t n = cnt[q];
+        const uint32_t n = cnt[q * CNT_PITCH];
         const u64 *c = cand + q * (int64_t)cap;
         __syncthreads();
         if (n > cap || n < (uint32_t)k) {
@@ -637,7 +637,7 @@ hipError_t launch_select(u64 *cand, uint32_t *cnt, uint32_t cap, int32_t k_prime
     return hipGetLastError();
 }
 
-hipError_t launch_rescore(const u64 *cand, const uint32_t *cnt, uint32_t cap, int32_t k_prime, const float *queries,
+hipError_t launch_rescore(const u64 *cand, const uint32_t *cnt, int cnt_pitch, uint32_t cap, int32_t k_prime, const float *queries,
                           int64_t Q, const void *exact, int32_t exact_dtype, int64_t ld, int32_t d, int32_t metric,
                           int32_t k, int32_t *out_ids, float *out_scores, float *out_margin,
                           const CertifyParams &cert, hipStream_t stream)
@@ -648,7 +648,7 @@ hipError_t launch_rescore(const u64 *cand, const uint32_t *cnt, uint32_t cap, in
     const size_t smem = (size_t)kp2 * sizeof(u64);
 #define RALM_RS(EXV, L2V)                                                                                    \
     hipLaunchKernelGGL((rescore_kernel<EXV, L2V>), dim3((unsigned)Q), dim3(RS_THREADS), smem, stream, cand, cnt, \
-                       cap, k_prime, kp2, queries, exact, ld, d, k, out_ids, out_scores, out_margin, cert)
+                       cnt_pitch, cap, k_prime, kp2, queries, exact, ld, d, k, out_ids, out_scores, out_margin, cert)
     if (exact_dtype == DT_F16) {
         if (metric == METRIC_L2) RALM_RS(DT_F16, true);
         else RALM_RS(DT_F16, false);
