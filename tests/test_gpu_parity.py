@@ -476,6 +476,24 @@ def test_cache_insert_matches_oracle(B, oracle, C, R, k, p, n_next, smax):
             assert len(set(got[0][r, :got[1][r]].tolist())) == got[1][r]
 
 
+@pytest.mark.parametrize("C", [1, 2, 63, 64, 65, 127, 128, 129, 700])
+def test_cache_insert_evicts_and_reinserts_inside_a_batch(B, oracle, C):
+    """Candidates from a range hardly larger than the cache, more of them than it has slots: entries
+    are evicted, asked for again and re-inserted within the 64 candidates that the kernel takes at a
+    time and across them; rings that become full on the way, with the pointer anywhere; duplicate
+    entries to begin with."""
+    rng = np.random.default_rng(C)
+    R, k, N = 24, 16, C + 12
+    off = (np.arange(R + 1) * 20).astype(np.int64)
+    truth = rng.integers(0, N, size=(R * 20, k)).astype(np.int32)
+    lens = np.array([max(0, C - d) for d in rng.integers(0, 5, size=R)], dtype=np.int32)
+    heads = rng.integers(0, C, size=R).astype(np.int32)
+    cache = rng.integers(0, N, size=(R, C)).astype(np.int32)     # with repeats
+    for n_next in (0, 3):
+        got, want = _insert_both(B, oracle, cache, lens, heads, truth, off, N, k, n_next, None)
+        _same_cache(got, want)
+
+
 def test_speculation_loop_closed_by_cache_insert(B, oracle):
     """Alg. 1 as a loop on the GPU entry points: speculate from the cache, verify with a batched
     retrieval, find the first mismatch, insert the verified results (top-5 update); the queries
