@@ -16,6 +16,7 @@
 #include <hip/hip_runtime.h>
 #include <atomic>
 #include <mutex>
+#include <vector>
 #include <stdarg.h>
 #include <stdio.h>
 #include <string.h>
@@ -59,12 +60,13 @@ struct Plan {
     int n_stages;
     int64_t stride[40];   // tile stride of each stage, first = coarsest, last = 1
     // workspace offsets
-    size_t off_q, off_tau, off_cnt, off_lost, off_fb, off_flags, off_cand, off_sel, total;
+    size_t off_q, off_tau, off_cnt, off_lost, off_fb, off_flags, off_cand, total;
 };
 
 // columns of a scan-copy row: the squared-distance metric keeps the row's squared norm behind it
 // one workgroup per request (or per four): keeps every launch below 2^32 work-items
 constexpr int64_t MAX_REQUESTS = 1 << 22;
+constexpr int64_t MAX_QUERIES = 1 << 20;   // of one retrieval call
 
 int32_t scan_cols(const ralm_datastore_t *ds) { return ds->d + (ds->metric == RALM_METRIC_L2 ? L2_EXTRA_COLS : 0); }
 
@@ -121,14 +123,14 @@ ralm_status make_plan(int64_t Q, const ralm_datastore_t *ds, int32_t k, int32_t 
     for (int i = 0; i < n; ++i) pl.stride[i] = rev[n - 1 - i];
 
     size_t off = 0;
-    pl.off_flags = off;  off += FLAG_BLOCK_BYTES;   // always first: the counters of the last call (FLAG_*)
+    // always first: the counters of the last call, per-query status and list lengths behind them
+    pl.off_flags = off;  off += stage_offset(Q, MAX_STAGE_SUMS);
     pl.off_q = off;      off += up256((size_t)pl.Qpad * pl.dpad * 2);
     pl.off_tau = off;    off += up256((size_t)pl.Qpad * 8);
     pl.off_cnt = off;    off += up256((size_t)pl.Qpad * CNT_PITCH * 4);
     pl.off_lost = off;   off += up256((size_t)pl.Qpad * 4);   // directly behind cnt: cleared together
     pl.off_fb = off;     off += up256((size_t)pl.Qpad * 4);
     pl.off_cand = off;   off += up256((size_t)Q * pl.cap * 8);
-    pl.off_sel = off;    off += up256((size_t)Q * k_prime * 8);   // scratch of the select kernel
     pl.total = off;
     return RALM_OK;
 }
@@ -222,7 +224,7 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
                           size_t workspace_bytes, void *stream_, bool sequential)
 {
     if (!queries || !out_ids || !out_scores) return fail(RALM_ERR_NULL, "queries/out_ids/out_scores is NULL");
-    if (Q < 1 || Q > (1 << 20)) return fail(RALM_ERR_SHAPE, "Q=%lld out of [1, 2^20]", (long long)Q);
+    if (Q < 1 || Q > MAX_QUERIES) return fail(RALM_ERR_SHAPE, "Q=%lld out of [1, 2^20]", (long long)Q);
     ralm_status st = check_datastore(ds, true);
     if (st != RALM_OK) return st;
     if (!aligned16(queries)) return fail(RALM_ERR_ALIGN, "queries must be 16-byte aligned");
@@ -247,7 +249,6 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
     int32_t *fb_list = reinterpret_cast<int32_t *>(ws + pl.off_fb);
     int32_t *flags = reinterpret_cast<int32_t *>(ws + pl.off_flags);
     u64 *cand = reinterpret_cast<u64 *>(ws + pl.off_cand);
-    u64 *sel = reinterpret_cast<u64 *>(ws + pl.off_sel);
 
     const void *scan = ds->scan ? ds->scan : ds->exact;
     const int scan_dt = ds->scan ? ds->scan_dtype : ds->exact_dtype;
@@ -271,7 +272,8 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
     sp.lists_empty = 0;
     // one stage: scan the tiles sp describes, then cut every list down to its k' best
     int32_t stage_no = 0;
-    auto run_stage = [&]() -> ralm_status {
+    // (the last stage's lists are cut down by the re-score)
+    auto run_stage = [&](int64_t expected, bool last) -> ralm_status {
         if (sp.n_row_tiles <= 0) return RALM_OK;
         const bool prof = g_prof_on && g_prof_n < MAX_PROF;
         if (prof) {
@@ -287,7 +289,8 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
             RALM_HIP(hipEventRecord(g_prof_ev[g_prof_n][1], stream));
             ++g_prof_n;
         }
-        RALM_HIP(launch_select(cand, cnt, pl.cap, pl.k_prime, Q, tau, sel, lost, flags, stage_no++, stream));
+        if (last) return RALM_OK;
+        RALM_HIP(launch_select(cand, cnt, pl.cap, pl.k_prime, Q, tau, lost, flags, stage_no++, expected, stream));
         return RALM_OK;
     };
 
@@ -300,7 +303,7 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
         for (int64_t t0 = 0; t0 < tiles; t0 += block) {
             sp.tile_begin = t0;
             sp.n_row_tiles = tiles - t0 < block ? tiles - t0 : block;
-            st = run_stage();
+            st = run_stage(pl.cap, t0 + block >= tiles);
             if (st != RALM_OK) return st;
         }
     } else {
@@ -308,6 +311,7 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
         for (int s = 0; s < pl.n_stages; ++s) {
             const int64_t stride = pl.stride[s];
             sp.tile_stride = stride;
+            int64_t expected = pl.cap;                              // keys per list when the stage ends
             if (s == 0) {
                 sp.tile_skip = 0;                                   // every multiple of the stride
                 sp.n_row_tiles = (tiles + stride - 1) / stride;
@@ -320,8 +324,9 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
                 sp.n_row_tiles = m_max - m_max / g;
                 sp.park_pushes = 1;
                 sp.lists_empty = 0;
+                expected = pl.k_prime * g;
             }
-            st = run_stage();
+            st = run_stage(expected, s + 1 == pl.n_stages);
             if (st != RALM_OK) return st;
         }
     }
@@ -332,6 +337,7 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
     CertifyParams cert;
     cert.flags = flags;
     cert.lost = lost;
+    cert.stage = stage_no;
     cert.cnt_rw = cnt;
     cert.tau_exact = tau;
     cert.fb_list = fb_list;
@@ -381,14 +387,21 @@ ralm_status ralm_workspace_stage_entries(const void *workspace, void *stream_, i
 {
     if (!workspace || !n_stages || !entries) return fail(RALM_ERR_NULL, "workspace/n_stages/entries is NULL");
     hipStream_t stream = static_cast<hipStream_t>(stream_);
-    unsigned char block[FLAG_BLOCK_BYTES];
+    int32_t words[8];
     RALM_HIP(hipStreamSynchronize(stream));
-    RALM_HIP(hipMemcpy(block, workspace, sizeof(block), hipMemcpyDeviceToHost));
-    int32_t n = reinterpret_cast<const int32_t *>(block)[FLAG_STAGES];
-    n = n < 0 ? 0 : (n > MAX_STAGE_SUMS ? MAX_STAGE_SUMS : n);
+    RALM_HIP(hipMemcpy(words, workspace, sizeof(words), hipMemcpyDeviceToHost));
+    int32_t n = words[FLAG_STAGES];
+    const int64_t Q = words[FLAG_QUERIES];
+    n = n < 0 || Q < 1 || Q > MAX_QUERIES ? 0 : (n > MAX_STAGE_SUMS ? MAX_STAGE_SUMS : n);
     *n_stages = n;
-    const unsigned long long *sums = reinterpret_cast<const unsigned long long *>(block + STAGE_SUMS_BYTE);
-    for (int i = 0; i < RALM_MAX_LADDER_STAGES; ++i) entries[i] = i < n ? (int64_t)sums[i] : 0;
+    std::vector<uint32_t> lengths(n ? Q : 0);
+    for (int i = 0; i < RALM_MAX_LADDER_STAGES; ++i) {
+        entries[i] = 0;
+        if (i >= n) continue;
+        RALM_HIP(hipMemcpy(lengths.data(), static_cast<const unsigned char *>(workspace) + stage_offset(Q, i), (size_t)Q * 4,
+                           hipMemcpyDeviceToHost));
+        for (uint32_t v : lengths) entries[i] += v;
+    }
     return RALM_OK;
 }
 
@@ -401,8 +414,16 @@ ralm_status ralm_workspace_counters(const void *workspace, void *stream_, ralm_c
     RALM_HIP(hipMemcpy(words, workspace, sizeof(words), hipMemcpyDeviceToHost));
     out->unanswered = words[FLAG_UNANSWERED];
     out->ladder_overflows = words[FLAG_LADDER_OVERFLOWS];
-    out->hard_certified = words[FLAG_HARD_CERTIFIED];
-    out->soft_certified = words[FLAG_SOFT_CERTIFIED];
+    out->hard_certified = out->soft_certified = 0;
+    const int64_t Q = words[FLAG_QUERIES];
+    std::vector<uint32_t> status(Q < 1 || Q > MAX_QUERIES ? 0 : Q);
+    if (!status.empty())
+        RALM_HIP(hipMemcpy(status.data(), static_cast<const unsigned char *>(workspace) + status_offset(), status.size() * 4,
+                           hipMemcpyDeviceToHost));
+    for (uint32_t v : status) {
+        out->soft_certified += v & STATUS_SOFT ? 1 : 0;
+        out->hard_certified += v & STATUS_HARD ? 1 : 0;
+    }
     out->exact_pass = words[FLAG_FALLBACKS];
     return RALM_OK;
 }

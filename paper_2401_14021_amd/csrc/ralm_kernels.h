@@ -50,7 +50,7 @@ hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t strea
 hipError_t launch_fill_u64(u64 *p, u64 v, int64_t n, hipStream_t stream);
 
 // fp32 [Q, d] -> scan dtype [Qpad, dpad], zero padded
-// also clears the n0 words at z0 and the n1 words at z1
+// also clears the n0 words at z0 (the flag block, but for its number of queries) and the n1 words at z1
 hipError_t launch_query_prep(const float *q, int64_t Q, int32_t d, uint16_t *out, int64_t Qpad,
                              int32_t dpad, int32_t scan_dtype, int32_t metric, uint32_t *z0, int64_t n0,
                              uint32_t *z1, int64_t n1, hipStream_t stream);
@@ -60,24 +60,33 @@ hipError_t launch_l2_scan_copy(const void *src, int32_t src_dtype, int64_t src_l
 hipError_t launch_convert_rows(const float *src, int64_t src_ld, void *dst, int32_t dst_dtype,
                                int64_t dst_ld, int64_t N, int32_t d, hipStream_t stream);
 
-// A retrieval call's flag block (first FLAG_BLOCK_BYTES of its workspace): 32-bit words FLAG_*,
-// counts of queries; from byte STAGE_SUMS_BYTE on, one 64-bit sum per ladder stage (entries that
-// the lists held when the stage ended, over all queries).
-constexpr int FLAG_BLOCK_BYTES = 1024, STAGE_SUMS_BYTE = 256, MAX_STAGE_SUMS = 40;
+// A retrieval call's workspace begins with its flag block (FLAG_BLOCK_BYTES: 32-bit words FLAG_*), one status
+// word per query (STATUS_*, padded to a multiple of SCAN_QPAD queries) and, stage by stage of the ladder, the
+// length of every query's list when the stage ended.  They are per query, and summed by the calls that report them,
+// because one counter for all queries costs 15 ns per query and launch: adds to one address are
+// served one after the other (2341 queries: 35 us per select, 70 us per re-score).
+constexpr int FLAG_BLOCK_BYTES = 1024, MAX_STAGE_SUMS = 40;
+constexpr uint32_t STATUS_SOFT = 1, STATUS_HARD = 2;   // of a query's status word: the check's verdicts
+__host__ __device__ inline int64_t padded_queries(int64_t Q) { return (Q + SCAN_QPAD - 1) / SCAN_QPAD * SCAN_QPAD; }
+__host__ __device__ inline size_t status_offset() { return FLAG_BLOCK_BYTES; }   // bytes from the flag block
+__host__ __device__ inline size_t stage_offset(int64_t Q, int stage)
+{
+    return FLAG_BLOCK_BYTES + (size_t)padded_queries(Q) * 4 * (1 + stage);
+}
 enum {
     FLAG_UNANSWERED = 0,        // answered with id -1 / score NaN
     FLAG_LADDER_OVERFLOWS = 1,  // candidate list lost entries during the scan (answered by the exact pass)
-    FLAG_HARD_CERTIFIED = 2,    // margin above the deterministic rounding bound
-    FLAG_SOFT_CERTIFIED = 3,    // margin above 8x the rounding spread seen on the candidates (includes the above)
-    FLAG_FALLBACKS = 4,         // answered by the exact pass
-    FLAG_STAGES = 5             // stages of the ladder whose sums were recorded
+    FLAG_FALLBACKS = 2,         // answered by the exact pass
+    FLAG_STAGES = 3,            // stages of the ladder whose list lengths were recorded
+    FLAG_QUERIES = 4            // queries of the call
 };
 
 // What the re-score needs to check its own result and to queue a query for the exact pass; all
 // pointers NULL: no check (flags == NULL decides).
 struct CertifyParams {
     int32_t *flags;        // flag block
-    const uint32_t *lost;  // [Q] != 0: the query's list lost entries during the scan
+    uint32_t *lost;        // [Q] != 0: the query's list lost entries during the scan
+    int32_t stage;         // of the ladder's last stage
     uint32_t *cnt_rw;      // [Q] list lengths (CNT_PITCH), reset for queued queries
     u64 *tau_exact;        // [Q] out: exact rank-k key of the queued query
     int32_t *fb_list;      // [Q] out: queued queries
@@ -85,15 +94,19 @@ struct CertifyParams {
 };
 
 // per query: k'-th best key of cand[q, 0..cnt[q]) -> tau[q]; the list is then cut down, in place,
-// to its k' best keys (cnt[q] <- min(cnt[q], k')).  tmp is scratch of [Q, k'] keys.  A list
+// to its k' best keys (cnt[q] <- min(cnt[q], k')).  A list
 // that was sent more than cap keys holds the first cap of them: lost[q] is set and the query
 // counted once in flags[FLAG_LADDER_OVERFLOWS].
-// stage >= 0: the lists' lengths before the cut are added to the stage's sum in the flag block.
+// The lists' lengths before the cut are recorded behind the flag block if stage < MAX_STAGE_SUMS.
+// expected: keys that a list should hold (any number is handled).
 hipError_t launch_select(u64 *cand, uint32_t *cnt, uint32_t cap, int32_t k_prime, int64_t Q, u64 *tau,
-                         u64 *tmp, uint32_t *lost, int32_t *flags, int32_t stage, hipStream_t stream);
+                         uint32_t *lost, int32_t *flags, int32_t stage, int64_t expected,
+                         hipStream_t stream);
 
-// per query: exact scores of the (at most k') rows left in its list, final ranking, top k out;
+// per query: exact scores of the k' best rows of its list, final ranking, top k out;
 // with cert.flags: the result is checked and queries that fail are queued for launch_exact_pass
+// with cert.flags, cand are the lists as the ladder's last stage left them: more than k' keys are
+// cut down to the k' best first and the stage's lengths recorded, as by launch_select
 hipError_t launch_rescore(const u64 *cand, const uint32_t *cnt, int cnt_pitch, uint32_t cap, int32_t k_prime,
                           const float *queries, int64_t Q, const void *exact, int32_t exact_dtype, int64_t ld,
                           int32_t d, int32_t metric, int32_t k, int32_t *out_ids, float *out_scores,

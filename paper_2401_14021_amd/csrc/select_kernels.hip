@@ -1,8 +1,7 @@
 // Per-query selection and exact re-scoring (gfx950).
 //
-//  select_kernel   exact k'-th best of a query's candidate keys by an 8-bit radix descent
-//                  over the 64-bit ranking key; writes it as the admission key for the next
-//                  scan stage and cuts the list down to its k' best keys in place.
+//  select_kernel   exact k'-th best of a query's candidate keys; writes it as the admission key
+//                  for the next scan stage and cuts the list down to its k' best keys in place.
 //  rescore_kernel  for the k' rows kept by the scan: inner product with the fp32 query from
 //                  the EXACT datastore copy, products and sum in double, one rounding to
 //                  fp32; final ranking (score descending, id ascending); first k written.
@@ -25,21 +24,22 @@ namespace ralm {
 
 namespace {
 
-constexpr int SEL_THREADS = 1024;
+constexpr int SEL_THREADS = 1024;   // of the workgroups that rank a list (lists known to be short take fewer)
 
 // Exact rank-th best (1-based) key of c[0, n), n >= rank >= 1, by a radix descent over the 64-bit
 // ranking key, 8 bits per pass from the top.  A pass histograms the digit of the keys that match
 // the prefix found so far; wave 0 walks the 256 bins from the best digit down to the one that
 // holds the wanted key.  As soon as that bin holds a single key the descent stops and one more
 // pass over the list fetches that key (scores are mostly distinct, so this usually happens
-// before the id bits are reached).  Called by all SEL_THREADS threads of a workgroup; keys must
-// be distinct.
+// before the id bits are reached).  Called by all NT threads of a workgroup; keys must be
+// distinct.
 struct RadixShared {
     uint32_t hist[256];
     uint32_t digit, remaining, bin;
     u64 kth;
 };
 
+template <int NT>
 __device__ u64 radix_kth(const u64 *__restrict__ c, uint32_t n, uint32_t rank, RadixShared &sh)
 {
     const int tid = threadIdx.x, lane = tid & 63;
@@ -49,7 +49,7 @@ __device__ u64 radix_kth(const u64 *__restrict__ c, uint32_t n, uint32_t rank, R
     for (int shift = 56; shift >= 0; shift -= 8) {
         if (tid < 256) sh.hist[tid] = 0;
         __syncthreads();
-        for (uint32_t i = tid; i < n; i += SEL_THREADS) {
+        for (uint32_t i = tid; i < n; i += NT) {
             const u64 key = c[i];
             if ((key & mask) == prefix) atomicAdd(&sh.hist[(uint32_t)(key >> shift) & 255u], 1u);
         }
@@ -90,7 +90,7 @@ __device__ u64 radix_kth(const u64 *__restrict__ c, uint32_t n, uint32_t rank, R
     }
     u64 kth = prefix;
     if (single) {   // the only key under the prefix is the wanted one
-        for (uint32_t i = tid; i < n; i += SEL_THREADS) {
+        for (uint32_t i = tid; i < n; i += NT) {
             const u64 key = c[i];
             if ((key & mask) == prefix) sh.kth = key;
         }
@@ -101,37 +101,204 @@ __device__ u64 radix_kth(const u64 *__restrict__ c, uint32_t n, uint32_t rank, R
     return kth;
 }
 
+// ---- the best `rank` keys of a list -----------------------------------------------------------
+// The digits of a radix descent are a poor histogram for scores: the top byte of a float is its
+// sign and most of its exponent, so thousands of keys fall into two or three bins and their LDS
+// atomics queue on one address.  Here the bins divide the range of the list's scores evenly (the map
+// from score to bin is monotone, so it never reorders keys), which spreads the bulk and leaves a
+// handful of keys in the bin that holds the wanted one; those are ranked by counting.  Lists of up
+// to SEL_REGS keys per thread are read once and stay in registers.  What bounds it now is that one
+// read and the barriers.  15872 keys, one list per workgroup: 81 lists 23 -> 10 us, 1024
+// lists 65 -> 38 us, 2341 lists 227 -> 113 us.  A range that is not positive and finite, or a bin with more keys
+// than SEL_BIN_KEYS (many equal or nearly equal scores), takes the radix descent.
+constexpr int SEL_REGS = 16, SEL_BIN_KEYS = 1024;
+
+template <int NT>
+struct SelectShared {
+    union {
+        uint32_t hist[2 * NT];
+        RadixShared radix;
+    };
+    u64 bin_keys[SEL_BIN_KEYS];
+    uint32_t lo[NT / 64], hi[NT / 64], total[NT / 64];
+    uint32_t bin, rest, in_bin, n_bin, n_out;
+    u64 kth;
+};
+
+// Exact rank-th best key of c[0, n), n >= rank >= 1, and the keys that reach it (exactly `rank`:
+// keys are distinct) in out[0, rank), in any order.  All NT threads of a workgroup; out is in
+// LDS and complete when the function returns; c is not read after that.
+template <int NT>
+__device__ __forceinline__ u64 select_best(const u64 *__restrict__ c, uint32_t n, uint32_t rank, SelectShared<NT> &sh, u64 *out)
+{
+    constexpr int SEL_BINS = 2 * NT, SEL_WAVES = NT / 64;
+    // a short list (a stage that refines by 2 leaves about 2 k' keys): every key's rank by counting
+    constexpr uint32_t SHORT = 256;
+    if (n <= SHORT) {
+        for (uint32_t i = threadIdx.x; i < n; i += NT) sh.bin_keys[i] = c[i];
+        __syncthreads();
+        for (uint32_t i = threadIdx.x; i < n; i += NT) {
+            const u64 mine = sh.bin_keys[i];
+            uint32_t better = 0;
+            for (uint32_t j = 0; j < n; ++j) better += sh.bin_keys[j] > mine ? 1u : 0u;
+            if (better < rank) out[better] = mine;
+        }
+        __syncthreads();
+        return out[rank - 1];
+    }
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool in_regs = n <= (uint32_t)(SEL_REGS * NT);
+    u64 reg[SEL_REGS];
+    if (in_regs) {
+#pragma unroll
+        for (int i = 0; i < SEL_REGS; ++i) {
+            const uint32_t at = (uint32_t)(i * NT + tid);
+            reg[i] = at < n ? c[at] : 0ull;    // 0 is no key: scores of any value have non-zero keys
+        }
+    }
+    // f(key) for every key of the list and for zeros in between; every thread takes part in each step
+    auto each = [&](auto f) __attribute__((always_inline)) {
+        if (in_regs) {
+#pragma unroll
+            for (int i = 0; i < SEL_REGS; ++i)
+                if ((uint32_t)(i * NT) < n) f(reg[i]);
+        } else {
+            for (uint32_t i = 0; i < n; i += NT) f(i + tid < n ? c[i + tid] : 0ull);
+        }
+    };
+
+    // range of the score bits
+    uint32_t lo = 0xffffffffu, hi = 0u;
+    each([&](u64 key) {
+        const uint32_t b = (uint32_t)(key >> 32);
+        lo = key && b < lo ? b : lo;
+        hi = key && b > hi ? b : hi;
+    });
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const uint32_t l2 = __shfl_xor(lo, o, 64), h2 = __shfl_xor(hi, o, 64);
+        lo = l2 < lo ? l2 : lo;
+        hi = h2 > hi ? h2 : hi;
+    }
+    if (lane == 0) {
+        sh.lo[wave] = lo;
+        sh.hi[wave] = hi;
+    }
+    for (int i = tid; i < SEL_BINS; i += NT) sh.hist[i] = 0;
+    if (tid == 0) sh.n_bin = sh.n_out = 0;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < SEL_WAVES; ++w) {
+        lo = sh.lo[w] < lo ? sh.lo[w] : lo;
+        hi = sh.hi[w] > hi ? sh.hi[w] : hi;
+    }
+    const float s_lo = bits_score(lo), range = bits_score(hi) - s_lo, scale = (float)SEL_BINS / range;
+    // (NaN compares false; scale may overflow for a range of denormals)
+    bool even = range > 0.f && range < __builtin_inff() && scale < __builtin_inff();
+    auto bin_of = [&](u64 key) __attribute__((always_inline)) {
+        const uint32_t b = (uint32_t)((bits_score((uint32_t)(key >> 32)) - s_lo) * scale);
+        return b < (uint32_t)SEL_BINS ? b : (uint32_t)SEL_BINS - 1u;
+    };
+    if (even) {
+        each([&](u64 key) {
+            if (key) atomicAdd(&sh.hist[bin_of(key)], 1u);
+        });
+        __syncthreads();
+        // thread t owns bins SEL_BINS-1-2t and SEL_BINS-2-2t, best first
+        const uint32_t h0 = sh.hist[SEL_BINS - 1 - 2 * tid], h1 = sh.hist[SEL_BINS - 2 - 2 * tid];
+        uint32_t incl = h0 + h1;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += y;
+        }
+        if (lane == 63) sh.total[wave] = incl;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < SEL_WAVES; ++w) incl += w < wave ? sh.total[w] : 0u;
+        uint32_t better = incl - h0 - h1;     // keys in better bins than this thread's
+        if (better < rank && rank <= incl) {
+            const bool first = rank <= better + h0;
+            sh.bin = (uint32_t)(SEL_BINS - 1 - 2 * tid - (first ? 0 : 1));
+            sh.rest = rank - better - (first ? 0u : h0);
+            sh.in_bin = first ? h0 : h1;
+        }
+        __syncthreads();
+        even = sh.in_bin <= (uint32_t)SEL_BIN_KEYS;
+    }
+    u64 kth;
+    if (even) {
+        const uint32_t bin = sh.bin, in_bin = sh.in_bin, rest = sh.rest;
+        each([&](u64 key) {
+            if (key && bin_of(key) == bin) sh.bin_keys[atomicAdd(&sh.n_bin, 1u)] = key;
+        });
+        __syncthreads();
+        for (uint32_t i = tid; i < in_bin; i += NT) {
+            const u64 mine = sh.bin_keys[i];
+            uint32_t better = 0;
+            for (uint32_t j = 0; j < in_bin; ++j) better += sh.bin_keys[j] > mine ? 1u : 0u;
+            if (better == rest - 1) sh.kth = mine;
+        }
+        __syncthreads();
+        kth = sh.kth;
+    } else {
+        __syncthreads();
+        kth = radix_kth<NT>(c, n, rank, sh.radix);
+    }
+    each([&](u64 key) {
+        const bool keep = key >= kth;         // kth is a key, so zeros never pass
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(keep);
+        if (m) {                              // wave-uniform: one atomic per wave step
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(&sh.n_out, (uint32_t)__popcll(m));
+            at = __builtin_amdgcn_readfirstlane(at) +
+                 __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            if (keep && at < rank) out[at] = key;
+        }
+    });
+    __syncthreads();
+    return kth;
+}
+
+// What select_kernel and the re-score do with a query's list before they read it: the length that the
+// stage left is recorded, and a list that was sent more keys than it has slots, of which it kept the first
+// `cap`, is marked.  Returns the number of keys in the list.
+__device__ uint32_t list_length(uint32_t n, int64_t q, uint32_t cap, uint32_t *__restrict__ lost, int32_t *__restrict__ flags,
+                                int stage)
+{
+    if (threadIdx.x == 0) {
+        // entries the scan sent to this list in the stage that just ended, plus the (at most k') kept before
+        if (stage < MAX_STAGE_SUMS) {
+            reinterpret_cast<uint32_t *>(reinterpret_cast<unsigned char *>(flags) + stage_offset(gridDim.x, stage))[q] = n;
+            if (q == 0) flags[FLAG_STAGES] = stage + 1;
+        }
+        if (n > cap) {
+            if (lost[q] == 0) atomicAdd(flags + FLAG_LADDER_OVERFLOWS, 1);
+            lost[q] = 1;
+        }
+    }
+    return n < cap ? n : cap;
+}
+
 // Per query: the k'-th best key of its list becomes the admission key of the next scan stage
 // and the list is cut down to its k' best keys in place.  A list that was sent more keys than
 // it has slots kept only the first `cap` of them: it is processed as it is (its k'-th best key
 // is still a valid lower bound, the rows behind those keys were all scanned) and the query is
 // marked in `lost`, so that it is answered by the exact pass at the end of the call.
-__global__ __launch_bounds__(SEL_THREADS) void select_kernel(u64 *__restrict__ cand, uint32_t *__restrict__ cnt,
+template <int NT>
+__global__ __launch_bounds__(NT) void select_kernel(u64 *__restrict__ cand, uint32_t *__restrict__ cnt,
                                                              uint32_t cap, int k_prime, u64 *__restrict__ tau,
-                                                             u64 *__restrict__ tmp, uint32_t *__restrict__ lost,
-                                                             int32_t *__restrict__ flags, int stage)
+                                                             uint32_t *__restrict__ lost, int32_t *__restrict__ flags,
+                                                             int stage)
 {
-    __shared__ RadixShared sh;
-    __shared__ uint32_t s_out;
+    extern __shared__ __align__(16) unsigned char smem[];
+    u64 *out = reinterpret_cast<u64 *>(smem);   // [k_prime]
+    __shared__ SelectShared<NT> sh;
 
     const int64_t q = blockIdx.x;
     const int tid = threadIdx.x;
-    uint32_t n = cnt[q * CNT_PITCH];
     u64 *c = cand + q * (int64_t)cap;
-    // entries the scan sent to this list in the stage that just ended, plus the (at most k') kept before
-    if (tid == 0 && stage >= 0 && stage < MAX_STAGE_SUMS) {
-        unsigned long long *sums = reinterpret_cast<unsigned long long *>(reinterpret_cast<unsigned char *>(flags) + STAGE_SUMS_BYTE);
-        atomicAdd(sums + stage, (unsigned long long)n);
-        if (q == 0) flags[FLAG_STAGES] = stage + 1;
-    }
-
-    if (n > cap) {
-        n = cap;
-        if (tid == 0) {
-            if (lost[q] == 0) atomicAdd(flags + FLAG_LADDER_OVERFLOWS, 1);
-            lost[q] = 1;
-        }
-    }
+    const uint32_t n = list_length(cnt[q * CNT_PITCH], q, cap, lost, flags, stage);
     if (n < (uint32_t)k_prime) {    // fewer than k' candidates exist so far: keep admitting everything
         if (tid == 0) {
             tau[q] = 0ull;
@@ -139,23 +306,8 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(u64 *__restrict__ c
         }
         return;
     }
-
-    const u64 kth = radix_kth(c, n, (uint32_t)k_prime, sh);
-    // keys are distinct: exactly k' of them are >= kth
-
-    // cut the list down to those k' keys, in place (via tmp)
-    if (tid == 0) s_out = 0;
-    __syncthreads();
-    u64 *t = tmp + q * (int64_t)k_prime;
-    for (uint32_t i = tid; i < n; i += SEL_THREADS) {
-        const u64 key = c[i];
-        if (key >= kth) {
-            const uint32_t at = atomicAdd(&s_out, 1u);
-            if (at < (uint32_t)k_prime) t[at] = key;
-        }
-    }
-    __syncthreads();
-    for (int i = tid; i < k_prime; i += SEL_THREADS) c[i] = t[i];
+    const u64 kth = select_best<NT>(c, n, (uint32_t)k_prime, sh, out);
+    for (int i = tid; i < k_prime; i += NT) c[i] = out[i];
     if (tid == 0) {
         tau[q] = kth;
         cnt[q * CNT_PITCH] = (uint32_t)k_prime;
@@ -201,13 +353,19 @@ __device__ __forceinline__ float4 exact_load4(const void *__restrict__ exact, in
     }
 }
 
-constexpr int RS_THREADS = 1024, RS_WAVES = RS_THREADS / 64;
+constexpr int RS_ROWS = 4;             // rows that a wave scores together: their loads are in flight at once
+constexpr int RS_COUNT_MAX = 256;      // up to this many candidates are ranked by counting
 
 // Re-score of the candidates, final ranking, and the check of the result (see CertifyParams).
 // EX: DT_F32 or DT_F16 exact rows.  L2: the score is minus the squared distance; the scan's
 // score of a row is then 2<q, x> - |x|^2, so |q|^2 is subtracted from it wherever the two are
 // compared.
-template <int EX, bool L2>
+// What bounds it: the gather of Q k' rows for large batches, and for few queries the latency of
+// one wave's rows, which is why a wave takes RS_ROWS of them at a time (k' = 64: each of the 16
+// waves has its four rows in flight at once) and why the list is cut down here and not by a launch of
+// its own.  With the last select (a launch of its own before): Q = 1, k' = 64: 26 -> 14 us;
+// Q = 1024: 103 -> 50 us; Q = 256, k' = 2048, 1024 fp16 elements: 563 -> 326 us.
+template <int EX, bool L2, int RS_THREADS>
 __global__ __launch_bounds__(RS_THREADS) void rescore_kernel(const u64 *__restrict__ cand,
                                                       const uint32_t *__restrict__ cnt, int cnt_pitch, uint32_t cap,
                                                       int k_prime, int kp2, const float *__restrict__ queries,
@@ -216,15 +374,17 @@ __global__ __launch_bounds__(RS_THREADS) void rescore_kernel(const u64 *__restri
                                                       float *__restrict__ out_scores,
                                                       float *__restrict__ out_margin, const CertifyParams cert)
 {
+    constexpr int RS_WAVES = RS_THREADS / 64;
     extern __shared__ __align__(16) unsigned char smem[];
-    u64 *keys = reinterpret_cast<u64 *>(smem);   // [kp2]
+    u64 *keys = reinterpret_cast<u64 *>(smem);   // [kp2] exact keys
+    u64 *list = keys + kp2;                      // [k_prime] the candidates' scan keys
+    __shared__ SelectShared<RS_THREADS> sel;
     __shared__ u64 s_min_scan[RS_WAVES];
     __shared__ double s_e2[RS_WAVES], s_x2[RS_WAVES], s_q2[RS_WAVES];
+    __shared__ uint32_t s_rank[RS_COUNT_MAX];
 
     const int64_t q = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint32_t n_raw = cnt[q * cnt_pitch];
-    const int n = (int)(n_raw < (uint32_t)k_prime ? n_raw : (uint32_t)k_prime);
     const u64 *mine = cand + q * (int64_t)cap;
     const float *qv = queries + q * (int64_t)d;
     const bool stats = out_margin || cert.flags;   // wave-uniform
@@ -236,6 +396,16 @@ __global__ __launch_bounds__(RS_THREADS) void rescore_kernel(const u64 *__restri
         q2 = wave_sum(q2);
         if (lane == 0) s_q2[wave] = q2;
     }
+    if (tid < RS_COUNT_MAX) s_rank[tid] = 0;
+    uint32_t n_list = cnt[q * cnt_pitch];
+    n_list = cert.flags ? list_length(n_list, q, cap, cert.lost, cert.flags, cert.stage) : (n_list < cap ? n_list : cap);
+    int n = (int)n_list;
+    if (n > k_prime) {
+        n = k_prime;
+        select_best<RS_THREADS>(mine, n_list, (uint32_t)k_prime, sel, list);
+    } else {
+        for (int i = tid; i < n; i += RS_THREADS) list[i] = mine[i];
+    }
     __syncthreads();
     if (stats) {
         q2 = 0.0;
@@ -245,58 +415,92 @@ __global__ __launch_bounds__(RS_THREADS) void rescore_kernel(const u64 *__restri
 
     u64 min_scan = ~0ull;
     double e2 = 0.0, x2max = 0.0;   // sum of squared scan errors, largest squared row norm (lane 0)
-    for (int c = wave; c < n; c += RS_WAVES) {
-        const u64 skey = mine[c];
-        min_scan = skey < min_scan ? skey : min_scan;
-        const int32_t id = key_id(skey);
-        const int64_t row_off = (int64_t)id * ld;
-        double sum = 0.0, x2 = 0.0;
+    for (int c0 = wave; c0 < n; c0 += RS_WAVES * RS_ROWS) {
+        int64_t row_off[RS_ROWS];
+        double sum[RS_ROWS], x2[RS_ROWS];
+#pragma unroll
+        for (int u = 0; u < RS_ROWS; ++u) {
+            const int c = c0 + u * RS_WAVES;
+            row_off[u] = (int64_t)key_id(list[c < n ? c : c0]) * ld;   // past the end: the first row again
+            sum[u] = x2[u] = 0.0;
+        }
         for (int j = lane * 4; j < d; j += 256) {
-            const float4 x = exact_load4<EX>(exact, row_off, j);
+            float4 x[RS_ROWS];
+#pragma unroll
+            for (int u = 0; u < RS_ROWS; ++u) x[u] = exact_load4<EX>(exact, row_off[u], j);
             const float4 y = *reinterpret_cast<const float4 *>(qv + j);
-            exact_accum4<L2>(sum, x, y);
-            if (stats)
-                x2 += (double)x.x * (double)x.x + (double)x.y * (double)x.y + (double)x.z * (double)x.z +
-                      (double)x.w * (double)x.w;
+#pragma unroll
+            for (int u = 0; u < RS_ROWS; ++u) {
+                exact_accum4<L2>(sum[u], x[u], y);
+                if (stats)
+                    x2[u] += (double)x[u].x * (double)x[u].x + (double)x[u].y * (double)x[u].y +
+                             (double)x[u].z * (double)x[u].z + (double)x[u].w * (double)x[u].w;
+            }
         }
-        sum = wave_sum(sum);
-        const float score = L2 ? (float)(-sum) : (float)sum;
-        if (stats) {
-            x2 = wave_sum(x2);
-            const double e = (double)(key_score(skey) - q_sq) - (double)score;
-            e2 += e * e;
-            x2max = x2 > x2max ? x2 : x2max;
+#pragma unroll
+        for (int u = 0; u < RS_ROWS; ++u) {
+            const int c = c0 + u * RS_WAVES;
+            if (c < n) {   // wave-uniform
+                const u64 skey = list[c];
+                min_scan = skey < min_scan ? skey : min_scan;
+                const double t = wave_sum(sum[u]);
+                const float score = L2 ? (float)(-t) : (float)t;
+                if (stats) {
+                    const double r2 = wave_sum(x2[u]);
+                    const double e = (double)(key_score(skey) - q_sq) - (double)score;
+                    e2 += e * e;
+                    x2max = r2 > x2max ? r2 : x2max;
+                }
+                if (lane == 0) keys[c] = make_key(score, key_id(skey));
+            }
         }
-        if (lane == 0) keys[c] = make_key(score, id);
     }
-    for (int c = n + tid; c < kp2; c += RS_THREADS) keys[c] = 0ull;
     if (lane == 0) {
         s_min_scan[wave] = min_scan;
         s_e2[wave] = e2;
         s_x2[wave] = x2max;
     }
-    __syncthreads();
 
-    // bitonic sort, descending by key
-    for (int size = 2; size <= kp2; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int t = tid; t < kp2 / 2; t += RS_THREADS) {
-                const int lo = 2 * t - (t & (stride - 1));
-                const int hi = lo + stride;
-                const bool desc = (lo & size) == 0;
-                const u64 a = keys[lo], b = keys[hi];
-                if ((a < b) == desc) {
-                    keys[lo] = b;
-                    keys[hi] = a;
-                }
-            }
-            __syncthreads();
+    const u64 *ranked;   // descending by key
+    if (kp2 <= RS_COUNT_MAX) {
+        // every candidate counts the better ones, RS_THREADS / kp2 threads share the counting (equal keys,
+        // a cached id listed twice, keep their order)
+        __syncthreads();
+        const int i = tid & (kp2 - 1), part = tid / kp2, parts = RS_THREADS / kp2;
+        if (i < n) {
+            const u64 key = keys[i];
+            uint32_t better = 0;
+            for (int j = part; j < n; j += parts) better += keys[j] > key || (keys[j] == key && j < i) ? 1u : 0u;
+            if (better) atomicAdd(&s_rank[i], better);
         }
+        __syncthreads();
+        if (tid < n) list[s_rank[tid]] = keys[tid];
+        __syncthreads();
+        ranked = list;
+    } else {
+        for (int c = n + tid; c < kp2; c += RS_THREADS) keys[c] = 0ull;
+        __syncthreads();
+        for (int size = 2; size <= kp2; size <<= 1) {   // bitonic
+            for (int stride = size >> 1; stride > 0; stride >>= 1) {
+                for (int t = tid; t < kp2 / 2; t += RS_THREADS) {
+                    const int lo = 2 * t - (t & (stride - 1));
+                    const int hi = lo + stride;
+                    const bool desc = (lo & size) == 0;
+                    const u64 a = keys[lo], b = keys[hi];
+                    if ((a < b) == desc) {
+                        keys[lo] = b;
+                        keys[hi] = a;
+                    }
+                }
+                __syncthreads();
+            }
+        }
+        ranked = keys;
     }
 
     for (int r = tid; r < k; r += RS_THREADS) {
-        const u64 key = keys[r];
         const bool have = r < n;
+        const u64 key = have ? ranked[r] : 0ull;
         out_ids[q * k + r] = have ? key_id(key) : -1;
         out_scores[q * k + r] = have ? key_score(key) : -__builtin_inff();
     }
@@ -317,7 +521,7 @@ __global__ __launch_bounds__(RS_THREADS) void rescore_kernel(const u64 *__restri
         else if (n < k_prime)
             margin = __builtin_inff();   // every row of the datastore was re-scored
         else
-            margin = key_score(keys[k - 1]) - (key_score(ms) - q_sq);
+            margin = key_score(ranked[k - 1]) - (key_score(ms) - q_sq);
         if (out_margin) out_margin[q] = margin;
         if (cert.flags) {
             // what the scan's rounding can do to a score: the deterministic bound (every rounding
@@ -332,15 +536,14 @@ __global__ __launch_bounds__(RS_THREADS) void rescore_kernel(const u64 *__restri
             const bool all_rows = n < k_prime && !truncated;
             const double m = (double)margin;
             const bool soft_ok = all_rows || (!truncated && n >= k && (m > soft || (soft == 0.0 && m >= 0.0)));
-            if (soft_ok) {
-                atomicAdd(cert.flags + FLAG_SOFT_CERTIFIED, 1);
-                if (all_rows || m > hard) atomicAdd(cert.flags + FLAG_HARD_CERTIFIED, 1);
-            } else if (n >= k) {
+            uint32_t *status = reinterpret_cast<uint32_t *>(reinterpret_cast<unsigned char *>(cert.flags) + status_offset());
+            status[q] = soft_ok ? (all_rows || m > hard ? STATUS_SOFT | STATUS_HARD : STATUS_SOFT) : 0u;
+            if (!soft_ok && n >= k) {
                 // answered again by the exact pass: every row whose exact key reaches the exact
                 // rank-k key found here (a lower bound of the true one) is collected in the list
                 const int at = atomicAdd(cert.flags + FLAG_FALLBACKS, 1);
                 cert.fb_list[at] = (int32_t)q;
-                cert.tau_exact[q] = keys[k - 1];
+                cert.tau_exact[q] = ranked[k - 1];
                 cert.cnt_rw[q * cnt_pitch] = 0u;
             }
         }
@@ -592,7 +795,7 @@ __global__ __launch_bounds__(SEL_THREADS) void exact_finish_kernel(const u64 *__
             if (tid == 0) atomicAdd(flags + FLAG_UNANSWERED, 1);
             continue;
         }
-        const u64 kth = radix_kth(c, n, (uint32_t)k, sh);
+        const u64 kth = radix_kth<SEL_THREADS>(c, n, (uint32_t)k, sh);
         if (tid == 0) s_out = 0;
         for (int r = tid; r < kp2; r += SEL_THREADS) keys[r] = 0ull;
         __syncthreads();
@@ -628,12 +831,19 @@ __global__ __launch_bounds__(SEL_THREADS) void exact_finish_kernel(const u64 *__
 
 }  // namespace
 
-hipError_t launch_select(u64 *cand, uint32_t *cnt, uint32_t cap, int32_t k_prime, int64_t Q, u64 *tau, u64 *tmp,
-                         uint32_t *lost, int32_t *flags, int32_t stage, hipStream_t stream)
+hipError_t launch_select(u64 *cand, uint32_t *cnt, uint32_t cap, int32_t k_prime, int64_t Q, u64 *tau,
+                         uint32_t *lost, int32_t *flags, int32_t stage, int64_t expected, hipStream_t stream)
 {
     if (Q <= 0) return hipSuccess;
-    hipLaunchKernelGGL(select_kernel, dim3((unsigned)Q), dim3(SEL_THREADS), 0, stream, cand, cnt, cap, k_prime, tau, tmp,
-                       lost, flags, stage);
+    const size_t smem = (size_t)k_prime * sizeof(u64);
+    // lists that should be short are ranked by small workgroups, eight to a CU instead of two: 2341 lists of
+    // about 128 keys 11 us instead of 20 (any length is right in either)
+    if (expected <= 512)
+        hipLaunchKernelGGL(select_kernel<256>, dim3((unsigned)Q), dim3(256), smem, stream, cand, cnt, cap, k_prime, tau, lost,
+                           flags, stage);
+    else
+        hipLaunchKernelGGL(select_kernel<SEL_THREADS>, dim3((unsigned)Q), dim3(SEL_THREADS), smem, stream, cand, cnt, cap,
+                           k_prime, tau, lost, flags, stage);
     return hipGetLastError();
 }
 
@@ -645,10 +855,28 @@ hipError_t launch_rescore(const u64 *cand, const uint32_t *cnt, int cnt_pitch, u
     if (Q <= 0) return hipSuccess;
     int kp2 = 2;
     while (kp2 < k_prime) kp2 <<= 1;
-    const size_t smem = (size_t)kp2 * sizeof(u64);
-#define RALM_RS(EXV, L2V)                                                                                    \
-    hipLaunchKernelGGL((rescore_kernel<EXV, L2V>), dim3((unsigned)Q), dim3(RS_THREADS), smem, stream, cand, cnt, \
-                       cnt_pitch, cap, k_prime, kp2, queries, exact, ld, d, k, out_ids, out_scores, out_margin, cert)
+    const size_t smem = (size_t)(kp2 + k_prime) * sizeof(u64);
+#define RALM_RS_NT(EXV, L2V, NTV)                                                                              \
+    do {                                                                                                     \
+        auto kern = rescore_kernel<EXV, L2V, NTV>;                                                           \
+        static std::atomic<bool> attr_done{false};                                                           \
+        if (!attr_done.load(std::memory_order_acquire)) {                                                    \
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),                         \
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);       \
+            if (e != hipSuccess) return e;                                                                   \
+            attr_done.store(true, std::memory_order_release);                                                \
+        }                                                                                                    \
+        hipLaunchKernelGGL(kern, dim3((unsigned)Q), dim3(NTV), smem, stream, cand, cnt, \
+                       cnt_pitch, cap, k_prime, kp2, queries, exact, ld, d, k, out_ids, out_scores, out_margin, cert);                     \
+    } while (0)
+    // With more queries than two large workgroups per CU hold, small ones (eight per CU) overlap one query's
+    // chain of list, rows and ranking with the others' gathers: 1024 queries, k' = 64: 50 us instead of 91,
+    // 2341: 96 instead of 200.  Fewer queries, or many candidates each, need the large workgroup's waves.
+#define RALM_RS(EXV, L2V)                                  \
+    do {                                                   \
+        if (Q >= 512 && k_prime <= RS_COUNT_MAX) RALM_RS_NT(EXV, L2V, 256); \
+        else RALM_RS_NT(EXV, L2V, SEL_THREADS);            \
+    } while (0)
     if (exact_dtype == DT_F16) {
         if (metric == METRIC_L2) RALM_RS(DT_F16, true);
         else RALM_RS(DT_F16, false);
@@ -657,6 +885,7 @@ hipError_t launch_rescore(const u64 *cand, const uint32_t *cnt, int cnt_pitch, u
         else RALM_RS(DT_F32, false);
     }
 #undef RALM_RS
+#undef RALM_RS_NT
     return hipGetLastError();
 }
 

@@ -787,6 +787,24 @@ def test_k_and_k_prime_boundaries(B, oracle, k, k_prime, N):
     assert np.array_equal(ids, wi) and np.array_equal(sc, wsc)
 
 
+@pytest.mark.parametrize("Q", [3, 600])
+@pytest.mark.parametrize("k,k_prime", [(20, 64), (100, 256), (600, 1000), (40, 257)])
+@pytest.mark.parametrize("values", ["few", "outlier", "spread"])
+def test_list_selection_branches(B, oracle, Q, k, k_prime, values):
+    """Lists of every length that the selection treats differently (short ones, ones that fit the
+    registers, longer ones), in both sizes of its workgroups; scores that take a handful of values
+    (bins with thousands of keys) or span so wide a range that all but one fall into one bin."""
+    g = torch.Generator().manual_seed(Q + k)
+    N, d = 42000, 16
+    hi = 3 if values == "few" else 9
+    X = torch.randint(0, hi, (N, d), generator=g).float()
+    Qm = torch.randint(0, hi, (Q, d), generator=g).float()
+    if values == "outlier":
+        X[777] = 2.0 ** 40
+    ids, sc, wi, wsc, _ = _retrieve_both(B, oracle, X, Qm, k, k_prime=k_prime)
+    assert np.array_equal(ids, wi) and np.array_equal(sc, wsc)
+
+
 @pytest.mark.parametrize("d,Q", [(8, 3), (2048, 5), (2048, 70), (4096, 33), (16384, 2)])
 def test_extreme_row_lengths(B, oracle, d, Q):
     """The shortest and the longest rows the library accepts (cache lookup: up to d = 2048)."""
