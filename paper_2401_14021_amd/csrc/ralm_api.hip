@@ -299,10 +299,10 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
         const int64_t block = ((int64_t)pl.cap - pl.k_prime) / SCAN_BM;   // >= 1: cap >= 16384, k' <= 4096
         sp.tile_stride = 1;
         sp.tile_skip = 0;
-        sp.park_pushes = 0;
         for (int64_t t0 = 0; t0 < tiles; t0 += block) {
             sp.tile_begin = t0;
             sp.n_row_tiles = tiles - t0 < block ? tiles - t0 : block;
+            sp.admits = sp.n_row_tiles * SCAN_BM;                    // at worst
             st = run_stage(pl.cap, t0 + block >= tiles);
             if (st != RALM_OK) return st;
         }
@@ -315,14 +315,14 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
             if (s == 0) {
                 sp.tile_skip = 0;                                   // every multiple of the stride
                 sp.n_row_tiles = (tiles + stride - 1) / stride;
-                sp.park_pushes = 0;                                 // admits everything
+                sp.admits = sp.n_row_tiles * SCAN_BM;               // everything
                 sp.lists_empty = 1;
             } else {
                 const int64_t m_max = (tiles + stride - 1) / stride - 1;   // multiples m >= 1 with m*stride < tiles
                 const int64_t g = pl.stride[s - 1] / stride;        // ... that no earlier stage visited
                 sp.tile_skip = (int32_t)g;
                 sp.n_row_tiles = m_max - m_max / g;
-                sp.park_pushes = 1;
+                sp.admits = pl.k_prime * (g - 1);
                 sp.lists_empty = 0;
                 expected = pl.k_prime * g;
             }
@@ -493,7 +493,7 @@ ralm_status ralm_retrieve_topk(const float *queries, int64_t Q, const float *dat
     // by the matrix cores, which the
     // pipelined bf16 kernel feeds far better: they get a bf16 copy (one read, one write, redone on
     // every call: the rows may have changed), kept between calls; if the device has no room for
-    // it the rows are scanned as they are by the staged kernel.  Same result either way.
+    // it the rows are scanned as they are.  Same result either way.
     if (Q > 768 && simple_reserve(&g_simple_scan, &g_simple_scan_bytes, (size_t)N * d * 2) &&
         launch_convert_rows(datastore, d, g_simple_scan, RALM_BF16, d, N, d, nullptr) == hipSuccess) {
         ds.scan = g_simple_scan;

@@ -37,9 +37,9 @@ struct ScanParams {
     int64_t tile_stride;    // visited tile t is datastore tile (tile_begin + m(t)) * tile_stride, where m(t) = t
     int32_t tile_skip;      // if tile_skip == 0, else the t-th positive integer that is no multiple of tile_skip
     int64_t tile_begin;
-    int32_t park_pushes;    // 1: thresholds are selective, collect admitted scores in LDS first
-    int32_t lists_empty;    // 1 (with park_pushes == 0): every list is empty and every score of this launch is
-                            // kept, so list positions follow from the row's place in the launch (no atomics)
+    int64_t admits;         // scores that the thresholds are expected to admit per query (any number is handled)
+    int32_t lists_empty;    // 1: every list is empty and every score of this launch is kept, so list positions
+                            // follow from the row's place in the launch (no atomics)
 };
 
 // query tile width chosen for Q

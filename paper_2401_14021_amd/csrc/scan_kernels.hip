@@ -13,19 +13,14 @@
 // every accumulator register of a lane belongs to ONE query (column = lane % 32) and the lane
 // can hold that query's threshold in a register.
 //
-// Two kernels share that tiling and the epilogue:
-//   scan_dma_kernel     bf16 / fp16 datastore copies, and fp32 rows as they are (rounded to
-//                       bf16 between the operand read and the multiply).  Strips go from global memory straight
-//                       into LDS (global_load_lds_dwordx4, no VGPR staging) through a ring of
-//                       S stages that runs ahead of the multiply and keeps running across tile
-//                       boundaries; the 16-byte chunks of a row are XOR-swizzled on the way in
-//                       (by choosing which global chunk each lane fetches) so that the MFMA
-//                       operand reads (32 rows, same chunk) are free of bank conflicts.
-//   scan_staged_kernel  global -> registers -> LDS, double buffered: launches that keep every
-//                       score: the first, small stage of a ladder with a partial last tile,
-//                       and the blocks of the sequential ladder.  Otherwise
-//                       the first stage runs in scan_dma_kernel<.., ALL>, which writes each
-//                       score to the list slot that its row's place in the launch determines.
+// scan_dma_kernel takes bf16 / fp16 datastore copies, and fp32 rows as they are (rounded to bf16
+// between the operand read and the multiply).  Strips go from global memory straight into LDS
+// (global_load_lds_dwordx4, no VGPR staging) through a ring of S stages that runs ahead of the
+// multiply and keeps running across tile boundaries; the 16-byte chunks of a row are XOR-swizzled
+// on the way in (by choosing which global chunk each lane fetches) so that the MFMA operand reads
+// (32 rows, same chunk) are free of bank conflicts.  What happens to a tile's scores depends on
+// how many of them a launch keeps (KEEP_*): thresholds that admit a few per tile, thresholds that
+// admit hundreds or more, or every score into empty lists.
 //
 // Work items (row tile, query tile) are dealt to a persistent grid so that workgroups that
 // run at the same time on one XCD (workgroup b lands on XCD b % 8) hold consecutive items:
@@ -42,44 +37,6 @@ namespace ralm {
 
 namespace {
 
-template <int IN>
-struct RawChunk {
-    uint4 v;
-};
-template <>
-struct RawChunk<DT_F32> {
-    float4 lo, hi;
-};
-
-template <int IN>
-__device__ __forceinline__ void load_chunk(RawChunk<IN> &r, const void *X, int64_t elem_off, bool ok)
-{
-    if constexpr (IN == DT_F32) {
-        if (ok) {
-            const float4 *p = reinterpret_cast<const float4 *>(static_cast<const float *>(X) + elem_off);
-            r.lo = p[0];
-            r.hi = p[1];
-        } else {
-            r.lo = make_float4(0.f, 0.f, 0.f, 0.f);
-            r.hi = r.lo;
-        }
-    } else {
-        if (ok)
-            r.v = *reinterpret_cast<const uint4 *>(static_cast<const uint16_t *>(X) + elem_off);
-        else
-            r.v = make_uint4(0u, 0u, 0u, 0u);
-    }
-}
-
-template <int IN>
-__device__ __forceinline__ uint4 chunk_bits(const RawChunk<IN> &r)
-{
-    if constexpr (IN == DT_F32)
-        return pack8<DT_BF16>(r.lo, r.hi);
-    else
-        return r.v;
-}
-
 template <bool F16>
 __device__ __forceinline__ f32x16 mfma32(const uint4 &a, const uint4 &b, const f32x16 &c)
 {
@@ -92,6 +49,7 @@ __device__ __forceinline__ f32x16 mfma32(const uint4 &a, const uint4 &b, const f
 }
 
 #define RALM_LDS __attribute__((address_space(3)))
+#define RALM_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
 
 // datastore tile of the t-th tile a launch visits (see ScanParams)
 __device__ __forceinline__ int64_t visited_tile(const ScanParams &p, int64_t t)
@@ -110,54 +68,11 @@ __device__ __forceinline__ int64_t visited_tile(const ScanParams &p, int64_t t)
 // against query  q0 + (wn*TN + j)*32 + lane%32.  A score is admitted (appended to its query's
 // candidate list) iff its ranking key is >= the query's admission key.
 
-// Direct epilogue (staged kernel): admitted scores go straight to the global candidate lists,
-// one atomic per lane and 32x32 block.
-template <int WM, int WN, int TM, int TN>
-__device__ __forceinline__ void select_epilogue_direct(const ScanParams &p, f32x16 (&acc)[TM][TN], int32_t row0,
-                                                       int q0, int wm, int wn, int lane)
-{
-    const int fr = lane & 31;
-    const int32_t n_rows = (int32_t)p.N;
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const int q = q0 + (wn * TN + j) * 32 + fr;
-        const bool qok = q < p.Q;
-        const u64 tkey = qok ? p.tau[q] : ~0ull;
-        const float tsc = qok ? key_score(tkey) : __builtin_inff();
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            float m = acc[i][j][0];
-#pragma unroll
-            for (int v = 1; v < 16; ++v) m = fmaxf(m, acc[i][j][v]);
-            // tkey == 0 admits everything (its score bits decode to NaN: compare separately)
-            if (qok && (tkey == 0ull || m >= tsc)) {
-                const int32_t rbase = row0 + (wm * TM + i) * 32 + (lane >> 5) * 4;
-                uint32_t pass = 0;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int32_t g = rbase + (v >> 2) * 8 + (v & 3);
-                    if (g < n_rows && make_key(acc[i][j][v], g) >= tkey) pass |= 1u << v;
-                }
-                if (pass) {
-                    uint32_t at = atomicAdd(p.cnt + (int64_t)q * CNT_PITCH, (uint32_t)__popc(pass));
-                    u64 *dst = p.cand + (int64_t)q * p.cap;
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        if (pass & (1u << v)) {
-                            if (at < p.cap) dst[at] = make_key(acc[i][j][v], rbase + (v >> 2) * 8 + (v & 3));
-                            ++at;
-                        }
-                    }
-                }
-            }
-        }
-    }
-}
-
 // Parked epilogue (pipelined kernel).  Admitted scores are first parked in a small LDS list
 // (an LDS atomic is ~20x quicker than a global atomic round trip, which a lone wave per SIMD
 // cannot hide) and moved to the global lists in batches by flush_parked().  An entry that
 // finds the list full goes to its global list directly, so nothing is ever lost.
+constexpr int PARK_CAP = 672;   // parked admitted scores per workgroup (12 bytes each)
 struct PushList {
     RALM_LDS uint32_t *count;   // entries appended so far (may exceed cap; the excess went to global)
     RALM_LDS u64 *keys;         // [cap]
@@ -171,11 +86,38 @@ __device__ __forceinline__ void push_global(const ScanParams &p, int q, u64 key)
     if (at < p.cap) p.cand[(int64_t)q * p.cap + at] = key;
 }
 
-// all threads of the workgroup, after a barrier that follows the last append: moves the first n parked
-// entries to the global lists and empties the LDS list
-__device__ __forceinline__ void flush_parked(const ScanParams &p, const PushList pl, uint32_t n)
+// All threads of the workgroup, after a barrier that follows the last append: moves the first n parked
+// entries to the global lists and empties the LDS list.  GROUP (batches of up to 128 queries, one
+// query tile): the entries of each query are counted in LDS first (`tally`, one word per query): a query's length is then moved once per
+// flush and not once per entry.  Adds to one length are served one after the other wherever they come
+// from (about 13 ns each here), so a stage that admits 3800 scores per query was bound by them.  Q = 8,
+// 1M x 768, k' = 64, refining by 64 at once: whole call 328 -> 271 us.  With more queries an entry of a
+// flush seldom shares its query with another, and the widest tile has no registers to spare.
+template <int NT, bool GROUP>
+__device__ __forceinline__ void flush_parked(const ScanParams &p, const PushList pl, RALM_LDS uint32_t *tally, uint32_t n)
 {
-    for (uint32_t e = threadIdx.x; e < n; e += blockDim.x) push_global(p, (int)pl.qs[e], pl.keys[e]);
+    if constexpr (GROUP) {
+        for (int q = threadIdx.x; q < p.Q; q += NT) tally[q] = 0;
+        __syncthreads();
+#pragma unroll 1
+        for (uint32_t e = threadIdx.x; e < n; e += NT) {   // an entry's place among its query's, kept beside the query
+            const uint32_t q = pl.qs[e];
+            pl.qs[e] = q | __hip_atomic_fetch_add(tally + q, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) << 8;
+        }
+        __syncthreads();
+        for (int q = threadIdx.x; q < p.Q; q += NT) {
+            const uint32_t m = tally[q];
+            if (m) tally[q] = atomicAdd(p.cnt + (int64_t)q * CNT_PITCH, m);
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (uint32_t e = threadIdx.x; e < n; e += NT) {
+            const uint32_t q = pl.qs[e] & 255u, at = tally[q] + (pl.qs[e] >> 8);
+            if (at < p.cap) p.cand[(int64_t)q * p.cap + at] = pl.keys[e];
+        }
+    } else {
+        for (uint32_t e = threadIdx.x; e < n; e += NT) push_global(p, (int)pl.qs[e], pl.keys[e]);
+    }
     __syncthreads();
     if (threadIdx.x == 0) *pl.count = 0;
     __syncthreads();
@@ -243,7 +185,8 @@ __device__ __forceinline__ void select_block_parked(const ScanParams &p, const P
 
 // Epilogue of a launch that keeps every score into empty lists (the first stage of a ladder): the
 // score of the launch's r-th row goes to slot r of its query's list, no atomics.  A lane's 16
-// values are 4 runs of 4 consecutive rows: 8 stores of two keys each.
+// values are 4 runs of 4 consecutive rows: 8 stores of two keys each.  Rows past the datastore's
+// end are the launch's last ones: their slots lie behind the list's length, which leaves them out.
 __device__ __forceinline__ void store_block_all(const ScanParams &p, const f32x16 &out, int32_t row_id0, int64_t pos0,
                                                 int q, bool qok)
 {
@@ -261,102 +204,78 @@ __device__ __forceinline__ void store_block_all(const ScanParams &p, const f32x1
     }
 }
 
-// IN: dtype of the datastore copy being scanned.  WM x WN waves, each TM x TN MFMA blocks.
-template <int IN, int WM, int WN, int TM, int TN>
-__global__ __launch_bounds__(256) void scan_staged_kernel(const ScanParams p, const int nqt)
+// Epilogue of a launch whose thresholds admit many of a tile's scores.  Taken one by one (above) they
+// fill the parking list many times over, and every one that finds it full costs a round trip to its
+// query's length.  Here the tile's scores stay in the accumulators, each lane counts those of its
+// columns that are admitted, the counts meet per query in LDS (`tally`, one word per column), the
+// lengths move once per tile and query, and the keys are stored where their lane's share of the
+// list begins.  All threads of the workgroup; tally is zero on entry and on return.
+// 256 queries, 1024 fp16 elements, k' = 2048, tiles that admit half of their scores: 292 -> 55 us
+// for a launch of 40 tiles.
+template <int TM, int TN, int NT>
+__device__ __forceinline__ void select_tile_counted(const ScanParams &p, const f32x16 (&acc)[TM][TN], RALM_LDS uint32_t *tally,
+                                                    int32_t row_id0, int32_t n_rows, int q0, int col0, int BN,
+                                                    const u64 (&tkey)[TN], const float (&tsc)[TN])
 {
-    constexpr int BM = WM * TM * 32, BN = WN * TN * 32, BK = SCAN_BK, LDA = BK + 8;
-    constexpr int PA = BM / 32, PB = BN / 32;
-    constexpr bool F16 = (IN == DT_F16);
-    static_assert(WM * WN == 4 && BM == SCAN_BM, "4 waves, 256-row tiles");
-
-    extern __shared__ __align__(16) unsigned char smem[];
-    uint16_t *As = reinterpret_cast<uint16_t *>(smem);      // [2][BM][LDA]
-    uint16_t *Bs = As + 2 * BM * LDA;                        // [2][BN][LDA]
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WN, wn = wave % WN;
-    const int ld_c = tid & 7, ld_r = tid >> 3;   // staging: 8 lanes cover 64 elements of a row
-    const int fr = lane & 31, fk = (lane >> 5) * 8;
-
-    const int64_t G = gridDim.x;
-    const int64_t vb = (int64_t)(blockIdx.x % 8) * (G / 8) + blockIdx.x / 8;
-    const int64_t total = p.n_row_tiles * nqt;
-    const int KT = p.dpad / BK;
-
-    for (int64_t item = vb; item < total; item += G) {
-        const int64_t rt = item / nqt;
-        const int qt = (int)(item % nqt);
-        const int64_t row0 = visited_tile(p, rt) * BM;
-        const int q0 = qt * BN;
-
-        f32x16 acc[TM][TN];
+    uint32_t pass[TM][TN], at[TN];
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+    for (int j = 0; j < TN; ++j) {
+        const bool every = tkey[j] == 0ull;   // fewer than k' keys so far: everything is admitted
+        uint32_t n = 0;
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
+        for (int i = 0; i < TM; ++i) {
+            uint32_t m = 0;
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-        RawChunk<IN> ra[PA];
-        uint4 rb[PB];
-
-        auto load_stage = [&](int kt) {
-            const int kc = kt * BK + ld_c * 8;
-            const bool kok = kc < p.d;
-#pragma unroll
-            for (int pa = 0; pa < PA; ++pa) {
-                const int64_t g = row0 + pa * 32 + ld_r;
-                load_chunk<IN>(ra[pa], p.X, g * p.ldx + kc, kok && g < p.N);
+            for (int v = 0; v < 16; ++v) {
+                const int32_t row = row_id0 + i * 32 + (v >> 2) * 8 + (v & 3);
+                const bool in = row < n_rows && (every || acc[i][j][v] >= tsc[j]) && make_key(acc[i][j][v], row) >= tkey[j];
+                m |= in ? 1u << v : 0u;
             }
-#pragma unroll
-            for (int pb = 0; pb < PB; ++pb) {
-                const int64_t qrow = q0 + pb * 32 + ld_r;
-                rb[pb] = *reinterpret_cast<const uint4 *>(p.Qs + qrow * p.dpad + kc);
-            }
-        };
-        auto store_stage = [&](int buf) {
-            uint16_t *a = As + buf * BM * LDA;
-            uint16_t *b = Bs + buf * BN * LDA;
-#pragma unroll
-            for (int pa = 0; pa < PA; ++pa)
-                *reinterpret_cast<uint4 *>(a + (pa * 32 + ld_r) * LDA + ld_c * 8) = chunk_bits<IN>(ra[pa]);
-#pragma unroll
-            for (int pb = 0; pb < PB; ++pb)
-                *reinterpret_cast<uint4 *>(b + (pb * 32 + ld_r) * LDA + ld_c * 8) = rb[pb];
-        };
-
-        load_stage(0);
-        store_stage(0);
-        __syncthreads();
-
-        for (int kt = 0; kt < KT; ++kt) {
-            const int buf = kt & 1;
-            if (kt + 1 < KT) load_stage(kt + 1);
-            const uint16_t *a = As + buf * BM * LDA + (wm * TM * 32 + fr) * LDA + fk;
-            const uint16_t *b = Bs + buf * BN * LDA + (wn * TN * 32 + fr) * LDA + fk;
-#pragma unroll
-            for (int kk = 0; kk < BK / 16; ++kk) {
-                uint4 fa[TM], fb[TN];
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-                    fa[i] = *reinterpret_cast<const uint4 *>(a + i * 32 * LDA + kk * 16);
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    fb[j] = *reinterpret_cast<const uint4 *>(b + j * 32 * LDA + kk * 16);
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) acc[i][j] = mfma32<F16>(fa[i], fb[j], acc[i][j]);
-            }
-            if (kt + 1 < KT) store_stage(buf ^ 1);
-            __syncthreads();
+            pass[i][j] = m;
+            n += (uint32_t)__popc(m);
+            // (kept as the word it is: the compiler would keep the 16 conditions and run out of registers)
+            asm("" : "+v"(pass[i][j]));
+            RALM_SCHED_FENCE();
         }
-
-        select_epilogue_direct<WM, WN, TM, TN>(p, acc, (int32_t)row0, q0, wm, wn, lane);
+        at[j] = n ? __hip_atomic_fetch_add(tally + col0 + j * 32, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : 0u;
     }
+    __syncthreads();
+    for (int c = threadIdx.x; c < BN; c += NT) {
+        const uint32_t m = tally[c];
+        if (m) tally[c] = atomicAdd(p.cnt + (int64_t)(q0 + c) * CNT_PITCH, m);   // padding columns have none
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        uint32_t to = tally[col0 + j * 32] + at[j];
+        u64 *dst = p.cand + (int64_t)(q0 + col0 + j * 32) * p.cap;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                if (pass[i][j] & (1u << v)) {
+                    // the keys are formed again: kept from above they would not fit the registers
+                    float score = acc[i][j][v];
+                    int32_t row = row_id0;
+                    asm("" : "+v"(score), "+v"(row));
+                    if (to < p.cap) dst[to] = make_key(score, row + i * 32 + (v >> 2) * 8 + (v & 3));
+                    ++to;
+                }
+            }
+            RALM_SCHED_FENCE();
+        }
+    }
+    __syncthreads();
+    for (int c = threadIdx.x; c < BN; c += NT) tally[c] = 0;
+    __syncthreads();
 }
 
+// What a launch keeps of a tile's scores, and how they get to the lists:
+enum {
+    KEEP_PARKED,    // the few that pass selective thresholds, by way of a list in LDS (select_block_parked)
+    KEEP_COUNTED,   // those that pass thresholds which admit many of a tile (select_tile_counted)
+    KEEP_ALL        // every score, into empty lists (store_block_all)
+};
 
 // ---- direct-to-LDS pipelined kernel ----------------------------------------------------------
 // LDS chunk swizzle: row r of a strip stores its global 16-byte chunk c at chunk slot c ^ swz(r).
@@ -411,9 +330,6 @@ __device__ __forceinline__ void wait_vmcnt()
 constexpr int TAU_LDS_MAX_Q = 2560;   // admission keys of up to this many queries are kept in LDS
 // ... by the widest query tile; the narrower tiles serve only batches of at most one tile
 constexpr int tau_lds_q(int BN) { return BN <= 128 ? BN : TAU_LDS_MAX_Q; }
-constexpr int PARK_CAP = 672;         // parked admitted scores per workgroup (12 bytes each)
-
-#define RALM_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
 
 // The instruction stream of a stage is laid out by hand (one wave per SIMD: nothing else fills
 // the issue slots between MFMAs).  After each MFMA exactly one "side" instruction follows: an
@@ -434,9 +350,9 @@ constexpr int PARK_CAP = 672;         // parked admitted scores per workgroup (1
 // A32: the datastore rows are fp32 (a datastore scanned as it is).  They travel to LDS as they
 // are, twice the bytes per strip row, and are rounded to bf16 between the operand read and the
 // multiply (two 16-byte reads and four conversions per operand instead of one read).
-// ALL: a launch into empty lists that keeps every score (see store_block_all); no thresholds.
+// KEEP: what is kept of the scores (KEEP_*).
 template <bool F16, int WM, int WN, int TM, int TN, int BK, int S, bool NTA, int D = S - 1, int RK = 0,
-          bool A32 = false, bool ALL = false>
+          bool A32 = false, int KEEP = KEEP_PARKED>
 __global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams p, const int nqt, const int tau_in_lds)
 {
     constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
@@ -469,6 +385,9 @@ __global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams 
     pl.count = pl.qs + PARK_CAP;
     pl.cap = PARK_CAP;
     RALM_LDS float *wave_slots = (RALM_LDS float *)(pl.count + 4) + (threadIdx.x >> 6) * (SLOW_SLOTS * 16);
+    // counts per query column: in the place of the slots, which no wave uses while the counts are needed
+    RALM_LDS uint32_t *tally = pl.count + 4;
+    static_assert(WM * WN * SLOW_SLOTS * 16 >= BN, "the counts fit the slots");
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -489,11 +408,15 @@ __global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams 
     };
     const int KT = p.dpad / BK;
     const int n_mine = vb < total ? (total - vb + G - 1) / G : 0;
-    if constexpr (ALL) {
-        // every list ends up with one entry per row of the launch (all of its tiles are full: host check)
-        if (blockIdx.x == 0)
-            for (int q = tid; q < p.Q; q += NT) p.cnt[(int64_t)q * CNT_PITCH] = (uint32_t)n_tiles * BM;
+    if constexpr (KEEP == KEEP_ALL) {
+        // every list ends up with one entry per row of the launch; only its last tile can be partial
+        if (blockIdx.x == 0) {
+            const int64_t rows = (p.n_row_tiles - 1) * SCAN_BM, left = p.N - visited_tile(p, p.n_row_tiles - 1) * SCAN_BM;
+            for (int q = tid; q < p.Q; q += NT) p.cnt[(int64_t)q * CNT_PITCH] = (uint32_t)(rows + (left < SCAN_BM ? left : SCAN_BM));
+        }
     }
+    if constexpr (KEEP == KEEP_COUNTED)
+        for (int c = tid; c < BN; c += NT) tally[c] = 0;
     if (n_mine == 0) return;
     const unsigned char *Xb = static_cast<const unsigned char *>(p.X);
     const unsigned char *Qb = reinterpret_cast<const unsigned char *>(p.Qs);
@@ -649,7 +572,8 @@ __global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams 
 
         // one stage; FIRST: accumulators start from zero; LAST: selection fused into the last k-step
         auto stage = [&](auto first_tag, auto last_tag) __attribute__((always_inline)) {
-            constexpr bool FIRST = decltype(first_tag)::value, LAST = decltype(last_tag)::value;
+            // (counted launches select after the stage, from the accumulators)
+            constexpr bool FIRST = decltype(first_tag)::value, LAST = decltype(last_tag)::value && KEEP != KEEP_COUNTED;
             const unsigned char *sb = smem + buf * STAGE;
             const int nbuf = buf + 1 == S ? 0 : buf + 1;
 #pragma unroll
@@ -719,7 +643,7 @@ __global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams 
                     }
                     if (LAST && last_kk && m >= LAG && m - LAG < NM) {
                         const int mm = m - LAG, i = mm / TN, j = mm % TN;
-                        if constexpr (ALL)
+                        if constexpr (KEEP == KEEP_ALL)
                             store_block_all(p, outs[mm % (LAG + 1)], row0 + (wm * TM + i) * 32 + (lane >> 5) * 4,
                                             (int64_t)cur_rt * BM + (wm * TM + i) * 32 + (lane >> 5) * 4,
                                             q0 + (wn * TN + j) * 32 + fr, qok[j]);
@@ -770,14 +694,26 @@ __global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams 
             stage(std::false_type{}, std::true_type{});
         }
 
+        if constexpr (KEEP == KEEP_COUNTED) {
+            if (wave_idle) {   // nothing was multiplied: nothing passes
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+            }
+            select_tile_counted<TM, TN, NT>(p, acc, tally, row0 + wm * TM * 32 + (lane >> 5) * 4, n_rows, q0, wn * TN * 32 + fr,
+                                            BN, tkey, tsc);
+        }
         // tile end: every few tiles the parked entries move to the global lists
         const bool last_tile = it + 1 == n_mine;
-        if ((it & 3) == 3 || last_tile) {
+        if (KEEP == KEEP_PARKED && ((it & 3) == 3 || last_tile)) {
             __syncthreads();
             const uint32_t n = *pl.count;   // uniform: read after the barrier
             const uint32_t held = n < pl.cap ? n : pl.cap;
             if (held >= pl.cap / 4 || (last_tile && held > 0)) {
-                flush_parked(p, pl, held);
+                flush_parked<NT, (BN <= 128)>(p, pl, tally, held);
                 parked = 0;
             } else {
                 parked = held;
@@ -795,14 +731,14 @@ __global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams 
 }
 
 template <bool F16, int WM, int WN, int TM, int TN, int BK, int S, bool NTA, int D = S - 1, int RK = 0,
-          bool A32 = false, bool ALL = false>
+          bool A32 = false, int KEEP = KEEP_PARKED>
 hipError_t launch_dma_variant(const ScanParams &p, int n_cu, hipStream_t stream)
 {
     constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
     constexpr size_t ring = (size_t)S * (BM * (A32 ? 4 : 2) + BN * 2) * BK;
     constexpr size_t smem = ring + (size_t)tau_lds_q(BN) * 8 + (size_t)PARK_CAP * 12 + 16 + WM * WN * SLOW_SLOTS * 64;
     static_assert(smem <= 160 * 1024, "LDS budget");
-    auto kern = scan_dma_kernel<F16, WM, WN, TM, TN, BK, S, NTA, D, RK, A32, ALL>;
+    auto kern = scan_dma_kernel<F16, WM, WN, TM, TN, BK, S, NTA, D, RK, A32, KEEP>;
     const int tau_in_lds = p.Q <= tau_lds_q(BN) ? 1 : 0;
     static std::atomic<bool> attr_done{false};   // per instantiation; setting it twice is harmless
     if (!attr_done.load(std::memory_order_acquire)) {
@@ -823,6 +759,7 @@ hipError_t launch_dma_variant(const ScanParams &p, int n_cu, hipStream_t stream)
     return hipGetLastError();
 }
 
+// thresholds that few of a tile's scores pass
 template <bool F16>
 hipError_t launch_dma(const ScanParams &p, int n_cu, hipStream_t stream)
 {
@@ -844,43 +781,40 @@ hipError_t launch_dma(const ScanParams &p, int n_cu, hipStream_t stream)
     }
 }
 
-template <int IN, int WM, int WN, int TM, int TN>
-hipError_t launch_variant(const ScanParams &p, int n_cu, hipStream_t stream)
+// launches that keep many or all of their scores (NTA: see launch_dma; not for several query tiles)
+template <bool F16, bool NTA, int KEEP>
+hipError_t launch_kept(const ScanParams &p, int n_cu, hipStream_t stream)
 {
-    constexpr int BM = WM * TM * 32, BN = WN * TN * 32, LDA = SCAN_BK + 8;
-    constexpr size_t smem = (size_t)2 * (BM + BN) * LDA * sizeof(uint16_t);
-    auto kern = scan_staged_kernel<IN, WM, WN, TM, TN>;
-    static std::atomic<bool> attr_done{false};   // per instantiation; setting it twice is harmless
-    if (!attr_done.load(std::memory_order_acquire)) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        if (e != hipSuccess) return e;
-        attr_done.store(true, std::memory_order_release);
+    switch (scan_bn_for(p.Q)) {
+        case 32: return launch_dma_variant<F16, 4, 1, 2, 1, 64, 4, NTA, 3, 0, false, KEEP>(p, n_cu, stream);
+        case 64: return launch_dma_variant<F16, 4, 2, 2, 1, 64, 3, NTA, 3, 2, false, KEEP>(p, n_cu, stream);
+        case 128: return launch_dma_variant<F16, 2, 4, 4, 1, 64, 3, NTA, 3, 2, false, KEEP>(p, n_cu, stream);
+        default:
+            if (NTA && p.Q > 256) return launch_dma_variant<F16, 2, 4, 4, 2, 64, 2, false, 2, 2, false, KEEP>(p, n_cu, stream);
+            return launch_dma_variant<F16, 2, 4, 4, 2, 64, 2, NTA, 2, 2, false, KEEP>(p, n_cu, stream);
     }
-    const int nqt = (int)((p.Q + BN - 1) / BN);
-    const int64_t total = p.n_row_tiles * nqt;
-    if (total <= 0) return hipSuccess;
-    const int per_cu = smem * 2 <= 160 * 1024 ? 2 : 1;
-    int64_t grid = (int64_t)n_cu * per_cu;
-    if (total < grid) grid = total;
-    grid = (grid + 7) / 8 * 8;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), smem, stream, p, nqt);
-    return hipGetLastError();
 }
 
-template <int IN>
-hipError_t launch_in(const ScanParams &p, int n_cu, hipStream_t stream)
+// fp32 rows: batches of one query tile stream them as they are and round on the way to the
+// matrix cores (32-element strips for 128 and 256 queries: an fp32 strip row is 128 bytes).
+// Several query tiles share the rows through L2 (default cache policy); 11.5 ms per query tile at
+// 21M x 768 against 6.5 ms from a bf16 copy, so callers with many tiles are better off with a copy.
+template <bool NTA, int KEEP>
+hipError_t launch_f32(const ScanParams &p, int n_cu, hipStream_t stream)
 {
-    const int bn = scan_bn_for(p.Q);
-    switch (bn) {
-        case 32: return launch_variant<IN, 4, 1, 2, 1>(p, n_cu, stream);
-        case 64: return launch_variant<IN, 4, 1, 2, 2>(p, n_cu, stream);
-        case 128: return launch_variant<IN, 2, 2, 4, 2>(p, n_cu, stream);
-        default: return launch_variant<IN, 2, 2, 4, 4>(p, n_cu, stream);
+    switch (scan_bn_for(p.Q)) {
+        case 32: return launch_dma_variant<false, 4, 1, 1, 1, 64, 4, NTA, 3, 0, true, KEEP>(p, n_cu, stream);
+        case 64: return launch_dma_variant<false, 4, 1, 1, 2, 64, 3, NTA, 3, 2, true, KEEP>(p, n_cu, stream);
+        case 128: return launch_dma_variant<false, 2, 4, 4, 1, 32, 3, NTA, 3, 0, true, KEEP>(p, n_cu, stream);
+        default:
+            if (NTA && p.Q > 256) return launch_dma_variant<false, 2, 4, 4, 2, 32, 2, false, 2, 0, true, KEEP>(p, n_cu, stream);
+            return launch_dma_variant<false, 2, 4, 4, 2, 32, 2, NTA, 2, 0, true, KEEP>(p, n_cu, stream);
     }
 }
 
 }  // namespace
+
+constexpr int64_t COUNT_MIN = 2;
 
 int scan_bn_for(int64_t Q)
 {
@@ -892,53 +826,26 @@ int scan_bn_for(int64_t Q)
 
 hipError_t launch_scan(const ScanParams &p, int n_cu, hipStream_t stream)
 {
-    // Launches whose thresholds admit everything (the first, tiny stage of the ladder) append
-    // nearly every score: they take the staged kernel, whose epilogue writes to the global lists
-    // with one atomic per lane and block.  fp32 rows always do (they are rounded on the way in).
-    // a launch that keeps every score into empty lists, all of its tiles full: fixed list positions
-    const int64_t last_tile = (p.tile_begin + p.n_row_tiles - 1) * p.tile_stride;
-    const bool all_kept = !p.park_pushes && p.lists_empty && p.tile_skip == 0 && p.n_row_tiles > 0 &&
-                          (last_tile + 1) * SCAN_BM <= p.N && p.n_row_tiles * SCAN_BM <= (int64_t)p.cap && p.cap % 2 == 0;
+    // every score into empty lists: fixed list positions
+    const bool all_kept = p.lists_empty && p.tile_skip == 0 && p.n_row_tiles > 0 && p.n_row_tiles * SCAN_BM <= (int64_t)p.cap;
+    // Thresholds that are expected to admit COUNT_MIN or more of a tile's 256 scores per query: the admitted
+    // scores of a tile are counted and stored together.  The line is flat: a round of 256 neighbour queries over
+    // 10M x 1024 (k' = 2048) takes 6525 us with it at 1.2, 6489 at 2, 6480 at 4, 7226 without counted launches;
+    // 200 queries over 2M rows in corpus order, whose admitted scores come in bursts, 2055 at 1.5, 2126 at 2.5,
+    // 2680 without; 100 queries, k' = 64, that admit 1.3 a tile: 134 counted, 112 parked.
+    const bool counted = p.admits >= COUNT_MIN * p.n_row_tiles;
     if (p.in_dtype == DT_F32) {
-        if (all_kept) {
-            const int bn = scan_bn_for(p.Q);
-            if (bn == 32) return launch_dma_variant<false, 4, 1, 1, 1, 64, 4, false, 3, 0, true, true>(p, n_cu, stream);
-            if (bn == 64) return launch_dma_variant<false, 4, 1, 1, 2, 64, 3, false, 3, 2, true, true>(p, n_cu, stream);
-            if (bn == 128) return launch_dma_variant<false, 2, 4, 4, 1, 32, 3, false, 3, 0, true, true>(p, n_cu, stream);
-            return launch_dma_variant<false, 2, 4, 4, 2, 32, 2, false, 2, 0, true, true>(p, n_cu, stream);
-        }
-        // fp32 rows: batches of one query tile stream them as they are and round on the way to the
-        // matrix cores (32-element strips for 128 and 256 queries: an fp32 strip row is 128 bytes)
-        if (p.park_pushes && p.Q <= 32) return launch_dma_variant<false, 4, 1, 1, 1, 64, 4, true, 3, 0, true>(p, n_cu, stream);
-        if (p.park_pushes && p.Q <= 64) return launch_dma_variant<false, 4, 1, 1, 2, 64, 3, true, 3, 2, true>(p, n_cu, stream);
-        if (p.park_pushes && p.Q <= 128) return launch_dma_variant<false, 2, 4, 4, 1, 32, 3, true, 3, 0, true>(p, n_cu, stream);
-        if (p.park_pushes && p.Q <= 256) return launch_dma_variant<false, 2, 4, 4, 2, 32, 2, true, 2, 0, true>(p, n_cu, stream);
-        // several query tiles: the rows are shared through L2 (default cache policy); 11.5 ms per query tile at
-        // 21M x 768 against 6.5 ms from a bf16 copy, so callers with many tiles are better off with a copy
-        if (p.park_pushes) return launch_dma_variant<false, 2, 4, 4, 2, 32, 2, false, 2, 0, true>(p, n_cu, stream);
-        return launch_in<DT_F32>(p, n_cu, stream);
+        if (all_kept) return launch_f32<false, KEEP_ALL>(p, n_cu, stream);
+        if (counted) return launch_f32<true, KEEP_COUNTED>(p, n_cu, stream);
+        return launch_f32<true, KEEP_PARKED>(p, n_cu, stream);
     }
-    if (!p.park_pushes) {
-        // The first stage of a ladder (every score kept, lists empty): the
-        // pipelined kernel with stores to fixed list positions; its tiles must all be full and fit
-        // the lists.  (One 256 x 256 tile takes the staged kernel 125 us, mostly its epilogue's
-        // atomics and its shallow pipeline.)
-        if (all_kept) {
-            const int bn = scan_bn_for(p.Q);
-            if (p.in_dtype == DT_F16) {
-                if (bn == 32) return launch_dma_variant<true, 4, 1, 2, 1, 64, 4, false, 3, 0, false, true>(p, n_cu, stream);
-                if (bn == 64) return launch_dma_variant<true, 4, 2, 2, 1, 64, 3, false, 3, 2, false, true>(p, n_cu, stream);
-                if (bn == 128) return launch_dma_variant<true, 2, 4, 4, 1, 64, 3, false, 3, 2, false, true>(p, n_cu, stream);
-                return launch_dma_variant<true, 2, 4, 4, 2, 64, 2, false, 2, 2, false, true>(p, n_cu, stream);
-            }
-            if (bn == 32) return launch_dma_variant<false, 4, 1, 2, 1, 64, 4, false, 3, 0, false, true>(p, n_cu, stream);
-            if (bn == 64) return launch_dma_variant<false, 4, 2, 2, 1, 64, 3, false, 3, 2, false, true>(p, n_cu, stream);
-            if (bn == 128) return launch_dma_variant<false, 2, 4, 4, 1, 64, 3, false, 3, 2, false, true>(p, n_cu, stream);
-            return launch_dma_variant<false, 2, 4, 4, 2, 64, 2, false, 2, 2, false, true>(p, n_cu, stream);
-        }
-        return p.in_dtype == DT_F16 ? launch_in<DT_F16>(p, n_cu, stream) : launch_in<DT_BF16>(p, n_cu, stream);
-    }
-    return p.in_dtype == DT_F16 ? launch_dma<true>(p, n_cu, stream) : launch_dma<false>(p, n_cu, stream);
+    const bool f16 = p.in_dtype == DT_F16;
+    if (all_kept)
+        return f16 ? launch_kept<true, false, KEEP_ALL>(p, n_cu, stream) : launch_kept<false, false, KEEP_ALL>(p, n_cu, stream);
+    if (counted)
+        return f16 ? launch_kept<true, true, KEEP_COUNTED>(p, n_cu, stream)
+                   : launch_kept<false, true, KEEP_COUNTED>(p, n_cu, stream);
+    return f16 ? launch_dma<true>(p, n_cu, stream) : launch_dma<false>(p, n_cu, stream);
 }
 
 }  // namespace ralm

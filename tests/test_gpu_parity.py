@@ -805,6 +805,27 @@ def test_list_selection_branches(B, oracle, Q, k, k_prime, values):
     assert np.array_equal(ids, wi) and np.array_equal(sc, wsc)
 
 
+@pytest.mark.parametrize("Q", [1, 33, 128, 129, 300])
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+def test_launches_that_admit_many_scores(B, oracle, dtype, Q):
+    """k' = 2048 over 42003 rows: the stages behind the first admit a few dozen scores per query and
+    tile, which are counted per tile; every query tile width and row type, a partial last tile, many
+    equal scores, the strided ladder and the sequential one."""
+    g = torch.Generator().manual_seed(Q)
+    N, d, k = 42003, 72, 700
+    X = torch.randint(0, 5, (N, d), generator=g).float()
+    Qm = torch.randint(0, 5, (Q, d), generator=g).float()
+    wi, wsc = oracle.retrieve_topk(Qm.numpy(), X.numpy(), k)
+    Xd = X.cuda()
+    ds = B.Datastore(Xd) if dtype == "f32" else B.Datastore.from_fp32(Xd, torch.bfloat16 if dtype == "bf16" else torch.float16)
+    for sequential in (False, True):
+        ws = B.alloc_workspace(Q, ds, k)
+        ids, sc = B.ralm_retrieve_topk_ex(Qm.cuda(), ds, k, workspace=ws, sequential=sequential)
+        counters = B.ralm_workspace_counters(ws)
+        assert counters["ladder_overflows"] == 0 and counters["unanswered"] == 0
+        assert np.array_equal(ids.cpu().numpy(), wi) and np.array_equal(sc.cpu().numpy(), wsc)
+
+
 @pytest.mark.parametrize("d,Q", [(8, 3), (2048, 5), (2048, 70), (4096, 33), (16384, 2)])
 def test_extreme_row_lengths(B, oracle, d, Q):
     """The shortest and the longest rows the library accepts (cache lookup: up to d = 2048)."""
