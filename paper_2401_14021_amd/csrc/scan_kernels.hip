@@ -759,29 +759,35 @@ hipError_t launch_dma_variant(const ScanParams &p, int n_cu, hipStream_t stream)
     return hipGetLastError();
 }
 
-// thresholds that few of a tile's scores pass
-template <bool F16>
+// Rows that are whole 128-byte lines.  Otherwise neighbouring strips share the lines that they meet in, and
+// a line that was streamed past L2 is fetched again: 100 queries over 2M rows of 904 bf16 elements read
+// 1.75 times the rows' bytes and take 1277 us, 994 us (1.08 times) with the default policy; 8 queries over 1M x
+// 392: 256 and 216 us.
+bool whole_lines(const ScanParams &p)
+{
+    return (p.ldx * (p.in_dtype == DT_F32 ? 4 : 2)) % 128 == 0 && reinterpret_cast<uintptr_t>(p.X) % 128 == 0;
+}
+
+// Thresholds that few of a tile's scores pass.
+// NTA: one query tile and rows of whole lines.  Nobody shares the rows through L2, they are streamed
+// non-temporally (strips of whole 128-byte lines; with 64-byte strips a line would be requested
+// twice, a stage apart, and would have to stay in L2 in between).
+template <bool F16, bool NTA>
 hipError_t launch_dma(const ScanParams &p, int n_cu, hipStream_t stream)
 {
-    const int bn = scan_bn_for(p.Q);
-    switch (bn) {
-        // One query tile: nobody shares the rows through L2, they are streamed non-temporally
-        // (strips of whole 128-byte lines; with 64-byte strips a line would be requested twice, a
-        // stage apart, and would have to stay in L2 in between).
-        case 32: return launch_dma_variant<F16, 4, 1, 2, 1, 64, 4, true>(p, n_cu, stream);
+    switch (scan_bn_for(p.Q)) {
+        case 32: return launch_dma_variant<F16, 4, 1, 2, 1, 64, 4, NTA>(p, n_cu, stream);
         // 64 and 128 queries: 8 waves (two per SIMD, wave tiles of 64 x 32 and 128 x 32), so that one wave's
         // waits are covered by the other's multiplies; with 4 waves of twice the width they were 5 % and 3 % slower
-        case 64: return launch_dma_variant<F16, 4, 2, 2, 1, 64, 3, true, 3, 2>(p, n_cu, stream);
-        case 128: return launch_dma_variant<F16, 2, 4, 4, 1, 64, 3, true, 3, 2>(p, n_cu, stream);
-        default:
-            // two slots of 64-element strips, refilled in place (D = S): same LDS as four 32-element
-            // slots, half the rendezvous and half the L2 requests per multiply
-            if (p.Q <= 256) return launch_dma_variant<F16, 2, 4, 4, 2, 64, 2, true, 2, 2>(p, n_cu, stream);
-            return launch_dma_variant<F16, 2, 4, 4, 2, 64, 2, false, 2, 2>(p, n_cu, stream);
+        case 64: return launch_dma_variant<F16, 4, 2, 2, 1, 64, 3, NTA, 3, 2>(p, n_cu, stream);
+        case 128: return launch_dma_variant<F16, 2, 4, 4, 1, 64, 3, NTA, 3, 2>(p, n_cu, stream);
+        // two slots of 64-element strips, refilled in place (D = S): same LDS as four 32-element
+        // slots, half the rendezvous and half the L2 requests per multiply
+        default: return launch_dma_variant<F16, 2, 4, 4, 2, 64, 2, NTA, 2, 2>(p, n_cu, stream);
     }
 }
 
-// launches that keep many or all of their scores (NTA: see launch_dma; not for several query tiles)
+// launches that keep many or all of their scores (NTA: see launch_dma)
 template <bool F16, bool NTA, int KEEP>
 hipError_t launch_kept(const ScanParams &p, int n_cu, hipStream_t stream)
 {
@@ -789,10 +795,17 @@ hipError_t launch_kept(const ScanParams &p, int n_cu, hipStream_t stream)
         case 32: return launch_dma_variant<F16, 4, 1, 2, 1, 64, 4, NTA, 3, 0, false, KEEP>(p, n_cu, stream);
         case 64: return launch_dma_variant<F16, 4, 2, 2, 1, 64, 3, NTA, 3, 2, false, KEEP>(p, n_cu, stream);
         case 128: return launch_dma_variant<F16, 2, 4, 4, 1, 64, 3, NTA, 3, 2, false, KEEP>(p, n_cu, stream);
-        default:
-            if (NTA && p.Q > 256) return launch_dma_variant<F16, 2, 4, 4, 2, 64, 2, false, 2, 2, false, KEEP>(p, n_cu, stream);
-            return launch_dma_variant<F16, 2, 4, 4, 2, 64, 2, NTA, 2, 2, false, KEEP>(p, n_cu, stream);
+        default: return launch_dma_variant<F16, 2, 4, 4, 2, 64, 2, NTA, 2, 2, false, KEEP>(p, n_cu, stream);
     }
+}
+
+template <bool F16>
+hipError_t launch_16(const ScanParams &p, bool all_kept, bool counted, bool nt, int n_cu, hipStream_t stream)
+{
+    if (all_kept) return launch_kept<F16, false, KEEP_ALL>(p, n_cu, stream);
+    if (counted)
+        return nt ? launch_kept<F16, true, KEEP_COUNTED>(p, n_cu, stream) : launch_kept<F16, false, KEEP_COUNTED>(p, n_cu, stream);
+    return nt ? launch_dma<F16, true>(p, n_cu, stream) : launch_dma<F16, false>(p, n_cu, stream);
 }
 
 // fp32 rows: batches of one query tile stream them as they are and round on the way to the
@@ -806,9 +819,7 @@ hipError_t launch_f32(const ScanParams &p, int n_cu, hipStream_t stream)
         case 32: return launch_dma_variant<false, 4, 1, 1, 1, 64, 4, NTA, 3, 0, true, KEEP>(p, n_cu, stream);
         case 64: return launch_dma_variant<false, 4, 1, 1, 2, 64, 3, NTA, 3, 2, true, KEEP>(p, n_cu, stream);
         case 128: return launch_dma_variant<false, 2, 4, 4, 1, 32, 3, NTA, 3, 0, true, KEEP>(p, n_cu, stream);
-        default:
-            if (NTA && p.Q > 256) return launch_dma_variant<false, 2, 4, 4, 2, 32, 2, false, 2, 0, true, KEEP>(p, n_cu, stream);
-            return launch_dma_variant<false, 2, 4, 4, 2, 32, 2, NTA, 2, 0, true, KEEP>(p, n_cu, stream);
+        default: return launch_dma_variant<false, 2, 4, 4, 2, 32, 2, NTA, 2, 0, true, KEEP>(p, n_cu, stream);
     }
 }
 
@@ -834,18 +845,14 @@ hipError_t launch_scan(const ScanParams &p, int n_cu, hipStream_t stream)
     // 200 queries over 2M rows in corpus order, whose admitted scores come in bursts, 2055 at 1.5, 2126 at 2.5,
     // 2680 without; 100 queries, k' = 64, that admit 1.3 a tile: 134 counted, 112 parked.
     const bool counted = p.admits >= COUNT_MIN * p.n_row_tiles;
+    const bool nt = p.Q <= 256 && whole_lines(p);
     if (p.in_dtype == DT_F32) {
         if (all_kept) return launch_f32<false, KEEP_ALL>(p, n_cu, stream);
-        if (counted) return launch_f32<true, KEEP_COUNTED>(p, n_cu, stream);
-        return launch_f32<true, KEEP_PARKED>(p, n_cu, stream);
+        if (counted) return nt ? launch_f32<true, KEEP_COUNTED>(p, n_cu, stream) : launch_f32<false, KEEP_COUNTED>(p, n_cu, stream);
+        return nt ? launch_f32<true, KEEP_PARKED>(p, n_cu, stream) : launch_f32<false, KEEP_PARKED>(p, n_cu, stream);
     }
-    const bool f16 = p.in_dtype == DT_F16;
-    if (all_kept)
-        return f16 ? launch_kept<true, false, KEEP_ALL>(p, n_cu, stream) : launch_kept<false, false, KEEP_ALL>(p, n_cu, stream);
-    if (counted)
-        return f16 ? launch_kept<true, true, KEEP_COUNTED>(p, n_cu, stream)
-                   : launch_kept<false, true, KEEP_COUNTED>(p, n_cu, stream);
-    return f16 ? launch_dma<true>(p, n_cu, stream) : launch_dma<false>(p, n_cu, stream);
+    return p.in_dtype == DT_F16 ? launch_16<true>(p, all_kept, counted, nt, n_cu, stream)
+                                : launch_16<false>(p, all_kept, counted, nt, n_cu, stream);
 }
 
 }  // namespace ralm
