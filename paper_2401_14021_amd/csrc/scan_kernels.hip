@@ -776,7 +776,10 @@ template <bool F16, bool NTA>
 hipError_t launch_dma(const ScanParams &p, int n_cu, hipStream_t stream)
 {
     switch (scan_bn_for(p.Q)) {
-        case 32: return launch_dma_variant<F16, 4, 1, 2, 1, 64, 4, NTA>(p, n_cu, stream);
+        // up to 32 queries: half tiles, two workgroups to a CU: a launch of few tiles spreads over twice as many
+        // workgroups, and one's selection and flush are covered by the other's loads.  Against whole tiles, one
+        // workgroup to a CU: Q = 8 over 1M x 768 271 -> 261 us, over 300K 118 -> 116 us, 1M x 392 216 -> 207 us
+        case 32: return launch_dma_variant<F16, 4, 1, 1, 1, 64, 3, NTA, 3, 2>(p, n_cu, stream);
         // 64 and 128 queries: 8 waves (two per SIMD, wave tiles of 64 x 32 and 128 x 32), so that one wave's
         // waits are covered by the other's multiplies; with 4 waves of twice the width they were 5 % and 3 % slower
         case 64: return launch_dma_variant<F16, 4, 2, 2, 1, 64, 3, NTA, 3, 2>(p, n_cu, stream);
@@ -792,7 +795,7 @@ template <bool F16, bool NTA, int KEEP>
 hipError_t launch_kept(const ScanParams &p, int n_cu, hipStream_t stream)
 {
     switch (scan_bn_for(p.Q)) {
-        case 32: return launch_dma_variant<F16, 4, 1, 2, 1, 64, 4, NTA, 3, 0, false, KEEP>(p, n_cu, stream);
+        case 32: return launch_dma_variant<F16, 4, 1, 1, 1, 64, 3, NTA, 3, 2, false, KEEP>(p, n_cu, stream);
         case 64: return launch_dma_variant<F16, 4, 2, 2, 1, 64, 3, NTA, 3, 2, false, KEEP>(p, n_cu, stream);
         case 128: return launch_dma_variant<F16, 2, 4, 4, 1, 64, 3, NTA, 3, 2, false, KEEP>(p, n_cu, stream);
         default: return launch_dma_variant<F16, 2, 4, 4, 2, 64, 2, NTA, 2, 2, false, KEEP>(p, n_cu, stream);
