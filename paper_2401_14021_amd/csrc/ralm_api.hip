@@ -88,19 +88,25 @@ ralm_status make_plan(int64_t Q, const ralm_datastore_t *ds, int32_t k, int32_t 
     pl.k_prime = k_prime;
     // Stage strides, finest first: 1, then multiplied by the stage's growth until a stage is
     // small enough to keep every score (that one is stage 0).  A stage that refines by g is
-    // expected to admit k'*(g-1) scores per query.  Large batches are limited by the matrix
-    // cores and by the rare path of the selection, so their big last stages refine in steps
-    // of 2; small batches are limited by HBM and prefer few launches.
-    // With a large k' (KNN-LM: 2048) a stage that refines by 8 admits 7 k' scores per query, more
-    // than its rows are worth: such batches refine by 2 throughout (100M x 1024, Q = 256: 2 %
-    // faster although the ladder has 14 stages instead of 7).
-    const int32_t g_fine = 2, g_coarse = Q > 64 ? (k_prime > 256 ? 2 : 8) : (k_prime <= 256 ? 64 : 32);
-    const int64_t fine_until = Q > 64 ? 8 : 1;    // strides below this refine by g_fine
+    // expected to admit k'*(g-1) scores per query; a stage more is a select, a launch and a last
+    // round of tiles that leaves CUs idle, 15 to 25 us together.  So: as few stages as a largest growth allows, all
+    // of about the same growth.  Whole calls, growths finest first:
+    //   up to 64 queries   an admitted score is cheap: Q = 8 over 1M x 768 by 62 271 us, by 8 and 8 285; Q = 40
+    //                      291, 300.  With large k' the lists would have to be long and the first stage costs more
+    //                      than it saves: Q = 64, k' = 512, 2M x 1024 by 32 and 2 1079 us, by 5, 5 and 5 1004; Q = 16, k' = 2048, 1M x 1024 1027, 912.
+    //   up to 256 queries  100 over 200K x 768 by 13 111 us, by 4 and 4 137, by 2, 2, 2 and 2 164; 81 over 1M round
+    //                      by 8 and 8 370, by 2, 2, 2 and 8 392; 100 over 8M by 8, 8 and 8 2072, by 2, 2, 2, 8 and 8
+    //                      2128.  k' > 256: 256 over 10M x 1024, k' = 2048, by 4 throughout 6497, by 2 6617.
+    //   more               bound by the matrix cores, which wait for the selection: seven eighths or more of the
+    //                      rows should see keys within a factor 2 of final, so the finest step is 2; 600 over
+    //                      400K by 2, 4 and 4 602 us, by 2, 2, 2 and 4 625, by 4 and 8 609.
+    const int32_t g_most = Q <= 64 ? (k_prime <= 256 ? 64 : 8) : (k_prime > 256 ? 4 : (Q <= 256 ? 16 : 8));
+    const int32_t g_finest = Q > 256 ? 2 : 0;   // 0: like the others
     // the slots leave 4x (2x for large k') head room over that expectation, far beyond the
     // spread of the count for rows in random order, and are never fewer than 16384 so that
     // stage 0 can be a real sample
     const int64_t safety = k_prime <= 256 ? 4 : 2;
-    pl.cap = (uint32_t)(safety * k_prime * (g_coarse - 1) + k_prime);
+    pl.cap = (uint32_t)(safety * k_prime * (g_most - 1) + k_prime);
     if (pl.cap < 16384u) pl.cap = 16384u;
     pl.cap = (pl.cap + 1u) & ~1u;   // even: lists start on 16-byte boundaries
     pl.Qpad = (Q + SCAN_QPAD - 1) / SCAN_QPAD * SCAN_QPAD;
@@ -112,12 +118,25 @@ ralm_status make_plan(int64_t Q, const ralm_datastore_t *ds, int32_t k, int32_t 
     int n = 0;
     int64_t s = 1;
     rev[n++] = s;
-    while (!fits(s)) {
-        const int32_t g = s < fine_until ? g_fine : g_coarse;
-        int32_t f = 2;
-        while (f < g && !fits(s * f)) ++f;     // the coarsest step may be shorter
-        s *= f;
-        rev[n++] = s;
+    if (g_finest && !fits(s)) rev[n++] = s = g_finest;
+    if (!fits(s)) {
+        const int64_t full = pl.cap / SCAN_BM, ratio = (tiles + s * full - 1) / (s * full);   // still to be bridged
+        int32_t steps = 0;
+        for (int64_t r = 1; r < ratio; r *= g_most) ++steps;
+        // (not where one growth nearly always does: the last stage is then as long as it can be, and the longer a
+        // launch the less its ends cost: one query over 8M x 768 by 64 and 8 1822 us, by 23 and 22 1865)
+        int32_t g = g_most < 64 ? 2 : g_most;
+        for (; g < g_most; ++g) {
+            int64_t r = 1;
+            for (int32_t i = 0; i < steps; ++i) r *= g;
+            if (r >= ratio) break;
+        }
+        while (!fits(s)) {
+            int32_t f = 2;
+            while (f < g && !fits(s * f)) ++f;     // the coarsest step may be shorter
+            s *= f;
+            rev[n++] = s;
+        }
     }
     pl.n_stages = n;
     for (int i = 0; i < n; ++i) pl.stride[i] = rev[n - 1 - i];
@@ -702,9 +721,9 @@ ralm_status ralm_cache_lookup_topk(const int32_t *cache_ids, const int32_t *cach
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     u64 *keys = static_cast<u64 *>(workspace);
     uint32_t *cnt = reinterpret_cast<uint32_t *>(static_cast<unsigned char *>(workspace) + up256((size_t)Qt * C * 8));
+    const int64_t ld = ds->exact_stride ? ds->exact_stride : ds->d;
     RALM_HIP(launch_cache_keys(cache_ids, cache_len, C, R, Qt, q_offsets, ds->N, keys, cnt, stream));
     // the cached rows are the candidates: exact scores, ranking and the first k, as after a scan
-    const int64_t ld = ds->exact_stride ? ds->exact_stride : ds->d;
     CertifyParams no_check;
     memset(&no_check, 0, sizeof(no_check));
     RALM_HIP(launch_rescore(keys, cnt, 1, (uint32_t)C, C, queries, Qt, ds->exact, ds->exact_dtype, ld, ds->d, ds->metric,
