@@ -98,21 +98,7 @@ __global__ __launch_bounds__(KP_THREADS) void knnlm_probs_kernel(
     __syncthreads();
 
     // entries grouped by token, ranks ascending inside a group
-    for (int size = 2; size <= kp2; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int t = tid; t < kp2 / 2; t += KP_THREADS) {
-                const int lo = 2 * t - (t & (stride - 1));
-                const int hi = lo + stride;
-                const bool asc = (lo & size) == 0;
-                const u64 a = keys[lo], b = keys[hi];
-                if ((a > b) == asc) {
-                    keys[lo] = b;
-                    keys[hi] = a;
-                }
-            }
-            __syncthreads();
-        }
-    }
+    sort_keys<KP_THREADS, false>(keys, kp2);
     // the thread at the start of a group adds the group's weights in rank order
     double my_p = -1.0;
     int32_t my_tok = -1;

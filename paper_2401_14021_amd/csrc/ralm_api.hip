@@ -581,7 +581,7 @@ ralm_status check_cache_lookup(const int32_t *cache_ids, const int32_t *cache_le
     if (Qt < 0) return fail(RALM_ERR_RANGE, "Qt=%lld is negative", (long long)Qt);
     ralm_status st = check_datastore(ds, false);
     if (st != RALM_OK) return st;
-    if (ds->d > 2048) return fail(RALM_ERR_SHAPE, "cache lookup supports d <= 2048");
+    if (ds->d > CACHE_LOOKUP_MAX_D) return fail(RALM_ERR_SHAPE, "cache lookup supports d <= 2048");
     if (!aligned16(queries)) return fail(RALM_ERR_ALIGN, "queries must be 16-byte aligned");
     return RALM_OK;
 }
@@ -722,6 +722,12 @@ ralm_status ralm_cache_lookup_topk(const int32_t *cache_ids, const int32_t *cach
     u64 *keys = static_cast<u64 *>(workspace);
     uint32_t *cnt = reinterpret_cast<uint32_t *>(static_cast<unsigned char *>(workspace) + up256((size_t)Qt * C * 8));
     const int64_t ld = ds->exact_stride ? ds->exact_stride : ds->d;
+    const int64_t ld = ds->exact_stride ? ds->exact_stride : ds->d;
+    if (ds->d <= CACHE_LOOKUP_MAX_D) {
+        RALM_HIP(launch_cache_lookup_topk(cache_ids, cache_len, C, R, queries, Qt, q_offsets, ds->exact, ds->exact_dtype, ld,
+                                          ds->N, ds->d, ds->metric, k, out_ids, out_scores, keys, cnt, stream));
+        return RALM_OK;
+    }
     RALM_HIP(launch_cache_keys(cache_ids, cache_len, C, R, Qt, q_offsets, ds->N, keys, cnt, stream));
     // the cached rows are the candidates: exact scores, ranking and the first k, as after a scan
     CertifyParams no_check;

@@ -102,4 +102,36 @@ __device__ __forceinline__ double wave64_sum(double v)
     return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
 }
 
+// ---- bitonic sort of n (a power of two) 64-bit keys in LDS, largest first (DESC) or smallest first ----
+// All NT threads of a workgroup; the keys were written before a barrier, and the result is complete
+// behind the function's last one.  Steps with a stride of up to 64 exchange keys inside
+// blocks of 128 that belong to one wave: they need no barrier, only the wave's LDS accesses in
+// order, so 2048 keys take 15 barriers instead of 66.
+template <int NT, bool DESC>
+__device__ __forceinline__ void sort_keys(u64 *keys, int n)
+{
+    for (int size = 2; size <= n; size <<= 1) {
+        for (int stride = size >> 1; stride > 0; stride >>= 1) {
+            for (int t = threadIdx.x; t < n / 2; t += NT) {
+                const int lo = 2 * t - (t & (stride - 1));
+                const int hi = lo + stride;
+                const u64 a = keys[lo], b = keys[hi];
+                if ((a < b) == (((lo & size) == 0) == DESC)) {
+                    keys[lo] = b;
+                    keys[hi] = a;
+                }
+            }
+            // the next step's stride decides who reads what was just written
+            if (stride > 64 || (stride == 1 && size >= 128)) {
+                __syncthreads();
+            } else {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            }
+        }
+    }
+    __syncthreads();
+}
+
 }  // namespace ralm

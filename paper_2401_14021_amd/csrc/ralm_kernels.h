@@ -125,6 +125,13 @@ hipError_t launch_cache_lookup(const int32_t *cache_ids, const int32_t *cache_le
                                int32_t metric, int32_t *spec_ids, float *spec_scores, u64 *partial,
                                hipStream_t stream);
 
+constexpr int CACHE_LOOKUP_MAX_D = 2048;   // the lookup kernels hold a row in registers
+// the k best cached entries per query; list [Qt, C] and list_len [Qt] are scratch
+hipError_t launch_cache_lookup_topk(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,
+                                    const float *queries, int64_t Qt, const int64_t *q_offsets, const void *exact,
+                                    int32_t exact_dtype, int64_t ld, int64_t N, int32_t d, int32_t metric, int32_t k,
+                                    int32_t *out_ids, float *out_scores, u64 *list, uint32_t *list_len, hipStream_t stream);
+
 constexpr int CACHE_INSERT_MAX_C = 16384;   // a request's cache row is held in LDS during an update
 hipError_t launch_cache_insert(int32_t *cache_ids, int32_t *cache_len, int32_t *cache_head, int32_t C, int64_t R,
                                const int32_t *truth, int64_t true_stride, int64_t Qt, const int64_t *q_offsets,

@@ -480,21 +480,7 @@ __global__ __launch_bounds__(RS_THREADS) void rescore_kernel(const u64 *__restri
     } else {
         for (int c = n + tid; c < kp2; c += RS_THREADS) keys[c] = 0ull;
         __syncthreads();
-        for (int size = 2; size <= kp2; size <<= 1) {   // bitonic
-            for (int stride = size >> 1; stride > 0; stride >>= 1) {
-                for (int t = tid; t < kp2 / 2; t += RS_THREADS) {
-                    const int lo = 2 * t - (t & (stride - 1));
-                    const int hi = lo + stride;
-                    const bool desc = (lo & size) == 0;
-                    const u64 a = keys[lo], b = keys[hi];
-                    if ((a < b) == desc) {
-                        keys[lo] = b;
-                        keys[hi] = a;
-                    }
-                }
-                __syncthreads();
-            }
-        }
+        sort_keys<RS_THREADS, true>(keys, kp2);
         ranked = keys;
     }
 
@@ -807,21 +793,7 @@ __global__ __launch_bounds__(SEL_THREADS) void exact_finish_kernel(const u64 *__
             }
         }
         __syncthreads();
-        for (int size = 2; size <= kp2; size <<= 1) {
-            for (int stride = size >> 1; stride > 0; stride >>= 1) {
-                for (int t = tid; t < kp2 / 2; t += SEL_THREADS) {
-                    const int lo = 2 * t - (t & (stride - 1));
-                    const int hi = lo + stride;
-                    const bool desc = (lo & size) == 0;
-                    const u64 a = keys[lo], b = keys[hi];
-                    if ((a < b) == desc) {
-                        keys[lo] = b;
-                        keys[hi] = a;
-                    }
-                }
-                __syncthreads();
-            }
-        }
+        sort_keys<SEL_THREADS, true>(keys, kp2);
         for (int r = tid; r < k; r += SEL_THREADS) {
             out_ids[q * k + r] = key_id(keys[r]);
             out_scores[q * k + r] = key_score(keys[r]);

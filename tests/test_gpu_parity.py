@@ -1083,6 +1083,32 @@ def test_cache_lookup_topk_matches_oracle(B, oracle, R, C, k, d, metric):
     assert np.array_equal(sc.cpu().numpy(), wsc)
 
 
+@pytest.mark.parametrize("dtype,d,metric", [("f16", 128, "ip"), ("f16", 136, "ip"), ("f16", 1024, "l2"), ("f32", 64, "ip"),
+                                            ("f32", 2048, "l2"), ("f32", 2056, "ip"), ("f16", 2176, "ip")])
+@pytest.mark.parametrize("C,k", [(1, 1), (129, 129), (600, 40)])
+def test_cache_lookup_topk_forms_and_row_lengths(B, oracle, dtype, d, metric, C, k):
+    """Every form that scores the cached rows once for a request's queries (fp64 matrix cores, vector
+    units, both row types), rows too long for them, more queries than a workgroup holds at a time, ids listed
+    twice, invalid ids, an empty cache, and queries in front of and behind those that requests own."""
+    rng = np.random.default_rng(d + C)
+    N = 3000
+    Xnp = rng.integers(-3, 4, size=(N, d)).astype(np.float32)
+    off = np.array([2, 23, 23, 24, 33], dtype=np.int64)              # 21, 0, 1 and 9 queries; Qt = 36
+    Qm = rng.integers(-3, 4, size=(36, d)).astype(np.float32)
+    cache = rng.integers(0, N, size=(4, C)).astype(np.int32)          # with repeats
+    cache[0, C // 2] = N
+    cache[3, -1] = -1
+    lens = np.array([C, C, 0, max(1, C - 3)], dtype=np.int32)
+    X = torch.from_numpy(Xnp).to(torch.float16 if dtype == "f16" else torch.float32).cuda()
+    ds = B.Datastore(X, metric=0) if metric == "ip" else B.Datastore.for_l2(X)
+    ids, sc = B.ralm_cache_lookup_topk(torch.from_numpy(cache).cuda(), torch.from_numpy(lens).cuda(),
+                                       torch.from_numpy(Qm).cuda(), torch.from_numpy(off).cuda(), ds, k)
+    wi, wsc = np.full((36, k), -1, np.int32), np.full((36, k), -np.inf, np.float32)
+    oi, osc = oracle.cache_lookup_topk(cache, lens, Qm[:33], off, Xnp, k, metric)
+    wi[2:33], wsc[2:33] = oi[2:], osc[2:]
+    assert np.array_equal(ids.cpu().numpy(), wi) and np.array_equal(sc.cpu().numpy(), wsc)
+
+
 def test_knnlm_speculation_from_the_cache_and_token_level_verification(B, oracle):
     """Section 5.3 end to end on the entry points: the cache holds the successors of previously
     retrieved entries (next-n update); the speculation step takes its k nearest entries from the
