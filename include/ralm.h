@@ -322,6 +322,16 @@ ralm_status ralm_cache_lookup(const int32_t *cache_ids, const int32_t *cache_len
                               void *workspace, size_t workspace_bytes, void *stream);
 
 /*
+ * ralm_cache_lookup that writes every row of the outputs: rows of [0, Qt) that no
+ * request owns get id -1 / score -inf, in a launch that the lookup needs anyway,
+ * so outputs need not be filled beforehand.
+ */
+ralm_status ralm_cache_lookup_all(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,
+                                  const float *queries, int64_t Qt, const int64_t *q_offsets,
+                                  const ralm_datastore_t *ds, int32_t *spec_ids, float *spec_scores,
+                                  void *workspace, size_t workspace_bytes, void *stream);
+
+/*
  * ralm_cache_lookup for callers that can neither allocate device memory nor
  * pass a workspace: code recorded under HIP graph capture, tight serving loops,
  * harnesses that forbid allocation.  Same arguments and same results as

@@ -71,6 +71,7 @@ def lib() -> ctypes.CDLL:
         L.ralm_build_scan_copy.argtypes = [vp, i64, vp, i32, i64, i64, i32, vp]
         L.ralm_build_scan_copy_l2.argtypes = [vp, i32, i64, vp, i32, i64, i64, i32, vp]
         L.ralm_cache_lookup.argtypes = [vp, vp, i32, i64, vp, i64, vp, dsp, vp, vp, vp, ctypes.c_size_t, vp]
+        L.ralm_cache_lookup_all.argtypes = L.ralm_cache_lookup.argtypes
         L.ralm_cache_lookup_static.argtypes = [vp, vp, i32, i64, vp, i64, vp, dsp, vp, vp, vp]
         L.ralm_cache_lookup_workspace_bytes.argtypes = [i64]
         L.ralm_cache_lookup_workspace_bytes.restype = ctypes.c_size_t
@@ -99,7 +100,8 @@ def lib() -> ctypes.CDLL:
         L.ralm_profile_scan_ms.argtypes = [ctypes.POINTER(ctypes.c_float), ctypes.POINTER(i32)]
         for name in ("ralm_retrieve_topk", "ralm_retrieve_topk_ex", "ralm_retrieve_topk_seq", "ralm_workspace_overflows",
                      "ralm_workspace_counters", "ralm_workspace_stage_entries",
-                     "ralm_build_scan_copy", "ralm_build_scan_copy_l2", "ralm_cache_lookup", "ralm_cache_lookup_static",
+                     "ralm_build_scan_copy", "ralm_build_scan_copy_l2", "ralm_cache_lookup", "ralm_cache_lookup_all",
+                     "ralm_cache_lookup_static",
                      "ralm_cache_lookup_topk", "ralm_verify", "ralm_cache_insert", "ralm_knnlm_probs",
                      "ralm_profile_scan_ms"):
             getattr(L, name).restype = ctypes.c_int
@@ -272,16 +274,21 @@ def ralm_cache_lookup(cache_ids: torch.Tensor, cache_len: torch.Tensor, queries:
     assert cache_ids.is_contiguous() and queries.is_contiguous()
     R, C = cache_ids.shape
     Qt = queries.shape[0]
-    if spec_ids is None:
+    # outputs allocated here hold -1 / -inf for queries that no request owns; both at once: the lookup sees to it
+    fn = lib().ralm_cache_lookup
+    if spec_ids is None and spec_scores is None:
+        fn = lib().ralm_cache_lookup_all
+        spec_ids = torch.empty(Qt, dtype=torch.int32, device=queries.device)
+        spec_scores = torch.empty(Qt, dtype=torch.float32, device=queries.device)
+    elif spec_ids is None:
         spec_ids = torch.full((Qt,), -1, dtype=torch.int32, device=queries.device)
-    if spec_scores is None:
+    elif spec_scores is None:
         spec_scores = torch.full((Qt,), float("-inf"), dtype=torch.float32, device=queries.device)
     if workspace is None and use_workspace:
         workspace = torch.empty(max(Qt, 1), dtype=torch.int64, device=queries.device)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().ralm_cache_lookup(cache_ids.data_ptr(), cache_len.data_ptr(), C, R, queries.data_ptr(), Qt,
-                                   q_offsets.data_ptr(), ctypes.byref(ds.desc), spec_ids.data_ptr(),
-                                   spec_scores.data_ptr(), _ptr(workspace), ws_bytes, _stream()))
+    _check(fn(cache_ids.data_ptr(), cache_len.data_ptr(), C, R, queries.data_ptr(), Qt, q_offsets.data_ptr(),
+              ctypes.byref(ds.desc), spec_ids.data_ptr(), spec_scores.data_ptr(), _ptr(workspace), ws_bytes, _stream()))
     return spec_ids, spec_scores
 
 

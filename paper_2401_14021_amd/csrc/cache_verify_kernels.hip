@@ -654,10 +654,16 @@ __global__ void fill_u32_kernel(uint32_t *p, uint32_t v, int64_t n)
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         p[i] = v;
 }
-__global__ void fill_u64_kernel(u64 *p, u64 v, int64_t n)
+// the merge slots of a split lookup, and the answer of queries that no request owns (NULL: not wanted)
+__global__ void lookup_init_kernel(u64 *partial, int32_t *ids, float *scores, int64_t n)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = v;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        if (partial) partial[i] = 0ull;
+        if (ids) {
+            ids[i] = -1;
+            scores[i] = -__builtin_inff();
+        }
+    }
 }
 
 // query preparation: queries rounded to the scan dtype, zero padded to [Qpad, dpad]
@@ -858,25 +864,26 @@ hipError_t launch_lookup(const int32_t *cache_ids, const int32_t *cache_len, int
 hipError_t launch_cache_lookup(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,
                                const float *queries, int64_t Qt, const int64_t *q_offsets,
                                const void *exact, int32_t exact_dtype, int64_t ld, int64_t N, int32_t d,
-                               int32_t metric, int32_t *spec_ids, float *spec_scores, u64 *partial,
+                               int32_t metric, int32_t *spec_ids, float *spec_scores, bool every_row, u64 *partial,
                                hipStream_t stream)
 {
-    if (R <= 0) return hipSuccess;
     // With few requests one workgroup per request leaves most of the chip idle: split every
     // request's cache over `parts` workgroups (at least 64 cached rows each), if the caller
     // gave scratch for the merge.
     int parts = 1;
-    if (partial && R < 128) {
+    if (partial && R > 0 && R < 128) {
         const int64_t want = (256 + R - 1) / R, most = (C + 63) / 64;
         parts = (int)(want < most ? want : most);
         if (parts < 1) parts = 1;
     }
-    if (parts == 1) partial = nullptr;
+    if (parts == 1 || R <= 0) partial = nullptr;
     hipError_t e = hipSuccess;
-    if (partial) {
-        e = launch_fill_u64(partial, 0ull, Qt, stream);
-        if (e != hipSuccess) return e;
+    if ((partial || every_row) && Qt > 0) {
+        hipLaunchKernelGGL(lookup_init_kernel, dim3(grid_for(Qt, 256)), dim3(256), 0, stream, partial,
+                           every_row ? spec_ids : nullptr, every_row ? spec_scores : nullptr, Qt);
+        e = hipGetLastError();
     }
+    if (e != hipSuccess || R <= 0) return e;
     e = launch_lookup(cache_ids, cache_len, C, R, queries, Qt, q_offsets, exact, exact_dtype, ld, N, d, metric, spec_ids,
                       spec_scores, partial, nullptr, nullptr, parts, stream);
     if (e != hipSuccess || !partial) return e;
@@ -955,13 +962,6 @@ hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t strea
     hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_for(n, 256)), dim3(256), 0, stream, p, v, n);
     return hipGetLastError();
 }
-hipError_t launch_fill_u64(u64 *p, u64 v, int64_t n, hipStream_t stream)
-{
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(fill_u64_kernel, dim3(grid_for(n, 256)), dim3(256), 0, stream, p, v, n);
-    return hipGetLastError();
-}
-
 hipError_t launch_l2_scan_copy(const void *src, int32_t src_dtype, int64_t src_ld, void *dst, int32_t dst_dtype,
                                int64_t dst_ld, int64_t N, int32_t d, hipStream_t stream)
 {

@@ -586,6 +586,22 @@ ralm_status check_cache_lookup(const int32_t *cache_ids, const int32_t *cache_le
     return RALM_OK;
 }
 
+ralm_status lookup_impl(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,
+                              const float *queries, int64_t Qt, const int64_t *q_offsets,
+                              const ralm_datastore_t *ds, int32_t *spec_ids, float *spec_scores, void *workspace,
+                              size_t workspace_bytes, void *stream, bool every_row)
+{
+    ralm_status st = check_cache_lookup(cache_ids, cache_len, C, R, queries, Qt, q_offsets, ds, spec_ids, spec_scores);
+    if (st != RALM_OK) return st;
+    if (workspace && ((reinterpret_cast<uintptr_t>(workspace) & 7u) || workspace_bytes < (size_t)Qt * 8))
+        return fail(RALM_ERR_WORKSPACE, "workspace must be 8-byte aligned and hold 8 bytes per query");
+    const int64_t ld = ds->exact_stride ? ds->exact_stride : ds->d;
+    RALM_HIP(launch_cache_lookup(cache_ids, cache_len, C, R, queries, Qt, q_offsets, ds->exact, ds->exact_dtype, ld,
+                                 ds->N, ds->d, ds->metric, spec_ids, spec_scores, every_row, static_cast<u64 *>(workspace),
+                                 static_cast<hipStream_t>(stream)));
+    return RALM_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -597,15 +613,17 @@ ralm_status ralm_cache_lookup(const int32_t *cache_ids, const int32_t *cache_len
                               const ralm_datastore_t *ds, int32_t *spec_ids, float *spec_scores, void *workspace,
                               size_t workspace_bytes, void *stream)
 {
-    ralm_status st = check_cache_lookup(cache_ids, cache_len, C, R, queries, Qt, q_offsets, ds, spec_ids, spec_scores);
-    if (st != RALM_OK) return st;
-    if (workspace && ((reinterpret_cast<uintptr_t>(workspace) & 7u) || workspace_bytes < (size_t)Qt * 8))
-        return fail(RALM_ERR_WORKSPACE, "workspace must be 8-byte aligned and hold 8 bytes per query");
-    const int64_t ld = ds->exact_stride ? ds->exact_stride : ds->d;
-    RALM_HIP(launch_cache_lookup(cache_ids, cache_len, C, R, queries, Qt, q_offsets, ds->exact, ds->exact_dtype, ld,
-                                 ds->N, ds->d, ds->metric, spec_ids, spec_scores, static_cast<u64 *>(workspace),
-                                 static_cast<hipStream_t>(stream)));
-    return RALM_OK;
+    return lookup_impl(cache_ids, cache_len, C, R, queries, Qt, q_offsets, ds, spec_ids, spec_scores, workspace,
+                       workspace_bytes, stream, false);
+}
+
+ralm_status ralm_cache_lookup_all(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,
+                              const float *queries, int64_t Qt, const int64_t *q_offsets,
+                              const ralm_datastore_t *ds, int32_t *spec_ids, float *spec_scores, void *workspace,
+                              size_t workspace_bytes, void *stream)
+{
+    return lookup_impl(cache_ids, cache_len, C, R, queries, Qt, q_offsets, ds, spec_ids, spec_scores, workspace,
+                       workspace_bytes, stream, true);
 }
 
 }  // extern "C"

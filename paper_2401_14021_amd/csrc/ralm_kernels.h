@@ -47,7 +47,6 @@ int scan_bn_for(int64_t Q);
 hipError_t launch_scan(const ScanParams &p, int n_cu, hipStream_t stream);
 
 hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t stream);
-hipError_t launch_fill_u64(u64 *p, u64 v, int64_t n, hipStream_t stream);
 
 // fp32 [Q, d] -> scan dtype [Qpad, dpad], zero padded
 // also clears the n0 words at z0 (the flag block, but for its number of queries) and the n1 words at z1
@@ -119,10 +118,11 @@ hipError_t launch_exact_pass(const float *queries, int64_t Q, const void *exact,
                              const u64 *tau_exact, u64 *cand, uint32_t *cnt, uint32_t cap, int32_t *out_ids,
                              float *out_scores, int n_cu, hipStream_t stream);
 
+// every_row: queries that no request owns are answered with id -1 / score -inf, in the launch that clears `partial`
 hipError_t launch_cache_lookup(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,
                                const float *queries, int64_t Qt, const int64_t *q_offsets,
                                const void *exact, int32_t exact_dtype, int64_t ld, int64_t N, int32_t d,
-                               int32_t metric, int32_t *spec_ids, float *spec_scores, u64 *partial,
+                               int32_t metric, int32_t *spec_ids, float *spec_scores, bool every_row, u64 *partial,
                                hipStream_t stream);
 
 constexpr int CACHE_LOOKUP_MAX_D = 2048;   // the lookup kernels hold a row in registers

@@ -1083,6 +1083,32 @@ def test_cache_lookup_topk_matches_oracle(B, oracle, R, C, k, d, metric):
     assert np.array_equal(sc.cpu().numpy(), wsc)
 
 
+@pytest.mark.parametrize("R,C", [(3, 40), (130, 40), (2, 500)])
+@pytest.mark.parametrize("use_workspace", [True, False])
+def test_cache_lookup_answers_queries_that_no_request_owns(B, oracle, R, C, use_workspace):
+    """Outputs that the binding allocates hold -1 / -inf for queries in front of and behind the owned ones, however the
+    lookup is split; the caller's own outputs are left as they are there."""
+    rng = np.random.default_rng(R + C)
+    N, d, lead, behind = 900, 64, 5, 300
+    X = torch.from_numpy(rng.integers(-3, 4, size=(N, d)).astype(np.float32))
+    off = lead + 2 * np.arange(R + 1, dtype=np.int64)
+    Qt = int(off[-1]) + behind
+    Qm = torch.from_numpy(rng.integers(-3, 4, size=(Qt, d)).astype(np.float32))
+    cache = rng.integers(0, N, size=(R, C)).astype(np.int32)
+    lens = np.full(R, C, dtype=np.int32)
+    args = (torch.from_numpy(cache).cuda(), torch.from_numpy(lens).cuda(), Qm.cuda(), torch.from_numpy(off).cuda(),
+            B.Datastore(X.cuda()))
+    wi, wsc = np.full(Qt, -1, np.int32), np.full(Qt, -np.inf, np.float32)
+    oi, osc = oracle.cache_lookup(cache, lens, Qm.numpy()[:Qt - behind], off, X.numpy())
+    wi[lead:Qt - behind], wsc[lead:Qt - behind] = oi[lead:], osc[lead:]
+    ids, sc = B.ralm_cache_lookup(*args, use_workspace=use_workspace)
+    assert np.array_equal(ids.cpu().numpy(), wi) and np.array_equal(sc.cpu().numpy(), wsc)
+    mine = torch.full((Qt,), 77, dtype=torch.int32, device="cuda"), torch.full((Qt,), 7.5, device="cuda")
+    ids, sc = B.ralm_cache_lookup(*args, spec_ids=mine[0], spec_scores=mine[1], use_workspace=use_workspace)
+    wi[:lead], wi[Qt - behind:], wsc[:lead], wsc[Qt - behind:] = 77, 77, 7.5, 7.5
+    assert np.array_equal(ids.cpu().numpy(), wi) and np.array_equal(sc.cpu().numpy(), wsc)
+
+
 @pytest.mark.parametrize("dtype,d,metric", [("f16", 128, "ip"), ("f16", 136, "ip"), ("f16", 1024, "l2"), ("f32", 64, "ip"),
                                             ("f32", 2048, "l2"), ("f32", 2056, "ip"), ("f16", 2176, "ip")])
 @pytest.mark.parametrize("C,k", [(1, 1), (129, 129), (600, 40)])
