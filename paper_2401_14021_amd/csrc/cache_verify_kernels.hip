@@ -74,7 +74,9 @@ static_assert(CL_QB == 4, "the block dispatch in cache_lookup_kernel is written 
 // L2: the score is minus the squared distance (KNN-LM datastores) instead of the inner product.
 // MAXQ (8 or 16): queries of a request held in LDS at a time (more are served in groups); their
 // bests sit in registers, which is why wide rows take 8.
-template <int EX, int NCH, int NW, bool L2, int MAXQ>
+// LIST: the keys of all (query, cached row) pairs go to `list` instead of the best to the outputs (a template
+// parameter: tested at run time it cost the lookup a quarter of its time).
+template <int EX, int NCH, int NW, bool L2, int MAXQ, bool LIST>
 __global__ __launch_bounds__(NW * 64) void cache_lookup_kernel(
     const int32_t *__restrict__ cache_ids, const int32_t *__restrict__ cache_len, int C,
     const float *__restrict__ queries, int64_t Qt, const int64_t *__restrict__ q_offsets,
@@ -99,7 +101,7 @@ __global__ __launch_bounds__(NW * 64) void cache_lookup_kernel(
     len = len < 0 ? 0 : (len > C ? C : len);
     const int32_t *ids = cache_ids + r * (int64_t)C;
     const int e_step = parts * NW * CL_ROWS;
-    if (list && part == 0)
+    if (LIST && part == 0)
         for (int64_t q = q_lo + tid; q < q_hi; q += NW * 64) list_len[q] = (uint32_t)len;
 
     for (int64_t g0 = q_lo; g0 < q_hi; g0 += qgroup) {
@@ -188,7 +190,7 @@ __global__ __launch_bounds__(NW * 64) void cache_lookup_kernel(
                 for (int u = 0; u < U; ++u) {
                     const double t = row16_sum(sum[u]);
                     const float sc = (L2 ? (float)(-t) : (float)t) + 0.0f;   // -0 counts as +0, as in a key
-                    if (list) {   // uniform
+                    if constexpr (LIST) {
                         if (sub == 0 && e0 + slot < len) list[(g0 + q0 + u) * C + e0 + slot] = ok ? make_key(sc, id) : 0ull;
                         continue;
                     }
@@ -215,7 +217,7 @@ __global__ __launch_bounds__(NW * 64) void cache_lookup_kernel(
                 if (nq > 12) block(std::integral_constant<int, 12>{});
             }
         }
-        if (list) continue;
+        if (LIST) continue;
         if (sub == 0) {
 #pragma unroll
             for (int i = 0; i < MAXQ; ++i)
@@ -756,8 +758,8 @@ int grid_for(int64_t n, int block)
     return (int)g;
 }
 
-template <int EX, bool L2>
-hipError_t launch_cache_ex(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,
+template <int EX, bool L2, bool LIST>
+hipError_t launch_cache_ex_form(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,
                            const float *queries, int64_t Qt, const int64_t *q_offsets, const void *exact,
                            int64_t ld, int64_t N, int32_t d, int32_t *spec_ids, float *spec_scores,
                            u64 *partial, u64 *list, uint32_t *list_len, int parts, hipStream_t stream)
@@ -771,7 +773,7 @@ hipError_t launch_cache_ex(const int32_t *cache_ids, const int32_t *cache_len, i
     // bounds the waves a block can hold
 #define RALM_CL(NCHV, NWV, MAXQV)                                                                           \
     do {                                                                                                    \
-        auto kern = cache_lookup_kernel<EX, NCHV, NWV, L2, MAXQV>;                                          \
+        auto kern = cache_lookup_kernel<EX, NCHV, NWV, L2, MAXQV, LIST>;                                    \
         static std::atomic<bool> attr_done{false};                                                          \
         if (!attr_done.load(std::memory_order_acquire)) {                                                   \
             hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),                        \
@@ -793,6 +795,18 @@ hipError_t launch_cache_ex(const int32_t *cache_ids, const int32_t *cache_len, i
     else return hipErrorInvalidValue;
 #undef RALM_CL
     return hipGetLastError();
+}
+
+template <int EX, bool L2>
+hipError_t launch_cache_ex(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,
+                           const float *queries, int64_t Qt, const int64_t *q_offsets, const void *exact,
+                           int64_t ld, int64_t N, int32_t d, int32_t *spec_ids, float *spec_scores,
+                           u64 *partial, u64 *list, uint32_t *list_len, int parts, hipStream_t stream)
+{
+    return list ? launch_cache_ex_form<EX, L2, true>(cache_ids, cache_len, C, R, queries, Qt, q_offsets, exact, ld, N, d, spec_ids,
+                                                     spec_scores, partial, list, list_len, parts, stream)
+                : launch_cache_ex_form<EX, L2, false>(cache_ids, cache_len, C, R, queries, Qt, q_offsets, exact, ld, N, d,
+                                                      spec_ids, spec_scores, partial, list, list_len, parts, stream);
 }
 
 // The matrix-core form of the lookup, for the shapes it is written for: inner product, rows of a
