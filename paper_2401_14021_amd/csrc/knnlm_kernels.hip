@@ -6,6 +6,7 @@
 //                      the probability of a token is the sum of the weights of the entries that
 //                      carry it; the most probable token (smallest id on ties) is reported.
 //                      All of it in double, rounded once to fp32 on output.
+#include "../../include/ralm.h"
 #include "ralm_common.h"
 #include "ralm_kernels.h"
 
@@ -14,6 +15,8 @@ namespace ralm {
 namespace {
 
 constexpr int KP_THREADS = 256, KP_WAVES = KP_THREADS / 64;
+constexpr int KP_MAX_PER = RALM_MAX_K / KP_THREADS;   // entries per thread
+static_assert(RALM_MAX_K % KP_THREADS == 0 && (RALM_MAX_K & (RALM_MAX_K - 1)) == 0, "a power of two of at least one entry per thread");
 
 __device__ __forceinline__ double block_sum(double x, double *red /*[KP_WAVES]*/)
 {
@@ -99,7 +102,20 @@ __global__ __launch_bounds__(KP_THREADS) void knnlm_probs_kernel(
 
     // entries grouped by token, ranks ascending inside a group
     sort_keys<KP_THREADS, false>(keys, kp2);
-    // the thread at the start of a group adds the group's weights in rank order
+    // weights into the sorted order, so that a group's are neighbours
+    double sorted[KP_MAX_PER];
+#pragma unroll
+    for (int c = 0; c < KP_MAX_PER; ++c) {
+        const int i = c * KP_THREADS + tid;
+        sorted[c] = i < kp2 && keys[i] != ~0ull ? e[(uint32_t)keys[i]] : 0.0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < KP_MAX_PER; ++c)
+        if (c * KP_THREADS + tid < kp2) e[c * KP_THREADS + tid] = sorted[c];
+    __syncthreads();
+    // the thread at the start of a group adds the group's weights in rank order, four entries' reads at a
+    // time (one after the other, a token with many entries was a chain of as many LDS round trips)
     double my_p = -1.0;
     int32_t my_tok = -1;
     for (int i = tid; i < kp2; i += KP_THREADS) {
@@ -108,8 +124,22 @@ __global__ __launch_bounds__(KP_THREADS) void knnlm_probs_kernel(
         const uint32_t t32 = (uint32_t)(key >> 32);
         if (i > 0 && (uint32_t)(keys[i - 1] >> 32) == t32) continue;
         double p = 0.0;
-        for (int j = i; j < kp2 && (uint32_t)(keys[j] >> 32) == t32 && keys[j] != ~0ull; ++j)
-            p += e[(uint32_t)keys[j]];
+        bool more = true;
+        for (int j = i; more && j < kp2; j += 4) {
+            u64 kj[4];
+            double ej[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int at = j + u < kp2 ? j + u : kp2 - 1;
+                kj[u] = keys[at];
+                ej[u] = e[at];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                more = more && j + u < kp2 && (uint32_t)(kj[u] >> 32) == t32 && kj[u] != ~0ull;
+                p = more ? p + ej[u] : p;
+            }
+        }
         const int32_t tok = (int32_t)(t32 ^ 0x80000000u);
         if (p > my_p || (p == my_p && tok < my_tok)) {
             my_p = p;
