@@ -291,7 +291,8 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
     sp.lists_empty = 0;
     // one stage: scan the tiles sp describes, then cut every list down to its k' best
     int32_t stage_no = 0;
-    // (the last stage's lists are cut down by the re-score)
+    // (short lists: the last stage's are cut down by the re-score)
+    const bool cut_in_rescore = pl.k_prime < RESCORE_CUT_MIN;
     auto run_stage = [&](int64_t expected, bool last) -> ralm_status {
         if (sp.n_row_tiles <= 0) return RALM_OK;
         const bool prof = g_prof_on && g_prof_n < MAX_PROF;
@@ -308,7 +309,7 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
             RALM_HIP(hipEventRecord(g_prof_ev[g_prof_n][1], stream));
             ++g_prof_n;
         }
-        if (last) return RALM_OK;
+        if (last && cut_in_rescore) return RALM_OK;
         RALM_HIP(launch_select(cand, cnt, pl.cap, pl.k_prime, Q, tau, lost, flags, stage_no++, expected, stream));
         return RALM_OK;
     };
@@ -363,8 +364,12 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
     const float u = mma_dt == RALM_F16 ? 1.f / 2048.f : 1.f / 256.f;   // 11 / 8 significant bits
     cert.u_query = u;
     cert.u_rows = (scan == ds->exact && scan_dt == ds->exact_dtype && scan_dt != RALM_F32) ? 0.f : u;
-    RALM_HIP(launch_rescore(cand, cnt, CNT_PITCH, pl.cap, pl.k_prime, queries, Q, ds->exact, ds->exact_dtype, exact_ld, ds->d,
-                            ds->metric, k, out_ids, out_scores, out_margin, cert, stream));
+    if (cut_in_rescore)
+        RALM_HIP(launch_rescore(cand, cnt, CNT_PITCH, pl.cap, pl.k_prime, queries, Q, ds->exact, ds->exact_dtype, exact_ld,
+                                ds->d, ds->metric, k, out_ids, out_scores, out_margin, cert, stream));
+    else
+        RALM_HIP(launch_rescore_cut(cand, cnt, pl.cap, pl.k_prime, queries, Q, ds->exact, ds->exact_dtype, exact_ld, ds->d,
+                                    ds->metric, k, out_ids, out_scores, out_margin, cert, stream));
     RALM_HIP(launch_exact_pass(queries, Q, ds->exact, ds->exact_dtype, exact_ld, ds->N, ds->d, ds->metric, k, fb_list,
                                flags, tau, cand, cnt, pl.cap, out_ids, out_scores, n_cu, stream));
     return RALM_OK;

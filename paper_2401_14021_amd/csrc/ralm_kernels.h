@@ -111,6 +111,14 @@ hipError_t launch_rescore(const u64 *cand, const uint32_t *cnt, int cnt_pitch, u
                           int32_t d, int32_t metric, int32_t k, int32_t *out_ids, float *out_scores,
                           float *out_margin, const CertifyParams &cert, hipStream_t stream);
 
+constexpr int RESCORE_CUT_MIN = 257;   // k' from which launch_rescore_cut is used
+// the same with the check, for lists that launch_select has cut down to their k' best (at least 16384 slots,
+// CNT_PITCH); overwrites the slots behind the k' keys
+hipError_t launch_rescore_cut(u64 *cand, const uint32_t *cnt, uint32_t cap, int32_t k_prime, const float *queries, int64_t Q,
+                              const void *exact, int32_t exact_dtype, int64_t ld, int32_t d, int32_t metric, int32_t k,
+                              int32_t *out_ids, float *out_scores, float *out_margin, const CertifyParams &cert,
+                              hipStream_t stream);
+
 // exact scan + final ranking for the queries queued by the re-score (two launches that return at
 // once when none is queued)
 hipError_t launch_exact_pass(const float *queries, int64_t Q, const void *exact, int32_t exact_dtype, int64_t ld,

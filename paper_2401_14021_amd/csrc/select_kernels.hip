@@ -16,6 +16,7 @@
 //                  key are collected, and the best k of them are the answer.  Both kernels
 //                  are always launched and return at once when nothing is queued.
 #include <atomic>
+#include <type_traits>
 
 #include "ralm_common.h"
 #include "ralm_kernels.h"
@@ -340,21 +341,154 @@ __device__ __forceinline__ void exact_accum4(double &sum, const float4 &x, const
     }
 }
 
-// elements j .. j+3 of a row of the exact copy, widened exactly to fp32
+// elements j .. j+3 of a row of the exact copy, as they are and widened exactly to fp32
+template <int EX>
+using ExactPiece = typename std::conditional<EX == DT_F32, float4, uint2>::type;
+
+__device__ __forceinline__ float4 widen(const float4 &v) { return v; }
+__device__ __forceinline__ float4 widen(const uint2 &h)
+{
+    return make_float4(f16_bits_to_f32(h.x & 0xffffu), f16_bits_to_f32(h.x >> 16), f16_bits_to_f32(h.y & 0xffffu),
+                       f16_bits_to_f32(h.y >> 16));
+}
+template <int EX>
+__device__ __forceinline__ ExactPiece<EX> exact_piece4(const void *__restrict__ exact, int64_t row_off, int j)
+{
+    const unsigned char *at = static_cast<const unsigned char *>(exact) + (row_off + j) * (EX == DT_F32 ? 4 : 2);
+    return *reinterpret_cast<const ExactPiece<EX> *>(at);
+}
 template <int EX>
 __device__ __forceinline__ float4 exact_load4(const void *__restrict__ exact, int64_t row_off, int j)
 {
-    if constexpr (EX == DT_F32) {
-        return *reinterpret_cast<const float4 *>(static_cast<const float *>(exact) + row_off + j);
-    } else {
-        const uint2 h = *reinterpret_cast<const uint2 *>(static_cast<const uint16_t *>(exact) + row_off + j);
-        return make_float4(f16_bits_to_f32(h.x & 0xffffu), f16_bits_to_f32(h.x >> 16), f16_bits_to_f32(h.y & 0xffffu),
-                           f16_bits_to_f32(h.y >> 16));
-    }
+    return widen(exact_piece4<EX>(exact, row_off, j));
 }
 
 constexpr int RS_ROWS = 4;             // rows that a wave scores together: their loads are in flight at once
 constexpr int RS_COUNT_MAX = 256;      // up to this many candidates are ranked by counting
+
+// What a wave learns from the rows that it scores (the sums are those of its lanes together).
+struct RowStats {
+    u64 min_scan = ~0ull;             // worst scan key
+    double e2 = 0.0, x2max = 0.0;     // sum of squared scan errors, largest squared row norm
+};
+
+// Exact scores of the candidates list[begin, end), whose scan keys are in LDS, by the NW waves of a workgroup: the
+// exact key of list[c] goes to keys[c].  A wave takes RS_ROWS rows at a time, whose loads are in flight
+// together.  stats: whether the check's numbers are wanted.
+template <int EX, bool L2, int NW>
+__device__ __forceinline__ RowStats score_rows(const u64 *list, int begin, int end, const float *__restrict__ qv, float q_sq,
+                                               const void *__restrict__ exact, int64_t ld, int d, bool stats, u64 *keys)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    RowStats st;
+    for (int c0 = begin + wave; c0 < end; c0 += NW * RS_ROWS) {
+        int64_t row_off[RS_ROWS];
+        double sum[RS_ROWS], x2[RS_ROWS];
+#pragma unroll
+        for (int u = 0; u < RS_ROWS; ++u) {
+            const int c = c0 + u * NW;
+            row_off[u] = (int64_t)key_id(list[c < end ? c : c0]) * ld;   // past the end: the first row again
+            sum[u] = x2[u] = 0.0;
+        }
+        // two steps' loads in flight at once (their sums in order)
+        for (int j = lane * 4; j < d; j += 512) {
+            const int j2 = j + 256 < d ? j + 256 : j;
+            ExactPiece<EX> x[2][RS_ROWS];
+#pragma unroll
+            for (int u = 0; u < RS_ROWS; ++u) x[0][u] = exact_piece4<EX>(exact, row_off[u], j);
+#pragma unroll
+            for (int u = 0; u < RS_ROWS; ++u) x[1][u] = exact_piece4<EX>(exact, row_off[u], j2);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (h == 1 && j2 == j) break;
+                const float4 y = *reinterpret_cast<const float4 *>(qv + j + h * 256);
+#pragma unroll
+                for (int u = 0; u < RS_ROWS; ++u) {
+                    const float4 xv = widen(x[h][u]);
+                    exact_accum4<L2>(sum[u], xv, y);
+                    if (stats)
+                        x2[u] += (double)xv.x * (double)xv.x + (double)xv.y * (double)xv.y + (double)xv.z * (double)xv.z +
+                                 (double)xv.w * (double)xv.w;
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < RS_ROWS; ++u) {
+            const int c = c0 + u * NW;
+            if (c < end) {   // wave-uniform
+                const u64 skey = list[c];
+                st.min_scan = skey < st.min_scan ? skey : st.min_scan;
+                const double t = wave_sum(sum[u]);
+                const float score = L2 ? (float)(-t) : (float)t;
+                if (stats) {
+                    const double r2 = wave_sum(x2[u]);
+                    const double e = (double)(key_score(skey) - q_sq) - (double)score;
+                    st.e2 += e * e;
+                    st.x2max = r2 > st.x2max ? r2 : st.x2max;
+                }
+                if (lane == 0) keys[c] = make_key(score, key_id(skey));
+            }
+        }
+    }
+    return st;
+}
+
+// |q|^2, every thread of the workgroup gets it: part of the scan's score under L2, and of the rounding bound
+template <int NT>
+__device__ __forceinline__ double query_norm2(const float *__restrict__ qv, int d, double *s_q2 /* [NT / 64] in LDS */)
+{
+    double q2 = 0.0;
+    for (int j = threadIdx.x; j < d; j += NT) q2 += (double)qv[j] * (double)qv[j];
+    q2 = wave_sum(q2);
+    if ((threadIdx.x & 63) == 0) s_q2[threadIdx.x >> 6] = q2;
+    __syncthreads();
+    q2 = 0.0;
+    for (int w = 0; w < NT / 64; ++w) q2 += s_q2[w];
+    return q2;
+}
+
+// The margin of query q and the verdict of the check (one thread): `rank_k` is the key at rank k of the
+// n re-scored candidates, the statistics are those of all of them.
+template <bool L2>
+__device__ void certify(const CertifyParams &cert, float *__restrict__ out_margin, int64_t q, int cnt_pitch, int n, int k,
+                        int k_prime, int d, double q2, u64 rank_k, u64 min_scan, double e2, double x2m)
+{
+    const float q_sq = L2 ? (float)q2 : 0.f;
+    // margin: exact score at rank k minus the scan's score of the worst kept candidate.  A row
+    // that was not kept has a scan score at most the latter, so it can belong in the top k only
+    // if the scan mis-scored it by at least the margin.
+    float margin;
+    if (n < k)
+        margin = __builtin_nanf("");
+    else if (n < k_prime)
+        margin = __builtin_inff();   // every row of the datastore was re-scored
+    else
+        margin = key_score(rank_k) - (key_score(min_scan) - q_sq);
+    if (out_margin) out_margin[q] = margin;
+    if (!cert.flags) return;
+    // what the scan's rounding can do to a score: the deterministic bound (every rounding
+    // error aligned; rows outside the candidates are taken to be no longer than the longest
+    // candidate), and the spread actually seen on this query's candidates
+    const double qn = sqrt(q2), xn = sqrt(x2m);
+    const double uq = cert.u_query, ux = cert.u_rows;
+    double hard = (uq + ux + uq * ux) * qn * xn + (double)d * 5.9604644775390625e-08 * qn * xn;
+    if (L2) hard = 2.0 * hard + (ux * ux + (double)d * 5.9604644775390625e-08) * x2m;
+    const double soft = n > 0 ? 8.0 * sqrt(e2 / (double)n) : 0.0;
+    const bool truncated = cert.lost && cert.lost[q] != 0;
+    const bool all_rows = n < k_prime && !truncated;
+    const double m = (double)margin;
+    const bool soft_ok = all_rows || (!truncated && n >= k && (m > soft || (soft == 0.0 && m >= 0.0)));
+    uint32_t *status = reinterpret_cast<uint32_t *>(reinterpret_cast<unsigned char *>(cert.flags) + status_offset());
+    status[q] = soft_ok ? (all_rows || m > hard ? STATUS_SOFT | STATUS_HARD : STATUS_SOFT) : 0u;
+    if (!soft_ok && n >= k) {
+        // answered again by the exact pass: every row whose exact key reaches the exact
+        // rank-k key found here (a lower bound of the true one) is collected in the list
+        const int at = atomicAdd(cert.flags + FLAG_FALLBACKS, 1);
+        cert.fb_list[at] = (int32_t)q;
+        cert.tau_exact[q] = rank_k;
+        cert.cnt_rw[q * cnt_pitch] = 0u;
+    }
+}
 
 // Re-score of the candidates, final ranking, and the check of the result (see CertifyParams).
 // EX: DT_F32 or DT_F16 exact rows.  L2: the score is minus the squared distance; the scan's
@@ -364,7 +498,7 @@ constexpr int RS_COUNT_MAX = 256;      // up to this many candidates are ranked 
 // one wave's rows, which is why a wave takes RS_ROWS of them at a time (k' = 64: each of the 16
 // waves has its four rows in flight at once) and why the list is cut down here and not by a launch of
 // its own.  With the last select (a launch of its own before): Q = 1, k' = 64: 26 -> 14 us;
-// Q = 1024: 103 -> 50 us; Q = 256, k' = 2048, 1024 fp16 elements: 563 -> 326 us.
+// Q = 1024: 103 -> 50 us.
 template <int EX, bool L2, int RS_THREADS>
 __global__ __launch_bounds__(RS_THREADS) void rescore_kernel(const u64 *__restrict__ cand,
                                                       const uint32_t *__restrict__ cnt, int cnt_pitch, uint32_t cap,
@@ -389,13 +523,7 @@ __global__ __launch_bounds__(RS_THREADS) void rescore_kernel(const u64 *__restri
     const float *qv = queries + q * (int64_t)d;
     const bool stats = out_margin || cert.flags;   // wave-uniform
 
-    // |q|^2: part of the scan's score under L2, and of the rounding bound
-    double q2 = 0.0;
-    if (stats) {
-        for (int j = tid; j < d; j += RS_THREADS) q2 += (double)qv[j] * (double)qv[j];
-        q2 = wave_sum(q2);
-        if (lane == 0) s_q2[wave] = q2;
-    }
+    const double q2 = stats ? query_norm2<RS_THREADS>(qv, d, s_q2) : 0.0;
     if (tid < RS_COUNT_MAX) s_rank[tid] = 0;
     uint32_t n_list = cnt[q * cnt_pitch];
     n_list = cert.flags ? list_length(n_list, q, cap, cert.lost, cert.flags, cert.stage) : (n_list < cap ? n_list : cap);
@@ -407,58 +535,11 @@ __global__ __launch_bounds__(RS_THREADS) void rescore_kernel(const u64 *__restri
         for (int i = tid; i < n; i += RS_THREADS) list[i] = mine[i];
     }
     __syncthreads();
-    if (stats) {
-        q2 = 0.0;
-        for (int w = 0; w < RS_WAVES; ++w) q2 += s_q2[w];
-    }
-    const float q_sq = L2 ? (float)q2 : 0.f;
-
-    u64 min_scan = ~0ull;
-    double e2 = 0.0, x2max = 0.0;   // sum of squared scan errors, largest squared row norm (lane 0)
-    for (int c0 = wave; c0 < n; c0 += RS_WAVES * RS_ROWS) {
-        int64_t row_off[RS_ROWS];
-        double sum[RS_ROWS], x2[RS_ROWS];
-#pragma unroll
-        for (int u = 0; u < RS_ROWS; ++u) {
-            const int c = c0 + u * RS_WAVES;
-            row_off[u] = (int64_t)key_id(list[c < n ? c : c0]) * ld;   // past the end: the first row again
-            sum[u] = x2[u] = 0.0;
-        }
-        for (int j = lane * 4; j < d; j += 256) {
-            float4 x[RS_ROWS];
-#pragma unroll
-            for (int u = 0; u < RS_ROWS; ++u) x[u] = exact_load4<EX>(exact, row_off[u], j);
-            const float4 y = *reinterpret_cast<const float4 *>(qv + j);
-#pragma unroll
-            for (int u = 0; u < RS_ROWS; ++u) {
-                exact_accum4<L2>(sum[u], x[u], y);
-                if (stats)
-                    x2[u] += (double)x[u].x * (double)x[u].x + (double)x[u].y * (double)x[u].y +
-                             (double)x[u].z * (double)x[u].z + (double)x[u].w * (double)x[u].w;
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < RS_ROWS; ++u) {
-            const int c = c0 + u * RS_WAVES;
-            if (c < n) {   // wave-uniform
-                const u64 skey = list[c];
-                min_scan = skey < min_scan ? skey : min_scan;
-                const double t = wave_sum(sum[u]);
-                const float score = L2 ? (float)(-t) : (float)t;
-                if (stats) {
-                    const double r2 = wave_sum(x2[u]);
-                    const double e = (double)(key_score(skey) - q_sq) - (double)score;
-                    e2 += e * e;
-                    x2max = r2 > x2max ? r2 : x2max;
-                }
-                if (lane == 0) keys[c] = make_key(score, key_id(skey));
-            }
-        }
-    }
+    const RowStats st = score_rows<EX, L2, RS_WAVES>(list, 0, n, qv, L2 ? (float)q2 : 0.f, exact, ld, d, stats, keys);
     if (lane == 0) {
-        s_min_scan[wave] = min_scan;
-        s_e2[wave] = e2;
-        s_x2[wave] = x2max;
+        s_min_scan[wave] = st.min_scan;
+        s_e2[wave] = st.e2;
+        s_x2[wave] = st.x2max;
     }
 
     const u64 *ranked;   // descending by key
@@ -491,48 +572,104 @@ __global__ __launch_bounds__(RS_THREADS) void rescore_kernel(const u64 *__restri
         out_scores[q * k + r] = have ? key_score(key) : -__builtin_inff();
     }
     if (stats && tid == 0) {
-        u64 ms = s_min_scan[0];
-        double se2 = s_e2[0], x2m = s_x2[0];
+        RowStats all = {s_min_scan[0], s_e2[0], s_x2[0]};
         for (int w = 1; w < RS_WAVES; ++w) {
-            ms = s_min_scan[w] < ms ? s_min_scan[w] : ms;
-            se2 += s_e2[w];
-            x2m = s_x2[w] > x2m ? s_x2[w] : x2m;
+            all.min_scan = s_min_scan[w] < all.min_scan ? s_min_scan[w] : all.min_scan;
+            all.e2 += s_e2[w];
+            all.x2max = s_x2[w] > all.x2max ? s_x2[w] : all.x2max;
         }
-        // margin: exact score at rank k minus the scan's score of the worst kept candidate.  A row
-        // that was not kept has a scan score at most the latter, so it can belong in the top k only
-        // if the scan mis-scored it by at least the margin.
-        float margin;
-        if (n < k)
-            margin = __builtin_nanf("");
-        else if (n < k_prime)
-            margin = __builtin_inff();   // every row of the datastore was re-scored
-        else
-            margin = key_score(ranked[k - 1]) - (key_score(ms) - q_sq);
-        if (out_margin) out_margin[q] = margin;
-        if (cert.flags) {
-            // what the scan's rounding can do to a score: the deterministic bound (every rounding
-            // error aligned; rows outside the candidates are taken to be no longer than the longest
-            // candidate), and the spread actually seen on this query's candidates
-            const double qn = sqrt(q2), xn = sqrt(x2m);
-            const double uq = cert.u_query, ux = cert.u_rows;
-            double hard = (uq + ux + uq * ux) * qn * xn + (double)d * 5.9604644775390625e-08 * qn * xn;
-            if (L2) hard = 2.0 * hard + (ux * ux + (double)d * 5.9604644775390625e-08) * x2m;
-            const double soft = n > 0 ? 8.0 * sqrt(se2 / (double)n) : 0.0;
-            const bool truncated = cert.lost && cert.lost[q] != 0;
-            const bool all_rows = n < k_prime && !truncated;
-            const double m = (double)margin;
-            const bool soft_ok = all_rows || (!truncated && n >= k && (m > soft || (soft == 0.0 && m >= 0.0)));
-            uint32_t *status = reinterpret_cast<uint32_t *>(reinterpret_cast<unsigned char *>(cert.flags) + status_offset());
-            status[q] = soft_ok ? (all_rows || m > hard ? STATUS_SOFT | STATUS_HARD : STATUS_SOFT) : 0u;
-            if (!soft_ok && n >= k) {
-                // answered again by the exact pass: every row whose exact key reaches the exact
-                // rank-k key found here (a lower bound of the true one) is collected in the list
-                const int at = atomicAdd(cert.flags + FLAG_FALLBACKS, 1);
-                cert.fb_list[at] = (int32_t)q;
-                cert.tau_exact[q] = ranked[k - 1];
-                cert.cnt_rw[q * cnt_pitch] = 0u;
-            }
+        certify<L2>(cert, out_margin, q, cnt_pitch, n, k, k_prime, d, q2, n >= k ? ranked[k - 1] : 0ull, all.min_scan, all.e2,
+                    all.x2max);
+    }
+}
+
+// The same in two launches for many candidates per query, whose list a select has cut down before: the rows
+// are scored by several workgroups per query, and one more ranks them.  In one workgroup the phases of a query
+// (its list, its rows, its sort) follow each other on a CU with nothing beside them, and few queries leave most
+// of the chip idle.  The exact keys go to the list's slots [k', 2 k') and the statistics of
+// part p to the four slots from 2 k' + 4 p on (lists have at least 16384 slots).
+// Neighbour rounds: 256 queries, k' = 2048, 1024 fp16 elements 6376 -> 6230 us; 16 queries 813 -> 596 us; 64 queries,
+// k' = 512, squared distance: 68 -> 36 us for the select and both launches; 800 queries, k' = 512: 1874 -> 1854 us.
+constexpr int RP_THREADS = 512, RP_WAVES = RP_THREADS / 64;
+
+template <int EX, bool L2>
+__global__ __launch_bounds__(RP_THREADS) void rescore_rows_kernel(u64 *__restrict__ cand, const uint32_t *__restrict__ cnt,
+                                                                  uint32_t cap, int k_prime, const float *__restrict__ queries,
+                                                                  const void *__restrict__ exact, int64_t ld, int d)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    u64 *list = reinterpret_cast<u64 *>(smem);   // [rows of a part]
+    __shared__ u64 s_min_scan[RP_WAVES];
+    __shared__ double s_e2[RP_WAVES], s_x2[RP_WAVES], s_q2[RP_WAVES];
+
+    const int64_t q = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int part = blockIdx.y, per = (k_prime + (int)gridDim.y - 1) / (int)gridDim.y;
+    u64 *mine = cand + q * (int64_t)cap;
+    const float *qv = queries + q * (int64_t)d;
+    const int n = (int)cnt[q * CNT_PITCH];       // at most k'
+    const int begin = part * per;
+    const int rows = n - begin < per ? (n - begin > 0 ? n - begin : 0) : per;
+    for (int i = tid; i < rows; i += RP_THREADS) list[i] = mine[begin + i];
+    const double q2 = L2 ? query_norm2<RP_THREADS>(qv, d, s_q2) : 0.0;
+    __syncthreads();
+    const RowStats st = score_rows<EX, L2, RP_WAVES>(list, 0, rows, qv, L2 ? (float)q2 : 0.f, exact, ld, d, true,
+                                                     mine + k_prime + begin);
+    if (lane == 0) {
+        s_min_scan[wave] = st.min_scan;
+        s_e2[wave] = st.e2;
+        s_x2[wave] = st.x2max;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        RowStats all = {s_min_scan[0], s_e2[0], s_x2[0]};
+        for (int w = 1; w < RP_WAVES; ++w) {
+            all.min_scan = s_min_scan[w] < all.min_scan ? s_min_scan[w] : all.min_scan;
+            all.e2 += s_e2[w];
+            all.x2max = s_x2[w] > all.x2max ? s_x2[w] : all.x2max;
         }
+        u64 *to = mine + 2 * k_prime + 4 * part;
+        to[0] = all.min_scan;
+        to[1] = (u64)__double_as_longlong(all.e2);
+        to[2] = (u64)__double_as_longlong(all.x2max);
+    }
+}
+
+template <bool L2, int NT>
+__global__ __launch_bounds__(NT) void rescore_rank_kernel(const u64 *__restrict__ cand, const uint32_t *__restrict__ cnt,
+                                                          uint32_t cap, int k_prime, int kp2, int parts,
+                                                          const float *__restrict__ queries, int d, int k,
+                                                          int32_t *__restrict__ out_ids, float *__restrict__ out_scores,
+                                                          float *__restrict__ out_margin, const CertifyParams cert)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    u64 *keys = reinterpret_cast<u64 *>(smem);   // [kp2]
+    __shared__ double s_q2[NT / 64];
+    const int64_t q = blockIdx.x;
+    const int tid = threadIdx.x;
+    const u64 *mine = cand + q * (int64_t)cap;
+    const int n = (int)cnt[q * CNT_PITCH];       // at most k'
+    for (int c = tid; c < kp2; c += NT) keys[c] = c < n ? mine[k_prime + c] : 0ull;
+    const double q2 = query_norm2<NT>(queries + q * (int64_t)d, d, s_q2);
+    __syncthreads();
+    sort_keys<NT, true>(keys, kp2);
+    for (int r = tid; r < k; r += NT) {
+        const bool have = r < n;
+        const u64 key = have ? keys[r] : 0ull;
+        out_ids[q * k + r] = have ? key_id(key) : -1;
+        out_scores[q * k + r] = have ? key_score(key) : -__builtin_inff();
+    }
+    if (tid == 0) {
+        RowStats all;
+        for (int p = 0; p < parts; ++p) {
+            const u64 *from = mine + 2 * k_prime + 4 * p;
+            const double e2 = __longlong_as_double((long long)from[1]), x2 = __longlong_as_double((long long)from[2]);
+            all.min_scan = from[0] < all.min_scan ? from[0] : all.min_scan;
+            all.e2 += e2;
+            all.x2max = x2 > all.x2max ? x2 : all.x2max;
+        }
+        certify<L2>(cert, out_margin, q, CNT_PITCH, n, k, k_prime, d, q2, n >= k ? keys[k - 1] : 0ull, all.min_scan, all.e2,
+                    all.x2max);
     }
 }
 
@@ -858,6 +995,46 @@ hipError_t launch_rescore(const u64 *cand, const uint32_t *cnt, int cnt_pitch, u
     }
 #undef RALM_RS
 #undef RALM_RS_NT
+    return hipGetLastError();
+}
+
+hipError_t launch_rescore_cut(u64 *cand, const uint32_t *cnt, uint32_t cap, int32_t k_prime, const float *queries, int64_t Q,
+                              const void *exact, int32_t exact_dtype, int64_t ld, int32_t d, int32_t metric, int32_t k,
+                              int32_t *out_ids, float *out_scores, float *out_margin, const CertifyParams &cert,
+                              hipStream_t stream)
+{
+    if (Q <= 0) return hipSuccess;
+    int kp2 = 2;
+    while (kp2 < k_prime) kp2 <<= 1;
+    // four workgroups of eight waves fill a CU; a part is at least four rows per wave
+    int64_t parts = (1024 + Q - 1) / Q;
+    const int64_t most = (k_prime + RP_WAVES * RS_ROWS - 1) / (RP_WAVES * RS_ROWS);
+    if (parts > most) parts = most;
+    const dim3 grid((unsigned)Q, (unsigned)parts), block(RP_THREADS);
+    const size_t rows_smem = (size_t)((k_prime + parts - 1) / parts) * sizeof(u64);
+    if (exact_dtype == DT_F16) {
+        if (metric == METRIC_L2)
+            hipLaunchKernelGGL((rescore_rows_kernel<DT_F16, true>), grid, block, rows_smem, stream, cand, cnt, cap, k_prime, queries, exact, ld, d);
+        else
+            hipLaunchKernelGGL((rescore_rows_kernel<DT_F16, false>), grid, block, rows_smem, stream, cand, cnt, cap, k_prime, queries, exact, ld, d);
+    } else {
+        if (metric == METRIC_L2)
+            hipLaunchKernelGGL((rescore_rows_kernel<DT_F32, true>), grid, block, rows_smem, stream, cand, cnt, cap, k_prime, queries, exact, ld, d);
+        else
+            hipLaunchKernelGGL((rescore_rows_kernel<DT_F32, false>), grid, block, rows_smem, stream, cand, cnt, cap, k_prime, queries, exact, ld, d);
+    }
+    const size_t smem = (size_t)kp2 * sizeof(u64);
+#define RALM_RANK(L2V, NTV)                                                                                             \
+    hipLaunchKernelGGL((rescore_rank_kernel<L2V, NTV>), dim3((unsigned)Q), dim3(NTV), smem, stream, cand, cnt, cap,     \
+                       k_prime, kp2, (int)parts, queries, d, k, out_ids, out_scores, out_margin, cert)
+    if (metric == METRIC_L2) {
+        if (kp2 <= 512) RALM_RANK(true, 256);
+        else RALM_RANK(true, 1024);
+    } else {
+        if (kp2 <= 512) RALM_RANK(false, 256);
+        else RALM_RANK(false, 1024);
+    }
+#undef RALM_RANK
     return hipGetLastError();
 }
 
