@@ -16,7 +16,6 @@
 //                  key are collected, and the best k of them are the answer.  Both kernels
 //                  are always launched and return at once when nothing is queued.
 #include <atomic>
-#include <type_traits>
 
 #include "ralm_common.h"
 #include "ralm_kernels.h"
@@ -341,26 +340,17 @@ __device__ __forceinline__ void exact_accum4(double &sum, const float4 &x, const
     }
 }
 
-// elements j .. j+3 of a row of the exact copy, as they are and widened exactly to fp32
-template <int EX>
-using ExactPiece = typename std::conditional<EX == DT_F32, float4, uint2>::type;
-
-__device__ __forceinline__ float4 widen(const float4 &v) { return v; }
-__device__ __forceinline__ float4 widen(const uint2 &h)
-{
-    return make_float4(f16_bits_to_f32(h.x & 0xffffu), f16_bits_to_f32(h.x >> 16), f16_bits_to_f32(h.y & 0xffffu),
-                       f16_bits_to_f32(h.y >> 16));
-}
-template <int EX>
-__device__ __forceinline__ ExactPiece<EX> exact_piece4(const void *__restrict__ exact, int64_t row_off, int j)
-{
-    const unsigned char *at = static_cast<const unsigned char *>(exact) + (row_off + j) * (EX == DT_F32 ? 4 : 2);
-    return *reinterpret_cast<const ExactPiece<EX> *>(at);
-}
+// elements j .. j+3 of a row of the exact copy, widened exactly to fp32
 template <int EX>
 __device__ __forceinline__ float4 exact_load4(const void *__restrict__ exact, int64_t row_off, int j)
 {
-    return widen(exact_piece4<EX>(exact, row_off, j));
+    if constexpr (EX == DT_F32) {
+        return *reinterpret_cast<const float4 *>(static_cast<const float *>(exact) + row_off + j);
+    } else {
+        const uint2 h = *reinterpret_cast<const uint2 *>(static_cast<const uint16_t *>(exact) + row_off + j);
+        return make_float4(f16_bits_to_f32(h.x & 0xffffu), f16_bits_to_f32(h.x >> 16), f16_bits_to_f32(h.y & 0xffffu),
+                           f16_bits_to_f32(h.y >> 16));
+    }
 }
 
 constexpr int RS_ROWS = 4;             // rows that a wave scores together: their loads are in flight at once
@@ -390,26 +380,17 @@ __device__ __forceinline__ RowStats score_rows(const u64 *list, int begin, int e
             row_off[u] = (int64_t)key_id(list[c < end ? c : c0]) * ld;   // past the end: the first row again
             sum[u] = x2[u] = 0.0;
         }
-        // two steps' loads in flight at once (their sums in order)
-        for (int j = lane * 4; j < d; j += 512) {
-            const int j2 = j + 256 < d ? j + 256 : j;
-            ExactPiece<EX> x[2][RS_ROWS];
+        for (int j = lane * 4; j < d; j += 256) {
+            float4 x[RS_ROWS];
 #pragma unroll
-            for (int u = 0; u < RS_ROWS; ++u) x[0][u] = exact_piece4<EX>(exact, row_off[u], j);
+            for (int u = 0; u < RS_ROWS; ++u) x[u] = exact_load4<EX>(exact, row_off[u], j);
+            const float4 y = *reinterpret_cast<const float4 *>(qv + j);
 #pragma unroll
-            for (int u = 0; u < RS_ROWS; ++u) x[1][u] = exact_piece4<EX>(exact, row_off[u], j2);
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                if (h == 1 && j2 == j) break;
-                const float4 y = *reinterpret_cast<const float4 *>(qv + j + h * 256);
-#pragma unroll
-                for (int u = 0; u < RS_ROWS; ++u) {
-                    const float4 xv = widen(x[h][u]);
-                    exact_accum4<L2>(sum[u], xv, y);
-                    if (stats)
-                        x2[u] += (double)xv.x * (double)xv.x + (double)xv.y * (double)xv.y + (double)xv.z * (double)xv.z +
-                                 (double)xv.w * (double)xv.w;
-                }
+            for (int u = 0; u < RS_ROWS; ++u) {
+                exact_accum4<L2>(sum[u], x[u], y);
+                if (stats)
+                    x2[u] += (double)x[u].x * (double)x[u].x + (double)x[u].y * (double)x[u].y +
+                             (double)x[u].z * (double)x[u].z + (double)x[u].w * (double)x[u].w;
             }
         }
 #pragma unroll

@@ -805,6 +805,33 @@ def test_list_selection_branches(B, oracle, Q, k, k_prime, values):
     assert np.array_equal(ids, wi) and np.array_equal(sc, wsc)
 
 
+@pytest.mark.parametrize("Q", [1, 70, 1030])
+@pytest.mark.parametrize("k,k_prime,N", [(200, 257, 3000), (257, 1000, 1001), (300, 1024, 700)])
+@pytest.mark.parametrize("metric,dtype", [("ip", "f32"), ("ip", "f16"), ("l2", "f32"), ("l2", "f16")])
+def test_rescore_spread_over_workgroups(B, oracle, metric, dtype, k, k_prime, N, Q):
+    """More than 256 candidates per query: rows scored by several workgroups, or by one where there are many
+    queries, parts that do not divide k', lists shorter than k'; the margin that the parts' statistics add up to.
+    Integer data: the scan is exact, so the margin is the distance of ranks k and k' in the full ranking."""
+    g = torch.Generator().manual_seed(Q + k)
+    d = 72
+    X = torch.randint(-3, 4, (N, d), generator=g).float()
+    Qm = torch.randint(-3, 4, (Q, d), generator=g).float()
+    Xd = X.cuda() if dtype == "f32" else X.half().cuda()
+    if metric == "l2":
+        ds = B.Datastore.for_l2(Xd)
+    else:
+        ds = B.Datastore(Xd)
+    ws = B.alloc_workspace(Q, ds, k, k_prime)
+    margin = torch.empty(Q, device="cuda")
+    ids, sc = B.ralm_retrieve_topk_ex(Qm.cuda(), ds, k, k_prime, workspace=ws, out_margin=margin)
+    wi, wsc = oracle.retrieve_topk(Qm.numpy(), X.numpy(), min(k_prime, N), metric=metric)
+    assert np.array_equal(ids.cpu().numpy(), wi[:, :k]) and np.array_equal(sc.cpu().numpy(), wsc[:, :k])
+    want = wsc[:, k - 1] - wsc[:, -1] if N >= k_prime else np.full(Q, np.inf, np.float32)
+    assert np.array_equal(margin.cpu().numpy(), want)
+    c = B.ralm_workspace_counters(ws)
+    assert c["soft_certified"] == Q and c["exact_pass"] == 0 and c["ladder_overflows"] == 0
+
+
 @pytest.mark.parametrize("Q", [1, 33, 128, 129, 300])
 @pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
 def test_launches_that_admit_many_scores(B, oracle, dtype, Q):
