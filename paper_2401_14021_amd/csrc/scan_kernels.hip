@@ -7,8 +7,8 @@
 // accumulation) and each one is compared at once with its query's admission key; the few
 // that pass are appended to that query's candidate list.
 //
-// Tiling: a workgroup of 4 or 8 waves owns a 256-row x BN-query tile (BN = 32 on 4 waves; 64,
-// 128 and 256 on 8 waves, two per SIMD); the reduction dimension is walked in strips of BK
+// Tiling: a workgroup of 4 or 8 waves owns a 256-row x BN-query tile (64,
+// 128 and 256 queries on 8 waves, two per SIMD; 32 queries: half of the rows, on 4 waves); the reduction dimension is walked in strips of BK
 // elements.  Datastore rows are the A operand of v_mfma_f32_32x32x16, queries the B operand, so
 // every accumulator register of a lane belongs to ONE query (column = lane % 32) and the lane
 // can hold that query's threshold in a register.
