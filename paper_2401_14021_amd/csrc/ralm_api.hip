@@ -55,6 +55,7 @@ int elem_bytes(int dt) { return dt == RALM_F32 ? 4 : 2; }
 struct Plan {
     int32_t k_prime;
     uint32_t cap;         // candidate slots per query
+    int64_t block_tiles;  // tiles of a block of the sequential ladder
     int64_t Qpad;
     int32_t dpad;
     int n_stages;
@@ -97,30 +98,42 @@ ralm_status make_plan(int64_t Q, const ralm_datastore_t *ds, int32_t k, int32_t 
     //   up to 256 queries  100 over 200K x 768 by 13 111 us, by 4 and 4 137, by 2, 2, 2 and 2 164; 81 over 1M round
     //                      by 8 and 8 370, by 2, 2, 2 and 8 392; 100 over 8M by 8, 8 and 8 2072, by 2, 2, 2, 8 and 8
     //                      2128.  k' > 256: 256 over 10M x 1024, k' = 2048, by 4 throughout 6497, by 2 6617.
-    //   more               bound by the matrix cores, which wait for the selection: seven eighths or more of the
-    //                      rows should see keys within a factor 2 of final, so the finest step is 2; 600 over
+    //   more               bound by the matrix cores, which wait for the selection: the last half of the rows should
+    //                      see keys within a factor 2 of final, so the finest step is 2; 600 over
     //                      400K by 2, 4 and 4 602 us, by 2, 2, 2 and 4 625, by 4 and 8 609.
-    const int32_t g_most = Q <= 64 ? (k_prime <= 256 ? 64 : 8) : (k_prime > 256 ? 4 : (Q <= 256 ? 16 : 8));
+    int32_t g_most = Q <= 64 ? (k_prime <= 256 ? 64 : 8) : (k_prime > 256 ? 4 : (Q <= 256 ? 16 : 8));
     const int32_t g_finest = Q > 256 ? 2 : 0;   // 0: like the others
-    // the slots leave 4x (2x for large k') head room over that expectation, far beyond the
-    // spread of the count for rows in random order, and are never fewer than 16384 so that
-    // stage 0 can be a real sample
-    const int64_t safety = k_prime <= 256 ? 4 : 2;
-    pl.cap = (uint32_t)(safety * k_prime * (g_most - 1) + k_prime);
-    if (pl.cap < 16384u) pl.cap = 16384u;
-    pl.cap = (pl.cap + 1u) & ~1u;   // even: lists start on 16-byte boundaries
+    // Slots of a list.  In a store sorted by cluster a sampled tile of 256 rows is one draw and not 256, so what the
+    // next stage admits is spread like the wait for the k' / 256-th sampled tile of good matches, and the longest
+    // list of a batch is a multiple of the expected k' g keys.  A model of the ladder (108 stores of 262144 and 4M rows,
+    // clusters of 320 and 1200 rows, 128 and 250 queries) has lists of up to 18 459 keys for k' = 64, 22 407 for 128,
+    // 27 136 for 256, 16 982 for 2048: at most 0.55 of these slots for k' <= 256 and 0.66 beyond; rows in random
+    // order fill 0.03 to 0.34.  Slots that no key reaches cost memory but no time; an overflow costs a
+    // pass over the exact copy (200 queries, k' = 256, 4M x 768 sorted by cluster, 16384 slots: one list of 200
+    // overflowed and the call took 4144 us, now 2084).  Batches of more than 16384 queries refine by 2 instead, so
+    // that their lists stay as short as they can be.
+    auto head_room = [&](int32_t g) { return k_prime + (int64_t)(g - 1) * (3 * k_prime + 10 * SCAN_BM); };
+    if (Q > 16384 && k_prime > 256) g_most = 2;
+    // The first stage keeps all of its rows' scores: 16384 rows are a real sample; more where a large growth
+    // needs long lists anyway (up to 64 queries: 4x the expectation, 2x for k' > 256).
+    int64_t first_rows = (k_prime <= 256 ? 4 : 2) * k_prime * (int64_t)(g_most - 1) + k_prime;
+    if (first_rows < 16384) first_rows = 16384;
+    int64_t cap = first_rows;
+    if (Q > 64 && (Q <= 256 || k_prime > 256) && cap < head_room(g_most)) cap = head_room(g_most);
+    pl.cap = (uint32_t)((cap + 1) & ~(int64_t)1);   // even: lists start on 16-byte boundaries
+    pl.block_tiles = (first_rows - k_prime) / SCAN_BM;   // >= 1: first_rows >= 16384, k' <= 4096
     pl.Qpad = (Q + SCAN_QPAD - 1) / SCAN_QPAD * SCAN_QPAD;
     pl.dpad = (scan_cols(ds) + SCAN_BK - 1) / SCAN_BK * SCAN_BK;
 
     const int64_t tiles = (ds->N + SCAN_BM - 1) / SCAN_BM;
-    auto fits = [&](int64_t s) { return ((tiles + s - 1) / s) * SCAN_BM <= (int64_t)pl.cap; };
+    auto fits = [&](int64_t s) { return ((tiles + s - 1) / s) * SCAN_BM <= first_rows; };
     int64_t rev[40];
     int n = 0;
     int64_t s = 1;
     rev[n++] = s;
     if (g_finest && !fits(s)) rev[n++] = s = g_finest;
     if (!fits(s)) {
-        const int64_t full = pl.cap / SCAN_BM, ratio = (tiles + s * full - 1) / (s * full);   // still to be bridged
+        const int64_t full = first_rows / SCAN_BM, ratio = (tiles + s * full - 1) / (s * full);   // still to be bridged
         int32_t steps = 0;
         for (int64_t r = 1; r < ratio; r *= g_most) ++steps;
         // (not where one growth nearly always does: the last stage is then as long as it can be, and the longer a
@@ -316,7 +329,7 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
 
     const int64_t tiles = (ds->N + SCAN_BM - 1) / SCAN_BM;
     if (sequential) {
-        const int64_t block = ((int64_t)pl.cap - pl.k_prime) / SCAN_BM;   // >= 1: cap >= 16384, k' <= 4096
+        const int64_t block = pl.block_tiles;   // a list holds its k' best so far and all of a block's rows
         sp.tile_stride = 1;
         sp.tile_skip = 0;
         for (int64_t t0 = 0; t0 < tiles; t0 += block) {

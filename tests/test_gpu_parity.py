@@ -254,6 +254,28 @@ def test_list_overflow_is_recovered_by_the_exact_pass_and_the_sequential_ladder_
     assert np.array_equal(ids.cpu().numpy(), wi) and np.array_equal(sc.cpu().numpy(), wsc)
 
 
+@pytest.mark.parametrize("Q,k,seed", [(250, 100, 1), (250, 50, 1), (128, 700, 3), (600, 700, 1)])
+def test_rows_sorted_by_cluster_fit_the_lists(B, oracle, Q, k, seed):
+    """A store sorted by clusters of 1200 rows: a strided sample sees few of the clusters, so the stages
+    behind it admit several times what they would admit of rows in random order (a model of the first
+    three puts their longest lists at 22711, 17977 and 16982 keys).  No list may overflow: every query that
+    does costs the call a pass over the exact copy."""
+    from paper_2401_14021_amd import inputs
+    N, d = 262144, 64
+    X, _ = inputs.clustered_datastore(N, d, N // 1200, seed, order="cluster")
+    Qm = inputs.queries_near_rows(X, inputs.pick_rows(N, Q, seed=seed + 1), seed=seed + 2)
+    ds = B.Datastore.from_fp32(X.cuda())
+    ws = B.alloc_workspace(Q, ds, k)
+    ids, sc = B.ralm_retrieve_topk_ex(Qm.cuda(), ds, k, workspace=ws)
+    c = B.ralm_workspace_counters(ws)
+    assert c["ladder_overflows"] == 0 and c["unanswered"] == 0, (c, B.ralm_workspace_stage_entries(ws))
+    few = slice(0, 8)
+    wi, wsc = oracle.retrieve_topk(Qm[few].numpy(), X.numpy(), k)
+    exact, subs, total = check_topk(ids[few].cpu().numpy(), sc[few].cpu().numpy(), wi, wsc,
+                                    _score_fn(oracle, Qm.numpy(), X.numpy()))
+    assert exact >= 0.99 * total
+
+
 @pytest.mark.parametrize("N", [16384, 16000, 16484, 32768 + 256, 256, 300])
 @pytest.mark.parametrize("Q", [5, 100, 300])
 def test_first_stage_with_full_and_partial_last_tiles(B, oracle, N, Q):
