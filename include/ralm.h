@@ -414,9 +414,10 @@ ralm_status ralm_verify(const int32_t *spec_ids, const int32_t *true_ids, int64_
  *   N           candidates outside [0, N) are dropped, as are negative ids
  *
  * Candidates are inserted in the order step, rank, successor; the result is
- * that of doing so one at a time.  Requests are independent (one wave each).
- * Cost per candidate grows with the number of cached ids (linear membership
- * test over the row in LDS); C <= 16384.
+ * that of doing so one at a time.  Requests are independent (one workgroup
+ * each, 64 candidates at a time).  Cost per candidate grows with the number of
+ * cached ids (linear membership test over the row in LDS); ranks without an id
+ * and successors outside [0, N) cost next to nothing; C <= 16384.
  */
 ralm_status ralm_cache_insert(int32_t *cache_ids, int32_t *cache_len, int32_t *cache_head, int32_t C,
                               int64_t R, const int32_t *true_ids, int64_t true_stride, int64_t Qt,

@@ -535,6 +535,14 @@ __global__ __launch_bounds__(CI_THREADS) void cache_insert_kernel(
             const int64_t e64 = t + first + off;
             if (t >= 0 && e64 < N) e = (int32_t)e64;
         }
+        // 64 places without a candidate (an unfilled rank, successors past the datastore's end): the rest of the last
+        // place's rank has none either.  65536 successors of each of 64 ids at the end, four requests: 46 ms batch by
+        // batch, 0.03 ms this way
+        if (!__any(e >= 0)) {              // the same in every wave
+            const int64_t c = base + 63;
+            base = c < total ? (c / per_rank + 1) * per_rank : total;
+            continue;
+        }
         // the zone: the slots behind the last entry, or the oldest entries once the ring is full
         const int zone_at = len < C ? len : head, room = len < C ? C - len : C;
         const int zone_n = room < 64 ? room : 64;

@@ -516,6 +516,34 @@ def test_cache_insert_evicts_and_reinserts_inside_a_batch(B, oracle, C):
         _same_cache(got, want)
 
 
+def test_cache_insert_passes_over_ranks_without_candidates(B, oracle):
+    """Unfilled ranks and successors past the datastore's end cost next to nothing, however many
+    successors are asked for (64 ids x 65536 successors taken one by one need tens of milliseconds)."""
+    R, C, N, p, n_next = 4, 300, 1000, 64, 65536
+    tid = torch.full((R, p), N - 1, dtype=torch.int32)
+    tid[1] = -1
+    tid[2, ::2] = -1
+    tid[3, 0], tid[3, 1], tid[3, 63] = N - 70, 5, N - 3
+    off = torch.arange(R + 1, dtype=torch.int64)
+    fresh = lambda: [torch.full((R, C), -1, dtype=torch.int32), torch.zeros(R, dtype=torch.int32), torch.zeros(R, dtype=torch.int32)]
+    wi, wl, wh = oracle.cache_insert(*[t.numpy() for t in fresh()], tid.numpy(), off.numpy(), N=N, p=p, n_next=n_next)
+    args = tid.cuda(), off.cuda()
+    ms = []
+    for _ in range(3):
+        st = [t.cuda() for t in fresh()]
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record()
+        B.ralm_cache_insert(*st, *args, N, p=p, n_next=n_next)
+        e1.record()
+        torch.cuda.synchronize()
+        ms.append(e0.elapsed_time(e1))
+        ids, ln, hd = (t.cpu().numpy() for t in st)
+        assert np.array_equal(ln, wl) and np.array_equal(hd, wh)
+        for r in range(R):
+            assert np.array_equal(ids[r, :wl[r]], wi[r, :wl[r]])
+    assert min(ms) < 5, ms
+
+
 def test_speculation_loop_closed_by_cache_insert(B, oracle):
     """Alg. 1 as a loop on the GPU entry points: speculate from the cache, verify with a batched
     retrieval, find the first mismatch, insert the verified results (top-5 update); the queries
