@@ -227,7 +227,8 @@ ralm_status ralm_workspace_overflows(const void *workspace, void *stream, int32_
 
 /*
  * Counters of the LAST ralm_retrieve_topk_ex / _seq call on this workspace, all
- * numbers of queries (host struct; synchronises `stream`):
+ * numbers of queries (host struct; synchronises `stream`).  All zero, as are
+ * the other reports, for a workspace that holds no call's:
  *   unanswered        id -1 / score NaN (what ralm_workspace_overflows returns)
  *   ladder_overflows  candidate list lost entries during the scan; answered by
  *                     the exact pass

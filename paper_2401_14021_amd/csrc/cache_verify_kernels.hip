@@ -688,7 +688,7 @@ __global__ void query_prep_kernel(const float *__restrict__ q, int64_t Q, int d,
 {
     const int64_t n = Qpad * dpad;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n0; i += (int64_t)gridDim.x * blockDim.x)
-        z0[i] = i == FLAG_QUERIES ? (uint32_t)Q : 0u;
+        z0[i] = i == FLAG_QUERIES ? (uint32_t)Q : (i == FLAG_MARK ? (uint32_t)Q ^ FLAG_MARK_XOR : 0u);
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n1; i += (int64_t)gridDim.x * blockDim.x) z1[i] = 0u;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const int64_t row = i / dpad;

@@ -16,7 +16,6 @@
 #include <hip/hip_runtime.h>
 #include <atomic>
 #include <mutex>
-#include <vector>
 #include <stdarg.h>
 #include <stdio.h>
 #include <string.h>
@@ -390,6 +389,38 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
 
 }  // namespace
 
+namespace {
+
+constexpr int FLAG_WORDS = 8;
+
+// The flag block's words once `stream` has run; all zero if the workspace holds no call's block (the number of queries
+// decides how much is read behind it, so it must not come from memory that no call has written).
+ralm_status read_flags(const void *workspace, void *stream, int32_t *words /* [FLAG_WORDS] */)
+{
+    RALM_HIP(hipStreamSynchronize(static_cast<hipStream_t>(stream)));
+    RALM_HIP(hipMemcpy(words, workspace, FLAG_WORDS * sizeof(int32_t), hipMemcpyDeviceToHost));
+    const int32_t Q = words[FLAG_QUERIES];
+    if ((uint32_t)words[FLAG_MARK] != ((uint32_t)Q ^ FLAG_MARK_XOR) || Q < 1 || Q > MAX_QUERIES)
+        memset(words, 0, FLAG_WORDS * sizeof(int32_t));
+    return RALM_OK;
+}
+
+// f(word) for n words of the workspace from byte `offset` on
+template <class F>
+ralm_status each_word(const void *workspace, size_t offset, int64_t n, F f)
+{
+    uint32_t buf[4096];
+    for (int64_t i = 0; i < n; i += 4096) {
+        const int64_t m = n - i < 4096 ? n - i : 4096;
+        RALM_HIP(hipMemcpy(buf, static_cast<const unsigned char *>(workspace) + offset + (size_t)i * 4, (size_t)m * 4,
+                           hipMemcpyDeviceToHost));
+        for (int64_t j = 0; j < m; ++j) f(buf[j]);
+    }
+    return RALM_OK;
+}
+
+}  // namespace
+
 extern "C" {
 
 ralm_status ralm_retrieve_topk_ex(const float *queries, int64_t Q, const ralm_datastore_t *ds, int32_t k,
@@ -408,61 +439,47 @@ ralm_status ralm_retrieve_topk_seq(const float *queries, int64_t Q, const ralm_d
                          stream, true);
 }
 
-ralm_status ralm_workspace_overflows(const void *workspace, void *stream_, int32_t *count)
+ralm_status ralm_workspace_overflows(const void *workspace, void *stream, int32_t *count)
 {
     if (!workspace || !count) return fail(RALM_ERR_NULL, "workspace/count is NULL");
-    hipStream_t stream = static_cast<hipStream_t>(stream_);
-    RALM_HIP(hipStreamSynchronize(stream));
-    RALM_HIP(hipMemcpy(count, static_cast<const int32_t *>(workspace) + FLAG_UNANSWERED, sizeof(int32_t),
-                       hipMemcpyDeviceToHost));
-    return RALM_OK;
+    int32_t words[FLAG_WORDS];
+    const ralm_status st = read_flags(workspace, stream, words);
+    if (st == RALM_OK) *count = words[FLAG_UNANSWERED];
+    return st;
 }
 
 static_assert(MAX_STAGE_SUMS == RALM_MAX_LADDER_STAGES, "the flag block holds one sum per reported stage");
 
-ralm_status ralm_workspace_stage_entries(const void *workspace, void *stream_, int32_t *n_stages, int64_t *entries)
+ralm_status ralm_workspace_stage_entries(const void *workspace, void *stream, int32_t *n_stages, int64_t *entries)
 {
     if (!workspace || !n_stages || !entries) return fail(RALM_ERR_NULL, "workspace/n_stages/entries is NULL");
-    hipStream_t stream = static_cast<hipStream_t>(stream_);
-    int32_t words[8];
-    RALM_HIP(hipStreamSynchronize(stream));
-    RALM_HIP(hipMemcpy(words, workspace, sizeof(words), hipMemcpyDeviceToHost));
-    int32_t n = words[FLAG_STAGES];
-    const int64_t Q = words[FLAG_QUERIES];
-    n = n < 0 || Q < 1 || Q > MAX_QUERIES ? 0 : (n > MAX_STAGE_SUMS ? MAX_STAGE_SUMS : n);
-    *n_stages = n;
-    std::vector<uint32_t> lengths(n ? Q : 0);
-    for (int i = 0; i < RALM_MAX_LADDER_STAGES; ++i) {
-        entries[i] = 0;
-        if (i >= n) continue;
-        RALM_HIP(hipMemcpy(lengths.data(), static_cast<const unsigned char *>(workspace) + stage_offset(Q, i), (size_t)Q * 4,
-                           hipMemcpyDeviceToHost));
-        for (uint32_t v : lengths) entries[i] += v;
+    int32_t words[FLAG_WORDS];
+    ralm_status st = read_flags(workspace, stream, words);
+    if (st != RALM_OK) return st;
+    const int32_t n = words[FLAG_STAGES] < 0 ? 0 : (words[FLAG_STAGES] > MAX_STAGE_SUMS ? MAX_STAGE_SUMS : words[FLAG_STAGES]);
+    for (int i = 0; i < RALM_MAX_LADDER_STAGES; ++i) entries[i] = 0;
+    for (int i = 0; i < n; ++i) {
+        st = each_word(workspace, stage_offset(words[FLAG_QUERIES], i), words[FLAG_QUERIES], [&](uint32_t v) { entries[i] += v; });
+        if (st != RALM_OK) return st;
     }
+    *n_stages = n;
     return RALM_OK;
 }
 
-ralm_status ralm_workspace_counters(const void *workspace, void *stream_, ralm_counters_t *out)
+ralm_status ralm_workspace_counters(const void *workspace, void *stream, ralm_counters_t *out)
 {
     if (!workspace || !out) return fail(RALM_ERR_NULL, "workspace/out is NULL");
-    hipStream_t stream = static_cast<hipStream_t>(stream_);
-    int32_t words[8];
-    RALM_HIP(hipStreamSynchronize(stream));
-    RALM_HIP(hipMemcpy(words, workspace, sizeof(words), hipMemcpyDeviceToHost));
+    int32_t words[FLAG_WORDS];
+    const ralm_status st = read_flags(workspace, stream, words);
+    if (st != RALM_OK) return st;
     out->unanswered = words[FLAG_UNANSWERED];
     out->ladder_overflows = words[FLAG_LADDER_OVERFLOWS];
     out->hard_certified = out->soft_certified = 0;
-    const int64_t Q = words[FLAG_QUERIES];
-    std::vector<uint32_t> status(Q < 1 || Q > MAX_QUERIES ? 0 : Q);
-    if (!status.empty())
-        RALM_HIP(hipMemcpy(status.data(), static_cast<const unsigned char *>(workspace) + status_offset(), status.size() * 4,
-                           hipMemcpyDeviceToHost));
-    for (uint32_t v : status) {
+    out->exact_pass = words[FLAG_FALLBACKS];
+    return each_word(workspace, status_offset(), words[FLAG_QUERIES], [&](uint32_t v) {
         out->soft_certified += v & STATUS_SOFT ? 1 : 0;
         out->hard_certified += v & STATUS_HARD ? 1 : 0;
-    }
-    out->exact_pass = words[FLAG_FALLBACKS];
-    return RALM_OK;
+    });
 }
 
 }  // extern "C"

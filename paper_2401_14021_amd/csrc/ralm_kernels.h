@@ -49,7 +49,7 @@ hipError_t launch_scan(const ScanParams &p, int n_cu, hipStream_t stream);
 hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t stream);
 
 // fp32 [Q, d] -> scan dtype [Qpad, dpad], zero padded
-// also clears the n0 words at z0 (the flag block, but for its number of queries) and the n1 words at z1
+// also clears the n0 words at z0 (the flag block, but for its number of queries and its mark) and the n1 words at z1
 hipError_t launch_query_prep(const float *q, int64_t Q, int32_t d, uint16_t *out, int64_t Qpad,
                              int32_t dpad, int32_t scan_dtype, int32_t metric, uint32_t *z0, int64_t n0,
                              uint32_t *z1, int64_t n1, hipStream_t stream);
@@ -77,8 +77,10 @@ enum {
     FLAG_LADDER_OVERFLOWS = 1,  // candidate list lost entries during the scan (answered by the exact pass)
     FLAG_FALLBACKS = 2,         // answered by the exact pass
     FLAG_STAGES = 3,            // stages of the ladder whose list lengths were recorded
-    FLAG_QUERIES = 4            // queries of the call
+    FLAG_QUERIES = 4,           // queries of the call
+    FLAG_MARK = 5               // FLAG_QUERIES ^ FLAG_MARK_XOR: the block is that of a call
 };
+constexpr uint32_t FLAG_MARK_XOR = 0x5ca1ab1eu;
 
 // What the re-score needs to check its own result and to queue a query for the exact pass; all
 // pointers NULL: no check (flags == NULL decides).

@@ -322,6 +322,28 @@ def test_list_entries_per_stage_are_reported(B, oracle):
     assert len(e2) == min(40, -(-tiles // ((16384 - 64) // 256)))
 
 
+def test_reports_on_a_workspace_that_no_call_has_used(B):
+    """The reports read as many words per query as the workspace says its call had queries: memory that
+    no call has written is reported as empty and nothing behind its first block is read."""
+    for fill in (0xff, 0x00, 0x01, 0x7f):
+        ws = torch.full((4096 + 256,), fill, dtype=torch.uint8, device="cuda")
+        assert set(B.ralm_workspace_counters(ws).values()) == {0}
+        assert B.ralm_workspace_overflows(ws) == 0 and B.ralm_workspace_stage_entries(ws) == []
+    words = torch.zeros(1024 + 64, dtype=torch.int32, device="cuda")
+    words[:64] = 1 << 20
+    assert set(B.ralm_workspace_counters(words.view(torch.uint8)).values()) == {0}
+    assert B.ralm_workspace_stage_entries(words.view(torch.uint8)) == []
+    # more queries than one read takes
+    X = torch.eye(8, 8, device="cuda").repeat(40, 1).contiguous()
+    ds = B.Datastore.from_fp32(X)
+    q = torch.ones(5000, 8, device="cuda")
+    ws = B.alloc_workspace(5000, ds, 2)
+    B.ralm_retrieve_topk_ex(q, ds, 2, workspace=ws)
+    c = B.ralm_workspace_counters(ws)
+    assert c["soft_certified"] + c["exact_pass"] == 5000 and c["unanswered"] == 0
+    assert B.ralm_workspace_stage_entries(ws)[0] == 5000 * 320
+
+
 @pytest.mark.parametrize("Q,k", [(4, 20), (150, 100)])
 def test_sequential_ladder_equals_the_strided_one(B, oracle, Q, k):
     from paper_2401_14021_amd import inputs
