@@ -489,12 +489,15 @@ int32_t ralm_os3_next_stride(const int32_t *strides, const int32_t *matched, int
  * costs (s-1) a + max(a, b) instead of s a + b).  Every call here is ordered on
  * the caller's stream only, so the batched retrieval of step t and the cache
  * lookup of step t+1 can be issued on two streams.  The scan, however, runs as
- * a persistent grid with one workgroup per compute unit whose LDS it fills, so
+ * a persistent grid whose workgroups fill the LDS of every compute unit (one
+ * each, or two for batches of up to 32 queries over 16-bit rows), so
  * a kernel on another stream finds no free unit until a scan launch ends.
  * ralm_scan_reserve_cus(n) makes every later retrieval call of the process
- * leave n compute units free (n = 8: one per XCD; 0 restores the default); the
- * scan slows down by about n / 256 and the other stream's kernels run beside
- * it.  Process-wide setting, read when a call is issued.
+ * launch its scans with at most 256 - n workgroups, rounded down to a multiple
+ * of 8, so that n compute units stay free (n = 8: one per XCD; 0 restores the
+ * default).  The scan slows down by about n / 256; batches of up to 32 queries
+ * put one workgroup on a unit then, which leaves half of every unit's LDS free
+ * (4 % slower).  Process-wide setting, read when a call is issued.
  */
 void ralm_scan_reserve_cus(int32_t n);
 

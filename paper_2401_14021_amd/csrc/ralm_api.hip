@@ -286,8 +286,11 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
     const int64_t scan_ld = ds->scan ? (ds->scan_stride ? ds->scan_stride : scan_cols(ds))
                                      : (ds->exact_stride ? ds->exact_stride : ds->d);
     const int mma_dt = scan_dt == RALM_F16 ? RALM_F16 : RALM_BF16;   // fp32 rows are rounded to bf16
-    // the scan's grids are persistent: one workgroup per CU (two for the small tiles), minus the reserve
-    int n_cu = device_cus() - g_scan_reserve.load(std::memory_order_relaxed);
+    // the scan's grids are persistent: one workgroup per CU (two for the small tiles).  With a reserve they have no
+    // more workgroups than the CUs that are left, rounded down as the grids are multiples of 8
+    const int reserve = g_scan_reserve.load(std::memory_order_relaxed);
+    int n_cu = device_cus() - reserve;
+    if (reserve > 0) n_cu -= n_cu % 8;
     if (n_cu < 8) n_cu = 8;
 
     // the same launch clears the flag block and, behind the queries, the admission keys, the list
@@ -301,6 +304,7 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
     sp.Qs = qs; sp.dpad = pl.dpad; sp.Q = (int32_t)Q;
     sp.tau = tau; sp.cand = cand; sp.cnt = cnt; sp.cap = pl.cap;
     sp.lists_empty = 0;
+    sp.one_per_cu = reserve > 0;
     // one stage: scan the tiles sp describes, then cut every list down to its k' best
     int32_t stage_no = 0;
     // (short lists: the last stage's are cut down by the re-score)

@@ -38,6 +38,7 @@ struct ScanParams {
     int32_t tile_skip;      // if tile_skip == 0, else the t-th positive integer that is no multiple of tile_skip
     int64_t tile_begin;
     int64_t admits;         // scores that the thresholds are expected to admit per query (any number is handled)
+    int32_t one_per_cu;     // 1: never more workgroups than the CUs that launch_scan is given
     int32_t lists_empty;    // 1: every list is empty and every score of this launch is kept, so list positions
                             // follow from the row's place in the launch (no atomics)
 };

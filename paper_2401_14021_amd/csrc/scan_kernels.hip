@@ -764,7 +764,7 @@ hipError_t launch_dma_variant(const ScanParams &p, int n_cu, hipStream_t stream)
     const int64_t total = p.n_row_tiles * (SCAN_BM / BM) * nqt;
     if (total <= 0) return hipSuccess;
     if (total > 0x7fffffffLL) return hipErrorInvalidValue;   // the kernel counts items in 32 bits
-    const int per_cu = smem * 2 <= 160 * 1024 ? 2 : 1;
+    const int per_cu = smem * 2 <= 160 * 1024 && !p.one_per_cu ? 2 : 1;
     int64_t grid = (int64_t)n_cu * per_cu;
     if (total < grid) grid = total;
     grid = (grid + 7) / 8 * 8;
@@ -791,7 +791,9 @@ hipError_t launch_dma(const ScanParams &p, int n_cu, hipStream_t stream)
     switch (scan_bn_for(p.Q)) {
         // up to 32 queries: half tiles, two workgroups to a CU: a launch of few tiles spreads over twice as many
         // workgroups, and one's selection and flush are covered by the other's loads.  Against whole tiles, one
-        // workgroup to a CU: Q = 8 over 1M x 768 271 -> 261 us, over 300K 118 -> 116 us, 1M x 392 216 -> 207 us
+        // workgroup to a CU: Q = 8 over 1M x 768 271 -> 261 us, over 300K 118 -> 116 us, 1M x 392 216 -> 207 us.
+        // With CUs reserved there is one to a CU (Q = 8 over 21M x 768 4606 -> 4782 us): two to each would leave none
+        // free, and a lookup of 8 requests issued 1.5 ms into that call took 2.6 ms instead of 0.05
         case 32: return launch_dma_variant<F16, 4, 1, 1, 1, 64, 3, NTA, 3, 2>(p, n_cu, stream);
         // 64 and 128 queries: 8 waves (two per SIMD, wave tiles of 64 x 32 and 128 x 32), so that one wave's
         // waits are covered by the other's multiplies; with 4 waves of twice the width they were 5 % and 3 % slower

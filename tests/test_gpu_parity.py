@@ -1,6 +1,7 @@
 """GPU parity: the HIP path, called through the C ABI, against the CPU oracle on the same
 seeded inputs.  Integer / index results are bit-exact; floating point follows tests/parity.py."""
 import os
+import time
 
 import numpy as np
 import pytest
@@ -645,6 +646,53 @@ def test_asynchronous_verification_on_two_streams(B, oracle):
     want_spec, _ = oracle.cache_lookup(cids.cpu().numpy(), clen.cpu().numpy(), q_next.cpu().numpy(), off.numpy(),
                                        X.numpy())
     assert np.array_equal(spec1.cpu().numpy(), want_spec)
+
+
+@pytest.mark.parametrize("Q", [1, 8, 32])
+def test_a_reserve_lets_a_lookup_run_beside_the_scan_of_a_small_batch(B, Q):
+    """ralm_scan_reserve_cus(8): batches of up to 32 queries put two workgroups on a compute unit otherwise,
+    and a lookup issued while the scan runs would wait for its end.  Several second streams, since
+    two streams may share a hardware queue."""
+    N, d, k, R, C = 6_000_000, 768, 5, 8, 256
+    X = torch.empty(N, d, dtype=torch.float16, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(5)
+    for r0 in range(0, N, 500_000):
+        X[r0:r0 + 500_000] = torch.randn(500_000, d, generator=g, device="cuda")
+    ds = B.Datastore(X)
+    q = torch.randn(Q, d, generator=g, device="cuda")
+    ql = torch.randn(R, d, generator=g, device="cuda")
+    cids = torch.randint(0, N, (R, C), generator=g, device="cuda", dtype=torch.int32)
+    clen, off = torch.full((R,), C, dtype=torch.int32, device="cuda"), torch.arange(R + 1, device="cuda")
+    lookup_ws = torch.empty(R, dtype=torch.int64, device="cuda")
+    ws = B.alloc_workspace(Q, ds, k)
+    ids0, sc0 = B.ralm_retrieve_topk_ex(q, ds, k, workspace=ws)
+    spec0, ssc0 = B.ralm_cache_lookup(cids, clen, ql, off, ds, workspace=lookup_ws)
+    ids, sc, spec, ssc = (torch.empty_like(t) for t in (ids0, sc0, spec0, ssc0))
+    ev = lambda: torch.cuda.Event(enable_timing=True)
+    a = torch.cuda.Stream()
+    shares = []
+    try:
+        for reserve in (8, 8, 8, 8, 8, 8, 3, 300):
+            B.ralm_scan_reserve_cus(reserve)
+            b, begin, retrieved, looked_up = torch.cuda.Stream(), ev(), ev(), ev()
+            torch.cuda.synchronize()
+            with torch.cuda.stream(a):
+                begin.record()
+                B.ralm_retrieve_topk_ex(q, ds, k, workspace=ws, out_ids=ids, out_scores=sc)
+                retrieved.record()
+            t = time.perf_counter()
+            while time.perf_counter() - t < 0.5e-3:
+                pass
+            with torch.cuda.stream(b):
+                B.ralm_cache_lookup(cids, clen, ql, off, ds, spec, ssc, workspace=lookup_ws)
+                looked_up.record()
+            torch.cuda.synchronize()
+            if reserve == 8:
+                shares.append(begin.elapsed_time(looked_up) / begin.elapsed_time(retrieved))
+            assert torch.equal(ids, ids0) and torch.equal(sc, sc0) and torch.equal(spec, spec0) and torch.equal(ssc, ssc0)
+    finally:
+        B.ralm_scan_reserve_cus(0)
+    assert min(shares) < 0.8, shares
 
 
 # ----------------------------------------------------------------------------------------
