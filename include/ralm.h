@@ -497,7 +497,9 @@ int32_t ralm_os3_next_stride(const int32_t *strides, const int32_t *matched, int
  * of 8, so that n compute units stay free (n = 8: one per XCD; 0 restores the
  * default).  The scan slows down by about n / 256; batches of up to 32 queries
  * put one workgroup on a unit then, which leaves half of every unit's LDS free
- * (4 % slower).  Process-wide setting, read when a call is issued.
+ * (4 % slower); larger batches read the rows in more launches, none longer than
+ * half of the scan, between which kernels that need more than n units get onto
+ * the chip.  Process-wide setting, read when a call is issued.
  */
 void ralm_scan_reserve_cus(int32_t n);
 

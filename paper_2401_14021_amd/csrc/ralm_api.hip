@@ -78,7 +78,8 @@ int32_t default_k_prime(int32_t k)
     return kp;
 }
 
-ralm_status make_plan(int64_t Q, const ralm_datastore_t *ds, int32_t k, int32_t k_prime, Plan &pl)
+// short_launches: the ladder's last stages are kept short (its lists and the workspace are the same)
+ralm_status make_plan(int64_t Q, const ralm_datastore_t *ds, int32_t k, int32_t k_prime, Plan &pl, bool short_launches = false)
 {
     if (k_prime == 0) k_prime = default_k_prime(k);
     if (k < 1 || k > RALM_MAX_K || (int64_t)k > ds->N)
@@ -101,7 +102,12 @@ ralm_status make_plan(int64_t Q, const ralm_datastore_t *ds, int32_t k, int32_t 
     //                      see keys within a factor 2 of final, so the finest step is 2; 600 over
     //                      400K by 2, 4 and 4 602 us, by 2, 2, 2 and 4 625, by 4 and 8 609.
     int32_t g_most = Q <= 64 ? (k_prime <= 256 ? 64 : 8) : (k_prime > 256 ? 4 : (Q <= 256 ? 16 : 8));
-    const int32_t g_finest = Q > 256 ? 2 : 0;   // 0: like the others
+    // With CUs reserved (short_launches) more than 64 queries refine by 2 three times, so that no launch reads more
+    // than half of the rows, and the next ones a quarter and an eighth: kernels of another stream that need more than
+    // the reserved CUs get onto the chip between launches.  A lookup of 8 requests issued 3 ms into a retrieval of 1024
+    // queries over 21M x 768: done after 10.4 ms without the short launches, 0.5 ms with them; 128 queries, 1.5 ms: 3.8
+    // and 1.2 ms; the retrievals themselves 26.8 and 27.0, 5.43 and 5.41 ms.
+    const int32_t fine_until = Q <= 64 ? 1 : (short_launches ? 8 : (Q > 256 ? 2 : 1));   // strides that refine by 2
     // Slots of a list.  In a store sorted by cluster a sampled tile of 256 rows is one draw and not 256, so what the
     // next stage admits is spread like the wait for the k' / 256-th sampled tile of good matches, and the longest
     // list of a batch is a multiple of the expected k' g keys.  A model of the ladder (108 stores of 262144 and 4M rows,
@@ -130,7 +136,7 @@ ralm_status make_plan(int64_t Q, const ralm_datastore_t *ds, int32_t k, int32_t 
     int n = 0;
     int64_t s = 1;
     rev[n++] = s;
-    if (g_finest && !fits(s)) rev[n++] = s = g_finest;
+    while (s < fine_until && !fits(s)) rev[n++] = s *= 2;
     if (!fits(s)) {
         const int64_t full = first_rows / SCAN_BM, ratio = (tiles + s * full - 1) / (s * full);   // still to be bridged
         int32_t steps = 0;
@@ -260,7 +266,8 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
     if (st != RALM_OK) return st;
     if (!aligned16(queries)) return fail(RALM_ERR_ALIGN, "queries must be 16-byte aligned");
     Plan pl;
-    st = make_plan(Q, ds, k, k_prime, pl);
+    const int reserve = g_scan_reserve.load(std::memory_order_relaxed);
+    st = make_plan(Q, ds, k, k_prime, pl, reserve > 0);
     if (st != RALM_OK) return st;
     // the scan kernels count (row tile, query tile) work items in 32 bits
     if (((ds->N + SCAN_BM - 1) / SCAN_BM) * 2 * ((Q + 31) / 32) > 0x7fffffffLL)
@@ -288,7 +295,6 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
     const int mma_dt = scan_dt == RALM_F16 ? RALM_F16 : RALM_BF16;   // fp32 rows are rounded to bf16
     // the scan's grids are persistent: one workgroup per CU (two for the small tiles).  With a reserve they have no
     // more workgroups than the CUs that are left, rounded down as the grids are multiples of 8
-    const int reserve = g_scan_reserve.load(std::memory_order_relaxed);
     int n_cu = device_cus() - reserve;
     if (reserve > 0) n_cu -= n_cu % 8;
     if (n_cu < 8) n_cu = 8;

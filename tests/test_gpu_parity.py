@@ -695,6 +695,31 @@ def test_a_reserve_lets_a_lookup_run_beside_the_scan_of_a_small_batch(B, Q):
     assert min(shares) < 0.8, shares
 
 
+@pytest.mark.parametrize("Q,k", [(70, 5), (200, 200), (300, 5), (300, 200)])
+def test_a_reserve_keeps_the_launches_of_larger_batches_short(B, Q, k):
+    """With ralm_scan_reserve_cus the last three stages of the ladder double the rows scanned, so that a
+    kernel of another stream meets a launch boundary soon; same results, same workspace."""
+    N, d = 300000, 64
+    g = torch.Generator(device="cuda").manual_seed(Q)
+    ds = B.Datastore.from_fp32(torch.randn(N, d, generator=g, device="cuda"))
+    q = torch.randn(Q, d, generator=g, device="cuda")
+    ws = B.alloc_workspace(Q, ds, k)
+    ids0, sc0 = B.ralm_retrieve_topk_ex(q, ds, k, workspace=ws)
+    usual = B.ralm_workspace_stage_entries(ws)
+    try:
+        B.ralm_scan_reserve_cus(8)
+        assert B.ralm_workspace_bytes(Q, ds, k) <= ws.numel() - 256
+        ids, sc = B.ralm_retrieve_topk_ex(q, ds, k, workspace=ws)
+    finally:
+        B.ralm_scan_reserve_cus(0)
+    e = B.ralm_workspace_stage_entries(ws)
+    assert len(e) >= 5 and len(e) > len(usual)
+    kept = 64 if k == 5 else 512
+    for v in e[-3:]:                       # k' kept and about as many admitted
+        assert 1.7 * kept * Q < v < 2.3 * kept * Q, (e, usual)
+    assert torch.equal(ids, ids0) and torch.equal(sc, sc0)
+
+
 # ----------------------------------------------------------------------------------------
 # KNN-LM neighbour distribution
 # ----------------------------------------------------------------------------------------
