@@ -280,9 +280,9 @@ def test_rows_sorted_by_cluster_fit_the_lists(B, oracle, Q, k, seed):
 @pytest.mark.parametrize("N", [16384, 16000, 16484, 32768 + 256, 256, 300])
 @pytest.mark.parametrize("Q", [5, 100, 300])
 def test_first_stage_with_full_and_partial_last_tiles(B, oracle, N, Q):
-    """The first stage of the ladder keeps every score.  When all of its 256-row tiles are full it
-    writes each score to the list slot that the row's place in the stage determines; when the
-    datastore's partial last tile is among them it takes the atomic path.  Datastores of one stage
+    """The first stage of the ladder keeps every score and writes it to the list slot that the row's
+    place in the stage determines; rows past the end of a partial last tile lie behind the list's
+    length.  Datastores of one stage
     (N <= 16384) and of two, with and without a partial last tile in stage 0."""
     g = torch.Generator().manual_seed(N + Q)
     d, k = 64, 7
@@ -950,6 +950,24 @@ def test_list_selection_branches(B, oracle, Q, k, k_prime, values):
     assert np.array_equal(ids, wi) and np.array_equal(sc, wsc)
 
 
+@pytest.mark.parametrize("Q", [3, 600])
+@pytest.mark.parametrize("k,k_prime", [(1, 64), (20, 64), (100, 256), (600, 1000)])
+def test_list_selection_with_infinite_scores(B, oracle, Q, k, k_prime):
+    """Finite rows and queries whose scores overflow fp32 to either infinity: the range of a list's scores
+    is then not finite and its selection cannot use evenly spaced bins.  Three rows score +inf and rank by
+    id; one scores -inf."""
+    g = torch.Generator().manual_seed(Q + k)
+    N, d = 42000, 16
+    X = torch.randint(0, 9, (N, d), generator=g).float()
+    Qm = torch.randint(0, 9, (Q, d), generator=g).float()
+    Qm[:, 0] = 4
+    X[[31000, 777, 41999], 0] = 3e38
+    X[1234, 0] = -3e38
+    ids, sc, wi, wsc, _ = _retrieve_both(B, oracle, X, Qm, k, k_prime=k_prime)
+    assert np.array_equal(wi[:, 0], np.full(Q, 777)) and np.isinf(wsc[:, :min(k, 3)]).all()
+    assert np.array_equal(ids, wi) and np.array_equal(sc, wsc)
+
+
 @pytest.mark.parametrize("Q", [1, 70, 1030])
 @pytest.mark.parametrize("k,k_prime,N", [(200, 257, 3000), (257, 1000, 1001), (300, 1024, 700)])
 @pytest.mark.parametrize("metric,dtype", [("ip", "f32"), ("ip", "f16"), ("l2", "f32"), ("l2", "f16")])
@@ -996,6 +1014,25 @@ def test_launches_that_admit_many_scores(B, oracle, dtype, Q):
         counters = B.ralm_workspace_counters(ws)
         assert counters["ladder_overflows"] == 0 and counters["unanswered"] == 0
         assert np.array_equal(ids.cpu().numpy(), wi) and np.array_equal(sc.cpu().numpy(), wsc)
+
+
+@pytest.mark.parametrize("Q", [1, 64, 128, 129, 200, 256])
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+def test_launches_that_admit_many_scores_of_streamed_rows(B, oracle, dtype, Q):
+    """The same for rows that are whole 128-byte lines, which batches of one query tile load past L2: every
+    tile width, with full and ragged columns."""
+    g = torch.Generator().manual_seed(Q + 1)
+    N, d, k = 42003, 128, 700
+    X = torch.randint(0, 5, (N, d), generator=g).float()
+    Qm = torch.randint(0, 5, (Q, d), generator=g).float()
+    wi, wsc = oracle.retrieve_topk(Qm.numpy(), X.numpy(), k)
+    Xd = X.cuda()
+    ds = B.Datastore(Xd) if dtype == "f32" else B.Datastore.from_fp32(Xd, torch.bfloat16 if dtype == "bf16" else torch.float16)
+    ws = B.alloc_workspace(Q, ds, k)
+    ids, sc = B.ralm_retrieve_topk_ex(Qm.cuda(), ds, k, workspace=ws)
+    counters = B.ralm_workspace_counters(ws)
+    assert counters["ladder_overflows"] == 0 and counters["unanswered"] == 0
+    assert np.array_equal(ids.cpu().numpy(), wi) and np.array_equal(sc.cpu().numpy(), wsc)
 
 
 @pytest.mark.parametrize("d,Q", [(8, 3), (2048, 5), (2048, 70), (4096, 33), (16384, 2)])
