@@ -548,7 +548,6 @@ __global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams 
 #pragma unroll
     for (int idx = 0; idx < NR; ++idx) read_frag(0, smem, 0, idx);
 
-    uint32_t parked = 0;   // entries in the LDS list (uniform; maintained at tile ends)
     int buf = 0;
     int cur_rt = vb / nqt;
     int cur_qt = vb % nqt;
@@ -698,9 +697,10 @@ __global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams 
         if (wave_idle) {
             for (int kt = 0; kt < KT; ++kt) stage_idle();
         } else if constexpr (TN == 2 && NTA && !A32 && KEEP == KEEP_PARKED) {
-            // One query tile of 16-bit rows: a wave of whose two column blocks the second is all padding multiplies the
-            // first only.  The matrix cores set this tile's clock: 140 queries over 4M x 768 1507 -> 1452 us, 200 over 6M
-            // 2345 -> 2273 us, 256 the same.  (With several query tiles only the last one could gain, 0.6 % at most.)
+            // One query tile of 16-bit rows in whole lines: a wave of whose two column blocks the second is all padding
+            // multiplies the first only.  Waves w and w + 4, which hold the same columns, share a SIMD, so this idles that
+            // SIMD and the others set the tile's time; what is gained is power, and little: 200 queries over 6M x 768
+            // 2299 -> 2259 us, 224 2326 -> 2282, 140 2153 -> 2134, 170 2205 -> 2201, 256 the same within the noise.
             if (q0 + (wn * TN + 1) * 32 >= p.Q) tile(std::integral_constant<int, 1>{});   // wave-uniform
             else tile(std::integral_constant<int, TN>{});
         } else {
@@ -725,12 +725,7 @@ __global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams 
             __syncthreads();
             const uint32_t n = *pl.count;   // uniform: read after the barrier
             const uint32_t held = n < pl.cap ? n : pl.cap;
-            if (held >= pl.cap / 4 || (last_tile && held > 0)) {
-                flush_parked<NT, (BN <= 128)>(p, pl, tally, held);
-                parked = 0;
-            } else {
-                parked = held;
-            }
+            if (held >= pl.cap / 4 || (last_tile && held > 0)) flush_parked<NT, (BN <= 128)>(p, pl, tally, held);
         }
         cur_rt += step_rt;
         cur_qt += step_qt;
@@ -739,7 +734,6 @@ __global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams 
             ++cur_rt;
         }
     }
-    (void)parked;
     wait_vmcnt<0>();   // the run-ahead loads must land before this workgroup's LDS is released
 }
 
