@@ -255,8 +255,10 @@ constexpr int CM_NW = 8;
 constexpr int CM_MAX_GROUPS = 4;     // groups of 4 queries whose doubles are in LDS at a time
 
 // SEG = 16-byte pieces of a row that a lane has in flight per buffer; it divides the number of
-// pieces per lane and row, d / (4 * CH).
-template <int EX, int SEG>
+// pieces per lane and row, d / (4 * CH).  LIST: as above; tested at run time it took the registers of fp32 rows of 64
+// elements past 128 and with them the second workgroup of a CU, 30 to
+// 60 % of the time (500 requests x 4096 rows 87 us, 69 as a template parameter; 2000 x 2 queries x 64 rows 22.4 and 14.1).
+template <int EX, int SEG, bool LIST>
 __global__ __launch_bounds__(CM_NW * 64) void cache_lookup_mfma_kernel(
     const int32_t *__restrict__ cache_ids, const int32_t *__restrict__ cache_len, int C,
     const float *__restrict__ queries, int64_t Qt, const int64_t *__restrict__ q_offsets,
@@ -287,7 +289,7 @@ __global__ __launch_bounds__(CM_NW * 64) void cache_lookup_mfma_kernel(
     const int nblk = (len + 15) / 16;
     const int blk_step = parts * CM_NW;
     const unsigned char *base = static_cast<const unsigned char *>(exact) + kq * 16;
-    if (list && part == 0)
+    if (LIST && part == 0)
         for (int64_t q = q_lo + tid; q < q_hi; q += CM_NW * 64) list_len[q] = (uint32_t)len;
 
     for (int64_t g0 = q_lo; g0 < q_hi; g0 += 4 * ng_max) {
@@ -371,7 +373,7 @@ __global__ __launch_bounds__(CM_NW * 64) void cache_lookup_mfma_kernel(
 #pragma unroll
                     for (int g = 0; g < NG; ++g) {
                         const float sc = (float)acc[g] + 0.0f;   // -0 counts as +0, as in a key
-                        if (list) {   // uniform
+                        if constexpr (LIST) {
                             if (g * 4 + jq < nq && blk * 16 + ro < len)
                                 list[(g0 + g * 4 + jq) * C + blk * 16 + ro] = ok ? make_key(sc, id_out) : 0ull;
                             acc[g] = 0.0;
@@ -411,7 +413,7 @@ __global__ __launch_bounds__(CM_NW * 64) void cache_lookup_mfma_kernel(
         else if (n_groups == 2) run(std::integral_constant<int, 2>{});
         else if (n_groups == 3) run(std::integral_constant<int, 3>{});
         else run(std::integral_constant<int, 4>{});
-        if (list) continue;
+        if (LIST) continue;
         __syncthreads();
         for (int qi = tid; qi < nq; qi += CM_NW * 64) {
             const u64 b = best[qi];
@@ -826,8 +828,8 @@ bool cache_mfma_fits(int32_t d)
     return d % (EX == DT_F32 ? 64 : 128) == 0 && nc >= 4 && (size_t)d * 32 <= 64 * 1024;
 }
 
-template <int EX>
-hipError_t launch_cache_mfma(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,
+template <int EX, bool LIST>
+hipError_t launch_cache_mfma_form(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,
                              const float *queries, int64_t Qt, const int64_t *q_offsets, const void *exact,
                              int64_t ld, int64_t N, int32_t d, int32_t *spec_ids, float *spec_scores,
                              u64 *partial, u64 *list, uint32_t *list_len, int parts, hipStream_t stream)
@@ -839,7 +841,7 @@ hipError_t launch_cache_mfma(const int32_t *cache_ids, const int32_t *cache_len,
     const size_t smem = (size_t)ng * d * 32 + (size_t)4 * ng * sizeof(u64);
 #define RALM_CM(SEGV)                                                                                       \
     do {                                                                                                    \
-        auto kern = cache_lookup_mfma_kernel<EX, SEGV>;                                                     \
+        auto kern = cache_lookup_mfma_kernel<EX, SEGV, LIST>;                                               \
         static std::atomic<bool> attr_done{false};                                                          \
         if (!attr_done.load(std::memory_order_acquire)) {                                                   \
             hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),                        \
@@ -856,6 +858,18 @@ hipError_t launch_cache_mfma(const int32_t *cache_ids, const int32_t *cache_len,
     else RALM_CM(4);
 #undef RALM_CM
     return hipGetLastError();
+}
+
+template <int EX>
+hipError_t launch_cache_mfma(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,
+                             const float *queries, int64_t Qt, const int64_t *q_offsets, const void *exact,
+                             int64_t ld, int64_t N, int32_t d, int32_t *spec_ids, float *spec_scores,
+                             u64 *partial, u64 *list, uint32_t *list_len, int parts, hipStream_t stream)
+{
+    return list ? launch_cache_mfma_form<EX, true>(cache_ids, cache_len, C, R, queries, Qt, q_offsets, exact, ld, N, d, spec_ids,
+                                                   spec_scores, partial, list, list_len, parts, stream)
+                : launch_cache_mfma_form<EX, false>(cache_ids, cache_len, C, R, queries, Qt, q_offsets, exact, ld, N, d,
+                                                    spec_ids, spec_scores, partial, list, list_len, parts, stream);
 }
 
 }  // namespace
