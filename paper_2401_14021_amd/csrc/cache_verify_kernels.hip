@@ -633,7 +633,7 @@ __global__ __launch_bounds__(NT) void cache_rank_kernel(const u64 *__restrict__ 
     }
 }
 
-// Candidate lists for the k-entry cache retrieval over rows that the lookup kernels do not take (d > 2048): every query of a request gets the request's
+// Candidate lists for the k-entry cache retrieval by the re-score (cache_topk_by_rescore): every query of a request gets the request's
 // valid cached ids as ranking keys (score part 0), in any order; one workgroup per request.
 __global__ __launch_bounds__(256) void cache_keys_kernel(const int32_t *__restrict__ cache_ids,
                                                          const int32_t *__restrict__ cache_len, int C, int64_t Qt,
@@ -876,6 +876,12 @@ hipError_t launch_cache_mfma(const int32_t *cache_ids, const int32_t *cache_len,
 
 namespace {
 
+// whether the rows take the matrix-core form of the lookup
+bool lookup_on_matrix_cores(int32_t exact_dtype, int32_t metric, int32_t d)
+{
+    return metric == METRIC_IP && (exact_dtype == DT_F16 ? cache_mfma_fits<DT_F16>(d) : cache_mfma_fits<DT_F32>(d));
+}
+
 // the form of the lookup kernels that fits the rows
 hipError_t launch_lookup(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R, const float *queries, int64_t Qt,
                          const int64_t *q_offsets, const void *exact, int32_t exact_dtype, int64_t ld, int64_t N, int32_t d,
@@ -884,13 +890,14 @@ hipError_t launch_lookup(const int32_t *cache_ids, const int32_t *cache_len, int
 {
 #define RALM_CACHE(FN) \
     FN(cache_ids, cache_len, C, R, queries, Qt, q_offsets, exact, ld, N, d, spec_ids, spec_scores, partial, list, list_len, parts, stream)
+    const bool mfma = lookup_on_matrix_cores(exact_dtype, metric, d);
     if (exact_dtype == DT_F16) {
         if (metric == METRIC_L2) return RALM_CACHE((launch_cache_ex<DT_F16, true>));
-        if (cache_mfma_fits<DT_F16>(d)) return RALM_CACHE(launch_cache_mfma<DT_F16>);
+        if (mfma) return RALM_CACHE(launch_cache_mfma<DT_F16>);
         return RALM_CACHE((launch_cache_ex<DT_F16, false>));
     }
     if (metric == METRIC_L2) return RALM_CACHE((launch_cache_ex<DT_F32, true>));
-    if (cache_mfma_fits<DT_F32>(d)) return RALM_CACHE(launch_cache_mfma<DT_F32>);
+    if (mfma) return RALM_CACHE(launch_cache_mfma<DT_F32>);
     return RALM_CACHE((launch_cache_ex<DT_F32, false>));
 #undef RALM_CACHE
 }
@@ -928,6 +935,19 @@ hipError_t launch_cache_lookup(const int32_t *cache_ids, const int32_t *cache_le
     return hipGetLastError();
 }
 
+// fp16 rows on the vector units are 8-byte pieces, with few of them in flight; that pays where a row serves several
+// queries and not where there are enough queries for a workgroup each to fill the chip.  By the lookup kernels and
+// by the re-score, squared distance, us: 256 requests x 1 query x 2048 rows of 1024 elements 518 and 188; 128 x 1 x 2048 of
+// 2000 1125 and 317, 256 x 2 x 2048 2409 and 651, 256 x 4 x 512 577 and 339; inner product, 256 x 1 x 2048 of 392 216 and 119.
+// fp32 rows were at least as fast by the lookup kernels in every shape tried (64 to 2048 cached rows, 1 to 8 queries).
+bool cache_topk_by_rescore(int32_t exact_dtype, int32_t metric, int32_t d, int64_t R, int64_t Qt, int32_t C)
+{
+    if (d > CACHE_LOOKUP_MAX_D) return true;
+    if (exact_dtype != DT_F16 || lookup_on_matrix_cores(exact_dtype, metric, d)) return false;
+    if (d > 1024) return Qt >= 128 && (Qt <= 2 * R || (Qt >= 256 && C > 64));
+    return Qt >= 256 && Qt <= R && (int64_t)C * d >= 128 * 768;
+}
+
 hipError_t launch_cache_lookup_topk(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,
                                     const float *queries, int64_t Qt, const int64_t *q_offsets, const void *exact,
                                     int32_t exact_dtype, int64_t ld, int64_t N, int32_t d, int32_t metric, int32_t k,
@@ -937,8 +957,13 @@ hipError_t launch_cache_lookup_topk(const int32_t *cache_ids, const int32_t *cac
     hipError_t e = launch_fill_u32(list_len, 0u, Qt, stream);   // queries that no request owns have no entries
     if (e != hipSuccess) return e;
     if (R > 0) {
-        // two workgroups per CU (they hold their request's queries as doubles in LDS), at least 64 rows each
-        const int64_t want = (512 + R - 1) / R, most = (C + 63) / 64;
+        // two workgroups per CU, or one where the request's queries, as doubles in LDS, leave no room for two; each with
+        // rows for half a step of its waves (matrix cores: 8 waves of 16 rows) or a whole one (vector units: 8 or 4
+        // waves of 4 rows).  With 64 rows each, 16 requests x 8 queries x 64 fp16 rows of 1024 by squared distance were four
+        // steps one after the other: 43 us, now 20
+        const bool mfma = lookup_on_matrix_cores(exact_dtype, metric, d);
+        const int rows = mfma ? 64 : (d <= 768 ? 32 : 16), wgs = mfma || d <= 1024 ? 512 : 256;
+        const int64_t want = (wgs + R - 1) / R, most = (C + rows - 1) / rows;
         e = launch_lookup(cache_ids, cache_len, C, R, queries, Qt, q_offsets, exact, exact_dtype, ld, N, d, metric, nullptr,
                           nullptr, nullptr, list, list_len, (int)(want < most ? want : most), stream);
         if (e != hipSuccess) return e;

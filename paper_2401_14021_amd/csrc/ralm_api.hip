@@ -785,7 +785,7 @@ ralm_status ralm_cache_lookup_topk(const int32_t *cache_ids, const int32_t *cach
     u64 *keys = static_cast<u64 *>(workspace);
     uint32_t *cnt = reinterpret_cast<uint32_t *>(static_cast<unsigned char *>(workspace) + up256((size_t)Qt * C * 8));
     const int64_t ld = ds->exact_stride ? ds->exact_stride : ds->d;
-    if (ds->d <= CACHE_LOOKUP_MAX_D) {
+    if (!cache_topk_by_rescore(ds->exact_dtype, ds->metric, ds->d, R, Qt, C)) {
         RALM_HIP(launch_cache_lookup_topk(cache_ids, cache_len, C, R, queries, Qt, q_offsets, ds->exact, ds->exact_dtype, ld,
                                           ds->N, ds->d, ds->metric, k, out_ids, out_scores, keys, cnt, stream));
         return RALM_OK;

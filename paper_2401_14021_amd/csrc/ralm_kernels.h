@@ -137,6 +137,8 @@ hipError_t launch_cache_lookup(const int32_t *cache_ids, const int32_t *cache_le
                                hipStream_t stream);
 
 constexpr int CACHE_LOOKUP_MAX_D = 2048;   // the lookup kernels hold a row in registers
+// whether the k best cached entries are found by launch_cache_keys and launch_rescore instead of the next function
+bool cache_topk_by_rescore(int32_t exact_dtype, int32_t metric, int32_t d, int64_t R, int64_t Qt, int32_t C);
 // the k best cached entries per query; list [Qt, C] and list_len [Qt] are scratch
 hipError_t launch_cache_lookup_topk(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,
                                     const float *queries, int64_t Qt, const int64_t *q_offsets, const void *exact,

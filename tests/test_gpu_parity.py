@@ -1344,6 +1344,39 @@ def test_cache_lookup_topk_forms_and_row_lengths(B, oracle, dtype, d, metric, C,
     assert np.array_equal(ids.cpu().numpy(), wi) and np.array_equal(sc.cpu().numpy(), wsc)
 
 
+@pytest.mark.parametrize("d,metric", [(1000, "ip"), (1024, "l2"), (1032, "l2"), (2000, "ip"), (392, "ip")])
+@pytest.mark.parametrize("R,s,C", [(256, 1, 600), (256, 1, 129), (255, 1, 600), (300, 2, 300), (128, 1, 40), (127, 1, 40),
+                                   (64, 4, 200), (64, 4, 128), (16, 8, 70)])
+def test_cache_lookup_topk_of_fp16_rows_on_both_routes(B, oracle, d, metric, R, s, C):
+    """fp16 rows that the matrix cores do not take: with one or two queries per request and enough of them,
+    a workgroup per query scores the cached rows, otherwise the lookup kernels do, in parts of 16 or 32
+    rows.  Batches on both sides of every line, invalid ids, ragged and empty caches.  Integer data."""
+    g = torch.Generator().manual_seed(d + R + C)
+    N, k = 3000, min(C, 33)
+    X = torch.randint(-2, 3, (N, d), generator=g).half()
+    Qm = torch.randint(-2, 3, (R * s, d), generator=g).float()
+    off = torch.arange(R + 1, dtype=torch.int64) * s
+    cids = torch.stack([torch.randperm(N, generator=g)[:C] for _ in range(R)]).to(torch.int32)
+    cids[::3, 1] = -1
+    cids[::5, C // 2] = N
+    clen = torch.randint(0, C + 1, (R,), generator=g, dtype=torch.int32)
+    clen[0], clen[1] = C, 0
+    ds = B.Datastore(X.cuda())
+    ds.desc.metric = B.RALM_METRIC_L2 if metric == "l2" else B.RALM_METRIC_IP
+    ids, sc = B.ralm_cache_lookup_topk(cids.cuda(), clen.cuda(), Qm.cuda(), off.cuda(), ds, k)
+    ids, sc = ids.cpu().numpy(), sc.cpu().numpy()
+    Xn = X.float().numpy()
+    for r in range(0, R, max(1, R // 24)):
+        own = cids[r, :int(clen[r])].numpy()
+        own = own[(own >= 0) & (own < N)]
+        for i in range(r * s, r * s + s):
+            n = min(k, len(own))
+            score = oracle.scores(Qm[i].numpy(), Xn[own], metric) if len(own) else np.zeros(0, np.float32)
+            order = np.lexsort((own, -score))[:n]
+            assert np.array_equal(ids[i, :n], own[order]) and np.array_equal(sc[i, :n], score[order])
+            assert (ids[i, n:] == -1).all() and np.isneginf(sc[i, n:]).all()
+
+
 def test_knnlm_speculation_from_the_cache_and_token_level_verification(B, oracle):
     """Section 5.3 end to end on the entry points: the cache holds the successors of previously
     retrieved entries (next-n update); the speculation step takes its k nearest entries from the
