@@ -480,10 +480,12 @@ __global__ __launch_bounds__(256) void verify_kernel(const int32_t *__restrict__
 //   2. every wave compares the 64 candidates with its part of the remaining slots (an id read from
 //      LDS serves all lanes): whoever is found there is a member whatever happens in the zone;
 //   3. wave 0 walks the others in order: a member of the zone as it is by then is skipped, anyone
-//      else takes the zone's next slot.  A batch ends early when its zone is used up.
+//      else takes the zone's next slot.  A batch ends early when its zone is used up, unless the zone is the whole
+//      ring: then it goes round.
 // What bounds it: step 2's LDS reads, len / (4 waves) of them per 64 candidates, and the loop of step
 // 3.  The former version gave one wave to a request and spread one candidate's test over its
-// lanes, a chain of len / 256 LDS reads per candidate.  512 requests x up to 160 candidates, caches
+// lanes, a chain of len / 256 LDS reads per candidate.  64 requests x 80 candidates into caches of one entry, us: one
+// candidate at a time 34, in batches that end with the ring 87, now 15.  512 requests x up to 160 candidates, caches
 // of 4096: 456 -> 79 us; 32 requests x 640 candidates, caches of 2048: 811 -> 97 us.
 constexpr int CI_THREADS = 512, CI_WAVES = CI_THREADS / 64;
 
@@ -570,14 +572,19 @@ __global__ __launch_bounds__(CI_THREADS) void cache_insert_kernel(
             u64 safe = 0;
             for (int w = 0; w < CI_WAVES; ++w) safe |= s_member[w];
             todo &= ~safe;
-            int used = 0, taken = 64;
+            int used = 0, taken = 64;      // used: the zone's slot that takes the next insertion
+            bool round = false;            // the zone is the ring and has been gone round
             while (todo) {                 // wave-uniform
                 const int c = __ffsll((long long)todo) - 1;
                 const int32_t ec = __builtin_amdgcn_readlane(e, c);
                 if (!__any(zone == ec)) {
-                    if (used == zone_n) {  // no slot left in the zone: this candidate opens the next batch
-                        taken = c;
-                        break;
+                    if (used == zone_n) {
+                        if (len < C || zone_n < C) {   // no slot left in the zone: this candidate opens the next batch
+                            taken = c;
+                            break;
+                        }
+                        used = 0;
+                        round = true;
                     }
                     if (lane == used) zone = ec;
                     ++used;
@@ -586,7 +593,7 @@ __global__ __launch_bounds__(CI_THREADS) void cache_insert_kernel(
             }
             if (lane < zone_n) {
                 cs[slot] = zone;
-                if (lane < used) ids[slot] = zone;
+                if (lane < used || round) ids[slot] = zone;
             }
             if (lane == 0) {
                 s_taken = taken;
