@@ -313,6 +313,7 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
     sp.one_per_cu = reserve > 0;
     // one stage: scan the tiles sp describes, then cut every list down to its k' best
     int32_t stage_no = 0;
+    int64_t last_expected = 0;   // keys per list that the last stage should leave
     // (short lists: the last stage's are cut down by the re-score)
     const bool cut_in_rescore = pl.k_prime < RESCORE_CUT_MIN;
     auto run_stage = [&](int64_t expected, bool last) -> ralm_status {
@@ -331,6 +332,7 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
             RALM_HIP(hipEventRecord(g_prof_ev[g_prof_n][1], stream));
             ++g_prof_n;
         }
+        last_expected = expected;
         if (last && cut_in_rescore) return RALM_OK;
         RALM_HIP(launch_select(cand, cnt, pl.cap, pl.k_prime, Q, tau, lost, flags, stage_no++, expected, stream));
         return RALM_OK;
@@ -348,17 +350,19 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
             st = run_stage(pl.cap, t0 + block >= tiles);
             if (st != RALM_OK) return st;
         }
+        last_expected = tiles > block ? 2 * pl.k_prime : tiles * SCAN_BM;
     } else {
         sp.tile_begin = 0;
         for (int s = 0; s < pl.n_stages; ++s) {
             const int64_t stride = pl.stride[s];
             sp.tile_stride = stride;
-            int64_t expected = pl.cap;                              // keys per list when the stage ends
+            int64_t expected;                                       // keys per list when the stage ends
             if (s == 0) {
                 sp.tile_skip = 0;                                   // every multiple of the stride
                 sp.n_row_tiles = (tiles + stride - 1) / stride;
                 sp.admits = sp.n_row_tiles * SCAN_BM;               // everything
                 sp.lists_empty = 1;
+                expected = sp.admits;
             } else {
                 const int64_t m_max = (tiles + stride - 1) / stride - 1;   // multiples m >= 1 with m*stride < tiles
                 const int64_t g = pl.stride[s - 1] / stride;        // ... that no earlier stage visited
@@ -388,7 +392,7 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
     cert.u_rows = (scan == ds->exact && scan_dt == ds->exact_dtype && scan_dt != RALM_F32) ? 0.f : u;
     if (cut_in_rescore)
         RALM_HIP(launch_rescore(cand, cnt, CNT_PITCH, pl.cap, pl.k_prime, queries, Q, ds->exact, ds->exact_dtype, exact_ld,
-                                ds->d, ds->metric, k, out_ids, out_scores, out_margin, cert, stream));
+                                ds->d, ds->metric, k, out_ids, out_scores, out_margin, cert, last_expected, stream));
     else
         RALM_HIP(launch_rescore_cut(cand, cnt, pl.cap, pl.k_prime, queries, Q, ds->exact, ds->exact_dtype, exact_ld, ds->d,
                                     ds->metric, k, out_ids, out_scores, out_margin, cert, stream));
@@ -795,7 +799,7 @@ ralm_status ralm_cache_lookup_topk(const int32_t *cache_ids, const int32_t *cach
     CertifyParams no_check;
     memset(&no_check, 0, sizeof(no_check));
     RALM_HIP(launch_rescore(keys, cnt, 1, (uint32_t)C, C, queries, Qt, ds->exact, ds->exact_dtype, ld, ds->d, ds->metric,
-                            k, out_ids, out_scores, nullptr, no_check, stream));
+                            k, out_ids, out_scores, nullptr, no_check, 0, stream));
     return RALM_OK;
 }
 

@@ -109,10 +109,11 @@ hipError_t launch_select(u64 *cand, uint32_t *cnt, uint32_t cap, int32_t k_prime
 // with cert.flags: the result is checked and queries that fail are queued for launch_exact_pass
 // with cert.flags, cand are the lists as the ladder's last stage left them: more than k' keys are
 // cut down to the k' best first and the stage's lengths recorded, as by launch_select
+// expected: keys that a list should hold (any number is handled)
 hipError_t launch_rescore(const u64 *cand, const uint32_t *cnt, int cnt_pitch, uint32_t cap, int32_t k_prime,
                           const float *queries, int64_t Q, const void *exact, int32_t exact_dtype, int64_t ld,
                           int32_t d, int32_t metric, int32_t k, int32_t *out_ids, float *out_scores,
-                          float *out_margin, const CertifyParams &cert, hipStream_t stream);
+                          float *out_margin, const CertifyParams &cert, int64_t expected, hipStream_t stream);
 
 constexpr int RESCORE_CUT_MIN = 257;   // k' from which launch_rescore_cut is used
 // the same with the check, for lists that launch_select has cut down to their k' best (at least 16384 slots,

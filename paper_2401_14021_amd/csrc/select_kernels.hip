@@ -940,7 +940,7 @@ hipError_t launch_select(u64 *cand, uint32_t *cnt, uint32_t cap, int32_t k_prime
 hipError_t launch_rescore(const u64 *cand, const uint32_t *cnt, int cnt_pitch, uint32_t cap, int32_t k_prime, const float *queries,
                           int64_t Q, const void *exact, int32_t exact_dtype, int64_t ld, int32_t d, int32_t metric,
                           int32_t k, int32_t *out_ids, float *out_scores, float *out_margin,
-                          const CertifyParams &cert, hipStream_t stream)
+                          const CertifyParams &cert, int64_t expected, hipStream_t stream)
 {
     if (Q <= 0) return hipSuccess;
     int kp2 = 2;
@@ -961,10 +961,14 @@ hipError_t launch_rescore(const u64 *cand, const uint32_t *cnt, int cnt_pitch, u
     } while (0)
     // With more queries than two large workgroups per CU hold, small ones (eight per CU) overlap one query's
     // chain of list, rows and ranking with the others' gathers: 1024 queries, k' = 64: 50 us instead of 91,
-    // 2341: 96 instead of 200.  Fewer queries, or many candidates each, need the large workgroup's waves.
+    // 2341: 96 instead of 200.  Fewer queries, or many candidates each, need the large workgroup's waves; so do long
+    // lists, of which a small one holds only 4096 keys in registers (the one stage of a small datastore).  Whole calls
+    // with small and large ones, us: 512 queries over 16384 rows of 64, k = 5, 134 and 67, over 8000 rows 86 and 62, 1024
+    // over 8000 101 and 89, 3000 over 16384 451 and 353, over 8000 227 and 233, k = 100 364 and 410.
+    const bool short_lists = expected <= SEL_REGS * 256 || (expected <= SEL_REGS * 512 && Q >= 2048);
 #define RALM_RS(EXV, L2V)                                  \
     do {                                                   \
-        if (Q >= 512 && k_prime <= RS_COUNT_MAX) RALM_RS_NT(EXV, L2V, 256); \
+        if (Q >= 512 && k_prime <= RS_COUNT_MAX && short_lists) RALM_RS_NT(EXV, L2V, 256); \
         else RALM_RS_NT(EXV, L2V, SEL_THREADS);            \
     } while (0)
     if (exact_dtype == DT_F16) {
