@@ -291,9 +291,10 @@ ralm_status ralm_build_scan_copy_l2(const void *src, int32_t src_dtype, int64_t 
  * speculative retrieval step; Section 3 "Speculative retrieval"; Fig. 2: the
  * cache is ranked with the retriever's own metric).  A cache holds datastore
  * row ids; the key is re-read from the exact datastore so that a cached
- * entry's score is the very number the knowledge-base retrieval would give it
- * (this is what makes the cache top-1 equal the knowledge-base top-1 whenever
- * the latter is cached).
+ * entry's score is the double sum, rounded once, that the knowledge-base
+ * retrieval forms (the additions may come in another order).  This is what
+ * makes the cache top-1 equal the knowledge-base top-1 whenever the latter is
+ * cached.
  *
  *   cache_ids  device int32 [R, C]; request r owns entries [0, cache_len[r])
  *              of row r; every owned id must be in [0, N) (ids outside are

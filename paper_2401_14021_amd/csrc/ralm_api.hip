@@ -97,7 +97,8 @@ ralm_status make_plan(int64_t Q, const ralm_datastore_t *ds, int32_t k, int32_t 
     //                      than it saves: Q = 64, k' = 512, 2M x 1024 by 32 and 2 1079 us, by 5, 5 and 5 1004; Q = 16, k' = 2048, 1M x 1024 1027, 912.
     //   up to 256 queries  100 over 200K x 768 by 13 111 us, by 4 and 4 137, by 2, 2, 2 and 2 164; 81 over 1M round
     //                      by 8 and 8 370, by 2, 2, 2 and 8 392; 100 over 8M by 8, 8 and 8 2072, by 2, 2, 2, 8 and 8
-    //                      2128.  k' > 256: 256 over 10M x 1024, k' = 2048, by 4 throughout 6497, by 2 6617.
+    //                      2128; 200 over 6M by 4, 8 and 16 2243, by 2, 2, 2, 8 and 8 2268.  k' > 256:
+    //                      256 over 10M x 1024, k' = 2048, by 4 throughout 6497, by 2 6617.
     //   more               bound by the matrix cores, which wait for the selection: the last half of the rows should
     //                      see keys within a factor 2 of final, so the finest step is 2; 600 over
     //                      400K by 2, 4 and 4 602 us, by 2, 2, 2 and 4 625, by 4 and 8 609.
