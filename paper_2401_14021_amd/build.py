@@ -14,7 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libralm.so")
-SOURCES = ["ralm_api.hip", "scan_kernels.hip", "select_kernels.hip", "cache_verify_kernels.hip", "knnlm_kernels.hip",
+SOURCES = ["ralm_api.hip", "scan_kernels.hip", "scan_held_kernels.hip", "select_kernels.hip", "cache_verify_kernels.hip", "knnlm_kernels.hip",
            "os3_host.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -22,9 +22,13 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-u
          "-mllvm", "-pragma-unroll-threshold=1000000"]
 
 
+# matrix results in vector registers: the kernel fills the accumulation registers with its queries
+EXTRA = {"scan_held_kernels.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+
+
 def _compile(src: str) -> str:
     obj = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
-    cmd = ["hipcc", *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = ["hipcc", *FLAGS, *EXTRA.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     err = "\n".join(l for l in r.stderr.splitlines() if "packed-fp32-ops" not in l)
     if r.returncode != 0:

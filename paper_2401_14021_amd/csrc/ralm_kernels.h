@@ -46,6 +46,10 @@ struct ScanParams {
 // query tile width chosen for Q
 int scan_bn_for(int64_t Q);
 hipError_t launch_scan(const ScanParams &p, int n_cu, hipStream_t stream);
+// whether a launch whose thresholds admit few scores is better served by the kernel that holds the queries in registers
+bool scan_held_takes(const ScanParams &p, int n_cu);
+bool whole_lines(const ScanParams &p);   // rows that are whole 128-byte lines
+hipError_t launch_scan_held(const ScanParams &p, bool nt, int n_cu, hipStream_t stream);   // nt: rows stream past L2
 
 hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t stream);
 
