@@ -351,8 +351,12 @@ hipError_t launch_type(const ScanParams &p, bool nt, int n_cu, hipStream_t strea
 // us per launch, tiled and held, where the line lies.
 bool scan_held_takes(const ScanParams &p, int n_cu)
 {
-    // up to 64 queries the tiled kernel's stream of queries is small: 70 queries over 4M x 768 1038 and 982 us a call
-    if (p.in_dtype == DT_F32 || p.Q <= 64) return false;
+    if (p.in_dtype == DT_F32) return false;
+    // Up to 64 queries the tiled kernel's stream of queries is small and its rows come at the rate of a pure read: 50 over 4M x 768
+    // 997, 1030 us a call, 8 929, 966 (70: 1038, 982).  Rows that are no whole lines it fetches at less: 8 over 1M x 392
+    // in corpus order 197, 169, 4 over 2M x 904 740, 614, 60 over 1M x 600 329, 251.  With CUs reserved up to 32 queries leave half of a
+    // CU's LDS to other kernels, and this one takes all.
+    if (p.Q <= 64 && (whole_lines(p) || (p.Q <= 32 && p.one_per_cu))) return false;
     // the queries fit the registers; rows of less than 257 elements are too few multiplies for a tile's two rendezvous
     const int kt = p.dpad / 64, bn = p.Q <= 128 ? 128 : 256;
     if (kt < 5 || kt > (p.Q <= 128 ? 17 : 12)) return false;

@@ -67,6 +67,11 @@ def test_two_column_blocks_per_wave(rows, oracle, strips, full):
     _check(rows, oracle, d, 256 if full else 129, torch.float16 if full else torch.bfloat16)
 
 
+@pytest.mark.parametrize("d,Q", [(392, 1), (904, 40), (1032, 64), (328, 33)])
+def test_few_queries_over_rows_that_are_no_whole_lines(rows, oracle, d, Q):
+    _check(rows, oracle, d, Q, torch.float16)
+
+
 @pytest.mark.parametrize("d,Q", [(768, 512), (712, 1000), (392, 512), (576, 1024)])
 def test_several_query_tiles(rows, oracle, d, Q):
     _check(rows, oracle, d, Q, torch.bfloat16)
