@@ -252,9 +252,11 @@ __global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams 
     constexpr int NM = TM * TN, NR = TM + TN;
     constexpr int LAG = NM > 2 ? 2 : NM - 1;     // selection runs this many MFMAs behind
     constexpr int RV = NR - 1;                   // slot of k-step RK after which the stage rendezvous sits
-    // a workgroup tile covers the whole 256-row tile of the ladder, or half of it
+    // a workgroup tile covers the whole 256-row tile of the ladder, half or a quarter of it
     constexpr int PARTS = SCAN_BM / BM;
-    static_assert((NW == 4 || NW == 8) && (BM == SCAN_BM || BM * 2 == SCAN_BM) && NA >= 1 && NB >= 1, "tile shape");
+    static_assert((NW == 4 || NW == 8) && (PARTS == 1 || PARTS == 2 || PARTS == 4) && PARTS * BM == SCAN_BM &&
+                      NA >= 1 && NB >= 1,
+                  "tile shape");
     static_assert(S >= 2 && (D == S - 1 || D == S) && D >= 2 && KS % 2 == 0, "ring depth / k-steps per stage");
     static_assert(RK >= 0 && RK + 1 < KS && (D < S || RK == KS - 2), "rendezvous position");
     static_assert(LPS * (D - 1) < 64, "vmcnt range");
@@ -685,9 +687,39 @@ hipError_t launch_kept(const ScanParams &p, int n_cu, hipStream_t stream)
     }
 }
 
+// More than 32 queries (whose tiles are halves as it is), and whole tiles would leave half of the CUs idle.
+bool few_tiles(const ScanParams &p, int n_cu)
+{
+    const int bn = scan_bn_for(p.Q);
+    return p.Q > 32 && p.n_row_tiles * ((p.Q + bn - 1) / bn) * 2 <= n_cu;
+}
+
+// A first stage of few tiles (64 where the lists have 16384 slots) leaves most CUs without one, and a workgroup that has one
+// waits for its strips one after the other.  Quarter tiles spread it over four times as many workgroups, with deeper
+// rings.  us per launch, 62 whole tiles and 248 quarters of 768 elements: 40 queries 13.2, 9.0; 81 18.2, 12.0; 200 31.8, 17.3; 500 41.7,
+// 36.9; 3 queries, which have half tiles anyway, 8.1, 8.4.
+template <bool F16>
+hipError_t launch_quarter(const ScanParams &p, int n_cu, hipStream_t stream)
+{
+    switch (scan_bn_for(p.Q)) {
+        case 64: return launch_dma_variant<F16, 2, 2, 1, 1, 64, 6, false, 6, 2, false, KEEP_ALL>(p, n_cu, stream);
+        case 128: return launch_dma_variant<F16, 2, 4, 1, 1, 64, 5, false, 5, 2, false, KEEP_ALL>(p, n_cu, stream);
+        default: return launch_dma_variant<F16, 2, 4, 1, 2, 64, 3, false, 3, 2, false, KEEP_ALL>(p, n_cu, stream);
+    }
+}
+hipError_t launch_quarter_f32(const ScanParams &p, int n_cu, hipStream_t stream)
+{
+    switch (scan_bn_for(p.Q)) {
+        case 64: return launch_dma_variant<false, 2, 2, 1, 1, 64, 4, false, 3, 0, true, KEEP_ALL>(p, n_cu, stream);
+        case 128: return launch_dma_variant<false, 2, 4, 1, 1, 32, 5, false, 5, 0, true, KEEP_ALL>(p, n_cu, stream);
+        default: return launch_dma_variant<false, 2, 4, 1, 2, 32, 4, false, 4, 0, true, KEEP_ALL>(p, n_cu, stream);
+    }
+}
+
 template <bool F16>
 hipError_t launch_16(const ScanParams &p, bool all_kept, bool counted, bool nt, int n_cu, hipStream_t stream)
 {
+    if (all_kept && few_tiles(p, n_cu)) return launch_quarter<F16>(p, n_cu, stream);
     if (all_kept) return launch_kept<F16, false, KEEP_ALL>(p, n_cu, stream);
     if (counted)
         return nt ? launch_kept<F16, true, KEEP_COUNTED>(p, n_cu, stream) : launch_kept<F16, false, KEEP_COUNTED>(p, n_cu, stream);
@@ -743,6 +775,7 @@ hipError_t launch_scan(const ScanParams &p, int n_cu, hipStream_t stream)
     const bool nt = p.Q <= 256 && whole_lines(p);
     if (!all_kept && !counted && scan_held_takes(p, n_cu)) return launch_scan_held(p, nt, n_cu, stream);
     if (p.in_dtype == DT_F32) {
+        if (all_kept && few_tiles(p, n_cu)) return launch_quarter_f32(p, n_cu, stream);
         if (all_kept) return launch_f32<false, KEEP_ALL>(p, n_cu, stream);
         if (counted) return nt ? launch_f32<true, KEEP_COUNTED>(p, n_cu, stream) : launch_f32<false, KEEP_COUNTED>(p, n_cu, stream);
         return nt ? launch_f32<true, KEEP_PARKED>(p, n_cu, stream) : launch_f32<false, KEEP_PARKED>(p, n_cu, stream);
