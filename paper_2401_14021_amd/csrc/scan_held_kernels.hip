@@ -33,7 +33,7 @@ constexpr int HELD_LIST = 28;                        // blocks' columns that a w
 // scores is tested under the multiplies of the next one.  With TN = 1 the two chains are the even and the odd k-steps.
 template <bool F16, int KT, int TN, bool NTA>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
-void scan_held_kernel(const ScanParams p, const int nqt, const int streams_per_xcd)
+void scan_held_kernel(ScanParams p, const int nqt, const int streams_per_xcd)
 {
     constexpr int BN = TN * 128;
     constexpr int S = HELD_RING_STRIPS / KT;                 // tiles in the ring
@@ -71,16 +71,24 @@ void scan_held_kernel(const ScanParams p, const int nqt, const int streams_per_x
     auto tile_row0 = [&](int rt) __attribute__((always_inline)) -> int64_t {
         return visited_tile(p, rt / PARTS) * SCAN_BM + (rt % PARTS) * HELD_BM;
     };
-    const int q0 = qt * BN;
+    // from here on the batch is this workgroup's query tile
+    {
+        const int q0 = qt * BN;
+        p.Qs += (int64_t)q0 * p.dpad;
+        p.tau += q0;
+        p.cand += (int64_t)q0 * p.cap;
+        p.cnt += (int64_t)q0 * CNT_PITCH;
+        p.Q = p.Q - q0 < BN ? p.Q - q0 : BN;
+    }
     const int32_t n_rows = (int32_t)p.N;
     if (tid == 0) *pl.count = 0;
-    if (tid < BN) tau_lds[tid] = q0 + tid < p.Q ? p.tau[q0 + tid] : ~0ull;
+    if (tid < BN) tau_lds[tid] = tid < p.Q ? p.tau[tid] : ~0ull;
 
     // this wave's queries: elements 64 kt + 16 kk + 8 hi .. + 7 of columns 32 (TN wave + j) + fr
     const int column0 = wave * TN * 32;
     uint4 fb[KT][4][TN];
     {
-        const uint16_t *src = p.Qs + (int64_t)(q0 + column0 + fr) * p.dpad + hi * 8;
+        const uint16_t *src = p.Qs + (int64_t)(column0 + fr) * p.dpad + hi * 8;
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
@@ -109,7 +117,7 @@ void scan_held_kernel(const ScanParams p, const int nqt, const int streams_per_x
     for (int j = 0; j < TN; ++j) {
         const int c = column0 + j * 32 + fr;
         const u64 t = tau_lds[c];
-        tsc[j] = q0 + c < p.Q ? (t == 0ull ? -__builtin_inff() : key_score(t)) : __builtin_inff();
+        tsc[j] = c < p.Q ? (t == 0ull ? -__builtin_inff() : key_score(t)) : __builtin_inff();
     }
 
     // ---- load cursor ----
@@ -187,9 +195,9 @@ void scan_held_kernel(const ScanParams p, const int nqt, const int streams_per_x
                 const uint32_t at = __hip_atomic_fetch_add(pl.count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 if (at < pl.cap) {
                     pl.keys[at] = key;
-                    pl.qs[at] = (uint32_t)(q0 + c);
+                    pl.qs[at] = (uint32_t)c;
                 } else {
-                    push_global(p, q0 + c, key);
+                    push_global(p, c, key);
                 }
             }
         }
@@ -326,10 +334,13 @@ hipError_t launch_kt(const ScanParams &p, bool nt, int n_cu, hipStream_t stream)
     return nt ? launch_variant<F16, KT, TN, true>(p, n_cu, stream) : launch_variant<F16, KT, TN, false>(p, n_cu, stream);
 }
 
+// queries of a tile
+int scan_held_bn(const ScanParams &p) { return p.Q <= 128 || p.dpad > 768 ? 128 : 256; }
+
 template <bool F16>
 hipError_t launch_type(const ScanParams &p, bool nt, int n_cu, hipStream_t stream)
 {
-    if (p.Q <= 128) {
+    if (scan_held_bn(p) == 128) {
         switch (p.dpad / 64) {
 #define RALM_HELD(KT) case KT: return launch_kt<F16, KT, 1>(p, nt, n_cu, stream);
             RALM_HELD(5) RALM_HELD(6) RALM_HELD(7) RALM_HELD(8) RALM_HELD(9) RALM_HELD(10) RALM_HELD(11) RALM_HELD(12)
@@ -357,13 +368,17 @@ bool scan_held_takes(const ScanParams &p, int n_cu)
     // in corpus order 197, 169, 4 over 2M x 904 740, 614, 60 over 1M x 600 329, 251.  With CUs reserved up to 32 queries leave half of a
     // CU's LDS to other kernels, and this one takes all.
     if (p.Q <= 64 && (whole_lines(p) || (p.Q <= 32 && p.one_per_cu))) return false;
-    // the queries fit the registers; rows of less than 257 elements are too few multiplies for a tile's two rendezvous
-    const int kt = p.dpad / 64, bn = p.Q <= 128 ? 128 : 256;
-    if (kt < 5 || kt > (p.Q <= 128 ? 17 : 12)) return false;
+    // The queries fit the registers; of rows of more than 768 elements only 128 per workgroup, whose multiplies then read LDS as fast
+    // as it gives: 256 over 2M x 1024 1215, 1237, but 250 over 1M x 1000 759, 630, 1000 over 1M x 904 2037, 1879.  Rows of less
+    // than 257 elements are too few multiplies for a tile's two rendezvous.
+    const int kt = p.dpad / 64, bn = scan_held_bn(p);
+    if (kt < 5 || kt > 17 || (kt > 12 && p.Q > 128 && whole_lines(p))) return false;
     // every stream of rows needs a CU for each query tile on its XCD: a batch that leaves more than a twentieth of the columns or
     // CUs idle is better off in tiles (2341 queries, 10 tiles on 30 of 32 CUs: 13414, 14246 us a round)
     const int64_t nqt = (p.Q + bn - 1) / bn, per_xcd = n_cu / 8, streams = per_xcd / nqt;
-    if (nqt > 1 && p.Q * streams * 20 < per_xcd * bn * 19) return false;
+    if (streams < 1) return false;   // (nearly all CUs reserved)
+    // (two tiles of 128 were better at any size: 135 queries over 1M x 904 680, 564)
+    if (!(nqt == 2 && bn == 128) && nqt > 1 && p.Q * streams * 20 < per_xcd * bn * 19) return false;
     // several query tiles share the stream of rows, and short rows are few multiplies between two rendezvous: 1000 queries
     // over 2M x 384 1520, 1567 us, 512 over 2M x 512 1047, 1042.  Rows that are no whole lines cost the tiled kernel more: 512 over
     // 1M x 560 694, 620

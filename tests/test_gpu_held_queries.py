@@ -72,7 +72,7 @@ def test_few_queries_over_rows_that_are_no_whole_lines(rows, oracle, d, Q):
     _check(rows, oracle, d, Q, torch.float16)
 
 
-@pytest.mark.parametrize("d,Q", [(768, 512), (712, 1000), (392, 512), (576, 1024)])
+@pytest.mark.parametrize("d,Q", [(768, 512), (712, 1000), (392, 512), (576, 1024), (904, 129), (1000, 256), (1080, 384), (840, 1000)])
 def test_several_query_tiles(rows, oracle, d, Q):
     _check(rows, oracle, d, Q, torch.bfloat16)
 
@@ -80,3 +80,15 @@ def test_several_query_tiles(rows, oracle, d, Q):
 @pytest.mark.parametrize("d,Q", [(1024, 100), (632, 200)])
 def test_squared_distance(rows, oracle, d, Q):
     _check(rows, oracle, d, Q, torch.float16, metric_l2=True)
+
+
+@pytest.mark.parametrize("reserve", [8, 240, 300])
+def test_compute_units_reserved(rows, oracle, reserve):
+    from paper_2401_14021_amd import binding as B
+    B.ralm_scan_reserve_cus(reserve)
+    try:
+        _check(rows, oracle, 904, 129, torch.bfloat16)
+        _check(rows, oracle, 768, 100, torch.bfloat16)
+        _check(rows, oracle, 392, 20, torch.float16)
+    finally:
+        B.ralm_scan_reserve_cus(0)
