@@ -26,6 +26,9 @@
 // run at the same time on one XCD (workgroup b lands on XCD b % 8) hold consecutive items:
 // all query tiles of a row tile, then the next row tile.  The row tile's second to last
 // readers therefore hit that XCD's L2.
+//
+// Launches with selective thresholds of batches whose queries fit the registers of a workgroup are served by
+// scan_held_kernels.hip.
 #include <type_traits>
 
 #include <atomic>
@@ -585,7 +588,8 @@ __global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams 
             // One query tile of 16-bit rows in whole lines: a wave of whose two column blocks the second is all padding
             // multiplies the first only.  Waves w and w + 4, which hold the same columns, share a SIMD, so this idles that
             // SIMD and the others set the tile's time; what is gained is power, and little: 200 queries over 6M x 768
-            // 2299 -> 2259 us, 224 2326 -> 2282, 140 2153 -> 2134, 170 2205 -> 2201, 256 the same within the noise.
+            // 2299 -> 2259 us, 224 2326 -> 2282, 140 2153 -> 2134, 170 2205 -> 2201, 256 the same within the noise.  (Rows of that
+            // length have a kernel of their own by now; longer ones and stages that admit more still come here.)
             if (q0 + (wn * TN + 1) * 32 >= p.Q) tile(std::integral_constant<int, 1>{});   // wave-uniform
             else tile(std::integral_constant<int, TN>{});
         } else {
