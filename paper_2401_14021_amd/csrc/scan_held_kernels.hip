@@ -30,7 +30,8 @@ constexpr int HELD_LIST = 28;                        // blocks' columns that a w
 // half before this one, which everyone has read, may be overwritten.
 //
 // Multiplies: a lone wave per SIMD has nothing to cover its waits, so operands are read a strip ahead, and a block of
-// scores is tested under the multiplies of the next one.  With TN = 1 the two chains are the even and the odd k-steps.
+// scores is tested under the multiplies of the next one.  A score is one chain of multiplies in the order of its elements, as in the
+// tiled kernel: added by even and odd k-steps, products that cancel in order may overflow to both infinities, and the row is lost.
 template <bool F16, int KT, int TN, bool NTA>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void scan_held_kernel(ScanParams p, const int nqt, const int streams_per_xcd)
@@ -174,9 +175,9 @@ void scan_held_kernel(ScanParams p, const int nqt, const int streams_per_xcd)
     int buf = 0;
     int cur_rt = stream;
     int32_t prev_row0 = 0;
-    f32x16 acc[2];   // TN = 2: one per column block; TN = 1: even and odd k-steps
+    f32x16 acc[TN];   // one per column block
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = 0.f;
+    for (int v = 0; v < 16; ++v) acc[0][v] = acc[TN - 1][v] = 0.f;
 
     // Columns of a block that may hold an admitted score are put aside as they are, 16 scores and where they belong, in a list
     // of this wave's own: no atomics and no waits between two multiplies.  sort_out() tests the scores later, 64 at a
@@ -250,21 +251,20 @@ void scan_held_kernel(ScanParams p, const int nqt, const int streams_per_xcd)
             if (kt == H - 1) rendezvous(std::integral_constant<int, (S - 2) * KT + H - 1>{});
             if (kt == KT - 1) rendezvous(std::integral_constant<int, (S - 2) * KT + KT - H - 1>{});
             RALM_SCHED_FENCE();
-            // The two chains take turns; with two column blocks a tile's first and last strips do one after the other, so that the
-            // block that is complete is tested under the other's multiplies.
+            // Two column blocks take turns; a tile's first and last strips do one after the other, so that the block that is
+            // complete is tested under the other's multiplies.
             const bool grouped = TN == 2 && (kt == 0 || kt == KT - 1);
             float m = 0.f;
 #pragma unroll
             for (int i = 0; i < 4 * TN; ++i) {
                 const int kk = TN == 1 ? i : (grouped ? i % 4 : i / 2), j = TN == 1 ? 0 : (grouped ? i / 4 : i % 2);
-                const int chain = TN == 1 ? i % 2 : j;
-                if (kt == 0 && (TN == 1 ? i < 2 : kk == 0)) {
+                if (kt == 0 && kk == 0) {
                     f32x16 zero;
 #pragma unroll
                     for (int v = 0; v < 16; ++v) zero[v] = 0.f;
-                    acc[chain] = mfma32<F16>(fa[set_of(kt)][kk], fb[kt][kk][j], zero);
+                    acc[j] = mfma32<F16>(fa[set_of(kt)][kk], fb[kt][kk][j], zero);
                 } else {
-                    acc[chain] = mfma32<F16>(fa[set_of(kt)][kk], fb[kt][kk][j], acc[chain]);
+                    acc[j] = mfma32<F16>(fa[set_of(kt)][kk], fb[kt][kk][j], acc[j]);
                 }
                 if (i % TN == 0) {
                     if (kt + 1 < KT) read_a(cb, kt + 1, i / TN);
@@ -292,10 +292,7 @@ void scan_held_kernel(ScanParams p, const int nqt, const int streams_per_xcd)
         if constexpr (TN == 1) {   // half as many multiplies per row: they wait for the rows, not the rows for them
             float m = -__builtin_inff();
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                acc[0][v] += acc[1][v];
-                m = fmaxf(m, acc[0][v]);
-            }
+            for (int v = 0; v < 16; ++v) m = fmaxf(m, acc[0][v]);
             select(0, m, row0);
         }
         prev_row0 = row0;

@@ -92,3 +92,28 @@ def test_compute_units_reserved(rows, oracle, reserve):
         _check(rows, oracle, 392, 20, torch.float16)
     finally:
         B.ralm_scan_reserve_cus(0)
+
+
+@pytest.mark.parametrize("d,Q", [(768, 100), (392, 40), (768, 200), (904, 250)])
+def test_products_that_cancel_in_order(oracle, d, Q):
+    """A score is one chain of sums over its elements in their order.  Products of one sign in every other group of 16
+    elements and of the other sign between them: in order they cancel, added by even and odd groups they overflow fp32 to
+    both infinities, the score is no number and the row is lost."""
+    from paper_2401_14021_amd import binding as B
+    N, r = 150_001, 391 * 256 + 77   # a row that only the last stage visits
+    g = torch.Generator().manual_seed(d)
+    X = torch.randint(-3, 4, (N, d), generator=g).float()
+    q = torch.randint(1, 4, (Q, d), generator=g).float()
+    q[:, :64] = 1.0
+    X[r] = 0.0
+    X[r, [0, 32]] = -2.0 ** 127
+    X[r, [16, 48]] = 2.0 ** 127
+    X[r, 64] = 2.0 ** 100            # the score, in double and in fp32 alike
+    ds = B.Datastore.from_fp32(X.cuda(), torch.bfloat16)
+    ids, sc = B.ralm_retrieve_topk_ex(q.cuda(), ds, 2, 4)
+    ids, sc = ids.cpu().numpy(), sc.cpu().numpy()
+    np.testing.assert_array_equal(ids[:, 0], np.full(Q, r))
+    np.testing.assert_array_equal(sc[:, 0], q[:, 64].numpy() * 2.0 ** 100)
+    wi, ws = oracle.retrieve_topk(q[:4].numpy(), X.numpy(), 2)
+    np.testing.assert_array_equal(ids[:4], wi)
+    np.testing.assert_array_equal(sc[:4], ws)
