@@ -265,6 +265,25 @@ ralm_status ralm_workspace_stage_entries(const void *workspace, void *stream, in
                                          int64_t *entries);
 
 /*
+ * Which scan kernel each stage of a ralm_retrieve_topk_ex call with these
+ * arguments takes, under the present reserve of compute units: routes[i],
+ * i < *n_stages, is RALM_SCAN_*, and 0 for a stage that has no rows to scan and
+ * for all elements behind.  routes is a HOST array of RALM_MAX_LADDER_STAGES
+ * elements.  Nothing is launched or read (of the datastore's pointers only the
+ * alignment counts), and no GPU is needed: without one the answer is that of a
+ * device with 256 compute units.  A diagnostic.
+ */
+enum {
+    RALM_SCAN_ALL = 1,           /* keeps every score (the first stage) */
+    RALM_SCAN_ALL_QUARTERS = 2,  /* the same in tiles of 64 rows */
+    RALM_SCAN_COUNTED = 3,       /* thresholds that admit many scores of a tile: counted per query, then stored */
+    RALM_SCAN_PARKED = 4,        /* thresholds that admit few: collected one by one */
+    RALM_SCAN_HELD = 5           /* the same, with the queries held in registers */
+};
+ralm_status ralm_scan_routes(int64_t Q, const ralm_datastore_t *ds, int32_t k, int32_t k_prime,
+                             int32_t *n_stages, int32_t *routes);
+
+/*
  * Build the low-precision scan copy of a datastore: dst[j, c] = round-to-
  * nearest-even(src[j, c]) in dst_dtype (RALM_BF16 or RALM_F16).  src is device
  * fp32 [N, d] with pitch src_stride elements, dst device [N, d] with pitch

@@ -68,6 +68,7 @@ def lib() -> ctypes.CDLL:
         L.ralm_workspace_overflows.argtypes = [vp, vp, ctypes.POINTER(i32)]
         L.ralm_workspace_counters.argtypes = [vp, vp, ctypes.POINTER(ralm_counters_t)]
         L.ralm_workspace_stage_entries.argtypes = [vp, vp, ctypes.POINTER(i32), ctypes.POINTER(i64)]
+        L.ralm_scan_routes.argtypes = [i64, dsp, i32, i32, ctypes.POINTER(i32), ctypes.POINTER(i32)]
         L.ralm_build_scan_copy.argtypes = [vp, i64, vp, i32, i64, i64, i32, vp]
         L.ralm_build_scan_copy_l2.argtypes = [vp, i32, i64, vp, i32, i64, i64, i32, vp]
         L.ralm_cache_lookup.argtypes = [vp, vp, i32, i64, vp, i64, vp, dsp, vp, vp, vp, ctypes.c_size_t, vp]
@@ -99,7 +100,7 @@ def lib() -> ctypes.CDLL:
         L.ralm_profile_enable.restype = None
         L.ralm_profile_scan_ms.argtypes = [ctypes.POINTER(ctypes.c_float), ctypes.POINTER(i32)]
         for name in ("ralm_retrieve_topk", "ralm_retrieve_topk_ex", "ralm_retrieve_topk_seq", "ralm_workspace_overflows",
-                     "ralm_workspace_counters", "ralm_workspace_stage_entries",
+                     "ralm_workspace_counters", "ralm_workspace_stage_entries", "ralm_scan_routes",
                      "ralm_build_scan_copy", "ralm_build_scan_copy_l2", "ralm_cache_lookup", "ralm_cache_lookup_all",
                      "ralm_cache_lookup_static",
                      "ralm_cache_lookup_topk", "ralm_verify", "ralm_cache_insert", "ralm_knnlm_probs",
@@ -241,6 +242,17 @@ def ralm_workspace_stage_entries(workspace: torch.Tensor) -> list:
     arr = (ctypes.c_int64 * RALM_MAX_LADDER_STAGES)()
     _check(lib().ralm_workspace_stage_entries(ws_ptr, _stream(), ctypes.byref(n), arr))
     return [int(arr[i]) for i in range(n.value)]
+
+
+SCAN_ROUTES = ("none", "all", "all_quarters", "counted", "parked", "held")
+
+
+def ralm_scan_routes(Q: int, ds: Datastore, k: int, k_prime: int = 0) -> list:
+    """Which scan kernel each ladder stage of ralm_retrieve_topk_ex takes, as a name of SCAN_ROUTES (host only)."""
+    n = ctypes.c_int32(0)
+    arr = (ctypes.c_int32 * RALM_MAX_LADDER_STAGES)()
+    _check(lib().ralm_scan_routes(Q, ctypes.byref(ds.desc), k, k_prime, ctypes.byref(n), arr))
+    return [SCAN_ROUTES[arr[i]] for i in range(n.value)]
 
 
 def ralm_retrieve_topk(queries: torch.Tensor, datastore: torch.Tensor, k: int

@@ -228,6 +228,48 @@ int device_cus()
 // compute units that the scan's persistent grids leave free (ralm_scan_reserve_cus)
 std::atomic<int> g_scan_reserve{0};
 
+// The scan's grids are persistent: one workgroup per CU (two for the small tiles).  With a reserve they have no
+// more workgroups than the CUs that are left, rounded down as the grids are multiples of 8.
+int scan_cus(int reserve)
+{
+    int n_cu = device_cus() - reserve;
+    if (reserve > 0) n_cu -= n_cu % 8;
+    return n_cu < 8 ? 8 : n_cu;
+}
+
+// the parts of a call's scan launches that the stage does not change; the lists and queries are the caller's to fill in
+ScanParams scan_params(const ralm_datastore_t *ds, int64_t Q, const Plan &pl, int reserve)
+{
+    ScanParams sp{};
+    sp.X = ds->scan ? ds->scan : ds->exact;
+    sp.in_dtype = ds->scan ? ds->scan_dtype : ds->exact_dtype;
+    sp.ldx = ds->scan ? (ds->scan_stride ? ds->scan_stride : scan_cols(ds)) : (ds->exact_stride ? ds->exact_stride : ds->d);
+    sp.N = ds->N; sp.d = scan_cols(ds); sp.dpad = pl.dpad; sp.Q = (int32_t)Q; sp.cap = pl.cap;
+    sp.one_per_cu = reserve > 0;
+    return sp;
+}
+
+// Stage s of the strided ladder; returns the keys per list that it should leave.
+int64_t ladder_stage(const Plan &pl, int64_t tiles, int s, ScanParams &sp)
+{
+    const int64_t stride = pl.stride[s];
+    sp.tile_begin = 0;
+    sp.tile_stride = stride;
+    sp.lists_empty = s == 0;
+    if (s == 0) {
+        sp.tile_skip = 0;                                   // every multiple of the stride
+        sp.n_row_tiles = (tiles + stride - 1) / stride;
+        sp.admits = sp.n_row_tiles * SCAN_BM;               // everything
+        return sp.admits;
+    }
+    const int64_t m_max = (tiles + stride - 1) / stride - 1;   // multiples m >= 1 with m*stride < tiles
+    const int64_t g = pl.stride[s - 1] / stride;               // ... that no earlier stage visited
+    sp.tile_skip = (int32_t)g;
+    sp.n_row_tiles = m_max - m_max / g;
+    sp.admits = pl.k_prime * (g - 1);
+    return pl.k_prime * g;
+}
+
 // ---- scan timing aid ------------------------------------------------------------------------
 constexpr int MAX_PROF = 2048;
 bool g_prof_on = false;
@@ -289,16 +331,11 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
     int32_t *flags = reinterpret_cast<int32_t *>(ws + pl.off_flags);
     u64 *cand = reinterpret_cast<u64 *>(ws + pl.off_cand);
 
-    const void *scan = ds->scan ? ds->scan : ds->exact;
-    const int scan_dt = ds->scan ? ds->scan_dtype : ds->exact_dtype;
-    const int64_t scan_ld = ds->scan ? (ds->scan_stride ? ds->scan_stride : scan_cols(ds))
-                                     : (ds->exact_stride ? ds->exact_stride : ds->d);
+    ScanParams sp = scan_params(ds, Q, pl, reserve);
+    const void *scan = sp.X;
+    const int scan_dt = sp.in_dtype;
     const int mma_dt = scan_dt == RALM_F16 ? RALM_F16 : RALM_BF16;   // fp32 rows are rounded to bf16
-    // the scan's grids are persistent: one workgroup per CU (two for the small tiles).  With a reserve they have no
-    // more workgroups than the CUs that are left, rounded down as the grids are multiples of 8
-    int n_cu = device_cus() - reserve;
-    if (reserve > 0) n_cu -= n_cu % 8;
-    if (n_cu < 8) n_cu = 8;
+    const int n_cu = scan_cus(reserve);
 
     // the same launch clears the flag block and, behind the queries, the admission keys, the list
     // lengths and the lost marks (contiguous in the workspace)
@@ -306,12 +343,7 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
                                reinterpret_cast<uint32_t *>(flags), FLAG_BLOCK_BYTES / 4,
                                reinterpret_cast<uint32_t *>(tau), (int64_t)(pl.off_fb - pl.off_tau) / 4, stream));
 
-    ScanParams sp;
-    sp.X = scan; sp.ldx = scan_ld; sp.N = ds->N; sp.d = scan_cols(ds); sp.in_dtype = scan_dt;
-    sp.Qs = qs; sp.dpad = pl.dpad; sp.Q = (int32_t)Q;
-    sp.tau = tau; sp.cand = cand; sp.cnt = cnt; sp.cap = pl.cap;
-    sp.lists_empty = 0;
-    sp.one_per_cu = reserve > 0;
+    sp.Qs = qs; sp.tau = tau; sp.cand = cand; sp.cnt = cnt;
     // one stage: scan the tiles sp describes, then cut every list down to its k' best
     int32_t stage_no = 0;
     int64_t last_expected = 0;   // keys per list that the last stage should leave
@@ -353,26 +385,8 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
         }
         last_expected = tiles > block ? 2 * pl.k_prime : tiles * SCAN_BM;
     } else {
-        sp.tile_begin = 0;
         for (int s = 0; s < pl.n_stages; ++s) {
-            const int64_t stride = pl.stride[s];
-            sp.tile_stride = stride;
-            int64_t expected;                                       // keys per list when the stage ends
-            if (s == 0) {
-                sp.tile_skip = 0;                                   // every multiple of the stride
-                sp.n_row_tiles = (tiles + stride - 1) / stride;
-                sp.admits = sp.n_row_tiles * SCAN_BM;               // everything
-                sp.lists_empty = 1;
-                expected = sp.admits;
-            } else {
-                const int64_t m_max = (tiles + stride - 1) / stride - 1;   // multiples m >= 1 with m*stride < tiles
-                const int64_t g = pl.stride[s - 1] / stride;        // ... that no earlier stage visited
-                sp.tile_skip = (int32_t)g;
-                sp.n_row_tiles = m_max - m_max / g;
-                sp.admits = pl.k_prime * (g - 1);
-                sp.lists_empty = 0;
-                expected = pl.k_prime * g;
-            }
+            const int64_t expected = ladder_stage(pl, tiles, s, sp);
             st = run_stage(expected, s + 1 == pl.n_stages);
             if (st != RALM_OK) return st;
         }
@@ -478,6 +492,26 @@ ralm_status ralm_workspace_stage_entries(const void *workspace, void *stream, in
         if (st != RALM_OK) return st;
     }
     *n_stages = n;
+    return RALM_OK;
+}
+
+ralm_status ralm_scan_routes(int64_t Q, const ralm_datastore_t *ds, int32_t k, int32_t k_prime, int32_t *n_stages, int32_t *routes)
+{
+    if (!n_stages || !routes) return fail(RALM_ERR_NULL, "n_stages/routes is NULL");
+    if (Q < 1 || Q > MAX_QUERIES) return fail(RALM_ERR_SHAPE, "Q=%lld out of [1, 2^20]", (long long)Q);
+    ralm_status st = check_datastore(ds, true);
+    if (st != RALM_OK) return st;
+    Plan pl;
+    const int reserve = g_scan_reserve.load(std::memory_order_relaxed);
+    st = make_plan(Q, ds, k, k_prime, pl, reserve > 0);
+    if (st != RALM_OK) return st;
+    ScanParams sp = scan_params(ds, Q, pl, reserve);
+    for (int i = 0; i < RALM_MAX_LADDER_STAGES; ++i) routes[i] = 0;
+    for (int i = 0; i < pl.n_stages; ++i) {
+        ladder_stage(pl, (ds->N + SCAN_BM - 1) / SCAN_BM, i, sp);
+        if (sp.n_row_tiles > 0) routes[i] = scan_route(sp, scan_cus(reserve));
+    }
+    *n_stages = pl.n_stages;
     return RALM_OK;
 }
 

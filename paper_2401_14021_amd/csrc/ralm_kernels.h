@@ -46,6 +46,7 @@ struct ScanParams {
 // query tile width chosen for Q
 int scan_bn_for(int64_t Q);
 hipError_t launch_scan(const ScanParams &p, int n_cu, hipStream_t stream);
+int scan_route(const ScanParams &p, int n_cu);   // RALM_SCAN_*: the kernel that launch_scan takes for p
 // whether a launch whose thresholds admit few scores is better served by the kernel that holds the queries in registers
 bool scan_held_takes(const ScanParams &p, int n_cu);
 bool whole_lines(const ScanParams &p);   // rows that are whole 128-byte lines

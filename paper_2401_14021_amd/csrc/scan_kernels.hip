@@ -33,6 +33,7 @@
 
 #include <atomic>
 
+#include "../../include/ralm.h"
 #include "scan_device.h"
 
 namespace ralm {
@@ -721,11 +722,11 @@ hipError_t launch_quarter_f32(const ScanParams &p, int n_cu, hipStream_t stream)
 }
 
 template <bool F16>
-hipError_t launch_16(const ScanParams &p, bool all_kept, bool counted, bool nt, int n_cu, hipStream_t stream)
+hipError_t launch_16(const ScanParams &p, int route, bool nt, int n_cu, hipStream_t stream)
 {
-    if (all_kept && few_tiles(p, n_cu)) return launch_quarter<F16>(p, n_cu, stream);
-    if (all_kept) return launch_kept<F16, false, KEEP_ALL>(p, n_cu, stream);
-    if (counted)
+    if (route == RALM_SCAN_ALL_QUARTERS) return launch_quarter<F16>(p, n_cu, stream);
+    if (route == RALM_SCAN_ALL) return launch_kept<F16, false, KEEP_ALL>(p, n_cu, stream);
+    if (route == RALM_SCAN_COUNTED)
         return nt ? launch_kept<F16, true, KEEP_COUNTED>(p, n_cu, stream) : launch_kept<F16, false, KEEP_COUNTED>(p, n_cu, stream);
     return nt ? launch_dma<F16, true>(p, n_cu, stream) : launch_dma<F16, false>(p, n_cu, stream);
 }
@@ -766,26 +767,32 @@ bool whole_lines(const ScanParams &p)
     return (p.ldx * (p.in_dtype == DT_F32 ? 4 : 2)) % 128 == 0 && reinterpret_cast<uintptr_t>(p.X) % 128 == 0;
 }
 
-hipError_t launch_scan(const ScanParams &p, int n_cu, hipStream_t stream)
+int scan_route(const ScanParams &p, int n_cu)
 {
     // every score into empty lists: fixed list positions
     const bool all_kept = p.lists_empty && p.tile_skip == 0 && p.n_row_tiles > 0 && p.n_row_tiles * SCAN_BM <= (int64_t)p.cap;
+    if (all_kept) return few_tiles(p, n_cu) ? RALM_SCAN_ALL_QUARTERS : RALM_SCAN_ALL;
     // Thresholds that are expected to admit COUNT_MIN or more of a tile's 256 scores per query: the admitted
     // scores of a tile are counted and stored together.  The line is flat: a round of 256 neighbour queries over
     // 10M x 1024 (k' = 2048) takes 6525 us with it at 1.2, 6489 at 2, 6480 at 4, 7226 without counted launches;
     // 200 queries over 2M rows in corpus order, whose admitted scores come in bursts, 2055 at 1.5, 2126 at 2.5,
     // 2680 without; 100 queries, k' = 64, that admit 1.3 a tile: 134 counted, 112 parked.
-    const bool counted = p.admits >= COUNT_MIN * p.n_row_tiles;
+    if (p.admits >= COUNT_MIN * p.n_row_tiles) return RALM_SCAN_COUNTED;
+    return scan_held_takes(p, n_cu) ? RALM_SCAN_HELD : RALM_SCAN_PARKED;
+}
+
+hipError_t launch_scan(const ScanParams &p, int n_cu, hipStream_t stream)
+{
+    const int route = scan_route(p, n_cu);
     const bool nt = p.Q <= 256 && whole_lines(p);
-    if (!all_kept && !counted && scan_held_takes(p, n_cu)) return launch_scan_held(p, nt, n_cu, stream);
+    if (route == RALM_SCAN_HELD) return launch_scan_held(p, nt, n_cu, stream);
     if (p.in_dtype == DT_F32) {
-        if (all_kept && few_tiles(p, n_cu)) return launch_quarter_f32(p, n_cu, stream);
-        if (all_kept) return launch_f32<false, KEEP_ALL>(p, n_cu, stream);
-        if (counted) return nt ? launch_f32<true, KEEP_COUNTED>(p, n_cu, stream) : launch_f32<false, KEEP_COUNTED>(p, n_cu, stream);
+        if (route == RALM_SCAN_ALL_QUARTERS) return launch_quarter_f32(p, n_cu, stream);
+        if (route == RALM_SCAN_ALL) return launch_f32<false, KEEP_ALL>(p, n_cu, stream);
+        if (route == RALM_SCAN_COUNTED) return nt ? launch_f32<true, KEEP_COUNTED>(p, n_cu, stream) : launch_f32<false, KEEP_COUNTED>(p, n_cu, stream);
         return nt ? launch_f32<true, KEEP_PARKED>(p, n_cu, stream) : launch_f32<false, KEEP_PARKED>(p, n_cu, stream);
     }
-    return p.in_dtype == DT_F16 ? launch_16<true>(p, all_kept, counted, nt, n_cu, stream)
-                                : launch_16<false>(p, all_kept, counted, nt, n_cu, stream);
+    return p.in_dtype == DT_F16 ? launch_16<true>(p, route, nt, n_cu, stream) : launch_16<false>(p, route, nt, n_cu, stream);
 }
 
 }  // namespace ralm

@@ -140,6 +140,64 @@ def test_argument_errors_return_status_without_a_device(L):
     assert L.ralm_workspace_stage_entries(None, None, ref(n), arr) == 1             # accessors check their pointers
     assert L.ralm_workspace_stage_entries(P, None, None, arr) == 1
     assert L.ralm_workspace_counters(None, None, ref(b.ralm_counters_t())) == 1
+    routes = (ctypes.c_int32 * b.RALM_MAX_LADDER_STAGES)()
+    assert L.ralm_scan_routes(8, ref(ds), 5, 0, None, routes) == 1 and L.ralm_scan_routes(8, ref(ds), 5, 0, ref(n), None) == 1
+    assert L.ralm_scan_routes(0, ref(ds), 5, 0, ref(n), routes) == 2
+    assert L.ralm_scan_routes(8, ref(ds), 0, 0, ref(n), routes) == 3
+
+
+def _routes(L, Q, k, N, d, scan_dtype=1, pitch=0, k_prime=0, metric=0):
+    from paper_2401_14021_amd import binding as b
+    ds = _ds(b, N=N, d=d, scan_dtype=scan_dtype)
+    ds.scan_stride, ds.metric = pitch, metric
+    n, arr = ctypes.c_int32(0), (ctypes.c_int32 * b.RALM_MAX_LADDER_STAGES)()
+    assert L.ralm_scan_routes(Q, ctypes.byref(ds), k, k_prime, ctypes.byref(n), arr) == 0
+    assert not any(arr[n.value:])
+    return [b.SCAN_ROUTES[v] for v in arr[:n.value]]
+
+
+# The rules' sides, one reason each (a device with 256 compute units; k = 10 keeps 64 candidates)
+@pytest.mark.parametrize("Q,N,d,more,want", [
+    (81, 1_000_000, 768, {}, ["all_quarters", "parked", "held"]),        # the second stage admits 10 scores per 32 rows
+    (64, 4_000_000, 768, {}, ["all_quarters", "parked", "parked"]),      # few queries over whole lines stay in tiles
+    (32, 4_000_000, 768, {}, ["all", "parked", "parked"]),               # ... and have no quarter tiles
+    (200, 6_000_000, 768, {}, None),
+    (90, 777_001, 392, dict(scan_dtype=2), ["all_quarters", "held", "held"]),
+    (1, 1_000_000, 392, {}, None),                                       # no whole lines: any number of queries
+    (1, 1_000_000, 392, dict(pitch=448), "parked"),                      # the same in whole lines
+    (100, 4_000_000, 256, {}, "parked"),                                 # rows too short
+    (100, 4_000_000, 1152, {}, "parked"),                                # ... and too long for the registers
+    (100, 4_000_000, 1088, {}, None),
+    (200, 4_000_000, 1024, {}, "parked"),                                # 128 queries a tile, whole lines
+    (200, 4_000_000, 1000, {}, None),
+    (1024, 10_000_000, 768, {}, None),
+    (512, 10_000_000, 512, {}, "parked"),                                # several query tiles over short rows in whole lines
+    (512, 10_000_000, 504, {}, None),
+    (2341, 4_000_000, 768, {}, "parked"),                                # ten query tiles on 32 compute units of an XCD
+    (100, 4_000_000, 768, dict(scan_dtype=0), "parked"),                 # fp32 rows
+    (100, 4_000_000, 1024, dict(metric=1, pitch=1088, scan_dtype=2), None),
+    (256, 10_000_000, 1024, dict(k=1024, scan_dtype=2), "parked"),
+])
+def test_scan_routes(L, Q, N, d, more, want):
+    """The kernel of every stage, or of the last one (None: the queries are held in registers)."""
+    more = dict(more)
+    got = _routes(L, Q, more.pop("k", 10), N, d, **more)
+    if isinstance(want, list):
+        assert got == want
+    else:
+        assert got[-1] == (want or "held"), got
+
+
+def test_scan_routes_with_compute_units_reserved(L):
+    from paper_2401_14021_amd import binding as b
+    try:
+        b.ralm_scan_reserve_cus(8)
+        assert _routes(L, 20, 10, 1_000_000, 392)[-1] == "parked"        # half of each unit's LDS stays free
+        assert _routes(L, 40, 10, 1_000_000, 392)[-1] == "held"
+        b.ralm_scan_reserve_cus(300)                                     # one unit per XCD is left: two tiles do not fit
+        assert _routes(L, 129, 10, 4_000_000, 904)[-1] == "parked"
+    finally:
+        b.ralm_scan_reserve_cus(0)
 
 
 def test_binding_refuses_to_run_without_the_library(monkeypatch):
