@@ -515,11 +515,13 @@ int32_t ralm_os3_next_stride(const int32_t *strides, const int32_t *matched, int
  * ralm_scan_reserve_cus(n) makes every later retrieval call of the process
  * launch its scans with at most 256 - n workgroups, rounded down to a multiple
  * of 8, so that n compute units stay free (n = 8: one per XCD; 0 restores the
- * default).  The scan slows down by about n / 256; batches of up to 32 queries
- * put one workgroup on a unit then, which leaves half of every unit's LDS free
- * (4 % slower); larger batches read the rows in more launches, none longer than
- * half of the scan, between which kernels that need more than n units get onto
- * the chip.  Process-wide setting, read when a call is issued.
+ * default).  The scan slows down by about n / 256 (n = 8, 1024 queries over
+ * 768 elements: 7 %, because four query tiles do not share out the units that
+ * are left and the scan takes another kernel); batches of up to 32 queries put
+ * one workgroup on a unit then, which leaves half of every unit's LDS free (4 %
+ * slower); larger batches read the rows in more launches, none longer than half
+ * of the scan, between which kernels that need more than n units get onto the
+ * chip.  Process-wide setting, read when a call is issued.
  */
 void ralm_scan_reserve_cus(int32_t n);
 

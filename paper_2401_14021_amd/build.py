@@ -22,7 +22,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-u
          "-mllvm", "-pragma-unroll-threshold=1000000"]
 
 
-# matrix results in vector registers: the kernel fills the accumulation registers with its queries
+# Matrix results in vector registers: the kernel fills the accumulation registers with its queries.  An option of the compiler's
+# back end (ROCm 7.2); one that does not know it refuses this file.
 EXTRA = {"scan_held_kernels.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 

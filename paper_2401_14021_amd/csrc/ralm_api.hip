@@ -106,8 +106,8 @@ ralm_status make_plan(int64_t Q, const ralm_datastore_t *ds, int32_t k, int32_t 
     // With CUs reserved (short_launches) more than 64 queries refine by 2 three times, so that no launch reads more
     // than half of the rows, and the next ones a quarter and an eighth: kernels of another stream that need more than
     // the reserved CUs get onto the chip between launches.  A lookup of 8 requests issued 3 ms into a retrieval of 1024
-    // queries over 21M x 768: done after 10.4 ms without the short launches, 0.5 ms with them; 128 queries, 1.5 ms: 3.8
-    // and 1.2 ms; the retrievals themselves 26.8 and 27.0, 5.43 and 5.41 ms.
+    // queries over 21M x 768: done after 9.7 ms without the short launches, 0.4 ms with them; 128 queries, 1.5 ms: 2.7
+    // and 0.25 ms; the retrievals themselves 26.8 and 26.8, 5.10 and 5.07 ms.
     const int32_t fine_until = Q <= 64 ? 1 : (short_launches ? 8 : (Q > 256 ? 2 : 1));   // strides that refine by 2
     // Slots of a list.  In a store sorted by cluster a sampled tile of 256 rows is one draw and not 256, so what the
     // next stage admits is spread like the wait for the k' / 256-th sampled tile of good matches, and the longest

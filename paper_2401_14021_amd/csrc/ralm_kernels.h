@@ -8,7 +8,7 @@ namespace ralm {
 
 typedef unsigned long long u64;
 
-constexpr int SCAN_BM = 256;       // datastore rows per tile of the stage ladder (a workgroup takes one, or half of one)
+constexpr int SCAN_BM = 256;       // datastore rows per tile of the stage ladder (a workgroup takes one, or parts of 128, 64 or 32 rows)
 constexpr int SCAN_BK = 64;        // reduction elements staged per pipeline step
 constexpr int SCAN_QPAD = 256;     // query matrix is zero-padded to a multiple of this
 // 32-bit words from one query's list length to the next: a 128-byte line each.  Every admitted score

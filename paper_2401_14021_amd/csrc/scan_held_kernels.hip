@@ -3,12 +3,13 @@
 // A workgroup of 4 waves, one per SIMD, keeps the queries of one query tile for a whole launch: every wave holds TN blocks of 32
 // of them over the full reduction length in its registers (TN = 2, 768 elements: 384 of the 512 that a lane has), and only
 // datastore rows move.  They go through a ring of 32-row tiles that takes all of LDS but 16 KB.  The tiled kernel
-// streams as many bytes of queries from L2 to LDS as of rows, and reads 6 operands from LDS per 8 multiplies and wave; here
-// it is none and 4.  A batch of 129 queries or more is bound by the power that its multiplies and these streams draw, a
-// smaller one by the stream of rows.
+// streams as many bytes of queries from L2 to LDS as of rows, and reads 6 operands from LDS per 8 multiplies and wave (5 per 4 in
+// its tile of 128 queries); here it is no query bytes and 4 operands per 8 multiplies (TN = 2) or per 4 (TN = 1).  In a stream of
+// calls the matrix cores are busy 0.77 to 0.78 of the cycles with 256 and 1024 queries, at 1.3 and 1.6 GHz of 2.4: power sets
+// the time.  Up to 128 queries wait for the rows (0.54 busy).
 //
-// us per call or round, tiled and held: 200 queries over 6M x 768 2186, 2034 (2205, 1801 from an idle card: in a stream of calls
-// both are bound by power); 1024 over 10M x 768 12583, 12013; 81 over 1M x 768 321, 308; 90 over 777001 x 392 222, 184.
+// us per call, tiled and held behind the same first stage: 200 queries over 6M x 768 2251, 2111; 1024 over 10M x 768 12755, 12102;
+// 81 over 1M x 768 318, 298; 140 over 1M x 768 434, 400; 90 over 777001 x 392 in corpus order 257, 183.
 #include <atomic>
 
 #include "scan_device.h"
@@ -356,36 +357,44 @@ hipError_t launch_type(const ScanParams &p, bool nt, int n_cu, hipStream_t strea
 
 }  // namespace
 
-// us per launch, tiled and held, where the line lies.
+// us per call, tiled and held, unless something else is said.
 bool scan_held_takes(const ScanParams &p, int n_cu)
 {
     if (p.in_dtype == DT_F32) return false;
     // Up to 64 queries the tiled kernel's stream of queries is small and its rows come at the rate of a pure read: 50 over 4M x 768
-    // 997, 1030 us a call, 8 929, 966 (70: 1038, 982).  Rows that are no whole lines it fetches at less: 8 over 1M x 392
-    // in corpus order 197, 169, 4 over 2M x 904 740, 614, 60 over 1M x 600 329, 251.  With CUs reserved up to 32 queries leave half of a
-    // CU's LDS to other kernels, and this one takes all.
+    // 991, 1036, 64 over 2M x 384 310, 345, x 512 382, 409, x 1024 688, 695 (70 over 4M x 768: 1073, 1010).  Only copies of 1032
+    // columns and more for the squared distance would gain: 64 over 2M 759, 728, 8 706, 697.  Rows that are no whole lines it
+    // fetches at less: 8 over 1M x 392 in corpus order 197, 169, 4 over 2M x 904 740, 614, 60 over 1M x 600 329, 251, 1 over
+    // 1M x 328 167, 148.  With CUs reserved up to 32 queries leave half of a CU's LDS to other kernels, and this one takes all.
     if (p.Q <= 64 && (whole_lines(p) || (p.Q <= 32 && p.one_per_cu))) return false;
     // The queries fit the registers; of rows of more than 768 elements only 128 per workgroup, whose multiplies then read LDS as fast
-    // as it gives: 256 over 2M x 1024 1215, 1237, but 250 over 1M x 1000 759, 630, 1000 over 1M x 904 2037, 1879.  Rows of less
-    // than 257 elements are too few multiplies for a tile's two rendezvous.
+    // as it gives: 200 over 2M x 1024 1063, 1276, 256 1114, 1203, 512 1955, 2049, but 250 over 1M x 1000 775, 656, 1000 over 1M x
+    // 904 2037, 1879.  Rows of less than 257 elements are too few multiplies for a tile's two rendezvous; those of 257 to 512
+    // gain: 129 over 1M x 320 237, 226, 256 257, 257, 200 over 2M x 512 579, 551.
     const int kt = p.dpad / 64, bn = scan_held_bn(p);
     if (kt < 5 || kt > 17 || (kt > 12 && p.Q > 128 && whole_lines(p))) return false;
-    // every stream of rows needs a CU for each query tile on its XCD: a batch that leaves more than a twentieth of the columns or
-    // CUs idle is better off in tiles (2341 queries, 10 tiles on 30 of 32 CUs: 13414, 14246 us a round)
+    // Every stream of rows needs a CU for each query tile on its XCD: a batch that leaves more than a twentieth of the columns or
+    // CUs idle is better off in tiles, or no worse: over 4M x 768 700 queries 3926, 3999, 1280 6537, 6562, 1536 7786, 7795, 1792 9033, 9349, 2341
+    // 12392, 12656 (three full tiles, 768 queries, would gain 2 %: 4072, 3990).
     const int64_t nqt = (p.Q + bn - 1) / bn, per_xcd = n_cu / 8, streams = per_xcd / nqt;
     if (streams < 1) return false;   // (nearly all CUs reserved)
     // (two tiles of 128 were better at any size: 135 queries over 1M x 904 680, 564)
     if (!(nqt == 2 && bn == 128) && nqt > 1 && p.Q * streams * 20 < per_xcd * bn * 19) return false;
     // several query tiles share the stream of rows, and short rows are few multiplies between two rendezvous: 1000 queries
-    // over 2M x 384 1520, 1567 us, 512 over 2M x 512 1047, 1042.  Rows that are no whole lines cost the tiled kernel more: 512 over
+    // over 2M x 384 1520, 1567, 512 over 2M x 512 1047, 1042.  Rows that are no whole lines cost the tiled kernel more: 512 over
     // 1M x 560 694, 620
     if (nqt > 1 && kt <= 8 && whole_lines(p)) return false;
-    // a workgroup loads 128 TN queries before its first row: at least 8 tiles each
+    // A workgroup loads 128 TN queries before its first row: at least 8 tiles each.  (On the safe side for rows that are no whole lines:
+    // 120 queries over 400 000 x 392, whose middle stage has 7.8 tiles for each, 128, 117.)
     if (p.n_row_tiles * (SCAN_BM / HELD_BM) < 64 * streams) return false;
-    // Admitted scores interrupt a lone wave.  Expected per tile of 32 rows: 26: 120, 159 us; 18: 61, 72; 10 (81 queries): 42, 44;
-    // 5.7: 578, 565; 4.7: 476, 516; 3.3 (100 queries): 235, 207; 2.3: 337, 294; 1.6: 1357, 1183; 0.8: 1968, 1870
-    // Rows that are no whole lines: 90 queries over 777001 x 392 in corpus order, the first of two such stages (11 a tile) in tiles or not
-    // 244, 214 us a round.
+    // Admitted scores interrupt a lone wave.  us per launch by the scores expected per tile of 32 rows: 26: 120, 159; 18: 61, 72; 10 (81
+    // queries): 42, 44; 5.7: 578, 565; 4.7: 476, 516; 3.3 (100 queries): 235, 207; 2.3: 337, 294; 1.6: 1357, 1183; 0.8: 1968, 1870.
+    // Rows that are no whole lines, in corpus order: 11 a tile (90 queries over 777001 x 392, the first of two such stages in tiles or
+    // not) 244, 214 us a round.  There and in stores sorted by cluster the lines are on the safe side: 200 queries whose middle stage is
+    // beyond 16 (29 a tile) and is left in tiles, or not: over 500 000 x 392 248, 194, over 600 000 x 600 292, 253, over 500 000 x
+    // 904 364, 314; beyond 4, whole lines sorted by cluster: 200 queries, k' = 256, over 4M x 768 1990, 1468, 100 over 1M x 768 334, 298.
+    // In random order (whole calls, the stages beyond 4 a tile in tiles or not): 81 over 1M x 768 (10 a tile) 298, 307, 200 over 200 000 x
+    // 768 (27) 141, 153, 100 over 150 000 x 768 (14) 99, 91.
     const int64_t most = whole_lines(p) ? 4 : 16;
     return p.admits * (p.Q < bn ? p.Q : bn) <= most * p.n_row_tiles * (SCAN_BM / HELD_BM);
 }

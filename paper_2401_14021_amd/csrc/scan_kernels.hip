@@ -8,8 +8,8 @@
 // that pass are appended to that query's candidate list.
 //
 // Tiling: a workgroup of 4 or 8 waves owns a 256-row x BN-query tile (64,
-// 128 and 256 queries on 8 waves, two per SIMD; 32 queries: half of the rows, on 4 waves); the reduction dimension is walked in strips of BK
-// elements.  Datastore rows are the A operand of v_mfma_f32_32x32x16, queries the B operand, so
+// 128 and 256 queries on 8 waves, two per SIMD; 32 queries: half of the rows, on 4 waves; a first stage of few tiles of more than 32
+// queries: a quarter of the rows); the reduction dimension is walked in strips of BK elements.  Datastore rows are the A operand of v_mfma_f32_32x32x16, queries the B operand, so
 // every accumulator register of a lane belongs to ONE query (column = lane % 32) and the lane
 // can hold that query's threshold in a register.
 //
@@ -588,9 +588,9 @@ __global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams 
         } else if constexpr (TN == 2 && NTA && !A32 && KEEP == KEEP_PARKED) {
             // One query tile of 16-bit rows in whole lines: a wave of whose two column blocks the second is all padding
             // multiplies the first only.  Waves w and w + 4, which hold the same columns, share a SIMD, so this idles that
-            // SIMD and the others set the tile's time; what is gained is power, and little: 200 queries over 6M x 768
-            // 2299 -> 2259 us, 224 2326 -> 2282, 140 2153 -> 2134, 170 2205 -> 2201, 256 the same within the noise.  (Rows of that
-            // length have a kernel of their own by now; longer ones and stages that admit more still come here.)
+            // SIMD and the others set the tile's time; what is gained is power, and little.  What comes here are rows of more
+            // than 768 elements or less than 257, and middle stages: 200 queries over 2M x 1024 1081 -> 1061 us a call, 224 1129 -> 1113, 200
+            // over 1M x 2048 1113 -> 1096, 200 over 4M x 256 657 -> 649, 140 and 170 over 2M x 1024 the same within the noise.
             if (q0 + (wn * TN + 1) * 32 >= p.Q) tile(std::integral_constant<int, 1>{});   // wave-uniform
             else tile(std::integral_constant<int, TN>{});
         } else {
@@ -702,7 +702,9 @@ bool few_tiles(const ScanParams &p, int n_cu)
 // A first stage of few tiles (64 where the lists have 16384 slots) leaves most CUs without one, and a workgroup that has one
 // waits for its strips one after the other.  Quarter tiles spread it over four times as many workgroups, with deeper
 // rings.  us per launch, 62 whole tiles and 248 quarters of 768 elements: 40 queries 13.2, 9.0; 81 18.2, 12.0; 200 31.8, 17.3; 500 41.7,
-// 36.9; 3 queries, which have half tiles anyway, 8.1, 8.4.
+// 36.9; 3 queries, which have half tiles anyway, 8.1, 8.4.  Whole calls of one or two stages, whole tiles and quarters: 40 over 300 000 x 16
+// 56.2, 54.5, 300 over 300 000 x 64 152, 143, 200 over 5000 x 768 54, 38, 300 over 20 000 x 4096 311, 294, 500 over 20 000 x 8192 576, 561;
+// fp32 rows: 40 over 300 000 x 64 65.9, 64.9, 100 over 300 000 x 768 230, 220, 400 over 20 000 x 8192 903, 840.
 template <bool F16>
 hipError_t launch_quarter(const ScanParams &p, int n_cu, hipStream_t stream)
 {
