@@ -19,6 +19,7 @@ def test_partial_last_tiles(oracle, N, d, Q, dtype):
     k = min(10, N)
     Xd = X.cuda()
     ds = B.Datastore(Xd) if dtype == "f32" else B.Datastore.from_fp32(Xd, torch.bfloat16 if dtype == "bf16" else torch.float16)
+    assert B.ralm_scan_routes(Q, ds, k)[0] == "all_quarters"
     ws = B.alloc_workspace(Q, ds, k)
     ids, sc = B.ralm_retrieve_topk_ex(q.cuda(), ds, k, workspace=ws)
     c = B.ralm_workspace_counters(ws)
