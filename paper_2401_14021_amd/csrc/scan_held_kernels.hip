@@ -308,6 +308,35 @@ void scan_held_kernel(ScanParams p, const int nqt, const int streams_per_xcd)
     wait_vmcnt<0>();   // the run-ahead loads must land before this workgroup's LDS is released
 }
 
+// queries of a tile
+int scan_held_bn(const ScanParams &p) { return p.Q <= 128 || p.dpad > 768 ? 128 : 256; }
+
+// Streams of rows per XCD; each takes a workgroup for every query tile.  As many as the CUs hold at once leave CUs idle where
+// their number is no multiple of the query tiles (seven tiles on 32 CUs: 4).  So a launch of several query tiles may have more workgroups than
+// CUs: the hardware starts the rest as the first ones end, tile by tile of a stream, and what is idle is less than one of
+// several rounds.  A round more costs a load of the queries and a ring that fills, 12 us (256 queries over 6M x 768 in 1, 2, 4 and 8 rounds
+// 2233, 2246, 2271, 2315 us); a hundredth of the CUs gains 0.4 hundredths of the time, because power sets the clock.  Both in
+// tiles of 32 rows: a tile of 256 queries x 768 takes 2.4 us.  Whole calls over 4M x 768, in one round and in the number that this takes:
+// 1280 queries 6297, 6269 us (three), 1792 8944, 8628 (two), 2304 11 713, 11 195 (two).  With CUs reserved a second round would
+// start on them, so there is one.
+int64_t held_streams(const ScanParams &p, int n_cu)
+{
+    const int64_t bn = scan_held_bn(p), nqt = (p.Q + bn - 1) / bn, per_xcd = n_cu / 8, n_tiles = p.n_row_tiles * (SCAN_BM / HELD_BM);
+    int64_t best = per_xcd / nqt;
+    if (nqt == 1 || p.one_per_cu) return best;
+    int64_t least = 0;
+    for (int64_t rounds = 1; rounds <= 16; ++rounds) {
+        const int64_t streams = rounds * per_xcd / nqt;
+        if (streams < 1) continue;
+        const int64_t cost = rounds * (11 + (n_tiles + 8 * streams - 1) / (8 * streams));
+        if (least == 0 || cost < least) {
+            least = cost;
+            best = streams;
+        }
+    }
+    return best;
+}
+
 template <bool F16, int KT, int TN, bool NTA>
 hipError_t launch_variant(const ScanParams &p, int n_cu, hipStream_t stream)
 {
@@ -322,7 +351,8 @@ hipError_t launch_variant(const ScanParams &p, int n_cu, hipStream_t stream)
         attr_done.store(true, std::memory_order_release);
     }
     const int nqt = (int)((p.Q + TN * 128 - 1) / (TN * 128));
-    hipLaunchKernelGGL(kern, dim3((unsigned)(n_cu / 8 * 8)), dim3(256), smem, stream, p, nqt, n_cu / 8 / nqt);
+    const int streams = (int)held_streams(p, n_cu);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(8 * nqt * streams)), dim3(256), smem, stream, p, nqt, streams);
     return hipGetLastError();
 }
 
@@ -331,9 +361,6 @@ hipError_t launch_kt(const ScanParams &p, bool nt, int n_cu, hipStream_t stream)
 {
     return nt ? launch_variant<F16, KT, TN, true>(p, n_cu, stream) : launch_variant<F16, KT, TN, false>(p, n_cu, stream);
 }
-
-// queries of a tile
-int scan_held_bn(const ScanParams &p) { return p.Q <= 128 || p.dpad > 768 ? 128 : 256; }
 
 template <bool F16>
 hipError_t launch_type(const ScanParams &p, bool nt, int n_cu, hipStream_t stream)
@@ -373,20 +400,31 @@ bool scan_held_takes(const ScanParams &p, int n_cu)
     // gain: 129 over 1M x 320 237, 226, 256 257, 257, 200 over 2M x 512 579, 551.
     const int kt = p.dpad / 64, bn = scan_held_bn(p);
     if (kt < 5 || kt > 17 || (kt > 12 && p.Q > 128 && whole_lines(p))) return false;
-    // Every stream of rows needs a CU for each query tile on its XCD: a batch that leaves more than a twentieth of the columns or
-    // CUs idle is better off in tiles, or no worse: over 4M x 768 700 queries 3926, 3999, 1280 6537, 6562, 1536 7786, 7795, 1792 9033, 9349, 2341
-    // 12392, 12656 (three full tiles, 768 queries, would gain 2 %: 4072, 3990).
-    const int64_t nqt = (p.Q + bn - 1) / bn, per_xcd = n_cu / 8, streams = per_xcd / nqt;
-    if (streams < 1) return false;   // (nearly all CUs reserved)
-    // (two tiles of 128 were better at any size: 135 queries over 1M x 904 680, 564)
-    if (!(nqt == 2 && bn == 128) && nqt > 1 && p.Q * streams * 20 < per_xcd * bn * 19) return false;
+    // Several query tiles: columns and CUs that are left idle cost the tiled kernel less.  Where at most a twentieth of both is idle in one round, or two
+    // tiles of 128 queries share the rows (135 over 1M x 904 680, 564), they are held.
+    const int64_t nqt = (p.Q + bn - 1) / bn, per_xcd = n_cu / 8, n_tiles = p.n_row_tiles * (SCAN_BM / HELD_BM);
+    const int64_t streams = held_streams(p, n_cu);
+    if (streams < 1) return false;   // (nearly all CUs reserved, or more query tiles than 16 rounds hold)
+    if (nqt > 1 && !(nqt == 2 && bn == 128) && p.Q * (per_xcd / nqt) * 20 < per_xcd * bn * 19) {
+        // Otherwise if a quarter of the columns is idle at most, over 4M x 768: 300 queries 2484, 2474, 400 2704, 2656, 450 2864, 2685, 550
+        // 3634, 3654, 600 3759, 3713, 700 3857, 3737, 850 4998, 4880, 1100 6238, 6148, 1280 6448, 6270, 1792 8927, 8628; over 1M x 700 queries
+        // 1126, 1125.  Two tiles over rows that are no whole lines at any size: 300 over 1M x 648 760, 690, over 1M x 392 533, 514.
+        // More than eight tiles only if a twentieth of the columns is idle: 2304 11 505, 11 195 (on the safe side: 2341, whose last tile
+        // is nearly empty, 12 290, 12 010).  Tiles of 128 up to four: 300 over 1M x 1000 1120, 894, 500 over 1M x 904 1117,
+        // 1096, but 700 1498, 1549 and 1200 2430, 2530.  Below 64 tiles of rows for a workgroup there is nothing in it: 600 over 500 000
+        // x 768 624, 624, 390 over 300 000 336, 336, 768 481, 486.
+        if (p.one_per_cu || n_tiles < 512 * streams) return false;
+        const int64_t columns = nqt * bn;
+        if (bn == 128 ? nqt > 4 : (nqt > 8 && p.Q * 20 < columns * 19)) return false;
+        if (!(nqt == 2 && !whole_lines(p)) && p.Q * 4 < columns * 3) return false;
+    }
     // several query tiles share the stream of rows, and short rows are few multiplies between two rendezvous: 1000 queries
     // over 2M x 384 1520, 1567, 512 over 2M x 512 1047, 1042.  Rows that are no whole lines cost the tiled kernel more: 512 over
     // 1M x 560 694, 620
     if (nqt > 1 && kt <= 8 && whole_lines(p)) return false;
     // A workgroup loads 128 TN queries before its first row: at least 8 tiles each.  (On the safe side for rows that are no whole lines:
     // 120 queries over 400 000 x 392, whose middle stage has 7.8 tiles for each, 128, 117.)
-    if (p.n_row_tiles * (SCAN_BM / HELD_BM) < 64 * streams) return false;
+    if (n_tiles < 64 * streams) return false;
     // Admitted scores interrupt a lone wave.  us per launch by the scores expected per tile of 32 rows: 26: 120, 159; 18: 61, 72; 10 (81
     // queries): 42, 44; 5.7: 578, 565; 4.7: 476, 516; 3.3 (100 queries): 235, 207; 2.3: 337, 294; 1.6: 1357, 1183; 0.8: 1968, 1870.
     // Rows that are no whole lines, in corpus order: 11 a tile (90 queries over 777001 x 392, the first of two such stages in tiles or
@@ -396,7 +434,7 @@ bool scan_held_takes(const ScanParams &p, int n_cu)
     // In random order (whole calls, the stages beyond 4 a tile in tiles or not): 81 over 1M x 768 (10 a tile) 298, 307, 200 over 200 000 x
     // 768 (27) 141, 153, 100 over 150 000 x 768 (14) 99, 91.
     const int64_t most = whole_lines(p) ? 4 : 16;
-    return p.admits * (p.Q < bn ? p.Q : bn) <= most * p.n_row_tiles * (SCAN_BM / HELD_BM);
+    return p.admits * (p.Q < bn ? p.Q : bn) <= most * n_tiles;
 }
 
 hipError_t launch_scan_held(const ScanParams &p, bool nt, int n_cu, hipStream_t stream)

@@ -188,6 +188,17 @@ def test_scan_routes(L, Q, N, d, more, want):
         assert got[-1] == (want or "held"), got
 
 
+@pytest.mark.parametrize("Q,N,d,want", [
+    (700, 4_000_000, 768, "held"), (600, 4_000_000, 768, "held"), (550, 4_000_000, 768, "parked"),   # idle columns: up to a quarter
+    (300, 4_000_000, 768, "parked"), (300, 4_000_000, 712, "held"),      # two tiles over rows that are no whole lines: any size
+    (2048, 4_000_000, 768, "held"), (2100, 4_000_000, 768, "parked"), (2200, 4_000_000, 768, "held"),   # nine tiles: a twentieth
+    (400, 4_000_000, 904, "held"), (700, 4_000_000, 904, "parked"),      # tiles of 128 queries: up to four
+    (768, 300_000, 768, "parked"),                                       # few rows for a workgroup
+])
+def test_scan_routes_of_several_query_tiles(L, Q, N, d, want):
+    assert _routes(L, Q, 10, N, d)[-1] == want
+
+
 def test_scan_routes_with_compute_units_reserved(L):
     from paper_2401_14021_amd import binding as b
     try:

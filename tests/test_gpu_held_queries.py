@@ -87,6 +87,31 @@ def test_several_query_tiles(rows, oracle, d, Q, last):
     _check(rows, oracle, d, Q, torch.bfloat16, last=last)
 
 
+@pytest.mark.parametrize("d,Q", [(392, 1700), (768, 1792)])
+def test_more_workgroups_than_compute_units(d, Q):
+    """Seven query tiles do not share out over an XCD's 32 compute units: the launch has a second round of workgroups, which begin as
+    the first ones end, in the LDS that those leave."""
+    from paper_2401_14021_amd import binding as B
+    n = 2 ** 19 - 1
+    g = torch.Generator().manual_seed(d)
+    X = torch.randint(-3, 4, (n, d), generator=g, dtype=torch.int8).float().cuda()
+    q = torch.randint(-3, 4, (Q, d), generator=g).float().cuda()
+    X[391 * 256 + 7:391 * 256 + 200] = 3
+    q[::3] = q[::3].abs()   # these queries' best rows are the run of equal ones
+    ds = B.Datastore.from_fp32(X, torch.bfloat16)
+    assert B.ralm_scan_routes(Q, ds, 2, 4)[-1] == "held"
+    ws = B.alloc_workspace(Q, ds, 2, 4)
+    ids, sc = B.ralm_retrieve_topk_ex(q, ds, 2, 4, workspace=ws)
+    c = B.ralm_workspace_counters(ws)
+    assert c["exact_pass"] == 0 and c["unanswered"] == 0 and c["ladder_overflows"] == 0, c
+    Xd, order = X.double(), (n - torch.arange(n, device="cuda", dtype=torch.float64))[:, None]
+    for i in range(0, Q, 64):   # whole numbers: exact in double, also with the order of equal scores behind them
+        full = Xd @ q[i:i + 64].double().T
+        want = (full * 2 ** 19 + order).topk(2, dim=0).indices.T
+        assert torch.equal(ids[i:i + 64].long(), want)
+        assert torch.equal(sc[i:i + 64], full.T.gather(1, want).float())
+
+
 @pytest.mark.parametrize("d,Q", [(1024, 100), (632, 200)])
 def test_squared_distance(rows, oracle, d, Q):
     _check(rows, oracle, d, Q, torch.float16, metric_l2=True)
