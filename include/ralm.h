@@ -332,9 +332,10 @@ ralm_status ralm_build_scan_copy_l2(const void *src, int32_t src_dtype, int64_t 
  *              8-byte aligned, contents undefined between calls.  Without it
  *              one workgroup serves a request, which leaves most of the chip
  *              idle when there are few requests (a single request with 4096
- *              cached rows then takes ~0.4 ms); with it the caches of fewer
- *              than 128 requests are each split over several workgroups that
- *              merge through the workspace (same results).
+ *              cached rows then takes ~0.4 ms); with it the caches of up to
+ *              512 requests are each split over several workgroups, where that
+ *              fills the chip better, that merge through the workspace and the
+ *              outputs (same results).
  */
 size_t ralm_cache_lookup_workspace_bytes(int64_t Qt);
 ralm_status ralm_cache_lookup(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,
@@ -344,8 +345,8 @@ ralm_status ralm_cache_lookup(const int32_t *cache_ids, const int32_t *cache_len
 
 /*
  * ralm_cache_lookup that writes every row of the outputs: rows of [0, Qt) that no
- * request owns get id -1 / score -inf, in a launch that the lookup needs anyway,
- * so outputs need not be filled beforehand.
+ * request owns get id -1 / score -inf, by the lookup itself or in a launch that it
+ * needs anyway, so outputs need not be filled beforehand.
  */
 ralm_status ralm_cache_lookup_all(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,
                                   const float *queries, int64_t Qt, const int64_t *q_offsets,

@@ -39,6 +39,76 @@ __device__ __forceinline__ void clamp_range(const int64_t *off, int64_t r, int64
     hi = hi < lo ? lo : (hi > Qt ? Qt : hi);
 }
 
+// Queries that no request owns get id -1 / score -inf; the NT threads of one workgroup.  They lie in front of the first range and
+// behind the last one; where the ranges are not in order (they should be) every one of these is looked for in all of them.
+template <int NT>
+__device__ __forceinline__ void answer_unowned(const int64_t *__restrict__ off, int64_t R, int64_t Qt, int32_t *__restrict__ ids,
+                                               float *__restrict__ scores)
+{
+    const int64_t first = off[0] < 0 ? 0 : (off[0] > Qt ? Qt : off[0]), end = off[R] < 0 ? 0 : (off[R] > Qt ? Qt : off[R]);
+    if (first == 0 && end == Qt) return;
+    int sorted = 1;
+    for (int64_t r = threadIdx.x; r < R; r += NT) sorted &= off[r] <= off[r + 1] ? 1 : 0;
+    sorted = __syncthreads_and(sorted);
+    auto answer = [&](int64_t q) {
+        bool owned = false;
+        for (int64_t r = 0; !sorted && !owned && r < R; ++r) owned = off[r] <= q && q < off[r + 1];
+        if (owned) return;
+        ids[q] = -1;
+        scores[q] = -__builtin_inff();
+    };
+    for (int64_t q = threadIdx.x; q < first; q += NT) answer(q);
+    for (int64_t q = end + threadIdx.x; q < Qt; q += NT) answer(q);
+}
+
+// A lookup whose requests are split over several workgroups.  Their best keys meet in partial[query] by an atomic max; who is the last
+// of a request to have sent its own decodes them.  The arrivals are counted in the request's first answer, which holds -1 before.
+// In a launch of its own the decoding cost 4 us on the GPU and 2.5 us on the host.
+constexpr int64_t SPLIT_MAX_R = 512;   // more requests are not split
+__device__ __forceinline__ void merge_parts(const u64 *__restrict__ partial, int64_t q_lo, int64_t q_hi, int parts, int32_t *ids,
+                                            float *scores)
+{
+    __shared__ int s_last;
+    __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wave's maxima are in place
+    __syncthreads();
+    if (threadIdx.x == 0)
+        s_last = __hip_atomic_fetch_add(ids + q_lo, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == parts - 2;
+    __syncthreads();
+    if (!s_last) return;
+    for (int64_t q = q_lo + threadIdx.x; q < q_hi; q += blockDim.x) {
+        const u64 b = __hip_atomic_load(partial + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        ids[q] = b ? key_id(b) : -1;
+        scores[q] = b ? key_score(b) : -__builtin_inff();
+    }
+}
+// Ranges that are not in order (they should be) may overlap, and with them the places that count arrivals: every request
+// is then served by its first workgroup alone.
+__device__ __forceinline__ bool ranges_in_order(const int64_t *__restrict__ off, int64_t R)
+{
+    bool sorted = true;
+    for (int64_t r = threadIdx.x & 63; r < R; r += 64) sorted = sorted && off[r] <= off[r + 1];
+    return __all(sorted);
+}
+
+// What cache_lookup_kernel needs before its rows and after them, its first argument.  It is read again from the arguments at the
+// end: kept all the time it took scalar registers that the loop over the rows needs (512 requests x up to 8 queries x 4096 entries of 392
+// 861 -> 978 us).
+struct LookupEnd {
+    const int64_t *q_offsets;
+    int64_t R, Qt;
+    int32_t *ids;
+    float *scores;
+    u64 *partial;   // NULL: a request has one workgroup
+    int fill;       // answer the queries that no request owns
+};
+__device__ __forceinline__ LookupEnd lookup_end()
+{
+    typedef const __attribute__((address_space(4))) LookupEnd *Args;
+    Args args = (Args)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    return {args->q_offsets, args->R, args->Qt, args->ids, args->scores, args->partial, args->fill};
+}
+
 // elements (c*CL_GS + sub)*4 .. +4 of a cached row, c = 0 .. NCH-1, widened exactly to fp32 (zeros
 // for a missing row and past d)
 template <int EX, int NCH>
@@ -78,11 +148,10 @@ static_assert(CL_QB == 4, "the block dispatch in cache_lookup_kernel is written 
 // parameter: tested at run time it cost the lookup a quarter of its time).
 template <int EX, int NCH, int NW, bool L2, int MAXQ, bool LIST>
 __global__ __launch_bounds__(NW * 64) void cache_lookup_kernel(
-    const int32_t *__restrict__ cache_ids, const int32_t *__restrict__ cache_len, int C,
-    const float *__restrict__ queries, int64_t Qt, const int64_t *__restrict__ q_offsets,
+    const LookupEnd to, const int32_t *__restrict__ cache_ids, const int32_t *__restrict__ cache_len, int C,
+    const float *__restrict__ queries,
     const void *__restrict__ exact, int64_t ld, int64_t N, int d, int qgroup,
-    int32_t *__restrict__ spec_ids, float *__restrict__ spec_scores, u64 *__restrict__ partial, u64 *__restrict__ list,
-    uint32_t *__restrict__ list_len)
+    u64 *__restrict__ list, uint32_t *__restrict__ list_len)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int dq = (d + 63) & ~63;                                  // a query's doubles in LDS
@@ -90,13 +159,26 @@ __global__ __launch_bounds__(NW * 64) void cache_lookup_kernel(
     u64 *best = reinterpret_cast<u64 *>(qs + (size_t)qgroup * dq);  // [NW waves][CL_ROWS][qgroup]
 
     // gridDim.y workgroups share a request (few requests: spread each over many CUs); they then
-    // merge their best keys with a 64-bit atomic max in `partial`, decoded by a second kernel
+    // merge their best keys (merge_parts)
     const int64_t r = blockIdx.x;
-    const int part = blockIdx.y, parts = gridDim.y;
+    const int part = blockIdx.y;
+    int parts = gridDim.y;
+    __shared__ int s_merge, s_fill;   // workgroups that merge (0: this one's bests are the answer); whether it answers the unowned
+    if (!LIST) {
+        const bool in_order = !to.partial || ranges_in_order(to.q_offsets, to.R);
+        if (!in_order) {
+            if (part > 0) return;
+            parts = 1;
+        }
+        if (threadIdx.x == 0) {
+            s_merge = to.partial && in_order ? parts : 0;
+            s_fill = to.fill && r == 0;
+        }
+    }
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int sub = lane % CL_GS, slot = lane / CL_GS;
     int64_t q_lo, q_hi;
-    clamp_range(q_offsets, r, Qt, q_lo, q_hi);
+    clamp_range(to.q_offsets, r, to.Qt, q_lo, q_hi);
     int len = cache_len[r];
     len = len < 0 ? 0 : (len > C ? C : len);
     const int32_t *ids = cache_ids + r * (int64_t)C;
@@ -224,19 +306,31 @@ __global__ __launch_bounds__(NW * 64) void cache_lookup_kernel(
                 if (i < nq && best_id[i] >= 0) my_best[i] = make_key(best_sc[i], best_id[i]);
         }
         __syncthreads();
+        const LookupEnd end = lookup_end();
+        const bool merge = s_merge != 0;
         for (int qi = tid; qi < nq; qi += NW * 64) {
             u64 b = 0ull;
             for (int w = 0; w < NW * CL_ROWS; ++w) {
                 const u64 v = best[w * qgroup + qi];
                 b = v > b ? v : b;
             }
-            if (partial) {
-                if (b) atomicMax(reinterpret_cast<unsigned long long *>(partial + g0 + qi), b);
+            if (merge) {
+                if (b) atomicMax(reinterpret_cast<unsigned long long *>(end.partial + g0 + qi), b);
             } else {
-                spec_ids[g0 + qi] = b ? key_id(b) : -1;
-                spec_scores[g0 + qi] = b ? key_score(b) : -__builtin_inff();
+                end.ids[g0 + qi] = b ? key_id(b) : -1;
+                end.scores[g0 + qi] = b ? key_score(b) : -__builtin_inff();
             }
         }
+    }
+    if (LIST) return;
+    __syncthreads();
+    if (s_merge && q_lo < q_hi) {
+        const LookupEnd end = lookup_end();
+        merge_parts(end.partial, q_lo, q_hi, s_merge, end.ids, end.scores);
+    }
+    if (s_fill) {
+        const LookupEnd end = lookup_end();
+        answer_unowned<NW * 64>(end.q_offsets, end.R, end.Qt, end.ids, end.scores);
     }
 }
 
@@ -263,8 +357,7 @@ __global__ __launch_bounds__(CM_NW * 64) void cache_lookup_mfma_kernel(
     const int32_t *__restrict__ cache_ids, const int32_t *__restrict__ cache_len, int C,
     const float *__restrict__ queries, int64_t Qt, const int64_t *__restrict__ q_offsets,
     const void *__restrict__ exact, int64_t ld, int64_t N, int d, int ng_max,
-    int32_t *__restrict__ spec_ids, float *__restrict__ spec_scores, u64 *__restrict__ partial, u64 *__restrict__ list,
-    uint32_t *__restrict__ list_len)
+    int32_t *spec_ids, float *spec_scores, u64 *partial, int fill, u64 *__restrict__ list, uint32_t *__restrict__ list_len)
 {
     constexpr int CH = EX == DT_F32 ? 4 : 8;        // elements per 16-byte piece
     constexpr int ES = EX == DT_F32 ? 4 : 2;
@@ -274,39 +367,73 @@ __global__ __launch_bounds__(CM_NW * 64) void cache_lookup_mfma_kernel(
     u64 *best = reinterpret_cast<u64 *>(bq + (size_t)ng_max * T * 16);   // [4 * ng_max]
 
     const int64_t r = blockIdx.x;
-    const int part = blockIdx.y, parts = gridDim.y;
+    const int part = blockIdx.y;
+    int parts = gridDim.y;
+    if (!LIST && partial && !ranges_in_order(q_offsets, gridDim.x)) {
+        if (part > 0) return;
+        parts = 1;
+        partial = nullptr;
+    }
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r16 = lane & 15, kq = lane >> 4;            // row of the step and k index this lane feeds
     const int ro = ((lane >> 2) & 3) * 4 + (lane >> 4);   // row of the step whose score this lane receives
     const int jq = lane & 3;                              // ... against this query of a group
+    const int32_t *ids = cache_ids + r * (int64_t)C;
+    const int blk_first = part * CM_NW + wave, blk_step = parts * CM_NW;
+    // What the first rows depend on, at once (a slot of the cache is there whether it is used or not): the ids of the rows
+    // this lane feeds and receives in its wave's first step and in the next.  Its rows then travel while the queries are laid out; one
+    // after the other, 64 requests x 1024 entries of 768 took 41.6 us, now 39.9; the k best of 32 x 8 x 2048 of 1024 fp16 61.6 and 51.1.
+    auto slot_at = [&](int e) { return e < C ? ids[e] : -1; };
+    const int32_t feed_0 = slot_at(blk_first * 16 + r16), out_0 = slot_at(blk_first * 16 + ro);
+    const int32_t feed_1 = slot_at((blk_first + blk_step) * 16 + r16), out_1 = slot_at((blk_first + blk_step) * 16 + ro);
     int64_t q_lo, q_hi;
     clamp_range(q_offsets, r, Qt, q_lo, q_hi);
     int len = cache_len[r];
     len = len < 0 ? 0 : (len > C ? C : len);
-    const int32_t *ids = cache_ids + r * (int64_t)C;
     const int NC = d / (4 * CH);                          // pieces per lane and row
     const int nsegs = NC / SEG;
     const int nblk = (len + 15) / 16;
-    const int blk_step = parts * CM_NW;
     const unsigned char *base = static_cast<const unsigned char *>(exact) + kq * 16;
     if (LIST && part == 0)
         for (int64_t q = q_lo + tid; q < q_hi; q += CM_NW * 64) list_len[q] = (uint32_t)len;
 
+    auto row_of = [&](int32_t id) {
+        const bool ok = id >= 0 && (int64_t)id < N;
+        return base + (int64_t)(ok ? id : 0) * ld * ES;
+    };
+    auto load = [&](uint4(&buf)[SEG], const unsigned char *rw, int sg) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < SEG; ++c) buf[c] = *reinterpret_cast<const uint4 *>(rw + (size_t)(sg * SEG + c) * 64);
+    };
+
     for (int64_t g0 = q_lo; g0 < q_hi; g0 += 4 * ng_max) {
         const int nq = (int)((q_hi - g0) < 4 * ng_max ? (q_hi - g0) : 4 * ng_max);
         const int n_groups = (nq + 3) >> 2;
-        __syncthreads();
-        for (int i = tid; i < n_groups * 4 * d; i += CM_NW * 64) {
-            const int qi = i / d, e = i - qi * d;
-            const double v = qi < nq ? (double)queries[(g0 + qi) * d + e] : 0.0;
-            const int t = CH * (e / (4 * CH)) + e % CH, k = (e / CH) & 3;
-            bq[((size_t)(qi >> 2) * T + t) * 16 + k * 4 + (qi & 3)] = v;
-        }
-        for (int i = tid; i < 4 * ng_max; i += CM_NW * 64) best[i] = 0ull;
-        __syncthreads();
-
+        if (g0 > q_lo) __syncthreads();   // (a barrier waits for all loads)
         auto run = [&](auto ng_tag) __attribute__((always_inline)) {
             constexpr int NG = decltype(ng_tag)::value;
+            // the first step's rows are on their way while the queries are laid out
+            uint4 buf0[SEG], buf1[SEG];
+            if (blk_first < nblk) load(buf0, row_of(blk_first * 16 + r16 < len ? feed_0 : -1), 0);
+            // four threads take the four queries of a group, piece by piece of four elements
+#pragma unroll 1
+            for (int g = 0; g < NG; ++g) {
+                const int qi = g * 4 + (tid & 3);
+                const float *src = queries + (g0 + qi) * d;
+#pragma unroll 1
+                for (int e = (tid >> 2) * 4; e < d; e += CM_NW * 64) {
+                    const float4 v = qi < nq ? *reinterpret_cast<const float4 *>(src + e) : make_float4(0.f, 0.f, 0.f, 0.f);
+                    double *to = bq + ((size_t)g * T + CH * (e / (4 * CH)) + e % CH) * 16 + ((e / CH) & 3) * 4 + (tid & 3);
+                    to[0] = (double)v.x;
+                    to[16] = (double)v.y;
+                    to[32] = (double)v.z;
+                    to[48] = (double)v.w;
+                }
+            }
+            for (int i = tid; i < 4 * ng_max; i += CM_NW * 64) best[i] = 0ull;
+            __syncthreads();
+            int blk = blk_first;
+            if (blk >= nblk) return;
             float best_sc[NG];
             int32_t best_id[NG];
             double acc[NG];
@@ -316,23 +443,13 @@ __global__ __launch_bounds__(CM_NW * 64) void cache_lookup_mfma_kernel(
                 best_id[g] = -1;
                 acc[g] = 0.0;
             }
-            int blk = part * CM_NW + wave;
-            if (blk >= nblk) return;
             // ids of the rows this lane feeds and receives, for this step and (ahead) the next
             auto id_at = [&](int e) { return e < len ? ids[e] : -1; };
-            auto row_of = [&](int32_t id) {
-                const bool ok = id >= 0 && (int64_t)id < N;
-                return base + (int64_t)(ok ? id : 0) * ld * ES;
-            };
-            int32_t id_out = id_at(blk * 16 + ro);
-            const unsigned char *row = row_of(id_at(blk * 16 + r16));
-            int32_t id_feed_n = id_at((blk + blk_step) * 16 + r16), id_out_n = id_at((blk + blk_step) * 16 + ro);
+            auto used = [&](int e, int32_t id) { return e < len ? id : -1; };
+            int32_t id_out = used(blk * 16 + ro, out_0);
+            const unsigned char *row = row_of(used(blk * 16 + r16, feed_0));
+            int32_t id_feed_n = used((blk + blk_step) * 16 + r16, feed_1), id_out_n = used((blk + blk_step) * 16 + ro, out_1);
             int seg = 0;
-            uint4 buf0[SEG], buf1[SEG];
-            auto load = [&](uint4(&buf)[SEG], const unsigned char *rw, int sg) __attribute__((always_inline)) {
-#pragma unroll
-                for (int c = 0; c < SEG; ++c) buf[c] = *reinterpret_cast<const uint4 *>(rw + (size_t)(sg * SEG + c) * 64);
-            };
             // one (step, segment) item: issue the next item's loads, multiply this one's pieces
             auto item = [&](uint4(&cur)[SEG], uint4(&nxt)[SEG]) __attribute__((always_inline)) -> bool {
                 const bool last_seg = seg + 1 == nsegs;
@@ -399,7 +516,6 @@ __global__ __launch_bounds__(CM_NW * 64) void cache_lookup_mfma_kernel(
                 }
                 return !more;
             };
-            load(buf0, row, 0);
             for (;;) {
                 if (item(buf0, buf1)) break;
                 if (item(buf1, buf0)) break;
@@ -425,24 +541,8 @@ __global__ __launch_bounds__(CM_NW * 64) void cache_lookup_mfma_kernel(
             }
         }
     }
-}
-
-// decodes the merged keys of the split lookup; one wave per request
-__global__ __launch_bounds__(256) void cache_lookup_finish_kernel(const u64 *__restrict__ partial, int64_t Qt,
-                                                                  const int64_t *__restrict__ q_offsets, int64_t R,
-                                                                  int32_t *__restrict__ spec_ids,
-                                                                  float *__restrict__ spec_scores)
-{
-    const int lane = threadIdx.x & 63;
-    const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (r >= R) return;
-    int64_t lo, hi;
-    clamp_range(q_offsets, r, Qt, lo, hi);
-    for (int64_t q = lo + lane; q < hi; q += 64) {
-        const u64 b = partial[q];
-        spec_ids[q] = b ? key_id(b) : -1;
-        spec_scores[q] = b ? key_score(b) : -__builtin_inff();
-    }
+    if (!LIST && partial && q_lo < q_hi) merge_parts(partial, q_lo, q_hi, parts, spec_ids, spec_scores);
+    if (!LIST && fill && r == 0) answer_unowned<CM_NW * 64>(q_offsets, gridDim.x, Qt, spec_ids, spec_scores);
 }
 
 __global__ __launch_bounds__(256) void verify_kernel(const int32_t *__restrict__ spec,
@@ -673,14 +773,22 @@ __global__ void fill_u32_kernel(uint32_t *p, uint32_t v, int64_t n)
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         p[i] = v;
 }
-// the merge slots of a split lookup, and the answer of queries that no request owns (NULL: not wanted)
-__global__ void lookup_init_kernel(u64 *partial, int32_t *ids, float *scores, int64_t n)
+// Before a lookup: the merge slots and, in the first answer of each of the R requests, the count of arrivals (merge_parts); the answer
+// of queries that no request owns.  partial == NULL, every_row == 0: not wanted.
+__global__ void lookup_init_kernel(u64 *partial, const int64_t *__restrict__ q_offsets, int64_t R, int32_t *ids, float *scores,
+                                   int every_row, int64_t Qt)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        if (partial) partial[i] = 0ull;
-        if (ids) {
+    const int64_t n = R > Qt ? R : Qt, step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += step) {
+        if (partial && i < Qt) partial[i] = 0ull;
+        if (every_row && i < Qt) {
             ids[i] = -1;
             scores[i] = -__builtin_inff();
+        }
+        if (partial && !every_row && i < R) {
+            int64_t lo, hi;
+            clamp_range(q_offsets, i, Qt, lo, hi);
+            if (lo < hi) ids[lo] = -1;
         }
     }
 }
@@ -779,7 +887,7 @@ template <int EX, bool L2, bool LIST>
 hipError_t launch_cache_ex_form(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,
                            const float *queries, int64_t Qt, const int64_t *q_offsets, const void *exact,
                            int64_t ld, int64_t N, int32_t d, int32_t *spec_ids, float *spec_scores,
-                           u64 *partial, u64 *list, uint32_t *list_len, int parts, hipStream_t stream)
+                           u64 *partial, int fill, u64 *list, uint32_t *list_len, int parts, hipStream_t stream)
 {
     int qgroup = CL_LDS_BYTES / (((d + 63) & ~63) * 8);
     const int nch = (d + CL_GS * 4 - 1) / (CL_GS * 4);
@@ -801,8 +909,8 @@ hipError_t launch_cache_ex_form(const int32_t *cache_ids, const int32_t *cache_l
         hipLaunchKernelGGL(kern, dim3((unsigned)R, (unsigned)parts), dim3(NWV * 64),                        \
                            (size_t)qgroup * ((d + 63) & ~63) * 8 + (size_t)NWV * CL_ROWS * qgroup * sizeof(u64),   \
                            stream,                                                                          \
-                           cache_ids, cache_len, C, queries, Qt, q_offsets, exact, ld, N, d, qgroup, spec_ids, \
-                           spec_scores, partial, list, list_len);                                           \
+                           LookupEnd{q_offsets, R, Qt, spec_ids, spec_scores, partial, fill}, cache_ids, cache_len, C, \
+                           queries, exact, ld, N, d, qgroup, list, list_len);                               \
     } while (0)
     if (nch <= 4) RALM_CL(4, 8, 16);
     else if (nch <= 8) RALM_CL(8, 8, 16);
@@ -818,12 +926,12 @@ template <int EX, bool L2>
 hipError_t launch_cache_ex(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,
                            const float *queries, int64_t Qt, const int64_t *q_offsets, const void *exact,
                            int64_t ld, int64_t N, int32_t d, int32_t *spec_ids, float *spec_scores,
-                           u64 *partial, u64 *list, uint32_t *list_len, int parts, hipStream_t stream)
+                           u64 *partial, int fill, u64 *list, uint32_t *list_len, int parts, hipStream_t stream)
 {
     return list ? launch_cache_ex_form<EX, L2, true>(cache_ids, cache_len, C, R, queries, Qt, q_offsets, exact, ld, N, d, spec_ids,
-                                                     spec_scores, partial, list, list_len, parts, stream)
+                                                     spec_scores, partial, fill, list, list_len, parts, stream)
                 : launch_cache_ex_form<EX, L2, false>(cache_ids, cache_len, C, R, queries, Qt, q_offsets, exact, ld, N, d,
-                                                      spec_ids, spec_scores, partial, list, list_len, parts, stream);
+                                                      spec_ids, spec_scores, partial, fill, list, list_len, parts, stream);
 }
 
 // The matrix-core form of the lookup, for the shapes it is written for: inner product, rows of a
@@ -839,7 +947,7 @@ template <int EX, bool LIST>
 hipError_t launch_cache_mfma_form(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,
                              const float *queries, int64_t Qt, const int64_t *q_offsets, const void *exact,
                              int64_t ld, int64_t N, int32_t d, int32_t *spec_ids, float *spec_scores,
-                             u64 *partial, u64 *list, uint32_t *list_len, int parts, hipStream_t stream)
+                             u64 *partial, int fill, u64 *list, uint32_t *list_len, int parts, hipStream_t stream)
 {
     const int nc = d / (EX == DT_F32 ? 16 : 32);
     // a group of 4 queries takes d * 32 bytes of LDS; up to 64 KB, so that two requests share a CU
@@ -858,7 +966,7 @@ hipError_t launch_cache_mfma_form(const int32_t *cache_ids, const int32_t *cache
         }                                                                                                   \
         hipLaunchKernelGGL(kern, dim3((unsigned)R, (unsigned)parts), dim3(CM_NW * 64), smem, stream, cache_ids, \
                            cache_len, C, queries, Qt, q_offsets, exact, ld, N, d, ng, spec_ids, spec_scores,   \
-                           partial, list, list_len);                                                        \
+                           partial, fill, list, list_len);                                                  \
     } while (0)
     if (nc % 8 == 0) RALM_CM(8);
     else if (nc % 6 == 0) RALM_CM(6);
@@ -871,12 +979,12 @@ template <int EX>
 hipError_t launch_cache_mfma(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,
                              const float *queries, int64_t Qt, const int64_t *q_offsets, const void *exact,
                              int64_t ld, int64_t N, int32_t d, int32_t *spec_ids, float *spec_scores,
-                             u64 *partial, u64 *list, uint32_t *list_len, int parts, hipStream_t stream)
+                             u64 *partial, int fill, u64 *list, uint32_t *list_len, int parts, hipStream_t stream)
 {
     return list ? launch_cache_mfma_form<EX, true>(cache_ids, cache_len, C, R, queries, Qt, q_offsets, exact, ld, N, d, spec_ids,
-                                                   spec_scores, partial, list, list_len, parts, stream)
+                                                   spec_scores, partial, fill, list, list_len, parts, stream)
                 : launch_cache_mfma_form<EX, false>(cache_ids, cache_len, C, R, queries, Qt, q_offsets, exact, ld, N, d,
-                                                    spec_ids, spec_scores, partial, list, list_len, parts, stream);
+                                                    spec_ids, spec_scores, partial, fill, list, list_len, parts, stream);
 }
 
 }  // namespace
@@ -892,11 +1000,11 @@ bool lookup_on_matrix_cores(int32_t exact_dtype, int32_t metric, int32_t d)
 // the form of the lookup kernels that fits the rows
 hipError_t launch_lookup(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R, const float *queries, int64_t Qt,
                          const int64_t *q_offsets, const void *exact, int32_t exact_dtype, int64_t ld, int64_t N, int32_t d,
-                         int32_t metric, int32_t *spec_ids, float *spec_scores, u64 *partial, u64 *list, uint32_t *list_len,
+                         int32_t metric, int32_t *spec_ids, float *spec_scores, u64 *partial, int fill, u64 *list, uint32_t *list_len,
                          int parts, hipStream_t stream)
 {
 #define RALM_CACHE(FN) \
-    FN(cache_ids, cache_len, C, R, queries, Qt, q_offsets, exact, ld, N, d, spec_ids, spec_scores, partial, list, list_len, parts, stream)
+    FN(cache_ids, cache_len, C, R, queries, Qt, q_offsets, exact, ld, N, d, spec_ids, spec_scores, partial, fill, list, list_len, parts, stream)
     const bool mfma = lookup_on_matrix_cores(exact_dtype, metric, d);
     if (exact_dtype == DT_F16) {
         if (metric == METRIC_L2) return RALM_CACHE((launch_cache_ex<DT_F16, true>));
@@ -911,35 +1019,53 @@ hipError_t launch_lookup(const int32_t *cache_ids, const int32_t *cache_len, int
 
 }  // namespace
 
+// Workgroups per request, at least 64 cached rows for each.  One holds a CU, so they run in rounds of 256: a round costs 7 us until rows
+// flow, and then its rows at what a CU takes alone (38 KB a us) or its share of the chip's 6000.  More than one needs slots cleared and a merge
+// (6 us).  What this finds is mostly one round that is as full as it can be, or about four of them where one
+// workgroup each would leave a last round of few.  us, one row of 768 fp32 per entry: 33 requests x 1024 entries by 8 (264
+// workgroups) 38.7, by 7 31.9; 100 x 1024 by 3 76.8, by 2 55.4; 70 x 2048 by 4 113.6, by 3 80.9; 300 x 1024 by 1 212, by 3 164; 1 x 128 by 2
+// 17.8, by 1 14.8, 1 x 256 by 4 17.7, by 1 25.1; 392 elements, 100 x 1024 by 3 44.0, by 2 33.3.
+int lookup_parts(int64_t R, int32_t C, int64_t row_bytes)
+{
+    if (R > SPLIT_MAX_R) return 1;
+    const int64_t most = (C + 63) / 64;
+    const double bytes = (double)C * (double)row_bytes;
+    int best = 1;
+    double least = 0.0;
+    for (int p = 1; p <= 256 && p <= most; ++p) {
+        const int64_t wgs = R * p, full = wgs / 256, rest = wgs % 256;
+        const double per_cu = rest > 0 && 6000.0 / (double)rest < 38.0 ? 6000.0 / (double)rest : 38.0;
+        const double us = 7.0 * (double)(full + (rest > 0)) + (p > 1 ? 6.0 : 0.0) +
+                          bytes / p / 1000.0 * ((double)full * 256.0 / 6000.0 + (rest > 0 ? 1.0 / per_cu : 0.0));
+        if (p == 1 || us < least + 0.1) {   // (of equals the one with more workgroups)
+            least = us;
+            best = p;
+        }
+    }
+    return best;
+}
+
+constexpr int64_t FILL_MAX_R = 4096;   // ranges that a workgroup checks in passing
+
 hipError_t launch_cache_lookup(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,
                                const float *queries, int64_t Qt, const int64_t *q_offsets,
                                const void *exact, int32_t exact_dtype, int64_t ld, int64_t N, int32_t d,
                                int32_t metric, int32_t *spec_ids, float *spec_scores, bool every_row, u64 *partial,
                                hipStream_t stream)
 {
-    // With few requests one workgroup per request leaves most of the chip idle: split every
-    // request's cache over `parts` workgroups (at least 64 cached rows each), if the caller
-    // gave scratch for the merge.
-    int parts = 1;
-    if (partial && R > 0 && R < 128) {
-        const int64_t want = (256 + R - 1) / R, most = (C + 63) / 64;
-        parts = (int)(want < most ? want : most);
-        if (parts < 1) parts = 1;
-    }
+    const int parts = partial && R > 0 ? lookup_parts(R, C, (int64_t)d * (exact_dtype == DT_F16 ? 2 : 4)) : 1;
     if (parts == 1 || R <= 0) partial = nullptr;
-    hipError_t e = hipSuccess;
-    if ((partial || every_row) && Qt > 0) {
-        hipLaunchKernelGGL(lookup_init_kernel, dim3(grid_for(Qt, 256)), dim3(256), 0, stream, partial,
-                           every_row ? spec_ids : nullptr, every_row ? spec_scores : nullptr, Qt);
-        e = hipGetLastError();
+    // Without merge slots to clear the lookup's first workgroup answers the queries that no request owns
+    const bool fill = every_row && !partial && R > 0 && R <= FILL_MAX_R;
+    if ((partial || (every_row && !fill)) && Qt > 0) {
+        hipLaunchKernelGGL(lookup_init_kernel, dim3(grid_for(Qt > R ? Qt : R, 256)), dim3(256), 0, stream, partial, q_offsets,
+                           R, spec_ids, spec_scores, every_row ? 1 : 0, Qt);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
-    if (e != hipSuccess || R <= 0) return e;
-    e = launch_lookup(cache_ids, cache_len, C, R, queries, Qt, q_offsets, exact, exact_dtype, ld, N, d, metric, spec_ids,
-                      spec_scores, partial, nullptr, nullptr, parts, stream);
-    if (e != hipSuccess || !partial) return e;
-    hipLaunchKernelGGL(cache_lookup_finish_kernel, dim3((unsigned)((R + 3) / 4)), dim3(256), 0, stream, partial, Qt,
-                       q_offsets, R, spec_ids, spec_scores);
-    return hipGetLastError();
+    if (R <= 0) return hipSuccess;
+    return launch_lookup(cache_ids, cache_len, C, R, queries, Qt, q_offsets, exact, exact_dtype, ld, N, d, metric, spec_ids,
+                         spec_scores, partial, fill ? 1 : 0, nullptr, nullptr, parts, stream);
 }
 
 // fp16 rows on the vector units are 8-byte pieces, with few of them in flight; that pays where a row serves several
@@ -970,9 +1096,9 @@ hipError_t launch_cache_lookup_topk(const int32_t *cache_ids, const int32_t *cac
         // steps one after the other: 43 us, now 20
         const bool mfma = lookup_on_matrix_cores(exact_dtype, metric, d);
         const int rows = mfma ? 64 : (d <= 768 ? 32 : 16), wgs = mfma || d <= 1024 ? 512 : 256;
-        const int64_t want = (wgs + R - 1) / R, most = (C + rows - 1) / rows;
+        const int64_t want = R < wgs ? wgs / R : 1, most = (C + rows - 1) / rows;
         e = launch_lookup(cache_ids, cache_len, C, R, queries, Qt, q_offsets, exact, exact_dtype, ld, N, d, metric, nullptr,
-                          nullptr, nullptr, list, list_len, (int)(want < most ? want : most), stream);
+                          nullptr, nullptr, 0, list, list_len, (int)(want < most ? want : most), stream);
         if (e != hipSuccess) return e;
     }
     int c2 = 2;

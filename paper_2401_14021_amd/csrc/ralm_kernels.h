@@ -135,7 +135,7 @@ hipError_t launch_exact_pass(const float *queries, int64_t Q, const void *exact,
                              const u64 *tau_exact, u64 *cand, uint32_t *cnt, uint32_t cap, int32_t *out_ids,
                              float *out_scores, int n_cu, hipStream_t stream);
 
-// every_row: queries that no request owns are answered with id -1 / score -inf, in the launch that clears `partial`
+// every_row: queries that no request owns are answered with id -1 / score -inf
 hipError_t launch_cache_lookup(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,
                                const float *queries, int64_t Qt, const int64_t *q_offsets,
                                const void *exact, int32_t exact_dtype, int64_t ld, int64_t N, int32_t d,
