@@ -129,11 +129,12 @@ hipError_t launch_rescore_cut(u64 *cand, const uint32_t *cnt, uint32_t cap, int3
                               hipStream_t stream);
 
 // exact scan + final ranking for the queries queued by the re-score (two launches that return at
-// once when none is queued)
+// once when none is queued).  host_mark (may be NULL): device address of a word in pinned host memory that is set to 1 where
+// a query stays unanswered
 hipError_t launch_exact_pass(const float *queries, int64_t Q, const void *exact, int32_t exact_dtype, int64_t ld,
                              int64_t N, int32_t d, int32_t metric, int32_t k, const int32_t *fb_list, int32_t *flags,
                              const u64 *tau_exact, u64 *cand, uint32_t *cnt, uint32_t cap, int32_t *out_ids,
-                             float *out_scores, int n_cu, hipStream_t stream);
+                             float *out_scores, int32_t *host_mark, int n_cu, hipStream_t stream);
 
 // every_row: queries that no request owns are answered with id -1 / score -inf
 hipError_t launch_cache_lookup(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,

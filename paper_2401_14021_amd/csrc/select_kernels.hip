@@ -875,7 +875,8 @@ __global__ __launch_bounds__(SEL_THREADS) void exact_finish_kernel(const u64 *__
                                                                    int k, int kp2, const int32_t *__restrict__ fb_list,
                                                                    int32_t *__restrict__ flags,
                                                                    int32_t *__restrict__ out_ids,
-                                                                   float *__restrict__ out_scores)
+                                                                   float *__restrict__ out_scores,
+                                                                   int32_t *__restrict__ host_mark)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     u64 *keys = reinterpret_cast<u64 *>(smem);   // [kp2]
@@ -896,7 +897,10 @@ __global__ __launch_bounds__(SEL_THREADS) void exact_finish_kernel(const u64 *__
                 out_ids[q * k + r] = -1;
                 out_scores[q * k + r] = __builtin_nanf("");
             }
-            if (tid == 0) atomicAdd(flags + FLAG_UNANSWERED, 1);
+            if (tid == 0) {
+                atomicAdd(flags + FLAG_UNANSWERED, 1);
+                if (host_mark) __hip_atomic_store(host_mark, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            }
             continue;
         }
         const u64 kth = radix_kth<SEL_THREADS>(c, n, (uint32_t)k, sh);
@@ -1026,7 +1030,7 @@ hipError_t launch_rescore_cut(u64 *cand, const uint32_t *cnt, uint32_t cap, int3
 hipError_t launch_exact_pass(const float *queries, int64_t Q, const void *exact, int32_t exact_dtype, int64_t ld,
                              int64_t N, int32_t d, int32_t metric, int32_t k, const int32_t *fb_list, int32_t *flags,
                              const u64 *tau_exact, u64 *cand, uint32_t *cnt, uint32_t cap, int32_t *out_ids,
-                             float *out_scores, int n_cu, hipStream_t stream)
+                             float *out_scores, int32_t *host_mark, int n_cu, hipStream_t stream)
 {
     if (Q <= 0) return hipSuccess;
     // as many of the queries at a time as fit 64 KB of LDS in fp32, at most XS_QG
@@ -1094,7 +1098,7 @@ hipError_t launch_exact_pass(const float *queries, int64_t Q, const void *exact,
     while (kp2 < k) kp2 <<= 1;
     const int64_t fgrid = Q < 256 ? Q : 256;
     hipLaunchKernelGGL(exact_finish_kernel, dim3((unsigned)fgrid), dim3(SEL_THREADS), (size_t)kp2 * sizeof(u64), stream,
-                       cand, cnt, cap, k, kp2, fb_list, flags, out_ids, out_scores);
+                       cand, cnt, cap, k, kp2, fb_list, flags, out_ids, out_scores, host_mark);
     return hipGetLastError();
 }
 
