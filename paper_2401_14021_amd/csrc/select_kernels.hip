@@ -968,11 +968,13 @@ hipError_t launch_rescore(const u64 *cand, const uint32_t *cnt, int cnt_pitch, u
     // 2341: 96 instead of 200.  Fewer queries, or many candidates each, need the large workgroup's waves; so do long
     // lists, of which a small one holds only 4096 keys in registers (the one stage of a small datastore).  Whole calls
     // with small and large ones, us: 512 queries over 16384 rows of 64, k = 5, 134 and 67, over 8000 rows 86 and 62, 1024
-    // over 8000 101 and 89, 3000 over 16384 451 and 353, over 8000 227 and 233, k = 100 364 and 410.
+    // over 8000 101 and 89, 3000 over 16384 451 and 353, over 8000 227 and 233, k = 100 364 and 410.  Of large ones a CU holds one, so
+    // between 257 and 511 queries a second round is nearly empty: 300 over 200 000 x 768 251 and 255, 500 284 and 289, 300 over 30 000 97 and
+    // 103, but 256 152 and 151, and k' = 256 361 and 357.
     const bool short_lists = expected <= SEL_REGS * 256 || (expected <= SEL_REGS * 512 && Q >= 2048);
 #define RALM_RS(EXV, L2V)                                  \
     do {                                                   \
-        if (Q >= 512 && k_prime <= RS_COUNT_MAX && short_lists) RALM_RS_NT(EXV, L2V, 256); \
+        if ((Q >= 512 || (Q > 256 && k_prime <= 64)) && k_prime <= RS_COUNT_MAX && short_lists) RALM_RS_NT(EXV, L2V, 256); \
         else RALM_RS_NT(EXV, L2V, SEL_THREADS);            \
     } while (0)
     if (exact_dtype == DT_F16) {
