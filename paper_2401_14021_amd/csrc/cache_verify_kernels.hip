@@ -968,9 +968,20 @@ hipError_t launch_cache_mfma_form(const int32_t *cache_ids, const int32_t *cache
                            cache_len, C, queries, Qt, q_offsets, exact, ld, N, d, ng, spec_ids, spec_scores,   \
                            partial, fill, list, list_len);                                                  \
     } while (0)
-    if (nc % 8 == 0) RALM_CM(8);
-    else if (nc % 6 == 0) RALM_CM(6);
-    else RALM_CM(4);
+    // Four pieces at a time take half the registers, and two workgroups fit a CU: for lists (the k best of 32 requests x 8 queries x 2048 fp16
+    // rows of 1024 51.1 and 49.4 us, 2 x 8 x 2048 31.3 and 30.1), for requests that are split and fill the chip (64 x 1024 entries of 768
+    // 38.8 and 37.4, 300 x 4 x 2000 302 and 292), and where one workgroup to a CU would leave a second round of few (350 x 300 73 and
+    // 66).  Fewer workgroups than CUs would pair up and leave others idle (100 x 1024 by 2 56.0 and 60.4), and full rounds of
+    // whole requests are the better for long loads (256 x 4 x 1024 121 and 125, 512 x 4 x 2048 467 and 475).
+    const int64_t wgs = R * parts;
+    if constexpr (LIST) {
+        RALM_CM(4);
+    } else {
+        if (wgs >= 256 && (parts > 1 || (R > 256 && R < 512))) RALM_CM(4);
+        else if (nc % 8 == 0) RALM_CM(8);
+        else if (nc % 6 == 0) RALM_CM(6);
+        else RALM_CM(4);
+    }
 #undef RALM_CM
     return hipGetLastError();
 }
