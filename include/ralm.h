@@ -395,6 +395,19 @@ ralm_status ralm_cache_lookup_topk(const int32_t *cache_ids, const int32_t *cach
                                    float *out_scores, void *workspace, size_t workspace_bytes, void *stream);
 
 /*
+ * How a cache lookup with these arguments is launched.  k = 0: ralm_cache_lookup_all
+ * with a workspace; k > 0: ralm_cache_lookup_topk.  workgroups: per request
+ * (0: the rows go through the re-score of a retrieval instead).  pieces: 16-byte
+ * pieces of a row that a lane of the matrix-core form has in flight (0: the vector
+ * units read the rows).  clears: 1 if a launch of its own clears merge slots or
+ * answers the queries that no request owns (0 for k > 0).  All three are HOST
+ * pointers; nothing is launched or read (of the datastore's pointers only the
+ * alignment counts), and no GPU is needed.  A diagnostic.
+ */
+ralm_status ralm_lookup_route(int64_t R, int64_t Qt, int32_t C, const ralm_datastore_t *ds, int32_t k,
+                              int32_t *workgroups, int32_t *pieces, int32_t *clears);
+
+/*
  * Verification compare (Alg. 1: m = argmin_i d^_i != d_i).  For request r with
  * stride s_r = q_offsets[r+1] - q_offsets[r]:
  *   first_mismatch[r] = min { i in [0, s_r) : spec_ids[q_offsets[r] + i] !=

@@ -79,6 +79,7 @@ def lib() -> ctypes.CDLL:
         L.ralm_cache_lookup_topk.argtypes = [vp, vp, i32, i64, vp, i64, vp, dsp, i32, vp, vp, vp, ctypes.c_size_t, vp]
         L.ralm_cache_lookup_topk_workspace_bytes.argtypes = [i64, i32]
         L.ralm_cache_lookup_topk_workspace_bytes.restype = ctypes.c_size_t
+        L.ralm_lookup_route.argtypes = [i64, i64, i32, dsp, i32, ctypes.POINTER(i32), ctypes.POINTER(i32), ctypes.POINTER(i32)]
         L.ralm_verify.argtypes = [vp, vp, i64, i64, vp, i64, vp, vp]
         L.ralm_cache_insert.argtypes = [vp, vp, vp, i32, i64, vp, i64, i64, vp, vp, i32, i32, i64, vp]
         L.ralm_knnlm_probs.argtypes = [vp, vp, i64, i32, vp, i64, ctypes.c_float, vp, vp, vp, vp, vp]
@@ -103,7 +104,7 @@ def lib() -> ctypes.CDLL:
                      "ralm_workspace_counters", "ralm_workspace_stage_entries", "ralm_scan_routes",
                      "ralm_build_scan_copy", "ralm_build_scan_copy_l2", "ralm_cache_lookup", "ralm_cache_lookup_all",
                      "ralm_cache_lookup_static",
-                     "ralm_cache_lookup_topk", "ralm_verify", "ralm_cache_insert", "ralm_knnlm_probs",
+                     "ralm_cache_lookup_topk", "ralm_lookup_route", "ralm_verify", "ralm_cache_insert", "ralm_knnlm_probs",
                      "ralm_profile_scan_ms"):
             getattr(L, name).restype = ctypes.c_int
         _lib = L
@@ -318,6 +319,14 @@ def ralm_cache_lookup_static(cache_ids: torch.Tensor, cache_len: torch.Tensor, q
                                           q_offsets.data_ptr(), ctypes.byref(ds.desc), spec_ids.data_ptr(),
                                           spec_scores.data_ptr(), _stream()))
     return spec_ids, spec_scores
+
+
+def ralm_lookup_route(R: int, Qt: int, C: int, ds: Datastore, k: int = 0) -> Tuple[int, int, bool]:
+    """(workgroups per request, pieces in flight, whether slots are cleared by a launch of its own) of ralm_cache_lookup
+    with a workspace and outputs of its own, or for k > 0 of ralm_cache_lookup_topk (host only)."""
+    w, p, c = ctypes.c_int32(0), ctypes.c_int32(0), ctypes.c_int32(0)
+    _check(lib().ralm_lookup_route(R, Qt, C, ctypes.byref(ds.desc), k, ctypes.byref(w), ctypes.byref(p), ctypes.byref(c)))
+    return int(w.value), int(p.value), bool(c.value)
 
 
 def ralm_cache_lookup_topk(cache_ids: torch.Tensor, cache_len: torch.Tensor, queries: torch.Tensor,

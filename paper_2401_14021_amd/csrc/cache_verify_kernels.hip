@@ -943,13 +943,26 @@ bool cache_mfma_fits(int32_t d)
     return d % (EX == DT_F32 ? 64 : 128) == 0 && nc >= 4 && (size_t)d * 32 <= 64 * 1024;
 }
 
+// 16-byte pieces of a row that a lane of the matrix-core form has in flight; LIST: see the kernels.
+// Four take half the registers, and two workgroups fit a CU: for lists (the k best of 32 requests x 8 queries x 2048 fp16
+// rows of 1024 51.1 and 49.4 us, 2 x 8 x 2048 31.3 and 30.1), for requests that are split and fill the chip (64 x 1024 entries of 768
+// 38.8 and 37.4, 300 x 4 x 2000 302 and 292), and where one workgroup to a CU would leave a second round of few (350 x 300 73 and
+// 66).  Fewer workgroups than CUs would pair up and leave others idle (100 x 1024 by 2 56.0 and 60.4), and full rounds of
+// whole requests are the better for long loads (256 x 4 x 1024 121 and 125, 512 x 4 x 2048 467 and 475).
+template <int EX, bool LIST>
+int lookup_pieces(int32_t d, int64_t R, int parts)
+{
+    const int nc = d / (EX == DT_F32 ? 16 : 32);
+    if (LIST || (R * parts >= 256 && (parts > 1 || (R > 256 && R < 512)))) return 4;
+    return nc % 8 == 0 ? 8 : (nc % 6 == 0 ? 6 : 4);
+}
+
 template <int EX, bool LIST>
 hipError_t launch_cache_mfma_form(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,
                              const float *queries, int64_t Qt, const int64_t *q_offsets, const void *exact,
                              int64_t ld, int64_t N, int32_t d, int32_t *spec_ids, float *spec_scores,
                              u64 *partial, int fill, u64 *list, uint32_t *list_len, int parts, hipStream_t stream)
 {
-    const int nc = d / (EX == DT_F32 ? 16 : 32);
     // a group of 4 queries takes d * 32 bytes of LDS; up to 64 KB, so that two requests share a CU
     int ng = (int)((64 * 1024) / ((size_t)d * 32));
     ng = ng > CM_MAX_GROUPS ? CM_MAX_GROUPS : ng;
@@ -968,19 +981,14 @@ hipError_t launch_cache_mfma_form(const int32_t *cache_ids, const int32_t *cache
                            cache_len, C, queries, Qt, q_offsets, exact, ld, N, d, ng, spec_ids, spec_scores,   \
                            partial, fill, list, list_len);                                                  \
     } while (0)
-    // Four pieces at a time take half the registers, and two workgroups fit a CU: for lists (the k best of 32 requests x 8 queries x 2048 fp16
-    // rows of 1024 51.1 and 49.4 us, 2 x 8 x 2048 31.3 and 30.1), for requests that are split and fill the chip (64 x 1024 entries of 768
-    // 38.8 and 37.4, 300 x 4 x 2000 302 and 292), and where one workgroup to a CU would leave a second round of few (350 x 300 73 and
-    // 66).  Fewer workgroups than CUs would pair up and leave others idle (100 x 1024 by 2 56.0 and 60.4), and full rounds of
-    // whole requests are the better for long loads (256 x 4 x 1024 121 and 125, 512 x 4 x 2048 467 and 475).
-    const int64_t wgs = R * parts;
     if constexpr (LIST) {
         RALM_CM(4);
     } else {
-        if (wgs >= 256 && (parts > 1 || (R > 256 && R < 512))) RALM_CM(4);
-        else if (nc % 8 == 0) RALM_CM(8);
-        else if (nc % 6 == 0) RALM_CM(6);
-        else RALM_CM(4);
+        switch (lookup_pieces<EX, LIST>(d, R, parts)) {
+            case 8: RALM_CM(8); break;
+            case 6: RALM_CM(6); break;
+            default: RALM_CM(4);
+        }
     }
 #undef RALM_CM
     return hipGetLastError();
@@ -1056,7 +1064,35 @@ int lookup_parts(int64_t R, int32_t C, int64_t row_bytes)
     return best;
 }
 
+// Workgroups per request of the list form: two workgroups per CU, or one where the request's queries, as doubles in LDS, leave no room
+// for two; each with rows for half a step of its waves (matrix cores: 8 waves of 16 rows) or a whole one (vector units: 8 or 4
+// waves of 4 rows).  With 64 rows each, 16 requests x 8 queries x 64 fp16 rows of 1024 by squared distance were four
+// steps one after the other: 43 us, now 20
+int list_parts(int64_t R, int32_t C, bool mfma, int32_t d)
+{
+    const int rows = mfma ? 64 : (d <= 768 ? 32 : 16), wgs = mfma || d <= 1024 ? 512 : 256;
+    const int64_t want = R < wgs ? wgs / R : 1, most = (C + rows - 1) / rows;
+    return (int)(want < most ? want : most);
+}
+
 constexpr int64_t FILL_MAX_R = 4096;   // ranges that a workgroup checks in passing
+
+LookupRoute lookup_route(int64_t R, int64_t Qt, int32_t C, int32_t exact_dtype, int32_t metric, int32_t d, bool scratch, bool every_row,
+                         bool list)
+{
+    const bool mfma = lookup_on_matrix_cores(exact_dtype, metric, d);
+    LookupRoute to{};
+    to.parts = list ? list_parts(R, C, mfma, d) : (scratch ? lookup_parts(R, C, (int64_t)d * (exact_dtype == DT_F16 ? 2 : 4)) : 1);
+    if (mfma) {
+        if (exact_dtype == DT_F16) to.pieces = list ? lookup_pieces<DT_F16, true>(d, R, to.parts) : lookup_pieces<DT_F16, false>(d, R, to.parts);
+        else to.pieces = list ? lookup_pieces<DT_F32, true>(d, R, to.parts) : lookup_pieces<DT_F32, false>(d, R, to.parts);
+    }
+    if (list) return to;
+    // Without merge slots to clear the lookup's first workgroup answers the queries that no request owns
+    to.fill = every_row && to.parts == 1 && R <= FILL_MAX_R;
+    to.init = (to.parts > 1 || (every_row && !to.fill)) && Qt > 0;
+    return to;
+}
 
 hipError_t launch_cache_lookup(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,
                                const float *queries, int64_t Qt, const int64_t *q_offsets,
@@ -1064,11 +1100,11 @@ hipError_t launch_cache_lookup(const int32_t *cache_ids, const int32_t *cache_le
                                int32_t metric, int32_t *spec_ids, float *spec_scores, bool every_row, u64 *partial,
                                hipStream_t stream)
 {
-    const int parts = partial && R > 0 ? lookup_parts(R, C, (int64_t)d * (exact_dtype == DT_F16 ? 2 : 4)) : 1;
-    if (parts == 1 || R <= 0) partial = nullptr;
-    // Without merge slots to clear the lookup's first workgroup answers the queries that no request owns
-    const bool fill = every_row && !partial && R > 0 && R <= FILL_MAX_R;
-    if ((partial || (every_row && !fill)) && Qt > 0) {
+    LookupRoute to{};
+    if (R > 0) to = lookup_route(R, Qt, C, exact_dtype, metric, d, partial != nullptr, every_row, false);
+    else to.init = every_row && Qt > 0;
+    if (to.parts <= 1) partial = nullptr;
+    if (to.init) {
         hipLaunchKernelGGL(lookup_init_kernel, dim3(grid_for(Qt > R ? Qt : R, 256)), dim3(256), 0, stream, partial, q_offsets,
                            R, spec_ids, spec_scores, every_row ? 1 : 0, Qt);
         const hipError_t e = hipGetLastError();
@@ -1076,7 +1112,7 @@ hipError_t launch_cache_lookup(const int32_t *cache_ids, const int32_t *cache_le
     }
     if (R <= 0) return hipSuccess;
     return launch_lookup(cache_ids, cache_len, C, R, queries, Qt, q_offsets, exact, exact_dtype, ld, N, d, metric, spec_ids,
-                         spec_scores, partial, fill ? 1 : 0, nullptr, nullptr, parts, stream);
+                         spec_scores, partial, to.fill ? 1 : 0, nullptr, nullptr, to.parts, stream);
 }
 
 // fp16 rows on the vector units are 8-byte pieces, with few of them in flight; that pays where a row serves several
@@ -1101,15 +1137,9 @@ hipError_t launch_cache_lookup_topk(const int32_t *cache_ids, const int32_t *cac
     hipError_t e = launch_fill_u32(list_len, 0u, Qt, stream);   // queries that no request owns have no entries
     if (e != hipSuccess) return e;
     if (R > 0) {
-        // two workgroups per CU, or one where the request's queries, as doubles in LDS, leave no room for two; each with
-        // rows for half a step of its waves (matrix cores: 8 waves of 16 rows) or a whole one (vector units: 8 or 4
-        // waves of 4 rows).  With 64 rows each, 16 requests x 8 queries x 64 fp16 rows of 1024 by squared distance were four
-        // steps one after the other: 43 us, now 20
-        const bool mfma = lookup_on_matrix_cores(exact_dtype, metric, d);
-        const int rows = mfma ? 64 : (d <= 768 ? 32 : 16), wgs = mfma || d <= 1024 ? 512 : 256;
-        const int64_t want = R < wgs ? wgs / R : 1, most = (C + rows - 1) / rows;
         e = launch_lookup(cache_ids, cache_len, C, R, queries, Qt, q_offsets, exact, exact_dtype, ld, N, d, metric, nullptr,
-                          nullptr, nullptr, 0, list, list_len, (int)(want < most ? want : most), stream);
+                          nullptr, nullptr, 0, list, list_len,
+                          lookup_route(R, Qt, C, exact_dtype, metric, d, true, false, true).parts, stream);
         if (e != hipSuccess) return e;
     }
     int c2 = 2;

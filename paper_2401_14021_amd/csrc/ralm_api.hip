@@ -741,6 +741,25 @@ ralm_status ralm_cache_lookup_all(const int32_t *cache_ids, const int32_t *cache
 
 }  // extern "C"
 
+extern "C" ralm_status ralm_lookup_route(int64_t R, int64_t Qt, int32_t C, const ralm_datastore_t *ds, int32_t k, int32_t *workgroups,
+                                         int32_t *pieces, int32_t *clears)
+{
+    if (!workgroups || !pieces || !clears) return fail(RALM_ERR_NULL, "workgroups/pieces/clears is NULL");
+    if (R < 1 || R > MAX_REQUESTS || C < 1 || (k > 0 && C > RALM_MAX_K_PRIME)) return fail(RALM_ERR_SHAPE, "R=%lld, C=%d out of range", (long long)R, C);
+    if (Qt < 0) return fail(RALM_ERR_RANGE, "Qt=%lld is negative", (long long)Qt);
+    if (k < 0 || k > C) return fail(RALM_ERR_K, "k=%d must be in [0, C]", k);
+    const ralm_status st = check_datastore(ds, false);
+    if (st != RALM_OK) return st;
+    *workgroups = *pieces = *clears = 0;
+    if (k > 0 && cache_topk_by_rescore(ds->exact_dtype, ds->metric, ds->d, R, Qt, C)) return RALM_OK;
+    if (ds->d > CACHE_LOOKUP_MAX_D) return fail(RALM_ERR_SHAPE, "cache lookup supports d <= 2048");
+    const LookupRoute to = lookup_route(R, Qt, C, ds->exact_dtype, ds->metric, ds->d, true, true, k > 0);
+    *workgroups = to.parts;
+    *pieces = to.pieces;
+    *clears = to.init ? 1 : 0;
+    return RALM_OK;
+}
+
 // Scratch of ralm_cache_lookup_static: one merge slot (8 bytes) per query, held by every GPU the
 // library runs on until the process ends.  In host code the array's name is only a stand-in for
 // the symbol; the device address is looked up once per device and used from then on.

@@ -136,6 +136,17 @@ hipError_t launch_exact_pass(const float *queries, int64_t Q, const void *exact,
                              const u64 *tau_exact, u64 *cand, uint32_t *cnt, uint32_t cap, int32_t *out_ids,
                              float *out_scores, int32_t *host_mark, int n_cu, hipStream_t stream);
 
+// How a cache lookup is launched (R > 0); scratch: the caller has given merge slots, every_row: see launch_cache_lookup,
+// list: the k best
+struct LookupRoute {
+    int parts;    // workgroups per request; more than one merge
+    int pieces;   // 16-byte pieces of a row that a lane has in flight; 0: the rows are read by the vector units
+    bool init;    // a launch before the lookup clears the merge slots or answers the queries that no request owns
+    bool fill;    // the lookup's first workgroup answers these queries
+};
+LookupRoute lookup_route(int64_t R, int64_t Qt, int32_t C, int32_t exact_dtype, int32_t metric, int32_t d, bool scratch, bool every_row,
+                         bool list);
+
 // every_row: queries that no request owns are answered with id -1 / score -inf
 hipError_t launch_cache_lookup(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,
                                const float *queries, int64_t Qt, const int64_t *q_offsets,

@@ -211,6 +211,36 @@ def test_scan_routes_with_compute_units_reserved(L):
         b.ralm_scan_reserve_cus(0)
 
 
+def _lookup(L, R, C, d, dtype=0, metric=0, Qt=None, k=0):
+    from paper_2401_14021_amd import binding as b
+    ds = _ds(b, d=d, exact_dtype=dtype, scan=None)
+    ds.metric = metric
+    out = [ctypes.c_int32(-1) for _ in range(3)]
+    assert L.ralm_lookup_route(R, R if Qt is None else Qt, C, ctypes.byref(ds), k, *map(ctypes.byref, out)) == 0
+    return tuple(v.value for v in out)
+
+
+def test_lookup_routes(L):
+    """(workgroups per request, pieces in flight, a launch that clears)"""
+    from paper_2401_14021_amd import binding as b
+    assert _lookup(L, 64, 1024, 768) == (4, 4, 1)
+    assert _lookup(L, 64, 64, 768) == (1, 8, 0)
+    assert _lookup(L, 600, 1024, 768) == (1, 8, 0)           # many requests are not split
+    assert _lookup(L, 5000, 64, 768)[2] == 1                 # ... and for more than 4096 a launch answers unowned queries
+    assert _lookup(L, 64, 1024, 776)[1] == 0                 # not a whole number of steps: vector units
+    assert _lookup(L, 64, 1024, 768, metric=1)[1] == 0
+    assert _lookup(L, 16, 1024, 768, k=10)[0] > 1
+    assert _lookup(L, 256, 2048, 1000, dtype=2, metric=1, k=10) == (0, 0, 0)   # the re-score ranks these
+    ds, n = _ds(b), [ctypes.c_int32(0) for _ in range(3)]
+    ref = list(map(ctypes.byref, n))
+    assert L.ralm_lookup_route(0, 1, 64, ctypes.byref(ds), 0, *ref) == 2
+    assert L.ralm_lookup_route(1, -1, 64, ctypes.byref(ds), 0, *ref) == 7
+    assert L.ralm_lookup_route(1, 1, 64, ctypes.byref(ds), 65, *ref) == 3
+    assert L.ralm_lookup_route(1, 1, 64, None, 0, *ref) == 1
+    assert L.ralm_lookup_route(1, 1, 64, ctypes.byref(ds), 0, ref[0], ref[1], None) == 1
+    assert L.ralm_lookup_route(1, 1, 64, ctypes.byref(_ds(b, d=4096)), 0, *ref) == 2
+
+
 def test_binding_refuses_to_run_without_the_library(monkeypatch):
     from paper_2401_14021_amd import binding
     monkeypatch.setattr(binding, "_lib", None)
