@@ -91,8 +91,9 @@ __device__ __forceinline__ bool ranges_in_order(const int64_t *__restrict__ off,
 }
 
 // What cache_lookup_kernel needs before its rows and after them, its first argument.  It is read again from the arguments at the
-// end: kept all the time it took scalar registers that the loop over the rows needs (512 requests x up to 8 queries x 4096 entries of 392
-// 861 -> 978 us).
+// end, and the request's range from LDS: kept all the time they took scalar registers that the loop over the rows needs (arguments: 512
+// requests x up to 8 queries x 4096 entries of 392 861 -> 978 us; range: 200 requests x 8 queries x 2048 entries of 600 286 -> 332, of 768 by
+// squared distance 410 -> 423).
 struct LookupEnd {
     const int64_t *q_offsets;
     int64_t R, Qt;
@@ -164,6 +165,7 @@ __global__ __launch_bounds__(NW * 64) void cache_lookup_kernel(
     const int part = blockIdx.y;
     int parts = gridDim.y;
     __shared__ int s_merge, s_fill;   // workgroups that merge (0: this one's bests are the answer); whether it answers the unowned
+    __shared__ int64_t s_lo, s_hi;    // the request's queries
     if (!LIST) {
         const bool in_order = !to.partial || ranges_in_order(to.q_offsets, to.R);
         if (!in_order) {
@@ -179,6 +181,10 @@ __global__ __launch_bounds__(NW * 64) void cache_lookup_kernel(
     const int sub = lane % CL_GS, slot = lane / CL_GS;
     int64_t q_lo, q_hi;
     clamp_range(to.q_offsets, r, to.Qt, q_lo, q_hi);
+    if (!LIST && threadIdx.x == 0) {
+        s_lo = q_lo;
+        s_hi = q_hi;
+    }
     int len = cache_len[r];
     len = len < 0 ? 0 : (len > C ? C : len);
     const int32_t *ids = cache_ids + r * (int64_t)C;
@@ -324,9 +330,9 @@ __global__ __launch_bounds__(NW * 64) void cache_lookup_kernel(
     }
     if (LIST) return;
     __syncthreads();
-    if (s_merge && q_lo < q_hi) {
+    if (s_merge && s_lo < s_hi) {
         const LookupEnd end = lookup_end();
-        merge_parts(end.partial, q_lo, q_hi, s_merge, end.ids, end.scores);
+        merge_parts(end.partial, s_lo, s_hi, s_merge, end.ids, end.scores);
     }
     if (s_fill) {
         const LookupEnd end = lookup_end();
