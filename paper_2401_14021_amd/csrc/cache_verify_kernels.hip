@@ -1044,25 +1044,26 @@ hipError_t launch_lookup(const int32_t *cache_ids, const int32_t *cache_len, int
 
 }  // namespace
 
-// Workgroups per request, at least 64 cached rows for each.  One holds a CU, so they run in rounds of 256: a round costs 7 us until rows
-// flow, and then its rows at what a CU takes alone (38 KB a us) or its share of the chip's 6000.  More than one needs slots cleared and a merge
-// (6 us).  What this finds is mostly one round that is as full as it can be, or about four of them where one
-// workgroup each would leave a last round of few.  us, one row of 768 fp32 per entry: 33 requests x 1024 entries by 8 (264
-// workgroups) 38.7, by 7 31.9; 100 x 1024 by 3 76.8, by 2 55.4; 70 x 2048 by 4 113.6, by 3 80.9; 300 x 1024 by 1 212, by 3 164; 1 x 128 by 2
-// 17.8, by 1 14.8, 1 x 256 by 4 17.7, by 1 25.1; 392 elements, 100 x 1024 by 3 44.0, by 2 33.3.
+// Workgroups per request, at most one for every 64 cached rows begun.  Up to 256 requests have one round at least that is as full as it
+// can be, of 256 workgroups on 256 CUs: 33 requests x 1024 fp32 rows of 768 by 8 (264 workgroups) 38.7 us, by 7 31.9; 100 x 1024 by 3 76.8, by 2
+// 55.4; 70 x 2048 by 4 113.6, by 3 80.9.  Fewer are never the better where the sums or the loads' latency take the time: 1 request x 8
+// queries x 256 fp16 rows of 392 by 1 35.3, by 4 15.6, 96 x 8 x 500 by 1 87.4, by 2 51.4, 8 x 1 x 129 of 1000 by squared distance by 1 33.7,
+// by 3 17.6.  Whether more rounds pay, a model of them says, a workgroup to a CU: a round costs 7 us until rows flow, and then its rows at what a
+// CU takes alone (38 KB a us) or its share of the chip's 6000; more than one workgroup needs slots cleared and a merge (6 us).
+// 300 x 1024 of 768 by 1 212, by 3 164.
 int lookup_parts(int64_t R, int32_t C, int64_t row_bytes)
 {
     if (R > SPLIT_MAX_R) return 1;
-    const int64_t most = (C + 63) / 64;
+    const int64_t most = (C + 63) / 64, round = R < 256 ? 256 / R : 1;
     const double bytes = (double)C * (double)row_bytes;
     int best = 1;
     double least = 0.0;
-    for (int p = 1; p <= 256 && p <= most; ++p) {
+    for (int p = (int)(round < most ? round : most); p <= 256 && p <= most; ++p) {
         const int64_t wgs = R * p, full = wgs / 256, rest = wgs % 256;
         const double per_cu = rest > 0 && 6000.0 / (double)rest < 38.0 ? 6000.0 / (double)rest : 38.0;
         const double us = 7.0 * (double)(full + (rest > 0)) + (p > 1 ? 6.0 : 0.0) +
                           bytes / p / 1000.0 * ((double)full * 256.0 / 6000.0 + (rest > 0 ? 1.0 / per_cu : 0.0));
-        if (p == 1 || us < least + 0.1) {   // (of equals the one with more workgroups)
+        if (least == 0.0 || us < least + 0.1) {   // (of equals the one with more workgroups)
             least = us;
             best = p;
         }

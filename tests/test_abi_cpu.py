@@ -231,6 +231,11 @@ def test_lookup_routes(L):
     assert _lookup(L, 64, 1024, 768, metric=1)[1] == 0
     assert _lookup(L, 16, 1024, 768, k=10)[0] > 1
     assert _lookup(L, 256, 2048, 1000, dtype=2, metric=1, k=10) == (0, 0, 0)   # the re-score ranks these
+    # up to 256 requests: one round of workgroups at least, also where rows are short or their sums are what takes the time
+    assert _lookup(L, 1, 256, 392, dtype=2)[0] == 4 and _lookup(L, 96, 500, 392, dtype=2)[0] == 2
+    assert _lookup(L, 8, 129, 1000, dtype=2, metric=1)[0] == 3 and _lookup(L, 33, 1024, 64)[0] == 7
+    assert _lookup(L, 127, 4096, 64)[0] == 2 and _lookup(L, 64, 300, 512, dtype=2)[0] == 4
+    assert _lookup(L, 33, 1024, 768)[0] == 7 and _lookup(L, 300, 1024, 768)[0] == 3 and _lookup(L, 200, 300, 768)[0] == 1
     ds, n = _ds(b), [ctypes.c_int32(0) for _ in range(3)]
     ref = list(map(ctypes.byref, n))
     assert L.ralm_lookup_route(0, 1, 64, ctypes.byref(ds), 0, *ref) == 2
