@@ -385,7 +385,11 @@ __global__ __launch_bounds__(CM_NW * 64) void cache_lookup_mfma_kernel(
     const int ro = ((lane >> 2) & 3) * 4 + (lane >> 4);   // row of the step whose score this lane receives
     const int jq = lane & 3;                              // ... against this query of a group
     const int32_t *ids = cache_ids + r * (int64_t)C;
-    const int blk_first = part * CM_NW + wave, blk_step = parts * CM_NW;
+    // Rows that are one step of the request's waves or less are dealt out to its workgroups in turn: one workgroup after the other, the rows of 16
+    // requests x 1024 entries by 16 went to the first eight (768 fp32 21.7 us, 17.6; 1 x 300 by 5 19.4, 13.5).  More are better off one after
+    // the other, where the last workgroups have a step less (257 x 1024 by 3 of 1024 fp16 in turn 149, 136).
+    const bool in_turn = C <= parts * (CM_NW * 16);
+    const int blk_first = in_turn ? wave * parts + part : part * CM_NW + wave, blk_step = parts * CM_NW;
     // What the first rows depend on, at once (a slot of the cache is there whether it is used or not): the ids of the rows
     // this lane feeds and receives in its wave's first step and in the next.  Its rows then travel while the queries are laid out; one
     // after the other, 64 requests x 1024 entries of 768 took 41.6 us, now 39.9; the k best of 32 x 8 x 2048 of 1024 fp16 61.6 and 51.1.
