@@ -387,8 +387,9 @@ __global__ __launch_bounds__(CM_NW * 64) void cache_lookup_mfma_kernel(
     const int32_t *ids = cache_ids + r * (int64_t)C;
     // Rows that are one step of the request's waves or less are dealt out to its workgroups in turn: one workgroup after the other, the rows of 16
     // requests x 1024 entries by 16 went to the first eight (768 fp32 21.7 us, 17.6; 1 x 300 by 5 19.4, 13.5).  More are better off one after
-    // the other, where the last workgroups have a step less (257 x 1024 by 3 of 1024 fp16 in turn 149, 136).
-    const bool in_turn = C <= parts * (CM_NW * 16);
+    // the other, where the last workgroups have a step less (257 x 1024 by 3 of 1024 fp16 in turn 149, 136), and so are more workgroups than
+    // CUs, where they make room for the next (the k best of 171 x 300 by 3 in turn 44.3, 37.6).
+    const bool in_turn = C <= parts * (CM_NW * 16) && gridDim.x * gridDim.y <= 256;
     const int blk_first = in_turn ? wave * parts + part : part * CM_NW + wave, blk_step = parts * CM_NW;
     // What the first rows depend on, at once (a slot of the cache is there whether it is used or not): the ids of the rows
     // this lane feeds and receives in its wave's first step and in the next.  Its rows then travel while the queries are laid out; one
