@@ -1056,9 +1056,12 @@ hipError_t launch_lookup(const int32_t *cache_ids, const int32_t *cache_len, int
 // by 3 17.6.  Whether more rounds pay, a model of them says, a workgroup to a CU: a round costs 7 us until rows flow, and then its rows at what a
 // CU takes alone (38 KB a us) or its share of the chip's 6000; more than one workgroup needs slots cleared and a merge (6 us).
 // 300 x 1024 of 768 by 1 212, by 3 164.
-int lookup_parts(int64_t R, int32_t C, int64_t row_bytes)
+// On the matrix cores few short rows are done before slots could be cleared: by 1 and by as many as can be, 33 requests x 300 fp32 rows
+// of 64 6.3, 7.8, 70 x 129 of 256 9.1, 10.1, 33 x 300 fp16 rows of 128 7.3, 8.1; but 33 x 1024 fp32 rows of 64 12.6, 8.2, 64 x 129 fp16 rows of 512
+// 12.6, 10.6.
+int lookup_parts(int64_t R, int32_t C, int32_t d, int64_t row_bytes, bool mfma)
 {
-    if (R > SPLIT_MAX_R) return 1;
+    if (R > SPLIT_MAX_R || (mfma && (int64_t)C * d <= 40000)) return 1;
     const int64_t most = (C + 63) / 64, round = R < 256 ? 256 / R : 1;
     const double bytes = (double)C * (double)row_bytes;
     int best = 1;
@@ -1094,7 +1097,7 @@ LookupRoute lookup_route(int64_t R, int64_t Qt, int32_t C, int32_t exact_dtype, 
 {
     const bool mfma = lookup_on_matrix_cores(exact_dtype, metric, d);
     LookupRoute to{};
-    to.parts = list ? list_parts(R, C, mfma, d) : (scratch ? lookup_parts(R, C, (int64_t)d * (exact_dtype == DT_F16 ? 2 : 4)) : 1);
+    to.parts = list ? list_parts(R, C, mfma, d) : (scratch ? lookup_parts(R, C, d, (int64_t)d * (exact_dtype == DT_F16 ? 2 : 4), mfma) : 1);
     if (mfma) {
         if (exact_dtype == DT_F16) to.pieces = list ? lookup_pieces<DT_F16, true>(d, R, to.parts) : lookup_pieces<DT_F16, false>(d, R, to.parts);
         else to.pieces = list ? lookup_pieces<DT_F32, true>(d, R, to.parts) : lookup_pieces<DT_F32, false>(d, R, to.parts);

@@ -236,6 +236,7 @@ def test_lookup_routes(L):
     assert _lookup(L, 8, 129, 1000, dtype=2, metric=1)[0] == 3 and _lookup(L, 33, 1024, 64)[0] == 7
     assert _lookup(L, 127, 4096, 64)[0] == 2 and _lookup(L, 64, 300, 512, dtype=2)[0] == 4
     assert _lookup(L, 33, 1024, 768)[0] == 7 and _lookup(L, 300, 1024, 768)[0] == 3 and _lookup(L, 200, 300, 768)[0] == 1
+    assert [_lookup(L, 33, C, 64)[0] for C in (129, 300, 625, 626)] == [1, 1, 1, 7] and _lookup(L, 33, 129, 72)[0] == 3   # few short rows
     ds, n = _ds(b), [ctypes.c_int32(0) for _ in range(3)]
     ref = list(map(ctypes.byref, n))
     assert L.ralm_lookup_route(0, 1, 64, ctypes.byref(ds), 0, *ref) == 2
