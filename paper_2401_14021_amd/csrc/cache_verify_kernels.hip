@@ -955,16 +955,17 @@ bool cache_mfma_fits(int32_t d)
 }
 
 // 16-byte pieces of a row that a lane of the matrix-core form has in flight; LIST: see the kernels.
-// Four take half the registers, and two workgroups fit a CU: for lists (the k best of 32 requests x 8 queries x 2048 fp16
-// rows of 1024 51.1 and 49.4 us, 2 x 8 x 2048 31.3 and 30.1), for requests that are split and fill the chip (64 x 1024 entries of 768
+// Four take half the registers, and two workgroups fit a CU: for requests that are split and fill the chip (64 x 1024 entries of 768
 // 38.8 and 37.4, 300 x 4 x 2000 302 and 292), and where one workgroup to a CU would leave a second round of few (350 x 300 73 and
 // 66).  Fewer workgroups than CUs would pair up and leave others idle (100 x 1024 by 2 56.0 and 60.4), and full rounds of
 // whole requests are the better for long loads (256 x 4 x 1024 121 and 125, 512 x 4 x 2048 467 and 475).
+// Lists: requests that are split into workgroups of one step of rows.  The k best, with the longest and with four: 16 requests x 8 queries x 2048
+// fp16 rows of 1024 35.3, 34.1, 33 x 8 x 1024 fp32 rows of 768 45.7, 42.9; more rows 128 x 4 x 2048 fp16 116, 122, 600 x 1 x 2048 531, 587.
 template <int EX, bool LIST>
-int lookup_pieces(int32_t d, int64_t R, int parts)
+int lookup_pieces(int32_t d, int64_t R, int32_t C, int parts)
 {
     const int nc = d / (EX == DT_F32 ? 16 : 32);
-    if (LIST || (R * parts >= 256 && (parts > 1 || (R > 256 && R < 512)))) return 4;
+    if (LIST ? parts > 1 && C <= parts * (CM_NW * 16) : (R * parts >= 256 && (parts > 1 || (R > 256 && R < 512)))) return 4;
     return nc % 8 == 0 ? 8 : (nc % 6 == 0 ? 6 : 4);
 }
 
@@ -992,14 +993,10 @@ hipError_t launch_cache_mfma_form(const int32_t *cache_ids, const int32_t *cache
                            cache_len, C, queries, Qt, q_offsets, exact, ld, N, d, ng, spec_ids, spec_scores,   \
                            partial, fill, list, list_len);                                                  \
     } while (0)
-    if constexpr (LIST) {
-        RALM_CM(4);
-    } else {
-        switch (lookup_pieces<EX, LIST>(d, R, parts)) {
-            case 8: RALM_CM(8); break;
-            case 6: RALM_CM(6); break;
-            default: RALM_CM(4);
-        }
+    switch (lookup_pieces<EX, LIST>(d, R, C, parts)) {
+        case 8: RALM_CM(8); break;
+        case 6: RALM_CM(6); break;
+        default: RALM_CM(4);
     }
 #undef RALM_CM
     return hipGetLastError();
@@ -1099,8 +1096,8 @@ LookupRoute lookup_route(int64_t R, int64_t Qt, int32_t C, int32_t exact_dtype, 
     LookupRoute to{};
     to.parts = list ? list_parts(R, C, mfma, d) : (scratch ? lookup_parts(R, C, d, (int64_t)d * (exact_dtype == DT_F16 ? 2 : 4), mfma) : 1);
     if (mfma) {
-        if (exact_dtype == DT_F16) to.pieces = list ? lookup_pieces<DT_F16, true>(d, R, to.parts) : lookup_pieces<DT_F16, false>(d, R, to.parts);
-        else to.pieces = list ? lookup_pieces<DT_F32, true>(d, R, to.parts) : lookup_pieces<DT_F32, false>(d, R, to.parts);
+        if (exact_dtype == DT_F16) to.pieces = list ? lookup_pieces<DT_F16, true>(d, R, C, to.parts) : lookup_pieces<DT_F16, false>(d, R, C, to.parts);
+        else to.pieces = list ? lookup_pieces<DT_F32, true>(d, R, C, to.parts) : lookup_pieces<DT_F32, false>(d, R, C, to.parts);
     }
     if (list) return to;
     // Without merge slots to clear the lookup's first workgroup answers the queries that no request owns

@@ -237,6 +237,9 @@ def test_lookup_routes(L):
     assert _lookup(L, 127, 4096, 64)[0] == 2 and _lookup(L, 64, 300, 512, dtype=2)[0] == 4
     assert _lookup(L, 33, 1024, 768)[0] == 7 and _lookup(L, 300, 1024, 768)[0] == 3 and _lookup(L, 200, 300, 768)[0] == 1
     assert [_lookup(L, 33, C, 64)[0] for C in (129, 300, 625, 626)] == [1, 1, 1, 7] and _lookup(L, 33, 129, 72)[0] == 3   # few short rows
+    # the k best: pieces as long as they can be unless a workgroup has one step of rows
+    assert [_lookup(L, R, 2048, 1024, dtype=2, k=64)[:2] for R in (16, 32, 33, 128, 600)] == [(32, 4), (16, 4), (15, 8), (4, 8), (1, 8)]
+    assert _lookup(L, 33, 1024, 768, k=64)[:2] == (15, 4) and _lookup(L, 256, 64, 192, k=5)[:2] == (1, 6)
     ds, n = _ds(b), [ctypes.c_int32(0) for _ in range(3)]
     ref = list(map(ctypes.byref, n))
     assert L.ralm_lookup_route(0, 1, 64, ctypes.byref(ds), 0, *ref) == 2
