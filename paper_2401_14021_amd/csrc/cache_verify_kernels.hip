@@ -1079,11 +1079,14 @@ int lookup_parts(int64_t R, int32_t C, int32_t d, int64_t row_bytes, bool mfma)
 // Workgroups per request of the list form: two workgroups per CU, or one where the request's queries, as doubles in LDS, leave no room
 // for two; each with rows for half a step of its waves (matrix cores: 8 waves of 16 rows) or a whole one (vector units: 8 or 4
 // waves of 4 rows).  With 64 rows each, 16 requests x 8 queries x 64 fp16 rows of 1024 by squared distance were four
-// steps one after the other: 43 us, now 20
+// steps one after the other: 43 us, now 20.  As many as run at once, unless they leave more than a fifth of the places empty; then one more:
+// by as many and by one more, 33 requests x 2048 fp16 rows of 1024 65.9, 69.6, 150 x 2048 136, 147, 400 x 1024 185, 189; 171 x 1024 105, 98, 200 x 1024
+// 99.8, 94.8, 257 x 2048 346, 270, 300 x 1024 181, 146.
 int list_parts(int64_t R, int32_t C, bool mfma, int32_t d)
 {
     const int rows = mfma ? 64 : (d <= 768 ? 32 : 16), wgs = mfma || d <= 1024 ? 512 : 256;
-    const int64_t want = R < wgs ? wgs / R : 1, most = (C + rows - 1) / rows;
+    const int64_t at_once = R < wgs ? wgs / R : 1, most = (C + rows - 1) / rows;
+    const int64_t want = R * at_once * 5 >= wgs * 4 ? at_once : at_once + 1;
     return (int)(want < most ? want : most);
 }
 

@@ -240,6 +240,9 @@ def test_lookup_routes(L):
     # the k best: pieces as long as they can be unless a workgroup has one step of rows
     assert [_lookup(L, R, 2048, 1024, dtype=2, k=64)[:2] for R in (16, 32, 33, 128, 600)] == [(32, 4), (16, 4), (15, 8), (4, 8), (1, 8)]
     assert _lookup(L, 33, 1024, 768, k=64)[:2] == (15, 4) and _lookup(L, 256, 64, 192, k=5)[:2] == (1, 6)
+    # ... and as many workgroups as run at once, or one more where they would leave more than a fifth of the places empty
+    assert [_lookup(L, R, 2048, 1024, dtype=2, k=64)[0] for R in (150, 171, 200, 205, 257, 300, 410, 511, 512, 600)] == [3, 3, 3, 2, 2, 2, 1, 1, 1, 1]
+    assert [_lookup(L, R, 2048, 392, k=64)[0] for R in (128, 171, 257, 400, 500)] == [4, 3, 2, 2, 1]
     ds, n = _ds(b), [ctypes.c_int32(0) for _ in range(3)]
     ref = list(map(ctypes.byref, n))
     assert L.ralm_lookup_route(0, 1, 64, ctypes.byref(ds), 0, *ref) == 2
