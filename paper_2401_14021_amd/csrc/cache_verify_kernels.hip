@@ -39,26 +39,36 @@ __device__ __forceinline__ void clamp_range(const int64_t *off, int64_t r, int64
     hi = hi < lo ? lo : (hi > Qt ? Qt : hi);
 }
 
-// Queries that no request owns get id -1 / score -inf; the NT threads of one workgroup.  They lie in front of the first range and
-// behind the last one; where the ranges are not in order (they should be) every one of these is looked for in all of them.
+// Queries that no request owns get id -1 / score -inf; the NT threads of one workgroup, for up to FILL_MAX_R requests and FILL_MAX_QT
+// queries.  If the ranges reach from the first query to the last all are owned, in whatever order they are.  Otherwise every range is marked in
+// a bit map in LDS (owned, of (Qt + 31) / 32 words).  More queries are answered by a launch over the whole chip: this workgroup took 157
+// us for 2^20 of which 4 are owned, the launch is 7.5, and no longer than this for 4096; ranges that are not in order (they should be),
+// each query looked for in all of them, 16 000 for 16384 queries and 4096 ranges.
+constexpr int64_t FILL_MAX_R = 4096, FILL_MAX_QT = 4096;
 template <int NT>
 __device__ __forceinline__ void answer_unowned(const int64_t *__restrict__ off, int64_t R, int64_t Qt, int32_t *__restrict__ ids,
-                                               float *__restrict__ scores)
+                                               float *__restrict__ scores, uint32_t *owned)
 {
     const int64_t first = off[0] < 0 ? 0 : (off[0] > Qt ? Qt : off[0]), end = off[R] < 0 ? 0 : (off[R] > Qt ? Qt : off[R]);
     if (first == 0 && end == Qt) return;
-    int sorted = 1;
-    for (int64_t r = threadIdx.x; r < R; r += NT) sorted &= off[r] <= off[r + 1] ? 1 : 0;
-    sorted = __syncthreads_and(sorted);
-    auto answer = [&](int64_t q) {
-        bool owned = false;
-        for (int64_t r = 0; !sorted && !owned && r < R; ++r) owned = off[r] <= q && q < off[r + 1];
-        if (owned) return;
+    __syncthreads();
+    const int n = (int)Qt;
+    for (int w = threadIdx.x; w * 32 < n; w += NT) owned[w] = 0u;
+    __syncthreads();
+    for (int64_t r = threadIdx.x; r < R; r += NT) {
+        int64_t lo, hi;
+        clamp_range(off, r, Qt, lo, hi);
+        for (int q = (int)lo; q < (int)hi; q = (q | 31) + 1) {   // a word at a time
+            const int to = (q | 31) < (int)hi ? 32 : (int)hi & 31;
+            atomicOr(owned + (q >> 5), (~0u << (q & 31)) & (to == 32 ? ~0u : (1u << to) - 1u));
+        }
+    }
+    __syncthreads();
+    for (int q = threadIdx.x; q < n; q += NT) {
+        if (owned[q >> 5] >> (q & 31) & 1u) continue;
         ids[q] = -1;
         scores[q] = -__builtin_inff();
-    };
-    for (int64_t q = threadIdx.x; q < first; q += NT) answer(q);
-    for (int64_t q = end + threadIdx.x; q < Qt; q += NT) answer(q);
+    }
 }
 
 // A lookup whose requests are split over several workgroups.  Their best keys meet in partial[query] by an atomic max; who is the last
@@ -336,7 +346,7 @@ __global__ __launch_bounds__(NW * 64) void cache_lookup_kernel(
     }
     if (s_fill) {
         const LookupEnd end = lookup_end();
-        answer_unowned<NW * 64>(end.q_offsets, end.R, end.Qt, end.ids, end.scores);
+        answer_unowned<NW * 64>(end.q_offsets, end.R, end.Qt, end.ids, end.scores, reinterpret_cast<uint32_t *>(smem));
     }
 }
 
@@ -553,7 +563,8 @@ __global__ __launch_bounds__(CM_NW * 64) void cache_lookup_mfma_kernel(
         }
     }
     if (!LIST && partial && q_lo < q_hi) merge_parts(partial, q_lo, q_hi, parts, spec_ids, spec_scores);
-    if (!LIST && fill && r == 0) answer_unowned<CM_NW * 64>(q_offsets, gridDim.x, Qt, spec_ids, spec_scores);
+    if (!LIST && fill && r == 0)
+        answer_unowned<CM_NW * 64>(q_offsets, gridDim.x, Qt, spec_ids, spec_scores, reinterpret_cast<uint32_t *>(smem));
 }
 
 __global__ __launch_bounds__(256) void verify_kernel(const int32_t *__restrict__ spec,
@@ -905,6 +916,7 @@ hipError_t launch_cache_ex_form(const int32_t *cache_ids, const int32_t *cache_l
     const int maxq = nch <= 12 ? 16 : 8;
     if (qgroup > maxq) qgroup = maxq;
     if (qgroup < 1) return hipErrorInvalidValue;
+    static_assert(64 * 8 >= FILL_MAX_QT / 8, "the bit map of answer_unowned fits the doubles of one query");
     // a lane keeps its NCH chunks in registers (as doubles, and the next rows' as floats), which
     // bounds the waves a block can hold
 #define RALM_CL(NCHV, NWV, MAXQV)                                                                           \
@@ -975,7 +987,7 @@ hipError_t launch_cache_mfma_form(const int32_t *cache_ids, const int32_t *cache
                              int64_t ld, int64_t N, int32_t d, int32_t *spec_ids, float *spec_scores,
                              u64 *partial, int fill, u64 *list, uint32_t *list_len, int parts, hipStream_t stream)
 {
-    // a group of 4 queries takes d * 32 bytes of LDS; up to 64 KB, so that two requests share a CU
+    // a group of 4 queries takes d * 32 bytes of LDS (2 KB at least, and a bit map of FILL_MAX_QT queries 512); up to 64 KB, so that two requests share a CU
     int ng = (int)((64 * 1024) / ((size_t)d * 32));
     ng = ng > CM_MAX_GROUPS ? CM_MAX_GROUPS : ng;
     const size_t smem = (size_t)ng * d * 32 + (size_t)4 * ng * sizeof(u64);
@@ -1090,8 +1102,6 @@ int list_parts(int64_t R, int32_t C, bool mfma, int32_t d)
     return (int)(want < most ? want : most);
 }
 
-constexpr int64_t FILL_MAX_R = 4096;   // ranges that a workgroup checks in passing
-
 LookupRoute lookup_route(int64_t R, int64_t Qt, int32_t C, int32_t exact_dtype, int32_t metric, int32_t d, bool scratch, bool every_row,
                          bool list)
 {
@@ -1104,7 +1114,7 @@ LookupRoute lookup_route(int64_t R, int64_t Qt, int32_t C, int32_t exact_dtype, 
     }
     if (list) return to;
     // Without merge slots to clear the lookup's first workgroup answers the queries that no request owns
-    to.fill = every_row && to.parts == 1 && R <= FILL_MAX_R;
+    to.fill = every_row && to.parts == 1 && R <= FILL_MAX_R && Qt <= FILL_MAX_QT;
     to.init = (to.parts > 1 || (every_row && !to.fill)) && Qt > 0;
     return to;
 }

@@ -243,6 +243,9 @@ def test_lookup_routes(L):
     # ... and as many workgroups as run at once, or one more where they would leave more than a fifth of the places empty
     assert [_lookup(L, R, 2048, 1024, dtype=2, k=64)[0] for R in (150, 171, 200, 205, 257, 300, 410, 511, 512, 600)] == [3, 3, 3, 2, 2, 2, 1, 1, 1, 1]
     assert [_lookup(L, R, 2048, 392, k=64)[0] for R in (128, 171, 257, 400, 500)] == [4, 3, 2, 2, 1]
+    # unowned queries: by the lookup's first workgroup up to 4096 requests and queries
+    assert [_lookup(L, 100, 64, 64, Qt=Qt)[2] for Qt in (107, 4096, 4097, 1 << 20)] == [0, 0, 1, 1]
+    assert [_lookup(L, R, 40, 64, Qt=4096)[2] for R in (4096, 4097)] == [0, 1]
     ds, n = _ds(b), [ctypes.c_int32(0) for _ in range(3)]
     ref = list(map(ctypes.byref, n))
     assert L.ralm_lookup_route(0, 1, 64, ctypes.byref(ds), 0, *ref) == 2
