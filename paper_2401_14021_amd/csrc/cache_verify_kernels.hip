@@ -970,14 +970,17 @@ bool cache_mfma_fits(int32_t d)
 // Four take half the registers, and two workgroups fit a CU: for requests that are split and fill the chip (64 x 1024 entries of 768
 // 38.8 and 37.4, 300 x 4 x 2000 302 and 292), and where one workgroup to a CU would leave a second round of few (350 x 300 73 and
 // 66).  Fewer workgroups than CUs would pair up and leave others idle (100 x 1024 by 2 56.0 and 60.4), and full rounds of
-// whole requests are the better for long loads (256 x 4 x 1024 121 and 125, 512 x 4 x 2048 467 and 475).
+// whole requests are the better for long loads (256 x 4 x 1024 121 and 125, 512 x 4 x 2048 467 and 475).  So are workgroups of many
+// elements, with the longest and with four: fp16 rows of 1024, 400 x 1 x 4096 whole 661, 723, 400 x 4 x 700 whole 124, 132, 64 x 1 x 4096 by 4 95.2, 101,
+// 300 x 4 x 300 whole 62.9, 62.9; fp32 rows of 768 450 x 4 x 2048 whole 427, 446, 300 x 1 x 4096 by 4 563, 555, 400 x 4 x 700 whole 149, 144, of 128 400 x 2 x 4096 whole 154, 134.
 // Lists: requests that are split into workgroups of one step of rows.  The k best, with the longest and with four: 16 requests x 8 queries x 2048
 // fp16 rows of 1024 35.3, 34.1, 33 x 8 x 1024 fp32 rows of 768 45.7, 42.9; more rows 128 x 4 x 2048 fp16 116, 122, 600 x 1 x 2048 531, 587.
 template <int EX, bool LIST>
 int lookup_pieces(int32_t d, int64_t R, int32_t C, int parts)
 {
     const int nc = d / (EX == DT_F32 ? 16 : 32);
-    if (LIST ? parts > 1 && C <= parts * (CM_NW * 16) : (R * parts >= 256 && (parts > 1 || (R > 256 && R < 512)))) return 4;
+    constexpr int FEW = EX == DT_F32 ? 1 << 20 : 1 << 19;   // elements of a workgroup's rows
+    if (LIST ? parts > 1 && C <= parts * (CM_NW * 16) : (R * parts >= 256 && (int64_t)C * d <= (int64_t)parts * FEW && (parts > 1 || (R > 256 && R < 512)))) return 4;
     return nc % 8 == 0 ? 8 : (nc % 6 == 0 ? 6 : 4);
 }
 

@@ -246,6 +246,10 @@ def test_lookup_routes(L):
     # unowned queries: by the lookup's first workgroup up to 4096 requests and queries
     assert [_lookup(L, 100, 64, 64, Qt=Qt)[2] for Qt in (107, 4096, 4097, 1 << 20)] == [0, 0, 1, 1]
     assert [_lookup(L, R, 40, 64, Qt=4096)[2] for R in (4096, 4097)] == [0, 1]
+    # the best one: four pieces where two workgroups to a unit pay, but not with many rows each
+    assert [_lookup(L, 400, C, 1024, dtype=2)[:2] for C in (300, 512, 700, 4096)] == [(1, 4), (1, 4), (1, 8), (1, 8)]
+    assert [_lookup(L, 64, C, 1024, dtype=2)[:2] for C in (1024, 2048, 4096)] == [(4, 4), (4, 4), (4, 8)]
+    assert [_lookup(L, 450, C, 768)[:2] for C in (700, 1024, 2048)] == [(1, 4), (1, 4), (1, 8)] and _lookup(L, 400, 4096, 256)[:2] == (1, 4) and _lookup(L, 200, 300, 768)[1] == 8
     ds, n = _ds(b), [ctypes.c_int32(0) for _ in range(3)]
     ref = list(map(ctypes.byref, n))
     assert L.ralm_lookup_route(0, 1, 64, ctypes.byref(ds), 0, *ref) == 2
