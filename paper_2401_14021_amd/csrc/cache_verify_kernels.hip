@@ -973,14 +973,14 @@ bool cache_mfma_fits(int32_t d)
 // whole requests are the better for long loads (256 x 4 x 1024 121 and 125, 512 x 4 x 2048 467 and 475).  So are workgroups of many
 // elements, with the longest and with four: fp16 rows of 1024, 400 x 1 x 4096 whole 661, 723, 400 x 4 x 700 whole 124, 132, 64 x 1 x 4096 by 4 95.2, 101,
 // 300 x 4 x 300 whole 62.9, 62.9; fp32 rows of 768 450 x 4 x 2048 whole 427, 446, 300 x 1 x 4096 by 4 563, 555, 400 x 4 x 700 whole 149, 144, of 128 400 x 2 x 4096 whole 154, 134.
-// Lists: requests that are split into workgroups of one step of rows.  The k best, with the longest and with four: 16 requests x 8 queries x 2048
-// fp16 rows of 1024 35.3, 34.1, 33 x 8 x 1024 fp32 rows of 768 45.7, 42.9; more rows 128 x 4 x 2048 fp16 116, 122, 600 x 1 x 2048 531, 587.
+// Lists: workgroups of one step of rows, of which there are at most two to a CU.  The k best, with the longest and with four: 16 requests x 8 queries x 2048
+// fp16 rows of 1024 35.3, 34.1, 33 x 8 x 1024 fp32 rows of 768 45.7, 42.9, 300 x 64 23.8, 21.0; more rows 128 x 4 x 2048 fp16 116, 122, 600 x 1 x 2048 531, 587.
 template <int EX, bool LIST>
 int lookup_pieces(int32_t d, int64_t R, int32_t C, int parts)
 {
     const int nc = d / (EX == DT_F32 ? 16 : 32);
     constexpr int FEW = EX == DT_F32 ? 1 << 20 : 1 << 19;   // elements of a workgroup's rows
-    if (LIST ? parts > 1 && C <= parts * (CM_NW * 16) : (R * parts >= 256 && (int64_t)C * d <= (int64_t)parts * FEW && (parts > 1 || (R > 256 && R < 512)))) return 4;
+    if (LIST ? (parts > 1 || (R > 256 && R <= 512)) && C <= parts * (CM_NW * 16) : (R * parts >= 256 && (int64_t)C * d <= (int64_t)parts * FEW && (parts > 1 || (R > 256 && R < 512)))) return 4;
     return nc % 8 == 0 ? 8 : (nc % 6 == 0 ? 6 : 4);
 }
 
@@ -1094,14 +1094,16 @@ int lookup_parts(int64_t R, int32_t C, int32_t d, int64_t row_bytes, bool mfma)
 // Workgroups per request of the list form: two workgroups per CU, or one where the request's queries, as doubles in LDS, leave no room
 // for two; each with rows for half a step of its waves (matrix cores: 8 waves of 16 rows) or a whole one (vector units: 8 or 4
 // waves of 4 rows).  With 64 rows each, 16 requests x 8 queries x 64 fp16 rows of 1024 by squared distance were four
-// steps one after the other: 43 us, now 20.  As many as run at once, unless they leave more than a fifth of the places empty; then one more:
+// steps one after the other: 43 us, now 20.  As many as run at once.  Of two to a CU, where they leave more than a fifth of the places empty (a
+// quarter if that is one per request), one more:
 // by as many and by one more, 33 requests x 2048 fp16 rows of 1024 65.9, 69.6, 150 x 2048 136, 147, 400 x 1024 185, 189; 171 x 1024 105, 98, 200 x 1024
-// 99.8, 94.8, 257 x 2048 346, 270, 300 x 1024 181, 146.
+// 99.8, 94.8, 257 x 2048 346, 270, 300 x 1024 181, 146; one to a CU, 100 x 1024 of 1200 by squared distance 347, 450.
 int list_parts(int64_t R, int32_t C, bool mfma, int32_t d)
 {
     const int rows = mfma ? 64 : (d <= 768 ? 32 : 16), wgs = mfma || d <= 1024 ? 512 : 256;
     const int64_t at_once = R < wgs ? wgs / R : 1, most = (C + rows - 1) / rows;
-    const int64_t want = R * at_once * 5 >= wgs * 4 ? at_once : at_once + 1;
+    const bool full = wgs == 256 || R * 4 >= wgs * 3 || R * at_once * 5 >= wgs * 4;
+    const int64_t want = full ? at_once : at_once + 1;
     return (int)(want < most ? want : most);
 }
 

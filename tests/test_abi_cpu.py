@@ -240,9 +240,11 @@ def test_lookup_routes(L):
     # the k best: pieces as long as they can be unless a workgroup has one step of rows
     assert [_lookup(L, R, 2048, 1024, dtype=2, k=64)[:2] for R in (16, 32, 33, 128, 600)] == [(32, 4), (16, 4), (15, 8), (4, 8), (1, 8)]
     assert _lookup(L, 33, 1024, 768, k=64)[:2] == (15, 4) and _lookup(L, 256, 64, 192, k=5)[:2] == (1, 6)
-    # ... and as many workgroups as run at once, or one more where they would leave more than a fifth of the places empty
+    assert [_lookup(L, R, 64, 768, k=5)[:2] for R in (256, 257, 512, 513)] == [(1, 8), (1, 4), (1, 4), (1, 8)]
+    # ... and as many workgroups as run at once, or one more where they would leave too many of the places empty
     assert [_lookup(L, R, 2048, 1024, dtype=2, k=64)[0] for R in (150, 171, 200, 205, 257, 300, 410, 511, 512, 600)] == [3, 3, 3, 2, 2, 2, 1, 1, 1, 1]
-    assert [_lookup(L, R, 2048, 392, k=64)[0] for R in (128, 171, 257, 400, 500)] == [4, 3, 2, 2, 1]
+    assert [_lookup(L, R, 2048, 392, k=64)[0] for R in (128, 171, 257, 383, 384, 500)] == [4, 3, 2, 2, 1, 1]
+    assert [_lookup(L, R, 1024, 1544, k=64)[0] for R in (20, 100, 150)] == [12, 2, 1]
     # unowned queries: by the lookup's first workgroup up to 4096 requests and queries
     assert [_lookup(L, 100, 64, 64, Qt=Qt)[2] for Qt in (107, 4096, 4097, 1 << 20)] == [0, 0, 1, 1]
     assert [_lookup(L, R, 40, 64, Qt=4096)[2] for R in (4096, 4097)] == [0, 1]
