@@ -199,6 +199,16 @@ def test_scan_routes_of_several_query_tiles(L, Q, N, d, want):
     assert _routes(L, Q, 10, N, d)[-1] == want
 
 
+@pytest.mark.parametrize("Q,N,d,want", [
+    (600, 1_000_000, 328, ["parked", "parked"]), (1100, 600_000, 392, ["parked", "parked"]), (1100, 1_000_000, 392, ["parked", "held"]),
+    (2304, 2_000_000, 328, ["parked", "held"]), (1500, 600_000, 456, ["parked", "parked"]), (1500, 4_000_000, 456, ["held", "held"]),
+    (450, 1_000_000, 392, ["held", "held"]), (600, 1_000_000, 520, ["held", "held"]),      # two tiles, longer rows: as ever
+])
+def test_scan_routes_of_short_rows_that_are_no_whole_lines(L, Q, N, d, want):
+    """Several query tiles: the two last stages."""
+    assert _routes(L, Q, 10, N, d)[-2:] == want
+
+
 def test_scan_routes_with_compute_units_reserved(L):
     from paper_2401_14021_amd import binding as b
     try:
