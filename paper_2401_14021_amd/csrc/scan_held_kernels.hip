@@ -417,10 +417,11 @@ bool scan_held_takes(const ScanParams &p, int n_cu)
         const int64_t columns = nqt * bn;
         if (bn == 128 ? nqt > 4 : (nqt > 8 && p.Q * 20 < columns * 19)) return false;
         if (!(nqt == 2 && !whole_lines(p)) && p.Q * 4 < columns * 3) return false;
-        // Of up to 512 elements, which are no whole lines: stages that admit as few scores as those of whole lines may, and not below 100 000 strips.
-        // Over 1M x 392 600 queries 743, 754, with these limits 734, 1100 1193, 1244, 1193, 4352 4176, 4215, 4176; over 1M x 328 600 669, 707,
-        // 1100 1078, 1160, in tiles; over 2M x 328 1100 1873, 1939, 1868; 1500 over 600 000 x 456 1134, 1168; 1500 over 4M x 456 5547, 5059, 5057.
-        if (nqt > 2 && kt <= 8 && (p.admits * bn > 4 * n_tiles || n_tiles * kt < 100000)) return false;
+        // Of up to 512 elements, which are no whole lines, admitted scores (below) interrupt few multiplies: a tile may admit a score for every six
+        // strips.  With all stages that the limit below lets through, and with this one (k' = 64; the last stage of 1M rows admits 1.05 a
+        // tile): 600 queries over 1M x 392 743, 754, 734, 1100 1193, 1244, 1193; over 1M x 328 600 669, 707, in tiles, 1100 1078, 1160, in tiles;
+        // 1100 over 2M x 328 1873, 1939, 1868; 1500 over 600 000 x 456 1134, 1168, in tiles; 1500 over 4M x 456 5547, 5059, 5057.
+        if (nqt > 2 && kt <= 8 && p.admits * bn * 6 > kt * n_tiles) return false;
     }
     // several query tiles share the stream of rows, and short rows are few multiplies between two rendezvous: 1000 queries
     // over 2M x 384 1520, 1567, 512 over 2M x 512 1047, 1042.  Rows that are no whole lines cost the tiled kernel more: 512 over

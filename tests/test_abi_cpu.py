@@ -207,6 +207,8 @@ def test_scan_routes_of_several_query_tiles(L, Q, N, d, want):
 def test_scan_routes_of_short_rows_that_are_no_whole_lines(L, Q, N, d, want):
     """Several query tiles: the two last stages."""
     assert _routes(L, Q, 10, N, d)[-2:] == want
+    if want[-1] == "held":
+        assert _routes(L, Q, 10, N, d, k_prime=4096)[-1] != "held"       # many candidates, many admitted scores
 
 
 def test_scan_routes_with_compute_units_reserved(L):
