@@ -87,10 +87,10 @@ def test_several_query_tiles(rows, oracle, d, Q, last):
     _check(rows, oracle, d, Q, torch.bfloat16, last=last)
 
 
-@pytest.mark.parametrize("d,Q", [(392, 1700), (768, 1792)])
+@pytest.mark.parametrize("d,Q", [(392, 1700), (768, 1792), (520, 2304), (520, 8448)])
 def test_more_workgroups_than_compute_units(d, Q):
-    """Seven query tiles do not share out over an XCD's 32 compute units: the launch has a second round of workgroups, which begin as
-    the first ones end, in the LDS that those leave."""
+    """Seven and nine query tiles do not share out over an XCD's 32 compute units, and 33 are more than it has: the launch has a
+    second round of workgroups or more, which begin as the first ones end, in the LDS that those leave."""
     from paper_2401_14021_amd import binding as B
     n = 2 ** 19 - 1
     g = torch.Generator().manual_seed(d)

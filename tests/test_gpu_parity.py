@@ -1142,8 +1142,8 @@ def test_a_verification_round_replays_from_a_hip_graph(B, oracle):
 @pytest.mark.parametrize("R,C,smax,d", [(1, 4096, 1, 768), (1, 64, 5, 768), (2, 1024, 4, 768), (7, 300, 8, 136),
                                         (40, 2000, 3, 64), (127, 128, 2, 256), (128, 512, 2, 64)])
 def test_cache_lookup_split_over_workgroups_equals_one_per_request(B, oracle, R, C, smax, d):
-    """With a workspace and fewer than 128 requests each cache is searched by several workgroups;
-    ragged cache lengths, empty caches and requests without queries included."""
+    """With a workspace a cache may be searched by several workgroups (here all but the 64 rows of one request and the
+    few short rows of 127 and 128 requests); ragged cache lengths, empty caches and requests without queries included."""
     from paper_2401_14021_amd import inputs
     N = 30000
     rng = np.random.default_rng(R * 7 + C)
@@ -1210,7 +1210,7 @@ def _random_lookup_shapes(n, seed):
 @pytest.mark.parametrize("d,R,C,smax,f16", _random_lookup_shapes(24, seed=77))
 def test_cache_lookup_random_shapes(B, oracle, d, R, C, smax, f16):
     """Seeded random shapes of the lookup around its block sizes (16 cached rows per matrix-core
-    step, 4 and 8 queries per pass, one workgroup or several per request), fp32 and fp16 rows,
+    step, 4 and 8 queries per pass; nearly always one workgroup per request), fp32 and fp16 rows,
     integer-valued (every sum exact: ids and scores bit for bit, ties by id) and real-valued."""
     from paper_2401_14021_amd import inputs
     N = 3000
