@@ -139,7 +139,7 @@ typedef struct {
 ralm_status ralm_retrieve_topk(const float *queries, int64_t Q, const float *datastore, int64_t N,
                                int32_t d, int32_t k, int32_t *out_ids, float *out_scores);
 
-/* Frees the device buffers that ralm_retrieve_topk keeps between calls (synchronises). */
+/* Frees the device buffers, and the word of pinned host memory, that ralm_retrieve_topk keeps between calls (synchronises). */
 void ralm_release_buffers(void);
 
 /* Bytes of workspace ralm_retrieve_topk_ex needs for (Q, ds, k, k_prime); 0 on bad arguments. */
@@ -335,7 +335,7 @@ ralm_status ralm_build_scan_copy_l2(const void *src, int32_t src_dtype, int64_t 
  *              cached rows then takes ~0.4 ms); with it the caches of up to
  *              512 requests are each split over several workgroups, where that
  *              fills the chip better, that merge through the workspace and the
- *              outputs (same results).
+ *              outputs (same results; ralm_lookup_route tells how many).
  */
 size_t ralm_cache_lookup_workspace_bytes(int64_t Qt);
 ralm_status ralm_cache_lookup(const int32_t *cache_ids, const int32_t *cache_len, int32_t C, int64_t R,

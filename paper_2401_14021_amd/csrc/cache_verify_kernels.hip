@@ -42,7 +42,7 @@ __device__ __forceinline__ void clamp_range(const int64_t *off, int64_t r, int64
 // Queries that no request owns get id -1 / score -inf; the NT threads of one workgroup, for up to FILL_MAX_R requests and FILL_MAX_QT
 // queries.  If the ranges reach from the first query to the last all are owned, in whatever order they are.  Otherwise every range is marked in
 // a bit map in LDS (owned, of (Qt + 31) / 32 words).  More queries are answered by a launch over the whole chip: this workgroup took 157
-// us for 2^20 of which 4 are owned, the launch is 7.5, and no longer than this for 4096; ranges that are not in order (they should be),
+// us for 2^20 of which 4 are owned, with the launch 7.5 (for 4096 5.2 and 5.9); ranges that are not in order (they should be),
 // each query looked for in all of them, 16 000 for 16384 queries and 4096 ranges.
 constexpr int64_t FILL_MAX_R = 4096, FILL_MAX_QT = 4096;
 template <int NT>
@@ -73,8 +73,12 @@ __device__ __forceinline__ void answer_unowned(const int64_t *__restrict__ off, 
 
 // A lookup whose requests are split over several workgroups.  Their best keys meet in partial[query] by an atomic max; who is the last
 // of a request to have sent its own decodes them.  The arrivals are counted in the request's first answer, which holds -1 before.
-// In a launch of its own the decoding cost 4 us on the GPU and 2.5 us on the host.
-constexpr int64_t SPLIT_MAX_R = 512;   // more requests are not split
+// In a launch of its own the decoding cost 4 us on the GPU and 2.5 us on the host.  Where a few requests have 32 or 64 workgroups each, their
+// arrivals one after the other take longer than that launch replayed from a graph (4 x 4 x 4096 entries of 392 14.4 us, 13.5; as ordinary calls 16.1, 17.7).
+// The order of maximum, count and decoding rests on gfx950 and not on the memory model, whose release and acquire write back and
+// invalidate a whole L2 (+3 us with 256 workgroups): the words are touched by agent-scope atomics alone, which are carried out at memory for all
+// XCDs; a wave waits for its own with vmcnt, the barrier joins the waves, and only then is the arrival sent.
+constexpr int64_t SPLIT_MAX_R = 512;   // more requests are not split: every wave reads all offsets, 64 at a time; not measured beyond
 __device__ __forceinline__ void merge_parts(const u64 *__restrict__ partial, int64_t q_lo, int64_t q_hi, int parts, int32_t *ids,
                                             float *scores)
 {
@@ -396,14 +400,14 @@ __global__ __launch_bounds__(CM_NW * 64) void cache_lookup_mfma_kernel(
     const int jq = lane & 3;                              // ... against this query of a group
     const int32_t *ids = cache_ids + r * (int64_t)C;
     // Rows that are one step of the request's waves or less are dealt out to its workgroups in turn: one workgroup after the other, the rows of 16
-    // requests x 1024 entries by 16 went to the first eight (768 fp32 21.7 us, 17.6; 1 x 300 by 5 19.4, 13.5).  More are better off one after
+    // requests x 1024 entries by 16 went to the first eight (768 fp32 19.1 us, 17.9; 1 x 300 by 5 18.3, 13.5).  More are better off one after
     // the other, where the last workgroups have a step less (257 x 1024 by 3 of 1024 fp16 in turn 149, 136), and so are more workgroups than
     // CUs, where they make room for the next (the k best of 171 x 300 by 3 in turn 44.3, 37.6).
     const bool in_turn = C <= parts * (CM_NW * 16) && gridDim.x * gridDim.y <= 256;
     const int blk_first = in_turn ? wave * parts + part : part * CM_NW + wave, blk_step = parts * CM_NW;
-    // What the first rows depend on, at once (a slot of the cache is there whether it is used or not): the ids of the rows
-    // this lane feeds and receives in its wave's first step and in the next.  Its rows then travel while the queries are laid out; one
-    // after the other, 64 requests x 1024 entries of 768 took 41.6 us, now 39.9; the k best of 32 x 8 x 2048 of 1024 fp16 61.6 and 51.1.
+    // What the first rows depend on, at once (a slot of the cache is there whether it is used or not; a split request has read all offsets
+    // before): the ids of the rows this lane feeds and receives in its wave's first step and in the next.  Its rows then travel while
+    // the queries are laid out; one after the other, 64 requests x 1024 entries of 768 took 41.6 us, now 39.9; the k best of 32 x 8 x 2048 of 1024 fp16 61.6 and 51.1.
     auto slot_at = [&](int e) { return e < C ? ids[e] : -1; };
     const int32_t feed_0 = slot_at(blk_first * 16 + r16), out_0 = slot_at(blk_first * 16 + ro);
     const int32_t feed_1 = slot_at((blk_first + blk_step) * 16 + r16), out_1 = slot_at((blk_first + blk_step) * 16 + ro);

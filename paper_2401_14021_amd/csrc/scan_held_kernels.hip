@@ -406,13 +406,20 @@ bool scan_held_takes(const ScanParams &p, int n_cu)
     const int64_t streams = held_streams(p, n_cu);
     if (streams < 1) return false;   // (nearly all CUs reserved, or more query tiles than 16 rounds hold)
     if (nqt > 1 && !(nqt == 2 && bn == 128) && p.Q * (per_xcd / nqt) * 20 < per_xcd * bn * 19) {
-        // Otherwise if a quarter of the columns is idle at most, over 4M x 768: 300 queries 2484, 2474, 400 2704, 2656, 450 2864, 2685, 550
-        // 3634, 3654, 600 3759, 3713, 700 3857, 3737, 850 4998, 4880, 1100 6238, 6148, 1280 6448, 6270, 1792 8927, 8628; over 1M x 700 queries
-        // 1126, 1125.  Two tiles over rows that are no whole lines at any size: 300 over 1M x 648 760, 690, over 1M x 392 533, 514.
-        // More than eight tiles only if a twentieth of the columns is idle: 2304 11 505, 11 195 (on the safe side: 2341, whose last tile
-        // is nearly empty, 12 290, 12 010).  Tiles of 128 up to four: 300 over 1M x 1000 1120, 894, 500 over 1M x 904 1117,
-        // 1096, but 700 1498, 1549 and 1200 2430, 2530.  Below 64 tiles of rows for a workgroup there is nothing in it: 600 over 500 000
-        // x 768 624, 624, 390 over 300 000 336, 336, 768 481, 486.
+        // Otherwise if a quarter of the columns is idle at most.  Queries and both times, each line on one card and in turn:
+        // over 4M x 768    300: 2484, 2474   400: 2704, 2656   450: 2864, 2685   550: 3634, 3654   600: 3759, 3713
+        //                  700: 3857, 3737   850: 4998, 4880   1100: 6238, 6148   1280: 6448, 6270   1792: 8927, 8628
+        // over 1M x 768    400: 780, 746   600: 1058, 1044   768: 1157, 1124   1100: 1726, 1698   1500: 2162, 2099
+        // over 500 000 x 768   600: 607, 599   850: 776, 755   1500: 1204, 1196   3000: 2352, 2315
+        // Two tiles over rows that are no whole lines at any size: 300 over 1M x 648 755, 657, over 4M x 392 1634, 1515, over 1M x 392 544, 548.
+        // More than eight tiles only if a twentieth of the columns is idle at most.  That gives away 2341, whose last tile is nearly empty: 12 290,
+        // 12 010 over 4M x 768.
+        // over 4M x 768    2304: 11 505, 11 195   4352: 22 991, 21 634   8448: 47 471, 42 647
+        // over 1M x 768    2304: 3435, 3378   8192: 12 427, 12 378   16 384: 25 658, 24 325   65 536: 104 091, 96 386   131 072: 208 373, 192 334
+        // Beyond 32 tiles an XCD holds only some of a stream's at a time, and the later ones read its rows again: 8448 queries fetch 3.0 times the
+        // rows' bytes from HBM (2304 1.18, 1280 1.13, 1024 1.00), the tiled kernel 34 times.
+        // Tiles of 128 up to four: 300 over 1M x 1000 1120, 894, 500 over 1M x 904 1117, 1096, but 700 1498, 1549 and 1200 2430, 2530.
+        // Below 64 tiles of rows for a workgroup there is little in it: 390 over 300 000 x 768 336, 336, 768 481, 486.
         if (p.one_per_cu || n_tiles < 512 * streams) return false;
         const int64_t columns = nqt * bn;
         if (bn == 128 ? nqt > 4 : (nqt > 8 && p.Q * 20 < columns * 19)) return false;

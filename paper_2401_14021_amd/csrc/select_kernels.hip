@@ -963,14 +963,14 @@ hipError_t launch_rescore(const u64 *cand, const uint32_t *cnt, int cnt_pitch, u
         hipLaunchKernelGGL(kern, dim3((unsigned)Q), dim3(NTV), smem, stream, cand, cnt, \
                        cnt_pitch, cap, k_prime, kp2, queries, exact, ld, d, k, out_ids, out_scores, out_margin, cert);                     \
     } while (0)
-    // With more queries than two large workgroups per CU hold, small ones (eight per CU) overlap one query's
-    // chain of list, rows and ranking with the others' gathers: 1024 queries, k' = 64: 50 us instead of 91,
-    // 2341: 96 instead of 200.  Fewer queries, or many candidates each, need the large workgroup's waves; so do long
+    // A CU holds one large workgroup or eight small ones, which overlap one query's chain of list, rows and ranking with
+    // the others' gathers.  From two rounds of large ones on small ones are the better, 1024 queries, k' = 64: 50 us instead of 91,
+    // 2341: 96 instead of 200; with few candidates already where the second round is nearly empty, whole calls with small and large ones:
+    // 300 over 200 000 x 768 251 and 255, 500 284 and 289, 300 over 30 000 97 and 103, but 256 152 and 151, and 300 with k' = 256 361 and 357.
+    // Fewer queries, or many candidates each, need the large workgroup's waves; so do long
     // lists, of which a small one holds only 4096 keys in registers (the one stage of a small datastore).  Whole calls
-    // with small and large ones, us: 512 queries over 16384 rows of 64, k = 5, 134 and 67, over 8000 rows 86 and 62, 1024
-    // over 8000 101 and 89, 3000 over 16384 451 and 353, over 8000 227 and 233, k = 100 364 and 410.  Of large ones a CU holds one, so
-    // between 257 and 511 queries a second round is nearly empty: 300 over 200 000 x 768 251 and 255, 500 284 and 289, 300 over 30 000 97 and
-    // 103, but 256 152 and 151, and k' = 256 361 and 357.
+    // with small and large ones: 512 queries over 16384 rows of 64, k = 5, 134 and 67, over 8000 rows 86 and 62, 1024
+    // over 8000 101 and 89, 3000 over 16384 451 and 353, over 8000 227 and 233, k = 100 364 and 410.
     const bool short_lists = expected <= SEL_REGS * 256 || (expected <= SEL_REGS * 512 && Q >= 2048);
 #define RALM_RS(EXV, L2V)                                  \
     do {                                                   \
