@@ -1065,6 +1065,19 @@ hipError_t launch_lookup(const int32_t *cache_ids, const int32_t *cache_len, int
 
 }  // namespace
 
+// Few cached rows are done whole about when the slots of a split request are cleared, in one launch instead of two.  On the matrix
+// cores by their elements, in steps of 128 rows, GPU time and time in a stream of calls, by 1 and by as many as can be, one request x 4 queries: one step, fp32 rows of 640
+// 13.2, 12.6 and 13.4, 14.5, fp16 rows of 1024 15.0, 14.8 and 15.1, 14.9; two, 129 fp32 rows of 512 13.7, 11.0 and 14.1, 14.7, of 640 16.4, 11.8 and 16.5,
+// 14.6, 160 fp16 rows of 512 12.6, 10.6 and 12.9, 14.7; more, 33 x 1 x 300 fp32 rows of 64 6.3, 7.8, 384 of 128 9.5, 7.6 and 12.1, 14.7.  On the vector units, fp32
+// rows and few queries: 16 x 1 x 160 of 392 10.0, 9.7 and 12.1, 14.7, 1 x 4 x 100 11.0, 11.3 and 11.9, 14.5; 8 x 8 x 129 19.0, 14.4 and 19.3, 14.6.
+// The lines lie where the GPU time of a whole request is that of the three launches which a split one once took (384 of 128 9.0).
+bool done_whole(int64_t R, int64_t Qt, int32_t C, int32_t exact_dtype, int32_t metric, int32_t d, bool mfma)
+{
+    const bool f16 = exact_dtype == DT_F16;
+    if (mfma) return (int64_t)C * d <= (C > 256 ? 40000 : (C > 128 ? (f16 ? 81920 : 65536) : (f16 ? 131072 : 81920)));
+    return !f16 && metric == METRIC_IP && d <= 768 && (C <= 128 ? Qt <= 4 * R : C <= 160 && Qt <= R);
+}
+
 // Workgroups per request, at most one for every 64 cached rows begun.  Up to 256 requests have one round at least that is as full as it
 // can be, of 256 workgroups on 256 CUs: 33 requests x 1024 fp32 rows of 768 by 8 (264 workgroups) 38.7 us, by 7 31.9; 100 x 1024 by 3 76.8, by 2
 // 55.4; 70 x 2048 by 4 113.6, by 3 80.9.  Fewer are never the better where the sums or the loads' latency take the time: 1 request x 8
@@ -1072,12 +1085,9 @@ hipError_t launch_lookup(const int32_t *cache_ids, const int32_t *cache_len, int
 // by 3 17.6.  Whether more rounds pay, a model of them says, a workgroup to a CU: a round costs 7 us until rows flow, and then its rows at what a
 // CU takes alone (38 KB a us) or its share of the chip's 6000; more than one workgroup needs slots cleared and a merge (6 us).
 // 300 x 1024 of 768 by 1 212, by 3 164.
-// On the matrix cores few short rows are done before slots could be cleared: by 1 and by as many as can be, 33 requests x 300 fp32 rows
-// of 64 6.3, 7.8, 70 x 129 of 256 9.1, 10.1, 33 x 300 fp16 rows of 128 7.3, 8.1; but 33 x 1024 fp32 rows of 64 12.6, 8.2, 64 x 129 fp16 rows of 512
-// 12.6, 10.6.
-int lookup_parts(int64_t R, int32_t C, int32_t d, int64_t row_bytes, bool mfma)
+int lookup_parts(int64_t R, int32_t C, int64_t row_bytes)
 {
-    if (R > SPLIT_MAX_R || (mfma && (int64_t)C * d <= 40000)) return 1;
+    if (R > SPLIT_MAX_R) return 1;
     const int64_t most = (C + 63) / 64, round = R < 256 ? 256 / R : 1;
     const double bytes = (double)C * (double)row_bytes;
     int best = 1;
@@ -1116,7 +1126,9 @@ LookupRoute lookup_route(int64_t R, int64_t Qt, int32_t C, int32_t exact_dtype, 
 {
     const bool mfma = lookup_on_matrix_cores(exact_dtype, metric, d);
     LookupRoute to{};
-    to.parts = list ? list_parts(R, C, mfma, d) : (scratch ? lookup_parts(R, C, d, (int64_t)d * (exact_dtype == DT_F16 ? 2 : 4), mfma) : 1);
+    if (list) to.parts = list_parts(R, C, mfma, d);
+    else if (!scratch || done_whole(R, Qt, C, exact_dtype, metric, d, mfma)) to.parts = 1;
+    else to.parts = lookup_parts(R, C, (int64_t)d * (exact_dtype == DT_F16 ? 2 : 4));
     if (mfma) {
         if (exact_dtype == DT_F16) to.pieces = list ? lookup_pieces<DT_F16, true>(d, R, C, to.parts) : lookup_pieces<DT_F16, false>(d, R, C, to.parts);
         else to.pieces = list ? lookup_pieces<DT_F32, true>(d, R, C, to.parts) : lookup_pieces<DT_F32, false>(d, R, C, to.parts);
