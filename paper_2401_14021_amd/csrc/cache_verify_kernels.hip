@@ -1069,13 +1069,13 @@ hipError_t launch_lookup(const int32_t *cache_ids, const int32_t *cache_len, int
 // cores by their elements, in steps of 128 rows, GPU time and time in a stream of calls, by 1 and by as many as can be, one request x 4 queries: one step, fp32 rows of 640
 // 13.2, 12.6 and 13.4, 14.5, fp16 rows of 1024 15.0, 14.8 and 15.1, 14.9; two, 129 fp32 rows of 512 13.7, 11.0 and 14.1, 14.7, of 640 16.4, 11.8 and 16.5,
 // 14.6, 160 fp16 rows of 512 12.6, 10.6 and 12.9, 14.7; more, 33 x 1 x 300 fp32 rows of 64 6.3, 7.8, 384 of 128 9.5, 7.6 and 12.1, 14.7.  On the vector units, fp32
-// rows and few queries: 16 x 1 x 160 of 392 10.0, 9.7 and 12.1, 14.7, 1 x 4 x 100 11.0, 11.3 and 11.9, 14.5; 8 x 8 x 129 19.0, 14.4 and 19.3, 14.6.
+// rows and few queries: 16 x 1 x 160 of 392 10.0, 9.7 and 12.1, 14.7, 1 x 4 x 100 11.0, 11.3 and 11.9, 14.5; 8 x 8 x 129 19.0, 14.4 and 19.3, 14.6, 16 x 1 x 160 of 712 12.3, 10.8 and 12.6, 13.7 (once 11.2).
 // The lines lie where the GPU time of a whole request is that of the three launches which a split one once took (384 of 128 9.0).
 bool done_whole(int64_t R, int64_t Qt, int32_t C, int32_t exact_dtype, int32_t metric, int32_t d, bool mfma)
 {
     const bool f16 = exact_dtype == DT_F16;
     if (mfma) return (int64_t)C * d <= (C > 256 ? 40000 : (C > 128 ? (f16 ? 81920 : 65536) : (f16 ? 131072 : 81920)));
-    return !f16 && metric == METRIC_IP && d <= 768 && (C <= 128 ? Qt <= 4 * R : C <= 160 && Qt <= R);
+    return !f16 && metric == METRIC_IP && (C <= 128 ? Qt <= 4 * R && d <= 640 : C <= 160 && Qt <= R && d <= 448);
 }
 
 // Workgroups per request, at most one for every 64 cached rows begun.  Up to 256 requests have one round at least that is as full as it

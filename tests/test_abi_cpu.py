@@ -252,6 +252,7 @@ def test_lookup_routes(L):
     assert [_lookup(L, 8, C, d)[0] for C, d in ((128, 640), (128, 704), (129, 448), (129, 512), (256, 256))] == [1, 2, 1, 3, 1]
     assert [_lookup(L, 8, C, d, dtype=2)[0] for C, d in ((128, 1024), (160, 512), (200, 512), (300, 128), (300, 256))] == [1, 1, 4, 1, 5]
     assert [_lookup(L, 8, C, 392, Qt=Qt)[0] for C, Qt in ((128, 32), (128, 33), (160, 8), (160, 9), (161, 8))] == [1, 2, 1, 3, 3]
+    assert [_lookup(L, 8, C, d)[0] for C, d in ((128, 632), (128, 648), (160, 440), (160, 456))] == [1, 2, 1, 3]
     assert _lookup(L, 8, 128, 392, dtype=2)[0] == 2 and _lookup(L, 8, 128, 392, metric=1)[0] == 2 and _lookup(L, 8, 128, 776)[0] == 2
     # the k best: pieces as long as they can be unless a workgroup has one step of rows
     assert [_lookup(L, R, 2048, 1024, dtype=2, k=64)[:2] for R in (16, 32, 33, 128, 600)] == [(32, 4), (16, 4), (15, 8), (4, 8), (1, 8)]
