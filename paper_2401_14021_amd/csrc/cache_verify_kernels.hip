@@ -1082,8 +1082,8 @@ bool done_whole(int64_t R, int64_t Qt, int32_t C, int32_t exact_dtype, int32_t m
 // can be, of 256 workgroups on 256 CUs: 33 requests x 1024 fp32 rows of 768 by 8 (264 workgroups) 38.7 us, by 7 31.9; 100 x 1024 by 3 76.8, by 2
 // 55.4; 70 x 2048 by 4 113.6, by 3 80.9.  Fewer are never the better where the sums or the loads' latency take the time: 1 request x 8
 // queries x 256 fp16 rows of 392 by 1 35.3, by 4 15.6, 96 x 8 x 500 by 1 87.4, by 2 51.4, 8 x 1 x 129 of 1000 by squared distance by 1 33.7,
-// by 3 17.6.  Whether more rounds pay, a model of them says, a workgroup to a CU: a round costs 7 us until rows flow, and then its rows at what a
-// CU takes alone (38 KB a us) or its share of the chip's 6000; more than one workgroup needs slots cleared and a merge (6 us).
+// by 3 17.6.  Whether more rounds pay, a model of them says, a workgroup to a CU (lookup_pieces may fit two, which it leaves out): a round costs 7
+// us until rows flow, and then its rows at what a CU takes alone (38 KB a us) or its share of the chip's 6000; more than one workgroup needs slots cleared and a merge (6 us).
 // 300 x 1024 of 768 by 1 212, by 3 164.
 int lookup_parts(int64_t R, int32_t C, int64_t row_bytes)
 {
