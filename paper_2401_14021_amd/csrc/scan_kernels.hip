@@ -45,70 +45,24 @@ namespace {
 // against query  q0 + (wn*TN + j)*32 + lane%32.  A score is admitted (appended to its query's
 // candidate list) iff its ranking key is >= the query's admission key.
 
-// Parked epilogue (pipelined kernel).  Admitted scores are first parked in a small LDS list
-// (an LDS atomic is ~20x quicker than a global atomic round trip, which a lone wave per SIMD
-// cannot hide) and moved to the global lists in batches by flush_parked().  An entry that
-// finds the list full goes to its global list directly, so nothing is ever lost.
-constexpr int PARK_CAP = 672;   // parked admitted scores per workgroup (12 bytes each)
-// one 32x32 block of one wave: out[v] for row rbase + (v/4)*8 + v%4 and query q.
+// Parked epilogue (pipelined kernel).  A column of a 32x32 block that may hold an admitted score is put aside as it is, its
+// 16 scores and where they belong, in a list of the wave's own: no atomics and no waits between the multiplies.  sort_aside()
+// tests the scores later, 64 at a time, and parks the admitted ones in a list of the workgroup's, which flush_parked() moves
+// to the global lists.  An entry that finds that list full goes to its global list directly, so nothing is ever lost.
 //
 // The common case (no lane of the wave holds an admitted score) must be a handful of
-// instructions: the pipelined kernel's last stage contains 16 copies of this function, and
-// anything bulky here pushes that stage out of the instruction cache.  So the rare case does
-// not unroll over the 16 values: a lane that may hold an admitted score writes its 16 values
-// to a 64-byte LDS slot and walks them in a rolled loop (registers cannot be indexed
-// dynamically, LDS can).  Slots are handed out by rank among the candidate lanes, 8 per round.
-constexpr int SLOW_SLOTS = 8;   // 64-byte slots per wave
-__device__ __forceinline__ void select_block_parked(const ScanParams &p, const PushList pl,
-                                                    RALM_LDS float *wave_slots, const f32x16 &out,
-                                                    int32_t rbase, int32_t n_rows, int q, bool qok, u64 tkey,
-                                                    float tsc)
-{
-    float m = out[0];
-#pragma unroll
-    for (int v = 1; v < 16; ++v) m = fmaxf(m, out[v]);
-    // tsc is -inf where the key admits everything and +inf for padding columns: one compare
-    bool cand = m >= tsc;
-    unsigned long long mask = __builtin_amdgcn_ballot_w64(cand);
-    while (mask) {   // wave-uniform
-        const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-        const bool mine = cand && rank < (uint32_t)SLOW_SLOTS;
-        if (mine) {
-            RALM_LDS float *slot = wave_slots + rank * 16;
-            typedef float f32x4v __attribute__((ext_vector_type(4)));
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                f32x4v t = {out[c * 4], out[c * 4 + 1], out[c * 4 + 2], out[c * 4 + 3]};
-                *(RALM_LDS f32x4v *)(slot + c * 4) = t;
-            }
-            // which of the 16 values reach the threshold score (cheap, in registers) ...
-            uint32_t pm = 0;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) pm |= out[v] >= tsc ? (1u << v) : 0u;
-            // ... and only those are fetched back and tested exactly (usually one or two)
-#pragma unroll 1
-            while (pm) {
-                const int v = __builtin_ctz(pm);
-                pm &= pm - 1;
-                const int32_t g = rbase + (v >> 2) * 8 + (v & 3);
-                const u64 key = make_key(slot[v], g);
-                if (g < n_rows && key >= tkey) {
-                    const uint32_t at =
-                        __hip_atomic_fetch_add(pl.count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    if (at < pl.cap) {
-                        pl.keys[at] = key;
-                        pl.qs[at] = (uint32_t)q;
-                    } else {
-                        push_global(p, q, key);
-                    }
-                }
-            }
-        }
-        cand = cand && !mine;
-        mask = __builtin_amdgcn_ballot_w64(cand);
-    }
-}
+// instructions: the pipelined kernel's last stage contains 16 copies of the test, and
+// anything bulky in it pushes that stage out of the instruction cache.  So the rare case does
+// not unroll over the 16 values (registers cannot be indexed dynamically, LDS can).
+constexpr int PARK_MIN = 512, PARK_MAX = 1024;   // parked admitted scores per workgroup (12 bytes each)
+constexpr int ASIDE_MAX = 28, ASIDE_BYTES = 72;  // columns that a wave puts aside: 16 scores, a row and a query each
+
+// How the LDS behind a launch's ring is used: `tau_n` admission keys, `park` parked scores, `aside` columns per wave.  Long
+// lists are sorted out and flushed less often, so they get what the admission keys leave.
+struct ParkLayout {
+    int tau_n, park, aside;
+    int flush_every;   // tiles (a power of two) from one look at the parked entries to the next
+};
 
 // Epilogue of a launch that keeps every score into empty lists (the first stage of a ladder): the
 // score of the launch's r-th row goes to slot r of its query's list, no atomics.  A lane's 16
@@ -214,9 +168,7 @@ __device__ __forceinline__ uint4 round8_bf16(const uint4 &lo, const uint4 &hi)
     return __builtin_bit_cast(uint4, __builtin_convertvector(f, bf16x8));
 }
 
-constexpr int TAU_LDS_MAX_Q = 2560;   // admission keys of up to this many queries are kept in LDS
-// ... by the widest query tile; the narrower tiles serve only batches of at most one tile
-constexpr int tau_lds_q(int BN) { return BN <= 128 ? BN : TAU_LDS_MAX_Q; }
+constexpr int TAU_LDS_MAX_Q = 2560;   // admission keys of up to this many queries are kept in LDS (by the widest query tile)
 
 // The instruction stream of a stage is laid out by hand (one wave per SIMD: nothing else fills
 // the issue slots between MFMAs).  After each MFMA exactly one "side" instruction follows: an
@@ -240,7 +192,7 @@ constexpr int tau_lds_q(int BN) { return BN <= 128 ? BN : TAU_LDS_MAX_Q; }
 // KEEP: what is kept of the scores (KEEP_*).
 template <bool F16, int WM, int WN, int TM, int TN, int BK, int S, bool NTA, int D = S - 1, int RK = 0,
           bool A32 = false, int KEEP = KEEP_PARKED>
-__global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams p, const int nqt, const int tau_in_lds)
+__global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams p, const int nqt, const ParkLayout lay)
 {
     constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
     constexpr int ESA = A32 ? 4 : 2;                       // bytes of a datastore element
@@ -269,14 +221,12 @@ __global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams 
     const uint32_t lds0 = (uint32_t)(size_t)(RALM_LDS unsigned char *)smem;
     RALM_LDS u64 *tau_lds = (RALM_LDS u64 *)(smem + S * STAGE);
     PushList pl;
-    pl.keys = tau_lds + tau_lds_q(BN);
-    pl.qs = (RALM_LDS uint32_t *)(pl.keys + PARK_CAP);
-    pl.count = pl.qs + PARK_CAP;
-    pl.cap = PARK_CAP;
-    RALM_LDS float *wave_slots = (RALM_LDS float *)(pl.count + 4) + (threadIdx.x >> 6) * (SLOW_SLOTS * 16);
-    // counts per query column: in the place of the slots, which no wave uses while the counts are needed
+    pl.keys = tau_lds + lay.tau_n;
+    pl.qs = (RALM_LDS uint32_t *)(pl.keys + lay.park);
+    pl.count = pl.qs + lay.park;
+    pl.cap = (uint32_t)lay.park;
+    // columns put aside, wave by wave; in their place, while there are none, the counts per query column of a flush or of a counted launch
     RALM_LDS uint32_t *tally = pl.count + 4;
-    static_assert(WM * WN * SLOW_SLOTS * 16 >= BN, "the counts fit the slots");
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -313,8 +263,60 @@ __global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams 
     const int32_t n_rows = (int32_t)p.N;
 
     if (tid == 0) *pl.count = 0;
-    if (tau_in_lds)
+    if (lay.tau_n)
         for (int q = tid; q < p.Q; q += NT) tau_lds[q] = p.tau[q];
+    RALM_LDS float *aside_scores = (RALM_LDS float *)tally + wave * (lay.aside * (ASIDE_BYTES / 4));
+    RALM_LDS int32_t *aside_rows = (RALM_LDS int32_t *)(aside_scores + lay.aside * 16), *aside_queries = aside_rows + lay.aside;
+    int n_aside = 0;   // wave-uniform
+    auto sort_aside = [&]() __attribute__((always_inline)) {
+#pragma unroll 1
+        for (int i = lane; i < n_aside * 16; i += 64) {
+            const int e = i >> 4, v = i & 15;
+            const float score = aside_scores[i];
+            const int32_t row = aside_rows[e] + (v >> 2) * 8 + (v & 3);
+            const int q = aside_queries[e];
+            const u64 key = make_key(score, row);
+            if (row < n_rows && score == score && key >= (lay.tau_n ? tau_lds[q] : p.tau[q])) {
+                const uint32_t at = __hip_atomic_fetch_add(pl.count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (at < pl.cap) {
+                    pl.keys[at] = key;
+                    pl.qs[at] = (uint32_t)q;
+                } else {
+                    push_global(p, q, key);
+                }
+            }
+        }
+        n_aside = 0;
+    };
+    // one 32x32 block of this wave: out[v] for row row0 + (v/4)*8 + v%4 + 4 (lane/32) and query q0 + lane%32
+    auto select_block = [&](const f32x16 &out, int32_t row0, int q0, float tsc) __attribute__((always_inline)) {
+        float m = out[0];
+#pragma unroll
+        for (int v = 1; v < 16; ++v) m = fmaxf(m, out[v]);
+        // tsc is -inf where the key admits everything and NaN for padding columns: one compare
+        bool cand = m >= tsc;
+        unsigned long long mask = __builtin_amdgcn_ballot_w64(cand);
+        while (mask) {   // wave-uniform
+            const int n = __builtin_popcountll(mask);
+            if (n_aside > 0 && n_aside + n > lay.aside) sort_aside();
+            uint32_t l = lane;   // (opaque, so that nothing of what follows is kept in registers)
+            asm volatile("" : "+v"(l));
+            const int at = n_aside + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+            const bool mine = cand && at < lay.aside;
+            if (mine) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const f32x4 t = {out[c * 4], out[c * 4 + 1], out[c * 4 + 2], out[c * 4 + 3]};
+                    *(RALM_LDS f32x4 *)(aside_scores + at * 16 + c * 4) = t;
+                }
+                aside_rows[at] = row0 + (int32_t)(l >> 5) * 4;
+                aside_queries[at] = q0 + (int)(l & 31);
+            }
+            n_aside = n_aside + n < lay.aside ? n_aside + n : lay.aside;
+            cand = cand && !mine;
+            mask = __builtin_amdgcn_ballot_w64(cand);
+        }
+    };
 
     // ---- issue cursor: runs S-1 stages ahead of the multiply, also across tile boundaries ----
     // per-lane constants of the loads: byte offset (tile row, swizzled chunk) of each wave load
@@ -446,7 +448,7 @@ __global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams 
         const int q0 = cur_qt * BN;
         // admission keys of this lane's TN queries
         // tsc: the score a value must reach to be looked at more closely; -inf for a key of 0
-        // (admit everything; its score bits decode to NaN), +inf for padding columns
+        // (admit everything; its score bits decode to NaN), NaN (which nothing reaches) for padding columns
         u64 tkey[TN];
         float tsc[TN];
         bool qok[TN];
@@ -454,8 +456,8 @@ __global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams 
         for (int j = 0; j < TN; ++j) {
             const int q = q0 + (wn * TN + j) * 32 + fr;
             qok[j] = q < p.Q;
-            tkey[j] = qok[j] ? (tau_in_lds ? tau_lds[q] : p.tau[q]) : ~0ull;
-            tsc[j] = qok[j] ? (tkey[j] == 0ull ? -__builtin_inff() : key_score(tkey[j])) : __builtin_inff();
+            tkey[j] = qok[j] ? (lay.tau_n ? tau_lds[q] : p.tau[q]) : ~0ull;
+            tsc[j] = qok[j] ? (tkey[j] == 0ull ? -__builtin_inff() : key_score(tkey[j])) : __builtin_nanf("");
         }
 
         // one stage; FIRST: accumulators start from zero; LAST: selection fused into the last k-step;
@@ -538,9 +540,7 @@ __global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams 
                                             (int64_t)cur_rt * BM + (wm * TM + i) * 32 + (lane >> 5) * 4,
                                             q0 + (wn * TN + j) * 32 + fr, qok[j]);
                         else
-                            select_block_parked(p, pl, wave_slots, outs[mm % (LAG + 1)],
-                                                row0 + (wm * TM + i) * 32 + (lane >> 5) * 4, n_rows,
-                                                q0 + (wn * TN + j) * 32 + fr, qok[j], tkey[j], tsc[j]);
+                            select_block(outs[mm % (LAG + 1)], row0 + (wm * TM + i) * 32, q0 + (wn * TN + j) * 32, tsc[j]);
                     }
                     RALM_SCHED_FENCE();
                 }
@@ -610,12 +610,18 @@ __global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams 
                                             BN, tkey, tsc);
         }
         // tile end: every few tiles the parked entries move to the global lists
-        const bool last_tile = it + 1 == n_mine;
-        if (KEEP == KEEP_PARKED && ((it & 3) == 3 || last_tile)) {
-            __syncthreads();
-            const uint32_t n = *pl.count;   // uniform: read after the barrier
-            const uint32_t held = n < pl.cap ? n : pl.cap;
-            if (held >= pl.cap / 4 || (last_tile && held > 0)) flush_parked<NT, (BN <= 128)>(p, pl, tally, held);
+        if constexpr (KEEP == KEEP_PARKED) {
+            const bool last_tile = it + 1 == n_mine, look = last_tile || (it & (lay.flush_every - 1)) == lay.flush_every - 1;
+            if (look || n_aside * 2 > lay.aside) sort_aside();
+            if (look) {
+                __syncthreads();
+                const uint32_t n = *pl.count;   // uniform: read after the barrier
+                const uint32_t parked = n < pl.cap ? n : pl.cap;
+                if (parked >= pl.cap / 4 || (last_tile && parked > 0)) {
+                    if (BN <= 128 || p.Q <= 256) flush_parked<NT, true>(p, pl, tally, parked);
+                    else flush_parked<NT, false>(p, pl, tally, parked);
+                }
+            }
         }
         cur_rt += step_rt;
         cur_qt += step_qt;
@@ -631,16 +637,25 @@ template <bool F16, int WM, int WN, int TM, int TN, int BK, int S, bool NTA, int
           bool A32 = false, int KEEP = KEEP_PARKED>
 hipError_t launch_dma_variant(const ScanParams &p, int n_cu, hipStream_t stream)
 {
-    constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
+    constexpr int BM = WM * TM * 32, BN = WN * TN * 32, NW = WM * WN;
     constexpr size_t ring = (size_t)S * (BM * (A32 ? 4 : 2) + BN * 2) * BK;
-    constexpr size_t smem = ring + (size_t)tau_lds_q(BN) * 8 + (size_t)PARK_CAP * 12 + 16 + WM * WN * SLOW_SLOTS * 64;
-    static_assert(smem <= 160 * 1024, "LDS budget");
+    constexpr size_t lds = ring <= 64 * 1024 ? 76 * 1024 : 160 * 1024;   // two workgroups to a CU, or one
+    ParkLayout lay;
+    lay.tau_n = BN <= 128 ? BN : (p.Q <= TAU_LDS_MAX_Q ? (int)((p.Q + 255) / 256 * 256) : 0);
+    static_assert(ring + (BN <= 128 ? BN : TAU_LDS_MAX_Q) * 8 + PARK_MIN * 12 + 16 + NW * 2 * ASIDE_BYTES <= lds && NW * 2 * ASIDE_BYTES >= BN * 4,
+                  "LDS budget; the counts fit the columns put aside");
+    int left = (int)(lds - ring) - lay.tau_n * 8 - PARK_MIN * 12 - 16;
+    lay.aside = left / (NW * ASIDE_BYTES) & ~1;   // (even: the lists begin on 16-byte boundaries)
+    if (lay.aside > ASIDE_MAX) lay.aside = ASIDE_MAX;
+    left -= lay.aside * NW * ASIDE_BYTES;
+    lay.park = PARK_MIN + (left / 12 & ~3);
+    if (lay.park > PARK_MAX) lay.park = PARK_MAX;
+    const size_t smem = ring + (size_t)lay.tau_n * 8 + (size_t)lay.park * 12 + 16 + (size_t)lay.aside * NW * ASIDE_BYTES;
     auto kern = scan_dma_kernel<F16, WM, WN, TM, TN, BK, S, NTA, D, RK, A32, KEEP>;
-    const int tau_in_lds = p.Q <= tau_lds_q(BN) ? 1 : 0;
     static std::atomic<bool> attr_done{false};   // per instantiation; setting it twice is harmless
     if (!attr_done.load(std::memory_order_acquire)) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         attr_done.store(true, std::memory_order_release);
     }
@@ -648,11 +663,14 @@ hipError_t launch_dma_variant(const ScanParams &p, int n_cu, hipStream_t stream)
     const int64_t total = p.n_row_tiles * (SCAN_BM / BM) * nqt;
     if (total <= 0) return hipSuccess;
     if (total > 0x7fffffffLL) return hipErrorInvalidValue;   // the kernel counts items in 32 bits
-    const int per_cu = smem * 2 <= 160 * 1024 && !p.one_per_cu ? 2 : 1;
+    // the parked entries are looked at before they are expected to fill a quarter of their places
+    const int64_t a_tile = p.admits * (p.Q < BN ? p.Q : BN) * BM / (p.n_row_tiles * SCAN_BM) + 1;
+    lay.flush_every = a_tile * 4 <= lay.park ? 4 : (a_tile * 2 <= lay.park ? 2 : 1);
+    const int per_cu = lds * 2 <= 160 * 1024 && !p.one_per_cu ? 2 : 1;
     int64_t grid = (int64_t)n_cu * per_cu;
     if (total < grid) grid = total;
     grid = (grid + 7) / 8 * 8;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(WM * WN * 64), smem, stream, p, nqt, tau_in_lds);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NW * 64), smem, stream, p, nqt, lay);
     return hipGetLastError();
 }
 
