@@ -15,6 +15,7 @@
 //   3. the k' keys left in each list are re-scored from the exact copy and ranked.
 #include <hip/hip_runtime.h>
 #include <atomic>
+#include <math.h>
 #include <mutex>
 #include <stdarg.h>
 #include <stdio.h>
@@ -270,6 +271,20 @@ int64_t ladder_stage(const Plan &pl, int64_t tiles, int s, ScanParams &sp)
     return pl.k_prime * g;
 }
 
+// Rank, among the keys kept after a stage that has scanned every `stride`-th row, of the next stage's admission key.  The final k'-th best
+// key has a rank of about k' / stride in that sample, binomial for rows in random order: five standard deviations and four
+// more, and it is as good as certain that k' rows of the datastore reach the admission key.  In other orders the sample
+// may hold a query's best rows all together; so it is never closer to rank k than a quarter of the way to k', which
+// keeps the check's margin whatever the order.  k' if the ladder is to admit no less than that.
+int32_t early_rank(int32_t k, int32_t k_prime, int64_t stride)
+{
+    const double mean = (double)k_prime / (double)stride;
+    const int32_t chance = (int32_t)ceil(mean + 5.0 * sqrt(mean * (1.0 - 1.0 / (double)stride)) + 4.0);
+    const int32_t least = k + (k_prime - k + 3) / 4;
+    const int32_t rank = chance > least ? chance : least;
+    return rank < k_prime ? rank : k_prime;
+}
+
 // ---- scan timing aid ------------------------------------------------------------------------
 constexpr int MAX_PROF = 2048;
 bool g_prof_on = false;
@@ -349,7 +364,7 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
     int64_t last_expected = 0;   // keys per list that the last stage should leave
     // (short lists: the last stage's are cut down by the re-score)
     const bool cut_in_rescore = pl.k_prime < RESCORE_CUT_MIN;
-    auto run_stage = [&](int64_t expected, bool last) -> ralm_status {
+    auto run_stage = [&](int64_t expected, bool last, int32_t tau_rank) -> ralm_status {
         if (sp.n_row_tiles <= 0) return RALM_OK;
         const bool prof = g_prof_on && g_prof_n < MAX_PROF;
         if (prof) {
@@ -367,7 +382,7 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
         }
         last_expected = expected;
         if (last && cut_in_rescore) return RALM_OK;
-        RALM_HIP(launch_select(cand, cnt, pl.cap, pl.k_prime, Q, tau, lost, flags, stage_no++, expected, stream));
+        RALM_HIP(launch_select(cand, cnt, pl.cap, pl.k_prime, last ? 0 : tau_rank, Q, tau, lost, flags, stage_no++, expected, stream));
         return RALM_OK;
     };
 
@@ -380,14 +395,18 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
             sp.tile_begin = t0;
             sp.n_row_tiles = tiles - t0 < block ? tiles - t0 : block;
             sp.admits = sp.n_row_tiles * SCAN_BM;                    // at worst
-            st = run_stage(pl.cap, t0 + block >= tiles);
+            st = run_stage(pl.cap, t0 + block >= tiles, pl.k_prime);
             if (st != RALM_OK) return st;
         }
         last_expected = tiles > block ? 2 * pl.k_prime : tiles * SCAN_BM;
     } else {
+        int32_t rank_before = pl.k_prime;   // of the admission key that a stage scans with
         for (int s = 0; s < pl.n_stages; ++s) {
-            const int64_t expected = ladder_stage(pl, tiles, s, sp);
-            st = run_stage(expected, s + 1 == pl.n_stages);
+            int64_t expected = ladder_stage(pl, tiles, s, sp);
+            if (s > 0) expected = pl.k_prime + (expected - pl.k_prime) * rank_before / pl.k_prime;
+            // (with CUs reserved the ladder's last steps are by 2 and admit little)
+            rank_before = reserve > 0 ? pl.k_prime : early_rank(k, pl.k_prime, pl.stride[s]);
+            st = run_stage(expected, s + 1 == pl.n_stages, rank_before);
             if (st != RALM_OK) return st;
         }
     }

@@ -37,7 +37,8 @@ struct ScanParams {
     int64_t tile_stride;    // visited tile t is datastore tile (tile_begin + m(t)) * tile_stride, where m(t) = t
     int32_t tile_skip;      // if tile_skip == 0, else the t-th positive integer that is no multiple of tile_skip
     int64_t tile_begin;
-    int64_t admits;         // scores that the thresholds are expected to admit per query (any number is handled)
+    int64_t admits;         // scores that the k'-th best of the rows scanned so far would admit per query: what the thresholds are
+                            // expected to admit at most (any number is handled)
     int32_t one_per_cu;     // 1: never more workgroups than the CUs that launch_scan is given
     int32_t lists_empty;    // 1: every list is empty and every score of this launch is kept, so list positions
                             // follow from the row's place in the launch (no atomics)
@@ -95,18 +96,18 @@ struct CertifyParams {
     uint32_t *lost;        // [Q] != 0: the query's list lost entries during the scan
     int32_t stage;         // of the ladder's last stage
     uint32_t *cnt_rw;      // [Q] list lengths (CNT_PITCH), reset for queued queries
-    u64 *tau_exact;        // [Q] out: exact rank-k key of the queued query
+    u64 *tau_exact;        // [Q] in: admission key of the ladder's last stage; out: exact rank-k key of a queued query
     int32_t *fb_list;      // [Q] out: queued queries
     float u_query, u_rows; // unit roundoff applied by the scan to the query / to the rows (0: not rounded)
 };
 
-// per query: k'-th best key of cand[q, 0..cnt[q]) -> tau[q]; the list is then cut down, in place,
-// to its k' best keys (cnt[q] <- min(cnt[q], k')).  A list
+// per query: the list cand[q, 0..cnt[q]) is cut down, in place, to its k' best keys (cnt[q] <- min(cnt[q], k')); the admission key
+// tau[q] is raised to one that at least the best tau_rank <= k' of them reach, to the k'-th best itself if tau_rank = k' (0: it stays).  A list
 // that was sent more than cap keys holds the first cap of them: lost[q] is set and the query
 // counted once in flags[FLAG_LADDER_OVERFLOWS].
 // The lists' lengths before the cut are recorded behind the flag block if stage < MAX_STAGE_SUMS.
 // expected: keys that a list should hold (any number is handled).
-hipError_t launch_select(u64 *cand, uint32_t *cnt, uint32_t cap, int32_t k_prime, int64_t Q, u64 *tau,
+hipError_t launch_select(u64 *cand, uint32_t *cnt, uint32_t cap, int32_t k_prime, int32_t tau_rank, int64_t Q, u64 *tau,
                          uint32_t *lost, int32_t *flags, int32_t stage, int64_t expected,
                          hipStream_t stream);
 

@@ -15,6 +15,8 @@
 //                  against the queued queries, the rows that reach the query's exact rank-k
 //                  key are collected, and the best k of them are the answer.  Both kernels
 //                  are always launched and return at once when nothing is queued.
+#include <type_traits>
+
 #include <atomic>
 
 #include "ralm_common.h"
@@ -101,6 +103,133 @@ __device__ u64 radix_kth(const u64 *__restrict__ c, uint32_t n, uint32_t rank, R
     return kth;
 }
 
+// ---- the best `rank` keys of a list that one wave holds in registers -----------------------------
+// The wanted score is bracketed by halving: a step counts the keys at or above the middle with one compare and one ballot per
+// register, no LDS and no barrier.  It stops as soon as exactly `rank` keys lie above, after about a dozen steps for scores that
+// differ; equal scores at the edge are told apart by the low words in the same way.  Lanes without a key hold zero.
+template <int K>
+__device__ __forceinline__ uint32_t wave_count(const uint32_t (&v)[K], uint32_t least)
+{
+    uint32_t n = 0;
+#pragma unroll
+    for (int i = 0; i < K; ++i) n += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(v[i] >= least));
+    return n;
+}
+// Halves [lo, hi) until the value at lo is reached by at least `rank` and at most `most` of the wave's values, or has no other left
+// beside it.  lo, hi and rank are uniform; on entry n values reach lo, n >= rank, and fewer than rank reach hi; on return n is that of
+// the result.  early, n_early: the smallest count seen on the way that is at least early_rank, and what is reached by it.
+template <int K>
+__device__ __forceinline__ uint32_t wave_bracket(const uint32_t (&v)[K], uint32_t lo, uint32_t hi, uint32_t rank, uint32_t most, uint32_t &n,
+                                                 uint32_t early_rank, uint32_t &early, uint32_t &n_early)
+{
+    early = lo;
+    n_early = n;
+    while (n > most && hi - lo > 1) {
+        const uint32_t mid = lo + (hi - lo) / 2, m = wave_count<K>(v, mid);
+        if (m >= early_rank && m < n_early) {
+            early = mid;
+            n_early = m;
+        }
+        if (m >= rank) {
+            lo = mid;
+            n = m;
+        } else {
+            hi = mid;
+        }
+    }
+    return lo;
+}
+// the largest value of the wave (exchanges without LDS: a step of a shuffle is ten times as long)
+__device__ __forceinline__ uint32_t wave_max(uint32_t v)
+{
+    auto larger = [](uint32_t a, uint32_t b) { return a > b ? a : b; };
+    v = larger(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, false));    // lane ^ 1
+    v = larger(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, false));    // lane ^ 2
+    v = larger(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, false));   // the other quad of the 8
+    v = larger(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, false));   // the other half of the 16
+    const uint32_t a = larger((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16));
+    const uint32_t b = larger((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48));
+    return larger(a, b);
+}
+__device__ __forceinline__ uint32_t wave_min(uint32_t v) { return ~wave_max(~v); }
+
+// The rank-th best of the wave's K * 64 registers, of which n >= rank >= 1 hold keys.  early_rank, early: see select_best.
+template <int K>
+__device__ __forceinline__ u64 wave_kth(const u64 (&key)[K], uint32_t n, uint32_t rank, uint32_t early_rank, u64 &early)
+{
+    uint32_t b[K], least = 0xffffffffu, most = 0u;
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+        b[i] = (uint32_t)(key[i] >> 32);
+        least = key[i] && b[i] < least ? b[i] : least;
+        most = b[i] > most ? b[i] : most;
+    }
+    const uint32_t hi = wave_max(most);
+    // (the best score: 0xffffffff has no value above it, but is no score of a finite key)
+    const uint32_t end = hi == 0xffffffffu ? hi : hi + 1;
+    if (early_rank == 0 || early_rank > rank) early_rank = rank;
+    uint32_t e, n_e, none, n_none;
+    const uint32_t at = wave_bracket<K>(b, wave_min(least), end, rank, rank, n, early_rank, e, n_e);
+    // the keys at the edge: those of the smallest score that reaches `at`
+    uint32_t edge = 0xffffffffu;
+#pragma unroll
+    for (int i = 0; i < K; ++i) edge = b[i] >= at && b[i] < edge ? b[i] : edge;
+    edge = wave_min(edge);
+    uint32_t low[K], cut = 1u;
+#pragma unroll
+    for (int i = 0; i < K; ++i) low[i] = key[i] && b[i] == edge ? (uint32_t)key[i] : 0u;   // (ids are below 2^31 - 1: no key's low word is zero)
+    if (n > rank) {   // equal scores at the edge
+        const uint32_t want = rank - (edge == 0xffffffffu ? 0u : wave_count<K>(b, edge + 1));
+        uint32_t m = wave_count<K>(low, 1u);
+        cut = wave_bracket<K>(low, 1u, 0x80000000u, want, want, m, want, none, n_none);
+    }
+    uint32_t worst = 0xffffffffu;
+#pragma unroll
+    for (int i = 0; i < K; ++i) worst = low[i] >= cut && low[i] < worst ? low[i] : worst;
+    const u64 kth = (u64)edge << 32 | wave_min(worst);
+    early = kth;
+    if (early_rank < rank && n_e <= rank) {
+        // any key between the two ranks serves, the nearer to early_rank the better; this many steps are enough to get near
+        uint32_t from = e, to = end;
+        for (int step = 0; step < 6 && n_e > early_rank + (rank - early_rank) / 4 && to - from > 1; ++step) {
+            const uint32_t mid = from + (to - from) / 2, m = wave_count<K>(b, mid);
+            if (m >= early_rank) {
+                from = mid;
+                n_e = m;
+            } else {
+                to = mid;
+            }
+        }
+        const u64 k = (u64)from << 32;
+        if (k > kth) early = k;
+    }
+    return kth;
+}
+// the `rank` keys from kth on, in any order; f(position, key)
+template <int K, class F>
+__device__ __forceinline__ void wave_compact(const u64 (&key)[K], u64 kth, uint32_t rank, F f)
+{
+    uint32_t base = 0;
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+        const bool keep = key[i] >= kth;   // kth is a key, so zeros never pass
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(keep);
+        const uint32_t at = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        if (keep && at < rank) f(at, key[i]);
+        base += (uint32_t)__builtin_popcountll(m);
+    }
+}
+template <int K>
+__device__ __forceinline__ void wave_load(u64 (&key)[K], const u64 *__restrict__ c, uint32_t n)
+{
+    const uint32_t lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+        const uint32_t at = (uint32_t)i * 64 + lane;
+        key[i] = at < n ? c[at] : 0ull;    // 0 is no key: scores of any value have non-zero keys
+    }
+}
+
 // ---- the best `rank` keys of a list -----------------------------------------------------------
 // The digits of a radix descent are a poor histogram for scores: the top byte of a float is its
 // sign and most of its exponent, so thousands of keys fall into two or three bins and their LDS
@@ -112,6 +241,7 @@ __device__ u64 radix_kth(const u64 *__restrict__ c, uint32_t n, uint32_t rank, R
 // lists 65 -> 38 us, 2341 lists 227 -> 113 us.  A range that is not positive and finite, or a bin with more keys
 // than SEL_BIN_KEYS (many equal or nearly equal scores), takes the radix descent.
 constexpr int SEL_REGS = 16, SEL_BIN_KEYS = 1024;
+constexpr int WAVE_KEYS = 512;   // keys that one wave selects from
 
 template <int NT>
 struct SelectShared {
@@ -122,30 +252,20 @@ struct SelectShared {
     u64 bin_keys[SEL_BIN_KEYS];
     uint32_t lo[NT / 64], hi[NT / 64], total[NT / 64];
     uint32_t bin, rest, in_bin, n_bin, n_out;
+    uint32_t early_bin, early_bits;
     u64 kth;
 };
 
 // Exact rank-th best key of c[0, n), n >= rank >= 1, and the keys that reach it (exactly `rank`:
 // keys are distinct) in out[0, rank), in any order.  All NT threads of a workgroup; out is in
 // LDS and complete when the function returns; c is not read after that.
+// early: the wanted key, or if 0 < early_rank < rank a better one that at least early_rank of the list reach, as few as the bins tell apart.
 template <int NT>
-__device__ __forceinline__ u64 select_best(const u64 *__restrict__ c, uint32_t n, uint32_t rank, SelectShared<NT> &sh, u64 *out)
+__device__ __forceinline__ u64 select_best(const u64 *__restrict__ c, uint32_t n, uint32_t rank, SelectShared<NT> &sh, u64 *out,
+                                           uint32_t early_rank, u64 &early)
 {
     constexpr int SEL_BINS = 2 * NT, SEL_WAVES = NT / 64;
-    // a short list (a stage that refines by 2 leaves about 2 k' keys): every key's rank by counting
-    constexpr uint32_t SHORT = 256;
-    if (n <= SHORT) {
-        for (uint32_t i = threadIdx.x; i < n; i += NT) sh.bin_keys[i] = c[i];
-        __syncthreads();
-        for (uint32_t i = threadIdx.x; i < n; i += NT) {
-            const u64 mine = sh.bin_keys[i];
-            uint32_t better = 0;
-            for (uint32_t j = 0; j < n; ++j) better += sh.bin_keys[j] > mine ? 1u : 0u;
-            if (better < rank) out[better] = mine;
-        }
-        __syncthreads();
-        return out[rank - 1];
-    }
+    const bool want_early = early_rank > 0 && early_rank < rank;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const bool in_regs = n <= (uint32_t)(SEL_REGS * NT);
     u64 reg[SEL_REGS];
@@ -185,7 +305,10 @@ __device__ __forceinline__ u64 select_best(const u64 *__restrict__ c, uint32_t n
         sh.hi[wave] = hi;
     }
     for (int i = tid; i < SEL_BINS; i += NT) sh.hist[i] = 0;
-    if (tid == 0) sh.n_bin = sh.n_out = 0;
+    if (tid == 0) {
+        sh.n_bin = sh.n_out = 0;
+        sh.early_bits = 0xffffffffu;
+    }
     __syncthreads();
 #pragma unroll
     for (int w = 0; w < SEL_WAVES; ++w) {
@@ -223,14 +346,19 @@ __device__ __forceinline__ u64 select_best(const u64 *__restrict__ c, uint32_t n
             sh.rest = rank - better - (first ? 0u : h0);
             sh.in_bin = first ? h0 : h1;
         }
+        if (want_early && better < early_rank && early_rank <= incl)
+            sh.early_bin = (uint32_t)(SEL_BINS - 1 - 2 * tid - (early_rank <= better + h0 ? 0 : 1));
         __syncthreads();
         even = sh.in_bin <= (uint32_t)SEL_BIN_KEYS;
     }
     u64 kth;
     if (even) {
-        const uint32_t bin = sh.bin, in_bin = sh.in_bin, rest = sh.rest;
+        const uint32_t bin = sh.bin, in_bin = sh.in_bin, rest = sh.rest, early_bin = want_early ? sh.early_bin : bin;
         each([&](u64 key) {
-            if (key && bin_of(key) == bin) sh.bin_keys[atomicAdd(&sh.n_bin, 1u)] = key;
+            if (!key) return;
+            const uint32_t b = bin_of(key);
+            if (b == bin) sh.bin_keys[atomicAdd(&sh.n_bin, 1u)] = key;
+            else if (b == early_bin) atomicMin(&sh.early_bits, (uint32_t)(key >> 32));
         });
         __syncthreads();
         for (uint32_t i = tid; i < in_bin; i += NT) {
@@ -241,9 +369,12 @@ __device__ __forceinline__ u64 select_best(const u64 *__restrict__ c, uint32_t n
         }
         __syncthreads();
         kth = sh.kth;
+        // the worst score of the bin that holds the early rank; in the wanted key's own bin that key itself
+        early = early_bin == bin ? kth : (u64)sh.early_bits << 32;
     } else {
         __syncthreads();
         kth = radix_kth<NT>(c, n, rank, sh.radix);
+        early = kth;
     }
     each([&](u64 key) {
         const bool keep = key >= kth;         // kth is a key, so zeros never pass
@@ -280,14 +411,19 @@ __device__ uint32_t list_length(uint32_t n, int64_t q, uint32_t cap, uint32_t *_
     return n < cap ? n : cap;
 }
 
-// Per query: the k'-th best key of its list becomes the admission key of the next scan stage
-// and the list is cut down to its k' best keys in place.  A list that was sent more keys than
+// Per query: the list is cut down to its k' best keys in place, and a key of rank tau_rank <= k' among them becomes the admission
+// key of the next scan stage (tau_rank 0: there is none).  A list that was sent more keys than
 // it has slots kept only the first `cap` of them: it is processed as it is (its k'-th best key
 // is still a valid lower bound, the rows behind those keys were all scanned) and the query is
 // marked in `lost`, so that it is answered by the exact pass at the end of the call.
+//
+// tau_rank < k' is the rank that the final k'-th best key has in the sample scanned so far, with room for chance
+// (early_rank in ralm_api.hip): the list then still ends up with k' keys that reach it, out of a fraction of the scores that the
+// sample's own k'-th best would admit.  If chance or the order of the rows has it otherwise, rows between the two were not admitted: the check
+// of the result (certify) takes the admission key for the score of the best row that may be missing.
 template <int NT>
 __global__ __launch_bounds__(NT) void select_kernel(u64 *__restrict__ cand, uint32_t *__restrict__ cnt,
-                                                             uint32_t cap, int k_prime, u64 *__restrict__ tau,
+                                                             uint32_t cap, int k_prime, int tau_rank, u64 *__restrict__ tau,
                                                              uint32_t *__restrict__ lost, int32_t *__restrict__ flags,
                                                              int stage)
 {
@@ -298,18 +434,33 @@ __global__ __launch_bounds__(NT) void select_kernel(u64 *__restrict__ cand, uint
     const int64_t q = blockIdx.x;
     const int tid = threadIdx.x;
     u64 *c = cand + q * (int64_t)cap;
+    const u64 before = tau[q];
     const uint32_t n = list_length(cnt[q * CNT_PITCH], q, cap, lost, flags, stage);
     if (n < (uint32_t)k_prime) {    // fewer than k' candidates exist so far: keep admitting everything
-        if (tid == 0) {
-            tau[q] = 0ull;
-            cnt[q * CNT_PITCH] = n;
-        }
+        if (tid == 0) cnt[q * CNT_PITCH] = n;   // (tau is 0 still)
         return;
     }
-    const u64 kth = select_best<NT>(c, n, (uint32_t)k_prime, sh, out);
-    for (int i = tid; i < k_prime; i += NT) c[i] = out[i];
+    u64 early, kth;
+    // A short list is one wave's work: no LDS, no barriers.
+    if (n <= (uint32_t)WAVE_KEYS) {   // (uniform)
+        if (tid >= 64) return;
+        auto cut = [&](auto size) __attribute__((always_inline)) {
+            constexpr int K = decltype(size)::value;
+            u64 key[K];
+            wave_load<K>(key, c, n);
+            kth = wave_kth<K>(key, n, (uint32_t)k_prime, (uint32_t)tau_rank, early);
+            wave_compact<K>(key, kth, (uint32_t)k_prime, [&](uint32_t at, u64 k) { c[at] = k; });
+        };
+        if (n <= 256) cut(std::integral_constant<int, 4>{});
+        else cut(std::integral_constant<int, WAVE_KEYS / 64>{});
+    } else {
+        kth = select_best<NT>(c, n, (uint32_t)k_prime, sh, out, (uint32_t)tau_rank, early);
+        for (int i = tid; i < k_prime; i += NT) c[i] = out[i];
+    }
     if (tid == 0) {
-        tau[q] = kth;
+        if (tau_rank > 0) {   // (an admission key is never lowered: what it kept out stays out)
+            tau[q] = early > before ? early : before;
+        }
         cnt[q * CNT_PITCH] = (uint32_t)k_prime;
     }
 }
@@ -435,8 +586,11 @@ __device__ void certify(const CertifyParams &cert, float *__restrict__ out_margi
                         int k_prime, int d, double q2, u64 rank_k, u64 min_scan, double e2, double x2m)
 {
     const float q_sq = L2 ? (float)q2 : 0.f;
+    // rows that reach the worst kept key were not admitted if the last stage's admission key lies above it
+    const u64 floor = cert.flags ? cert.tau_exact[q] : 0ull;
+    const bool open = floor > min_scan && n >= k_prime;
     // margin: exact score at rank k minus the scan's score of the worst kept candidate.  A row
-    // that was not kept has a scan score at most the latter, so it can belong in the top k only
+    // that was not kept has a scan score at most the latter (the admission key's, if that is higher), so it can belong in the top k only
     // if the scan mis-scored it by at least the margin.
     float margin;
     if (n < k)
@@ -444,7 +598,7 @@ __device__ void certify(const CertifyParams &cert, float *__restrict__ out_margi
     else if (n < k_prime)
         margin = __builtin_inff();   // every row of the datastore was re-scored
     else
-        margin = key_score(rank_k) - (key_score(min_scan) - q_sq);
+        margin = key_score(rank_k) - (key_score(open ? floor : min_scan) - q_sq);
     if (out_margin) out_margin[q] = margin;
     if (!cert.flags) return;
     // what the scan's rounding can do to a score: the deterministic bound (every rounding
@@ -458,7 +612,7 @@ __device__ void certify(const CertifyParams &cert, float *__restrict__ out_margi
     const bool truncated = cert.lost && cert.lost[q] != 0;
     const bool all_rows = n < k_prime && !truncated;
     const double m = (double)margin;
-    const bool soft_ok = all_rows || (!truncated && n >= k && (m > soft || (soft == 0.0 && m >= 0.0)));
+    const bool soft_ok = all_rows || (!truncated && n >= k && (m > soft || (soft == 0.0 && m >= 0.0 && !open)));
     uint32_t *status = reinterpret_cast<uint32_t *>(reinterpret_cast<unsigned char *>(cert.flags) + status_offset());
     status[q] = soft_ok ? (all_rows || m > hard ? STATUS_SOFT | STATUS_HARD : STATUS_SOFT) : 0u;
     if (!soft_ok && n >= k) {
@@ -504,14 +658,29 @@ __global__ __launch_bounds__(RS_THREADS) void rescore_kernel(const u64 *__restri
     const float *qv = queries + q * (int64_t)d;
     const bool stats = out_margin || cert.flags;   // wave-uniform
 
+    // the list's length and its first keys travel while |q|^2 is formed (every list has that many slots, or it is the caches')
+    constexpr int K = WAVE_KEYS / 64;
+    uint32_t n_list = cnt[q * cnt_pitch];
+    u64 key[K];
+    const bool ahead = wave == 0 && cap >= WAVE_KEYS;
+    if (ahead) wave_load<K>(key, mine, WAVE_KEYS);
     const double q2 = stats ? query_norm2<RS_THREADS>(qv, d, s_q2) : 0.0;
     if (tid < RS_COUNT_MAX) s_rank[tid] = 0;
-    uint32_t n_list = cnt[q * cnt_pitch];
     n_list = cert.flags ? list_length(n_list, q, cap, cert.lost, cert.flags, cert.stage) : (n_list < cap ? n_list : cap);
     int n = (int)n_list;
     if (n > k_prime) {
         n = k_prime;
-        select_best<RS_THREADS>(mine, n_list, (uint32_t)k_prime, sel, list);
+        u64 none;
+        if (n_list <= WAVE_KEYS && cap >= WAVE_KEYS) {   // one wave's work, see select_kernel
+            if (wave == 0) {
+#pragma unroll
+                for (int i = 0; i < K; ++i) key[i] = i * 64 + lane < (int)n_list ? key[i] : 0ull;
+                const u64 kth = wave_kth<K>(key, n_list, (uint32_t)k_prime, 0, none);
+                wave_compact<K>(key, kth, (uint32_t)k_prime, [&](uint32_t at, u64 k) { list[at] = k; });
+            }
+        } else {
+            select_best<RS_THREADS>(mine, n_list, (uint32_t)k_prime, sel, list, 0, none);
+        }
     } else {
         for (int i = tid; i < n; i += RS_THREADS) list[i] = mine[i];
     }
@@ -925,7 +1094,7 @@ __global__ __launch_bounds__(SEL_THREADS) void exact_finish_kernel(const u64 *__
 
 }  // namespace
 
-hipError_t launch_select(u64 *cand, uint32_t *cnt, uint32_t cap, int32_t k_prime, int64_t Q, u64 *tau,
+hipError_t launch_select(u64 *cand, uint32_t *cnt, uint32_t cap, int32_t k_prime, int32_t tau_rank, int64_t Q, u64 *tau,
                          uint32_t *lost, int32_t *flags, int32_t stage, int64_t expected, hipStream_t stream)
 {
     if (Q <= 0) return hipSuccess;
@@ -933,11 +1102,11 @@ hipError_t launch_select(u64 *cand, uint32_t *cnt, uint32_t cap, int32_t k_prime
     // lists that should be short are ranked by small workgroups, eight to a CU instead of two: 2341 lists of
     // about 128 keys 11 us instead of 20 (any length is right in either)
     if (expected <= 512)
-        hipLaunchKernelGGL(select_kernel<256>, dim3((unsigned)Q), dim3(256), smem, stream, cand, cnt, cap, k_prime, tau, lost,
-                           flags, stage);
+        hipLaunchKernelGGL(select_kernel<256>, dim3((unsigned)Q), dim3(256), smem, stream, cand, cnt, cap, k_prime,
+                           tau_rank, tau, lost, flags, stage);
     else
         hipLaunchKernelGGL(select_kernel<SEL_THREADS>, dim3((unsigned)Q), dim3(SEL_THREADS), smem, stream, cand, cnt, cap,
-                           k_prime, tau, lost, flags, stage);
+                           k_prime, tau_rank, tau, lost, flags, stage);
     return hipGetLastError();
 }
 

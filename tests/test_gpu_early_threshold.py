@@ -1,0 +1,75 @@
+"""Stages scan with an admission key of a better rank than k' of the rows scanned so far.  Stores whose first sample holds a
+query's best rows all together: rows between that rank and k' are then not admitted, the check has to take the
+admission key for the best row that may be missing, and rows that belong in the first k have to be found all the same.
+Whole numbers: ids and scores must be the oracle's."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+N, d = 200_001, 64
+
+
+def _rows(levels):
+    """Column c of four is query c's: tile 0, which every stage's sample has visited, holds 64 rows of the best scores in it, another
+    tile, which only the last stage visits (a prime number of tiles from the first), 100 rows with scores of ranks 40 to 60, and
+    five of the best."""
+    g = torch.Generator().manual_seed(3)
+    X = torch.randint(-1, 2, (N, d), generator=g).float()
+    X[:, :4] = torch.randint(0, 40, (N, 4), generator=g).float()
+    for c in range(4):
+        X[c * 64:c * 64 + 64, c] = 230 - (torch.arange(64) // levels).float()
+        t = 701 * 256 + c * 64
+        X[t:t + 59, c] = 230 - ((40 + torch.arange(59) % 20) // levels).float()
+        X[t + 59:t + 64, c] = 240.0
+    return X
+
+
+@pytest.mark.parametrize("levels", [1, 4, 32])   # rows of the same score among the best
+@pytest.mark.parametrize("Q", [3, 70, 200, 600])
+@pytest.mark.parametrize("dtype,metric", [("bf16", "ip"), ("f16", "ip"), ("f16", "l2"), ("f32", "ip")])
+def test_best_rows_in_the_first_sample(oracle, dtype, metric, Q, levels):
+    from paper_2401_14021_amd import binding as B
+    X = _rows(levels)
+    q = torch.zeros(Q, d)
+    q[torch.arange(Q), torch.arange(Q) % 4] = 1.0 + (torch.arange(Q) // 4 % 3).float()
+    if metric == "l2":   # rows of one norm in the columns that count rank by distance as by product
+        q[torch.arange(Q), torch.arange(Q) % 4] = 255.0
+    Xd = X.cuda()
+    if metric == "l2":
+        ds = B.Datastore.for_l2(Xd, torch.float16)
+    elif dtype == "f32":
+        ds = B.Datastore(Xd)
+    else:
+        ds = B.Datastore.from_fp32(Xd, torch.bfloat16 if dtype == "bf16" else torch.float16)
+    picked = list(range(min(Q, 24)))
+    for k in (5, 20, 60):
+        ws = B.alloc_workspace(Q, ds, k)
+        ids, sc = B.ralm_retrieve_topk_ex(q.cuda(), ds, k, workspace=ws)
+        c = B.ralm_workspace_counters(ws)
+        assert c["unanswered"] == 0 and c["ladder_overflows"] == 0, c
+        wi, wsc = oracle.retrieve_topk(q[picked].numpy(), X.numpy(), k, metric=metric)
+        np.testing.assert_array_equal(ids.cpu().numpy()[picked], wi)
+        np.testing.assert_array_equal(sc.cpu().numpy()[picked], wsc)
+        full = Xd.double() @ q.double().cuda().T
+        if metric == "ip" and Q > 24:   # all queries: whole numbers, equal scores by lower id
+            key = full * 2 ** 18 + (N - torch.arange(N, device="cuda", dtype=torch.float64))[:, None]
+            assert torch.equal(ids.long(), key.topk(k, dim=0).indices.T)
+
+
+def test_the_check_knows_what_was_not_admitted():
+    """The margin is taken from the admission key where it lies above the worst kept candidate."""
+    from paper_2401_14021_amd import binding as B
+    X, k = _rows(1), 20
+    q = torch.zeros(4, d)
+    q[torch.arange(4), torch.arange(4)] = 1.0
+    ds = B.Datastore.from_fp32(X.cuda())
+    ws, margin = B.alloc_workspace(4, ds, k), torch.empty(4, device="cuda")
+    ids, sc = B.ralm_retrieve_topk_ex(q.cuda(), ds, k, workspace=ws, out_margin=margin)
+    c = B.ralm_workspace_counters(ws)
+    assert c["exact_pass"] == 0 and c["soft_certified"] == 4, c
+    # The best: five of 240, then 230, 229, ..: rank 20 scores 216.  The admission key of the last stages is the first sample's rank 31
+    # (score 200) or a few ranks worse, above the other tile's 100 rows; the worst kept of 64 candidates scores 172.
+    assert sc[:, -1].cpu().tolist() == [216.0] * 4
+    m = margin.cpu()
+    assert ((m >= 216 - 200) & (m <= 216 - 191)).all(), m
