@@ -79,6 +79,9 @@ int32_t default_k_prime(int32_t k)
     return kp;
 }
 
+// the rank between k and k' that no admission key of the ladder is better than (early_rank)
+int32_t least_rank(int32_t k, int32_t k_prime) { return k + (k_prime - k + 3) / 4; }
+
 // short_launches: the ladder's last stages are kept short (its lists and the workspace are the same)
 ralm_status make_plan(int64_t Q, const ralm_datastore_t *ds, int32_t k, int32_t k_prime, Plan &pl, bool short_launches = false)
 {
@@ -88,22 +91,26 @@ ralm_status make_plan(int64_t Q, const ralm_datastore_t *ds, int32_t k, int32_t 
     if (k_prime < k || k_prime > RALM_MAX_K_PRIME)
         return fail(RALM_ERR_K, "k_prime=%d must be in [k, %d]", k_prime, RALM_MAX_K_PRIME);
     pl.k_prime = k_prime;
+    const bool few_admitted = !short_launches && least_rank(k, k_prime) * 3 <= k_prime * 2;
     // Stage strides, finest first: 1, then multiplied by the stage's growth until a stage is
-    // small enough to keep every score (that one is stage 0).  A stage that refines by g is
-    // expected to admit k'*(g-1) scores per query; a stage more is a select, a launch and a last
+    // small enough to keep every score (that one is stage 0).  A stage that refines by g admits up to
+    // k'*(g-1) scores per query (early_rank: usually about half); a stage more is a select, a launch and a last
     // round of tiles that leaves CUs idle, 15 to 25 us together.  So: as few stages as a largest growth allows, all
     // of about the same growth.  Whole calls, growths finest first:
-    //   up to 64 queries   an admitted score is cheap: Q = 8 over 1M x 768 by 62 271 us, by 8 and 8 285; Q = 40
-    //                      291, 300.  With large k' the lists would have to be long and the first stage costs more
-    //                      than it saves: Q = 64, k' = 512, 2M x 1024 by 32 and 2 1079 us, by 5, 5 and 5 1004; Q = 16, k' = 2048, 1M x 1024 1027, 912.
+    //   up to 64 queries   an admitted score is cheap: Q = 8 over 1M x 768 by 62 271 us, by 16 and 4 287, Q = 60 286, 292.
+    //                      k' of 65 to 256, over 2M x 768: Q = 60, k' = 256 by 123 672 us, by 16 and 8 551, by 31 and 4 549; k' = 128 620, 530,
+    //                      528; Q = 8, k' = 256 579, 533, 532.  Larger k': Q = 64, k' = 512, 2M x 1024 by 32 and 2 1079 us, by 5, 5 and 5 1004.
     //   up to 256 queries  100 over 200K x 768 by 13 111 us, by 4 and 4 137, by 2, 2, 2 and 2 164; 81 over 1M round
     //                      by 8 and 8 370, by 2, 2, 2 and 8 392; 100 over 8M by 8, 8 and 8 2072, by 2, 2, 2, 8 and 8
     //                      2128; 200 over 6M by 4, 8 and 16 2243, by 2, 2, 2, 8 and 8 2268.  k' > 256:
-    //                      256 over 10M x 1024, k' = 2048, by 4 throughout 6497, by 2 6617.
+    //                      144 over 2M x 1024, k' = 1024, by 4 throughout 1371, by 5 1326; 256 over 10M x 1024, k' = 2048, 5988 and 5980; only
+    //                      where the admission keys' rank is two thirds of k' or better, so that by 5 admits no more than by 4 with rank k'.
     //   more               bound by the matrix cores, which wait for the selection: the last half of the rows should
     //                      see keys within a factor 2 of final, so the finest step is 2; 600 over
     //                      400K by 2, 4 and 4 602 us, by 2, 2, 2 and 4 625, by 4 and 8 609.
-    int32_t g_most = Q <= 64 ? (k_prime <= 256 ? 64 : 8) : (k_prime > 256 ? 4 : (Q <= 256 ? 16 : 8));
+    int32_t g_most = Q <= 64 ? (k_prime <= 64 ? 64 : (k_prime <= 256 ? 32 : 8)) : (k_prime > 256 ? (few_admitted ? 5 : 4) : (Q <= 256 ? 16 : 8));
+    // the growth that the lists are made for
+    int32_t g_lists = Q <= 64 ? (k_prime <= 256 ? 64 : 8) : (k_prime > 256 ? 4 : (Q <= 256 ? 16 : 8));
     // With CUs reserved (short_launches) more than 64 queries refine by 2 three times, so that no launch reads more
     // than half of the rows, and the next ones a quarter and an eighth: kernels of another stream that need more than
     // the reserved CUs get onto the chip between launches.  A lookup of 8 requests issued 3 ms into a retrieval of 1024
@@ -120,15 +127,16 @@ ralm_status make_plan(int64_t Q, const ralm_datastore_t *ds, int32_t k, int32_t 
     // overflowed and the call took 4144 us, now 2084).  Batches of more than 16384 queries refine by 2 instead, so
     // that their lists stay as short as they can be.
     auto head_room = [&](int32_t g) { return k_prime + (int64_t)(g - 1) * (3 * k_prime + 10 * SCAN_BM); };
-    if (Q > 16384 && k_prime > 256) g_most = 2;
-    // The first stage keeps all of its rows' scores: 16384 rows are a real sample; more where a large growth
-    // needs long lists anyway (up to 64 queries: 4x the expectation, 2x for k' > 256).
-    int64_t first_rows = (k_prime <= 256 ? 4 : 2) * k_prime * (int64_t)(g_most - 1) + k_prime;
-    if (first_rows < 16384) first_rows = 16384;
-    int64_t cap = first_rows;
-    if (Q > 64 && (Q <= 256 || k_prime > 256) && cap < head_room(g_most)) cap = head_room(g_most);
+    if (Q > 16384 && k_prime > 256) g_most = g_lists = 2;
+    // Up to 64 queries: 4x what a stage is expected to send to a list, 2x for k' > 256.
+    int64_t cap = (k_prime <= 256 ? 4 : 2) * k_prime * (int64_t)(g_lists - 1) + k_prime;
+    if (cap < 16384) cap = 16384;
+    pl.block_tiles = (cap - k_prime) / SCAN_BM;   // >= 1: cap >= 16384, k' <= 4096
+    if (Q > 64 && (Q <= 256 || k_prime > 256) && cap < head_room(g_lists)) cap = head_room(g_lists);
     pl.cap = (uint32_t)((cap + 1) & ~(int64_t)1);   // even: lists start on 16-byte boundaries
-    pl.block_tiles = (first_rows - k_prime) / SCAN_BM;   // >= 1: first_rows >= 16384, k' <= 4096
+    // The first stage keeps all of its rows' scores.  16384 rows are a real sample, and as many keys as the select that follows holds in
+    // registers: 24 queries, k' = 256, over 700 000 x 768 with a first stage of 64 512 rows 335 us a round (62 of it that select), of 16384 290.
+    const int64_t first_rows = 16384;
     pl.Qpad = (Q + SCAN_QPAD - 1) / SCAN_QPAD * SCAN_QPAD;
     pl.dpad = (scan_cols(ds) + SCAN_BK - 1) / SCAN_BK * SCAN_BK;
 
@@ -280,8 +288,7 @@ int32_t early_rank(int32_t k, int32_t k_prime, int64_t stride)
 {
     const double mean = (double)k_prime / (double)stride;
     const int32_t chance = (int32_t)ceil(mean + 5.0 * sqrt(mean * (1.0 - 1.0 / (double)stride)) + 4.0);
-    const int32_t least = k + (k_prime - k + 3) / 4;
-    const int32_t rank = chance > least ? chance : least;
+    const int32_t least = least_rank(k, k_prime), rank = chance > least ? chance : least;
     return rank < k_prime ? rank : k_prime;
 }
 

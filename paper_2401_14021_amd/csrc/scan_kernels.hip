@@ -269,20 +269,42 @@ __global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams 
     RALM_LDS int32_t *aside_rows = (RALM_LDS int32_t *)(aside_scores + lay.aside * 16), *aside_queries = aside_rows + lay.aside;
     int n_aside = 0;   // wave-uniform
     auto sort_aside = [&]() __attribute__((always_inline)) {
+        // 128 scores at a time, so that one half's LDS reads travel with the other's; a place for all that are admitted by one add
 #pragma unroll 1
-        for (int i = lane; i < n_aside * 16; i += 64) {
-            const int e = i >> 4, v = i & 15;
-            const float score = aside_scores[i];
-            const int32_t row = aside_rows[e] + (v >> 2) * 8 + (v & 3);
-            const int q = aside_queries[e];
-            const u64 key = make_key(score, row);
-            if (row < n_rows && score == score && key >= (lay.tau_n ? tau_lds[q] : p.tau[q])) {
-                const uint32_t at = __hip_atomic_fetch_add(pl.count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                if (at < pl.cap) {
-                    pl.keys[at] = key;
-                    pl.qs[at] = (uint32_t)q;
-                } else {
-                    push_global(p, q, key);
+        for (int base = 0; base < n_aside * 16; base += 128) {
+            u64 key[2];
+            int query[2];
+            bool in[2];
+            unsigned long long m[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int i = base + h * 64 + lane, at = i < n_aside * 16 ? i : 0, e = at >> 4, v = at & 15;
+                const float score = aside_scores[at];
+                const int32_t row = aside_rows[e] + (v >> 2) * 8 + (v & 3);
+                query[h] = aside_queries[e];
+                key[h] = make_key(score, row);
+                in[h] = i < n_aside * 16 && row < n_rows && score == score;
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                in[h] = in[h] && key[h] >= (lay.tau_n ? tau_lds[query[h]] : p.tau[query[h]]);
+                m[h] = __builtin_amdgcn_ballot_w64(in[h]);
+            }
+            const uint32_t n0 = (uint32_t)__builtin_popcountll(m[0]), n = n0 + (uint32_t)__builtin_popcountll(m[1]);
+            if (n == 0) continue;   // wave-uniform
+            uint32_t first = 0;
+            if (lane == 0) first = __hip_atomic_fetch_add(pl.count, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            first = __builtin_amdgcn_readfirstlane(first);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (in[h]) {
+                    const uint32_t at = first + (h ? n0 : 0u) + __builtin_amdgcn_mbcnt_hi((uint32_t)(m[h] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[h], 0u));
+                    if (at < pl.cap) {
+                        pl.keys[at] = key[h];
+                        pl.qs[at] = (uint32_t)query[h];
+                    } else {
+                        push_global(p, query[h], key[h]);
+                    }
                 }
             }
         }
@@ -768,7 +790,7 @@ hipError_t launch_f32(const ScanParams &p, int n_cu, hipStream_t stream)
 
 }  // namespace
 
-constexpr int64_t COUNT_MIN = 2;
+constexpr int64_t COUNT_MIN = 8;
 
 int scan_bn_for(int64_t Q)
 {
@@ -792,11 +814,10 @@ int scan_route(const ScanParams &p, int n_cu)
     // every score into empty lists: fixed list positions
     const bool all_kept = p.lists_empty && p.tile_skip == 0 && p.n_row_tiles > 0 && p.n_row_tiles * SCAN_BM <= (int64_t)p.cap;
     if (all_kept) return few_tiles(p, n_cu) ? RALM_SCAN_ALL_QUARTERS : RALM_SCAN_ALL;
-    // Thresholds that are expected to admit COUNT_MIN or more of a tile's 256 scores per query: the admitted
-    // scores of a tile are counted and stored together.  The line is flat: a round of 256 neighbour queries over
-    // 10M x 1024 (k' = 2048) takes 6525 us with it at 1.2, 6489 at 2, 6480 at 4, 7226 without counted launches;
-    // 200 queries over 2M rows in corpus order, whose admitted scores come in bursts, 2055 at 1.5, 2126 at 2.5,
-    // 2680 without; 100 queries, k' = 64, that admit 1.3 a tile: 134 counted, 112 parked.
+    // Thresholds that may admit COUNT_MIN or more of a tile's 256 scores per query: the admitted
+    // scores of a tile are counted and stored together, which takes about 20 us a tile of 256 queries whatever their number.  Parked they take
+    // time by their number: rounds of 144 neighbour queries over 2M x 1024 (k' = 1024) 1410 us with the line at 2, 1373 at 3, 1370 at
+    // 8, 1375 at 16, of 256 over 10M x 1024 (k' = 2048) 6044 at 2, 5988 at 5, and about 90 us more with no counted launches.
     if (p.admits >= COUNT_MIN * p.n_row_tiles) return RALM_SCAN_COUNTED;
     return scan_held_takes(p, n_cu) ? RALM_SCAN_HELD : RALM_SCAN_PARKED;
 }
