@@ -605,14 +605,17 @@ __global__ __launch_bounds__(256) void verify_kernel(const int32_t *__restrict__
 //      per lane;
 //   2. every wave compares the 64 candidates with its part of the remaining slots (an id read from
 //      LDS serves all lanes): whoever is found there is a member whatever happens in the zone;
-//   3. wave 0 walks the others in order: a member of the zone as it is by then is skipped, anyone
-//      else takes the zone's next slot.  A batch ends early when its zone is used up, unless the zone is the whole
-//      ring: then it goes round.
-// What bounds it: step 2's LDS reads, len / (4 waves) of them per 64 candidates, and the loop of step
-// 3.  The former version gave one wave to a request and spread one candidate's test over its
+//   3. where none of the others is in the zone as it was (nothing waits there to be evicted before it is asked for), those that no
+//      earlier one of the batch equals take the zone's slots in order, all at once;
+//   4. otherwise wave 0 walks them in order: a member of the zone as it is by then is skipped, anyone
+//      else takes the zone's next slot.
+// A batch ends early when its zone is used up, unless the zone is the whole ring: then it goes round (step 4).
+// What bounds it: step 2's LDS reads, len / (4 waves) of them per 64 candidates (eight of a wave's travel together), four
+// barriers and the candidates' ids from memory.  The former version gave one wave to a request and spread one candidate's test over its
 // lanes, a chain of len / 256 LDS reads per candidate.  64 requests x 80 candidates into caches of one entry, us: one
 // candidate at a time 34, in batches that end with the ring 87, now 15.  512 requests x up to 160 candidates, caches
-// of 4096: 456 -> 79 us; 32 requests x 640 candidates, caches of 2048: 811 -> 97 us.
+// of 4096: 456 us one at a time, 71 in batches, 28 with step 3 and an exclusive or and a minimum per slot for a compare and its scalar
+// or, 32 requests x 640 candidates, caches of 2048: 811, 97, 32.
 constexpr int CI_THREADS = 512, CI_WAVES = CI_THREADS / 64;
 
 __global__ __launch_bounds__(CI_THREADS) void cache_insert_kernel(
@@ -645,26 +648,33 @@ __global__ __launch_bounds__(CI_THREADS) void cache_insert_kernel(
     // candidates in order: step, then rank, then successor offset
     const int64_t per_rank = n_next > 0 ? n_next : 1, per_step = per_rank * p, total = per_step * n;
     const int first = n_next > 0 ? 1 : 0;
-    for (int64_t base = 0; base < total;) {
-        int32_t e = -1;                    // -1: no candidate
-        if (base + lane < total) {
-            const int64_t c = base + lane;
-            int64_t step, rank, off;
-            if (total <= 0x7fffffffLL) {   // wave-uniform: 64-bit divisions are emulated
-                const uint32_t c32 = (uint32_t)c, ps = (uint32_t)per_step, pr = (uint32_t)per_rank;
-                const uint32_t s32 = c32 / ps, in_step = c32 - s32 * ps, k32 = in_step / pr;
-                step = s32;
-                rank = k32;
-                off = in_step - k32 * pr;
-            } else {
-                step = c / per_step;
-                rank = (c - step * per_step) / per_rank;
-                off = c - step * per_step - rank * per_rank;
-            }
-            const int64_t t = truth[(q_lo + step) * true_stride + rank];
-            const int64_t e64 = t + first + off;
-            if (t >= 0 && e64 < N) e = (int32_t)e64;
+    auto candidate = [&](int64_t c) __attribute__((always_inline)) -> int32_t {   // -1: none
+        if (c >= total) return -1;
+        int64_t step, rank, off;
+        if (total <= 0x7fffffffLL) {   // wave-uniform: 64-bit divisions are emulated
+            const uint32_t c32 = (uint32_t)c, ps = (uint32_t)per_step, pr = (uint32_t)per_rank;
+            const uint32_t s32 = c32 / ps, in_step = c32 - s32 * ps, k32 = in_step / pr;
+            step = s32;
+            rank = k32;
+            off = in_step - k32 * pr;
+        } else {
+            step = c / per_step;
+            rank = (c - step * per_step) / per_rank;
+            off = c - step * per_step - rank * per_rank;
         }
+        const int64_t t = truth[(q_lo + step) * true_stride + rank];
+        const int64_t e64 = t + first + off;
+        return t >= 0 && e64 < N ? (int32_t)e64 : -1;
+    };
+    // The barriers order LDS alone: the ids of the next batch travel across them, and so do the stores of the last one's.
+    auto meet = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+    int32_t e_next = candidate(lane);
+    int64_t next_at = 0;               // the first candidate that e_next holds
+    __syncthreads();
+    for (int64_t base = 0; base < total;) {
+        const int32_t e = base == next_at ? e_next : candidate(base + lane);
+        next_at = base + 64;
+        e_next = candidate(next_at + lane);
         // 64 places without a candidate (an unfilled rank, successors past the datastore's end): the rest of the last
         // place's rank has none either.  65536 successors of each of 64 ids at the end, four requests: 46 ms batch by
         // batch, 0.03 ms this way
@@ -678,21 +688,31 @@ __global__ __launch_bounds__(CI_THREADS) void cache_insert_kernel(
         const int zone_n = room < 64 ? room : 64;
         int slot = zone_at + lane;
         slot = slot >= C ? slot - C : slot;
-        __syncthreads();                   // the row is in LDS; the last batch's zone is back in it
+        meet();                   // the row is in LDS; the last batch's zone is back in it
         int32_t zone = -1;
         if (wave == 0 && lane < zone_n) {
             zone = cs[slot];
             cs[slot] = -1;
         }
-        __syncthreads();
-        bool member = false;
-        for (int x = wave * 4; x < len; x += CI_WAVES * 4) {
-            const int4 v = *reinterpret_cast<const int4 *>(cs + x);   // one address: every lane gets it
-            member |= v.x == e || v.y == e || v.z == e || v.w == e;
+        meet();
+        // the least exclusive or with a slot: zero if one equals (a compare per slot would write a scalar that the next one reads)
+        uint32_t apart = ~0u;
+        auto nearer = [&](uint32_t a, uint32_t b) __attribute__((always_inline)) {
+            const uint32_t m = a < b ? a : b;
+            apart = m < apart ? m : apart;
+        };
+        for (int x = wave * 32; x < len; x += CI_WAVES * 32) {   // (slots from len on hold -1)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int4 v = *reinterpret_cast<const int4 *>(cs + x + i * 4);   // one address: every lane gets it
+                nearer((uint32_t)(v.x ^ e), (uint32_t)(v.y ^ e));
+                nearer((uint32_t)(v.z ^ e), (uint32_t)(v.w ^ e));
+            }
         }
+        const bool member = apart == 0;
         const u64 found = __ballot(member && e >= 0);
         if (lane == 0) s_member[wave] = found;
-        __syncthreads();
+        meet();
         if (wave == 0) {
             u64 todo = __ballot(e >= 0);
             u64 safe = 0;
@@ -700,6 +720,29 @@ __global__ __launch_bounds__(CI_THREADS) void cache_insert_kernel(
             todo &= ~safe;
             int used = 0, taken = 64;      // used: the zone's slot that takes the next insertion
             bool round = false;            // the zone is the ring and has been gone round
+            if (__popcll((long long)todo) > 12) {   // (so few are walked faster than compared)
+                u64 repeated = 0, in_zone = 0;
+#pragma unroll 8
+                for (int c = 0; c < 64; ++c) {
+                    const int32_t ec = __builtin_amdgcn_readlane(e, c);
+                    repeated |= __ballot(e == ec) & (~1ull << c);
+                    in_zone |= __ballot(zone == ec) && ec >= 0 ? 1ull << c : 0ull;
+                }
+                const u64 fresh = todo & ~repeated;
+                const int n_fresh = __popcll((long long)fresh);
+                if (!(todo & in_zone) && (n_fresh <= zone_n || len < C || zone_n < C)) {   // wave-uniform
+                    used = n_fresh < zone_n ? n_fresh : zone_n;
+                    const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(fresh >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)fresh, 0u));
+                    const bool mine = (fresh >> lane) & 1;
+                    // no slot left in the zone for the first of these: it opens the next batch
+                    const u64 left = __ballot(mine && rank >= zone_n);
+                    if (left) taken = __ffsll((long long)left) - 1;
+                    // to the zone's lane `rank`; the others' go to lane 63, which listens only if there are no others
+                    const int32_t sent = __builtin_amdgcn_ds_permute((mine ? rank : 63) * 4, e);
+                    zone = lane < used ? sent : zone;
+                    todo = 0;
+                }
+            }
             while (todo) {                 // wave-uniform
                 const int c = __ffsll((long long)todo) - 1;
                 const int32_t ec = __builtin_amdgcn_readlane(e, c);
@@ -728,7 +771,7 @@ __global__ __launch_bounds__(CI_THREADS) void cache_insert_kernel(
                 s_head = len < C ? head : (h >= C ? h - C : h);
             }
         }
-        __syncthreads();
+        meet();
         base += s_taken;
         len = s_len;
         head = s_head;
