@@ -14,37 +14,33 @@ namespace ralm {
 
 namespace {
 
-constexpr int KP_THREADS = 256, KP_WAVES = KP_THREADS / 64;
-constexpr int KP_MAX_PER = RALM_MAX_K / KP_THREADS;   // entries per thread
-static_assert(RALM_MAX_K % KP_THREADS == 0 && (RALM_MAX_K & (RALM_MAX_K - 1)) == 0, "a power of two of at least one entry per thread");
-
-__device__ __forceinline__ double block_sum(double x, double *red /*[KP_WAVES]*/)
+template <int S>
+__device__ __forceinline__ double xor_f64(double x)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
-    __syncthreads();
-    double t = 0.0;
-    for (int w = 0; w < KP_WAVES; ++w) t += red[w];
-    return t;
+    return __hiloint2double((int)lane_xor<S>((uint32_t)__double2hiint(x)), (int)lane_xor<S>((uint32_t)__double2loint(x)));
 }
-__device__ __forceinline__ double block_max(double x, double *red)
+// x of all the workgroup's threads joined by f, every thread gets it; red: [NT / 64] in LDS
+template <int NT, class F>
+__device__ __forceinline__ double block_join(double x, double *red, F f)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const double y = __shfl_xor(x, o, 64);
-        x = y > x ? y : x;
-    }
+    x = f(x, xor_f64<32>(x));
+    x = f(x, xor_f64<16>(x));
+    x = f(x, xor_f64<8>(x));
+    x = f(x, xor_f64<4>(x));
+    x = f(x, xor_f64<2>(x));
+    x = f(x, xor_f64<1>(x));
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
     __syncthreads();
     double t = red[0];
-    for (int w = 1; w < KP_WAVES; ++w) t = red[w] > t ? red[w] : t;
+    for (int w = 1; w < NT / 64; ++w) t = f(t, red[w]);
     return t;
 }
 
-// one workgroup per query
+// One workgroup per query, a thread for every entry or every second one (up to four from 4096 entries on): what bounds it is the chain of
+// ids, scores and tokens from memory, exp, sort and sums, of which a thread with more entries has more in a row.  1024 entries each
+// for 256 queries: 27 us with 256 threads, 21.5 with 1024.
+template <int KP_THREADS>
 __global__ __launch_bounds__(KP_THREADS) void knnlm_probs_kernel(
     const int32_t *__restrict__ ids, const float *__restrict__ scores, int k, int kp2,
     const int32_t *__restrict__ values, int64_t N, double T, int32_t *__restrict__ tokens,
@@ -53,9 +49,12 @@ __global__ __launch_bounds__(KP_THREADS) void knnlm_probs_kernel(
     extern __shared__ __align__(16) unsigned char smem[];
     double *e = reinterpret_cast<double *>(smem);     // [kp2] weight of the entry at each rank
     u64 *keys = reinterpret_cast<u64 *>(e + kp2);      // [kp2] (token, rank), sorted by token then rank
+    constexpr int KP_WAVES = KP_THREADS / 64;
+    constexpr int KP_MAX_PER = KP_THREADS == 1024 ? RALM_MAX_K / KP_THREADS : 2;   // entries per thread
+    static_assert(RALM_MAX_K % 1024 == 0 && (RALM_MAX_K & (RALM_MAX_K - 1)) == 0, "a power of two of at least one entry per thread");
     __shared__ double red[KP_WAVES];
-    __shared__ double s_p[KP_THREADS];
-    __shared__ int32_t s_tok[KP_THREADS];
+    __shared__ double s_p[KP_WAVES];
+    __shared__ int32_t s_tok[KP_WAVES];
 
     const int64_t q = blockIdx.x;
     const int tid = threadIdx.x;
@@ -70,7 +69,7 @@ __global__ __launch_bounds__(KP_THREADS) void knnlm_probs_kernel(
             best = s > best ? s : best;
         }
     }
-    best = block_max(best, red);
+    best = block_join<KP_THREADS>(best, red, [](double a, double b) { return b > a ? b : a; });
 
     double part = 0.0;
     for (int i = tid; i < kp2; i += KP_THREADS) {
@@ -91,7 +90,7 @@ __global__ __launch_bounds__(KP_THREADS) void knnlm_probs_kernel(
         keys[i] = key;
         part += x;
     }
-    const double Z = block_sum(part, red);
+    const double Z = block_join<KP_THREADS>(part, red, [](double a, double b) { return a + b; });
     for (int i = tid; i < k; i += KP_THREADS) {
         const double w = Z > 0.0 ? e[i] / Z : 0.0;
         e[i] = w;
@@ -146,24 +145,28 @@ __global__ __launch_bounds__(KP_THREADS) void knnlm_probs_kernel(
             my_tok = tok;
         }
     }
-    s_p[tid] = my_p;
-    s_tok[tid] = my_tok;
-    __syncthreads();
-    for (int o = KP_THREADS / 2; o > 0; o >>= 1) {
-        if (tid < o) {
-            const double p2 = s_p[tid + o];
-            const int32_t t2 = s_tok[tid + o];
-            if (p2 > s_p[tid] || (p2 == s_p[tid] && p2 >= 0.0 && t2 < s_tok[tid])) {
-                s_p[tid] = p2;
-                s_tok[tid] = t2;
-            }
+    auto better = [&](double p2, int32_t t2) __attribute__((always_inline)) {
+        if (p2 > my_p || (p2 == my_p && p2 >= 0.0 && t2 < my_tok)) {
+            my_p = p2;
+            my_tok = t2;
         }
-        __syncthreads();
+    };
+    better(xor_f64<32>(my_p), (int32_t)lane_xor<32>((uint32_t)my_tok));
+    better(xor_f64<16>(my_p), (int32_t)lane_xor<16>((uint32_t)my_tok));
+    better(xor_f64<8>(my_p), (int32_t)lane_xor<8>((uint32_t)my_tok));
+    better(xor_f64<4>(my_p), (int32_t)lane_xor<4>((uint32_t)my_tok));
+    better(xor_f64<2>(my_p), (int32_t)lane_xor<2>((uint32_t)my_tok));
+    better(xor_f64<1>(my_p), (int32_t)lane_xor<1>((uint32_t)my_tok));
+    if ((tid & 63) == 0) {
+        s_p[tid >> 6] = my_p;
+        s_tok[tid >> 6] = my_tok;
     }
+    __syncthreads();
     if (tid == 0) {
-        const bool any = s_p[0] >= 0.0;
-        if (top_token) top_token[q] = any ? s_tok[0] : -1;
-        if (top_prob) top_prob[q] = any ? (float)s_p[0] : 0.f;
+        for (int w = 1; w < KP_WAVES; ++w) better(s_p[w], s_tok[w]);
+        const bool any = my_p >= 0.0;
+        if (top_token) top_token[q] = any ? my_tok : -1;
+        if (top_prob) top_prob[q] = any ? (float)my_p : 0.f;
     }
 }
 
@@ -177,8 +180,12 @@ hipError_t launch_knnlm_probs(const int32_t *ids, const float *scores, int64_t Q
     int kp2 = 2;
     while (kp2 < k) kp2 <<= 1;
     const size_t smem = (size_t)kp2 * 16;
-    hipLaunchKernelGGL(knnlm_probs_kernel, dim3((unsigned)Q), dim3(KP_THREADS), smem, stream, ids, scores, k, kp2,
-                       values, N, T, tokens, weights, top_token, top_prob);
+    if (kp2 <= 512)
+        hipLaunchKernelGGL(knnlm_probs_kernel<256>, dim3((unsigned)Q), dim3(256), smem, stream, ids, scores, k, kp2,
+                           values, N, T, tokens, weights, top_token, top_prob);
+    else
+        hipLaunchKernelGGL(knnlm_probs_kernel<1024>, dim3((unsigned)Q), dim3(1024), smem, stream, ids, scores, k, kp2,
+                           values, N, T, tokens, weights, top_token, top_prob);
     return hipGetLastError();
 }
 
