@@ -136,7 +136,7 @@ ralm_status make_plan(int64_t Q, const ralm_datastore_t *ds, int32_t k, int32_t 
     pl.cap = (uint32_t)((cap + 1) & ~(int64_t)1);   // even: lists start on 16-byte boundaries
     // The first stage keeps all of its rows' scores.  16384 rows are a real sample, and as many keys as the select that follows holds in
     // registers: 24 queries, k' = 256, over 700 000 x 768 with a first stage of 64 512 rows 335 us a round (62 of it that select), of 16384 290.
-    const int64_t first_rows = 16384;
+    const int64_t first_rows = FIRST_ROWS;
     pl.Qpad = (Q + SCAN_QPAD - 1) / SCAN_QPAD * SCAN_QPAD;
     pl.dpad = (scan_cols(ds) + SCAN_BK - 1) / SCAN_BK * SCAN_BK;
 
@@ -389,7 +389,10 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
         }
         last_expected = expected;
         if (last && cut_in_rescore) return RALM_OK;
-        RALM_HIP(launch_select(cand, cnt, pl.cap, pl.k_prime, last ? 0 : tau_rank, Q, tau, lost, flags, stage_no++, expected, stream));
+        if (sp.scores_only)
+            RALM_HIP(launch_select_first(cand, cnt, pl.cap, pl.k_prime, tau_rank, sp.tile_stride, Q, tau, lost, flags, stage_no++, stream));
+        else
+            RALM_HIP(launch_select(cand, cnt, pl.cap, pl.k_prime, last ? 0 : tau_rank, Q, tau, lost, flags, stage_no++, expected, stream));
         return RALM_OK;
     };
 
@@ -413,6 +416,9 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
             if (s > 0) expected = pl.k_prime + (expected - pl.k_prime) * rank_before / pl.k_prime;
             // (with CUs reserved the ladder's last steps are by 2 and admit little)
             rank_before = reserve > 0 ? pl.k_prime : early_rank(k, pl.k_prime, pl.stride[s]);
+            // the first of several stages leaves scores, of which its select reads few, where k' is small and the rows are enough blocks of 32
+            sp.scores_only = s == 0 && pl.n_stages > 1 && pl.k_prime <= FIRST_KEYS && sp.n_row_tiles * SCAN_BM <= FIRST_ROWS &&
+                             (sp.n_row_tiles - 1) * SCAN_BM >= FIRST_ROWS / 2;
             st = run_stage(expected, s + 1 == pl.n_stages, rank_before);
             if (st != RALM_OK) return st;
         }

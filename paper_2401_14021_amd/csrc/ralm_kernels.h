@@ -42,6 +42,7 @@ struct ScanParams {
     int32_t one_per_cu;     // 1: never more workgroups than the CUs that launch_scan is given
     int32_t lists_empty;    // 1: every list is empty and every score of this launch is kept, so list positions
                             // follow from the row's place in the launch (no atomics)
+    int32_t scores_only;    // 1, with lists_empty: the lists are left as launch_select_first reads them
 };
 
 // query tile width chosen for Q
@@ -110,6 +111,12 @@ struct CertifyParams {
 hipError_t launch_select(u64 *cand, uint32_t *cnt, uint32_t cap, int32_t k_prime, int32_t tau_rank, int64_t Q, u64 *tau,
                          uint32_t *lost, int32_t *flags, int32_t stage, int64_t expected,
                          hipStream_t stream);
+
+// The same behind a launch that kept every score as scores (ScanParams::scores_only) of every tile_stride-th tile, for k' = FIRST_KEYS at most
+// and at least FIRST_ROWS / 2 rows: the list's area holds FIRST_ROWS scores and the best of every 32 of them.
+constexpr int FIRST_ROWS = 16384, FIRST_KEYS = 64;
+hipError_t launch_select_first(u64 *cand, uint32_t *cnt, uint32_t cap, int32_t k_prime, int32_t tau_rank, int64_t tile_stride, int64_t Q, u64 *tau,
+                               uint32_t *lost, int32_t *flags, int32_t stage, hipStream_t stream);
 
 // per query: exact scores of the k' best rows of its list, final ranking, top k out;
 // with cert.flags: the result is checked and queries that fail are queued for launch_exact_pass

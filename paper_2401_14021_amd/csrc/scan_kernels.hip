@@ -85,6 +85,30 @@ __device__ __forceinline__ void store_block_all(const ScanParams &p, const f32x1
     }
 }
 
+// The same where a select that looks at few of these scores follows (launch_select_first): the scores alone, half the bytes, in the first
+// 64 KB of the query's list, and behind them the best score of every 32 rows, as the high word of a key.  Slot r is the launch's r-th row, so
+// the row's number need not be kept.
+__device__ __forceinline__ void store_block_scores(const ScanParams &p, const f32x16 &out, int32_t row_id0, int32_t n_rows, int64_t pos0,
+                                                   int q, bool qok)
+{
+    uint32_t best = 0;   // (no score's word)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const uint32_t b = row_id0 + (v >> 2) * 8 + (v & 3) < n_rows ? score_bits(out[v]) : 0u;   // rows past the end are the last row again
+        best = b > best ? b : best;
+    }
+    const uint32_t other = lane_xor<32>(best);   // the other lanes' 16 of the 32 rows
+    best = other > best ? other : best;
+    if (!qok) return;
+    float *dst = reinterpret_cast<float *>(p.cand + (int64_t)q * p.cap);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const f32x4 four = {out[c * 4], out[c * 4 + 1], out[c * 4 + 2], out[c * 4 + 3]};
+        *reinterpret_cast<f32x4 *>(dst + pos0 + c * 8) = four;
+    }
+    if ((threadIdx.x & 32) == 0) reinterpret_cast<uint32_t *>(dst + FIRST_ROWS)[pos0 >> 5] = best;
+}
+
 // Epilogue of a launch whose thresholds admit many of a tile's scores.  Taken one by one (above) they
 // fill the parking list many times over, and every one that finds it full costs a round trip to its
 // query's length.  Here the tile's scores stay in the accumulators, each lane counts those of its
@@ -155,7 +179,8 @@ __device__ __forceinline__ void select_tile_counted(const ScanParams &p, const f
 enum {
     KEEP_PARKED,    // the few that pass selective thresholds, by way of a list in LDS (select_block_parked)
     KEEP_COUNTED,   // those that pass thresholds which admit many of a tile (select_tile_counted)
-    KEEP_ALL        // every score, into empty lists (store_block_all)
+    KEEP_ALL,       // every score, into empty lists (store_block_all)
+    KEEP_SCORES     // the same as scores and bests of 32 (store_block_scores)
 };
 
 // ---- direct-to-LDS pipelined kernel ----------------------------------------------------------
@@ -247,7 +272,7 @@ __global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams 
     };
     const int KT = p.dpad / BK;
     const int n_mine = vb < total ? (total - vb + G - 1) / G : 0;
-    if constexpr (KEEP == KEEP_ALL) {
+    if constexpr (KEEP == KEEP_ALL || KEEP == KEEP_SCORES) {
         // every list ends up with one entry per row of the launch; only its last tile can be partial
         if (blockIdx.x == 0) {
             const int64_t rows = (p.n_row_tiles - 1) * SCAN_BM, left = p.N - visited_tile(p, p.n_row_tiles - 1) * SCAN_BM;
@@ -561,6 +586,10 @@ __global__ __launch_bounds__(WM *WN * 64) void scan_dma_kernel(const ScanParams 
                             store_block_all(p, outs[mm % (LAG + 1)], row0 + (wm * TM + i) * 32 + (lane >> 5) * 4,
                                             (int64_t)cur_rt * BM + (wm * TM + i) * 32 + (lane >> 5) * 4,
                                             q0 + (wn * TN + j) * 32 + fr, qok[j]);
+                        else if constexpr (KEEP == KEEP_SCORES)
+                            store_block_scores(p, outs[mm % (LAG + 1)], row0 + (wm * TM + i) * 32 + (lane >> 5) * 4, n_rows,
+                                               (int64_t)cur_rt * BM + (wm * TM + i) * 32 + (lane >> 5) * 4,
+                                               q0 + (wn * TN + j) * 32 + fr, qok[j]);
                         else
                             select_block(outs[mm % (LAG + 1)], row0 + (wm * TM + i) * 32, q0 + (wn * TN + j) * 32, tsc[j]);
                     }
@@ -745,29 +774,32 @@ bool few_tiles(const ScanParams &p, int n_cu)
 // 36.9; 3 queries, which have half tiles anyway, 8.1, 8.4.  Whole calls of one or two stages, whole tiles and quarters: 40 over 300 000 x 16
 // 56.2, 54.5, 300 over 300 000 x 64 152, 143, 200 over 5000 x 768 54, 38, 300 over 20 000 x 4096 311, 294, 500 over 20 000 x 8192 576, 561;
 // fp32 rows: 40 over 300 000 x 64 65.9, 64.9, 100 over 300 000 x 768 230, 220, 400 over 20 000 x 8192 903, 840.
-template <bool F16>
+template <bool F16, int KEEP>
 hipError_t launch_quarter(const ScanParams &p, int n_cu, hipStream_t stream)
 {
     switch (scan_bn_for(p.Q)) {
-        case 64: return launch_dma_variant<F16, 2, 2, 1, 1, 64, 6, false, 6, 2, false, KEEP_ALL>(p, n_cu, stream);
-        case 128: return launch_dma_variant<F16, 2, 4, 1, 1, 64, 5, false, 5, 2, false, KEEP_ALL>(p, n_cu, stream);
-        default: return launch_dma_variant<F16, 2, 4, 1, 2, 64, 3, false, 3, 2, false, KEEP_ALL>(p, n_cu, stream);
+        case 64: return launch_dma_variant<F16, 2, 2, 1, 1, 64, 6, false, 6, 2, false, KEEP>(p, n_cu, stream);
+        case 128: return launch_dma_variant<F16, 2, 4, 1, 1, 64, 5, false, 5, 2, false, KEEP>(p, n_cu, stream);
+        default: return launch_dma_variant<F16, 2, 4, 1, 2, 64, 3, false, 3, 2, false, KEEP>(p, n_cu, stream);
     }
 }
+template <int KEEP>
 hipError_t launch_quarter_f32(const ScanParams &p, int n_cu, hipStream_t stream)
 {
     switch (scan_bn_for(p.Q)) {
-        case 64: return launch_dma_variant<false, 2, 2, 1, 1, 64, 4, false, 3, 0, true, KEEP_ALL>(p, n_cu, stream);
-        case 128: return launch_dma_variant<false, 2, 4, 1, 1, 32, 5, false, 5, 0, true, KEEP_ALL>(p, n_cu, stream);
-        default: return launch_dma_variant<false, 2, 4, 1, 2, 32, 4, false, 4, 0, true, KEEP_ALL>(p, n_cu, stream);
+        case 64: return launch_dma_variant<false, 2, 2, 1, 1, 64, 4, false, 3, 0, true, KEEP>(p, n_cu, stream);
+        case 128: return launch_dma_variant<false, 2, 4, 1, 1, 32, 5, false, 5, 0, true, KEEP>(p, n_cu, stream);
+        default: return launch_dma_variant<false, 2, 4, 1, 2, 32, 4, false, 4, 0, true, KEEP>(p, n_cu, stream);
     }
 }
 
 template <bool F16>
 hipError_t launch_16(const ScanParams &p, int route, bool nt, int n_cu, hipStream_t stream)
 {
-    if (route == RALM_SCAN_ALL_QUARTERS) return launch_quarter<F16>(p, n_cu, stream);
-    if (route == RALM_SCAN_ALL) return launch_kept<F16, false, KEEP_ALL>(p, n_cu, stream);
+    if (route == RALM_SCAN_ALL_QUARTERS)
+        return p.scores_only ? launch_quarter<F16, KEEP_SCORES>(p, n_cu, stream) : launch_quarter<F16, KEEP_ALL>(p, n_cu, stream);
+    if (route == RALM_SCAN_ALL)
+        return p.scores_only ? launch_kept<F16, false, KEEP_SCORES>(p, n_cu, stream) : launch_kept<F16, false, KEEP_ALL>(p, n_cu, stream);
     if (route == RALM_SCAN_COUNTED)
         return nt ? launch_kept<F16, true, KEEP_COUNTED>(p, n_cu, stream) : launch_kept<F16, false, KEEP_COUNTED>(p, n_cu, stream);
     return nt ? launch_dma<F16, true>(p, n_cu, stream) : launch_dma<F16, false>(p, n_cu, stream);
@@ -828,8 +860,10 @@ hipError_t launch_scan(const ScanParams &p, int n_cu, hipStream_t stream)
     const bool nt = p.Q <= 256 && whole_lines(p);
     if (route == RALM_SCAN_HELD) return launch_scan_held(p, nt, n_cu, stream);
     if (p.in_dtype == DT_F32) {
-        if (route == RALM_SCAN_ALL_QUARTERS) return launch_quarter_f32(p, n_cu, stream);
-        if (route == RALM_SCAN_ALL) return launch_f32<false, KEEP_ALL>(p, n_cu, stream);
+        if (route == RALM_SCAN_ALL_QUARTERS)
+            return p.scores_only ? launch_quarter_f32<KEEP_SCORES>(p, n_cu, stream) : launch_quarter_f32<KEEP_ALL>(p, n_cu, stream);
+        if (route == RALM_SCAN_ALL)
+            return p.scores_only ? launch_f32<false, KEEP_SCORES>(p, n_cu, stream) : launch_f32<false, KEEP_ALL>(p, n_cu, stream);
         if (route == RALM_SCAN_COUNTED) return nt ? launch_f32<true, KEEP_COUNTED>(p, n_cu, stream) : launch_f32<false, KEEP_COUNTED>(p, n_cu, stream);
         return nt ? launch_f32<true, KEEP_PARKED>(p, n_cu, stream) : launch_f32<false, KEEP_PARKED>(p, n_cu, stream);
     }

@@ -260,18 +260,19 @@ struct SelectShared {
 // keys are distinct) in out[0, rank), in any order.  All NT threads of a workgroup; out is in
 // LDS and complete when the function returns; c is not read after that.
 // early: the wanted key, or if 0 < early_rank < rank a better one that at least early_rank of the list reach, as few as the bins tell apart.
-template <int NT>
+// REGS: keys per thread that are held in registers.
+template <int NT, int REGS = SEL_REGS>
 __device__ __forceinline__ u64 select_best(const u64 *__restrict__ c, uint32_t n, uint32_t rank, SelectShared<NT> &sh, u64 *out,
                                            uint32_t early_rank, u64 &early)
 {
     constexpr int SEL_BINS = 2 * NT, SEL_WAVES = NT / 64;
     const bool want_early = early_rank > 0 && early_rank < rank;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const bool in_regs = n <= (uint32_t)(SEL_REGS * NT);
-    u64 reg[SEL_REGS];
+    const bool in_regs = n <= (uint32_t)(REGS * NT);
+    u64 reg[REGS];
     if (in_regs) {
 #pragma unroll
-        for (int i = 0; i < SEL_REGS; ++i) {
+        for (int i = 0; i < REGS; ++i) {
             const uint32_t at = (uint32_t)(i * NT + tid);
             reg[i] = at < n ? c[at] : 0ull;    // 0 is no key: scores of any value have non-zero keys
         }
@@ -280,7 +281,7 @@ __device__ __forceinline__ u64 select_best(const u64 *__restrict__ c, uint32_t n
     auto each = [&](auto f) __attribute__((always_inline)) {
         if (in_regs) {
 #pragma unroll
-            for (int i = 0; i < SEL_REGS; ++i)
+            for (int i = 0; i < REGS; ++i)
                 if ((uint32_t)(i * NT) < n) f(reg[i]);
         } else {
             for (uint32_t i = 0; i < n; i += NT) f(i + tid < n ? c[i + tid] : 0ull);
@@ -465,6 +466,55 @@ __global__ __launch_bounds__(NT) void select_kernel(u64 *__restrict__ cand, uint
     }
 }
 
+// The first select of a ladder, of the lists that a scan left as scores (ScanParams::scores_only).  The k' blocks of 32
+// rows whose best scores are the highest hold the k' best keys: so many rows score at least as much as the least of those, and a
+// block that is left out has no better one (of blocks with that very best the first are taken, whose rows have the lower ids).  So
+// 2 KB of bests and k' x 128 bytes are read per query, and not 128 KB of keys.  A thread has one best and four scores: what bounds it is
+// the chain, and how much code is fetched for it (one wave per query with 8 bests and 32 scores per lane, all unrolled: 17 us for 3 lists).
+//   select_kernel before, now: 3 lists 9.3, , 81 lists , 1024 lists , 2341 lists  us
+constexpr int SF_THREADS = 512;
+__global__ __launch_bounds__(SF_THREADS) void select_first_kernel(u64 *__restrict__ cand, uint32_t *__restrict__ cnt, uint32_t cap, int k_prime,
+                                                                  int tau_rank, int64_t tile_stride, u64 *__restrict__ tau,
+                                                                  uint32_t *__restrict__ lost, int32_t *__restrict__ flags, int stage)
+{
+    constexpr int PER = FIRST_KEYS * 32 / SF_THREADS;   // scores per thread
+    static_assert(FIRST_ROWS / 32 == SF_THREADS, "one block of 32 rows per thread");
+    __shared__ SelectShared<SF_THREADS> sh;
+    __shared__ u64 s_key[FIRST_KEYS * 32], s_out[FIRST_KEYS];
+    const int64_t q = blockIdx.x;
+    const int tid = threadIdx.x;
+    u64 *c = cand + q * (int64_t)cap;
+    const float *scores = reinterpret_cast<const float *>(c);
+    const uint32_t best = reinterpret_cast<const uint32_t *>(scores + FIRST_ROWS)[tid];   // (all of them lie in the list)
+    const uint32_t n = list_length(cnt[q * CNT_PITCH], q, cap, lost, flags, stage);        // more than FIRST_ROWS / 2
+    const int nb = (int)((n + 31) / 32);
+    if (tid < nb) s_key[tid] = (u64)best << 32 | (uint32_t)(0x7fffffff - tid);   // distinct, and the first of equal ones the better
+    __syncthreads();
+    u64 early;
+    select_best<SF_THREADS, 1>(s_key, (uint32_t)nb, (uint32_t)k_prime, sh, s_out, 0, early);
+    float f[PER];
+    int32_t at[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int j = i * SF_THREADS + tid;   // 32 threads a block
+        at[i] = j < k_prime * 32 ? key_id(s_out[j >> 5]) * 32 + (j & 31) : 0x7fffffff;
+        f[i] = (uint32_t)at[i] < n ? scores[at[i]] : 0.f;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int64_t row = (int64_t)(at[i] / SCAN_BM) * tile_stride * SCAN_BM + at[i] % SCAN_BM;
+        if (i * SF_THREADS + tid < k_prime * 32) s_key[i * SF_THREADS + tid] = (uint32_t)at[i] < n ? make_key(f[i], (int32_t)row) : 0ull;
+    }
+    __syncthreads();
+    select_best<SF_THREADS, PER>(s_key, (uint32_t)k_prime * 32, (uint32_t)k_prime, sh, s_out, (uint32_t)tau_rank, early);
+    if (tid < k_prime) c[tid] = s_out[tid];
+    if (tid == 0) {
+        tau[q] = early;
+        cnt[q * CNT_PITCH] = (uint32_t)k_prime;
+    }
+}
+
 // every exact score ends in this sum over the wave's 64 lane sums (fixed order: the re-score and
 // the exact pass must give a row the same number)
 __device__ __forceinline__ double wave_sum(double x) { return wave64_sum(x); }
@@ -567,27 +617,37 @@ __device__ __forceinline__ RowStats score_rows(const u64 *list, int begin, int e
 
 // |q|^2, every thread of the workgroup gets it: part of the scan's score under L2, and of the rounding bound
 template <int NT>
-__device__ __forceinline__ double query_norm2(const float *__restrict__ qv, int d, double *s_q2 /* [NT / 64] in LDS */)
+__device__ __forceinline__ void query_norm2_part(const float *__restrict__ qv, int d, double *s_q2 /* [NT / 64] in LDS */)
 {
     double q2 = 0.0;
     for (int j = threadIdx.x; j < d; j += NT) q2 += (double)qv[j] * (double)qv[j];
     q2 = wave_sum(q2);
     if ((threadIdx.x & 63) == 0) s_q2[threadIdx.x >> 6] = q2;
-    __syncthreads();
-    q2 = 0.0;
+}
+template <int NT>
+__device__ __forceinline__ double query_norm2_sum(const double *s_q2)   // behind a barrier
+{
+    double q2 = 0.0;
     for (int w = 0; w < NT / 64; ++w) q2 += s_q2[w];
     return q2;
 }
+template <int NT>
+__device__ __forceinline__ double query_norm2(const float *__restrict__ qv, int d, double *s_q2)
+{
+    query_norm2_part<NT>(qv, d, s_q2);
+    __syncthreads();
+    return query_norm2_sum<NT>(s_q2);
+}
 
+// floor: the admission key of the last stage; truncated: the list lost entries.
 // The margin of query q and the verdict of the check (one thread): `rank_k` is the key at rank k of the
 // n re-scored candidates, the statistics are those of all of them.
 template <bool L2>
 __device__ void certify(const CertifyParams &cert, float *__restrict__ out_margin, int64_t q, int cnt_pitch, int n, int k,
-                        int k_prime, int d, double q2, u64 rank_k, u64 min_scan, double e2, double x2m)
+                        int k_prime, int d, double q2, u64 rank_k, u64 min_scan, double e2, double x2m, u64 floor, bool truncated)
 {
     const float q_sq = L2 ? (float)q2 : 0.f;
     // rows that reach the worst kept key were not admitted if the last stage's admission key lies above it
-    const u64 floor = cert.flags ? cert.tau_exact[q] : 0ull;
     const bool open = floor > min_scan && n >= k_prime;
     // margin: exact score at rank k minus the scan's score of the worst kept candidate.  A row
     // that was not kept has a scan score at most the latter (the admission key's, if that is higher), so it can belong in the top k only
@@ -609,7 +669,6 @@ __device__ void certify(const CertifyParams &cert, float *__restrict__ out_margi
     double hard = (uq + ux + uq * ux) * qn * xn + (double)d * 5.9604644775390625e-08 * qn * xn;
     if (L2) hard = 2.0 * hard + (ux * ux + (double)d * 5.9604644775390625e-08) * x2m;
     const double soft = n > 0 ? 8.0 * sqrt(e2 / (double)n) : 0.0;
-    const bool truncated = cert.lost && cert.lost[q] != 0;
     const bool all_rows = n < k_prime && !truncated;
     const double m = (double)margin;
     const bool soft_ok = all_rows || (!truncated && n >= k && (m > soft || (soft == 0.0 && m >= 0.0 && !open)));
@@ -664,8 +723,13 @@ __global__ __launch_bounds__(RS_THREADS) void rescore_kernel(const u64 *__restri
     u64 key[K];
     const bool ahead = wave == 0 && cap >= WAVE_KEYS;
     if (ahead) wave_load<K>(key, mine, WAVE_KEYS);
-    const double q2 = stats ? query_norm2<RS_THREADS>(qv, d, s_q2) : 0.0;
+    if (stats) query_norm2_part<RS_THREADS>(qv, d, s_q2);
     if (tid < RS_COUNT_MAX) s_rank[tid] = 0;
+    // what the check needs at the end travels with the rows
+    const bool checks = cert.flags && tid == 0;
+    const u64 floor = checks ? cert.tau_exact[q] : 0ull;
+    const uint32_t lost_before = checks && cert.lost ? cert.lost[q] : 0u;
+    const uint32_t raw_length = n_list;
     n_list = cert.flags ? list_length(n_list, q, cap, cert.lost, cert.flags, cert.stage) : (n_list < cap ? n_list : cap);
     int n = (int)n_list;
     if (n > k_prime) {
@@ -685,6 +749,7 @@ __global__ __launch_bounds__(RS_THREADS) void rescore_kernel(const u64 *__restri
         for (int i = tid; i < n; i += RS_THREADS) list[i] = mine[i];
     }
     __syncthreads();
+    const double q2 = L2 && stats ? query_norm2_sum<RS_THREADS>(s_q2) : 0.0;
     const RowStats st = score_rows<EX, L2, RS_WAVES>(list, 0, n, qv, L2 ? (float)q2 : 0.f, exact, ld, d, stats, keys);
     if (lane == 0) {
         s_min_scan[wave] = st.min_scan;
@@ -728,8 +793,8 @@ __global__ __launch_bounds__(RS_THREADS) void rescore_kernel(const u64 *__restri
             all.e2 += s_e2[w];
             all.x2max = s_x2[w] > all.x2max ? s_x2[w] : all.x2max;
         }
-        certify<L2>(cert, out_margin, q, cnt_pitch, n, k, k_prime, d, q2, n >= k ? ranked[k - 1] : 0ull, all.min_scan, all.e2,
-                    all.x2max);
+        certify<L2>(cert, out_margin, q, cnt_pitch, n, k, k_prime, d, L2 ? q2 : query_norm2_sum<RS_THREADS>(s_q2), n >= k ? ranked[k - 1] : 0ull,
+                    all.min_scan, all.e2, all.x2max, floor, lost_before != 0 || raw_length > cap);
     }
 }
 
@@ -819,7 +884,7 @@ __global__ __launch_bounds__(NT) void rescore_rank_kernel(const u64 *__restrict_
             all.x2max = x2 > all.x2max ? x2 : all.x2max;
         }
         certify<L2>(cert, out_margin, q, CNT_PITCH, n, k, k_prime, d, q2, n >= k ? keys[k - 1] : 0ull, all.min_scan, all.e2,
-                    all.x2max);
+                    all.x2max, cert.flags ? cert.tau_exact[q] : 0ull, cert.lost && cert.lost[q] != 0);
     }
 }
 
@@ -1107,6 +1172,16 @@ hipError_t launch_select(u64 *cand, uint32_t *cnt, uint32_t cap, int32_t k_prime
     else
         hipLaunchKernelGGL(select_kernel<SEL_THREADS>, dim3((unsigned)Q), dim3(SEL_THREADS), smem, stream, cand, cnt, cap,
                            k_prime, tau_rank, tau, lost, flags, stage);
+    return hipGetLastError();
+}
+
+hipError_t launch_select_first(u64 *cand, uint32_t *cnt, uint32_t cap, int32_t k_prime, int32_t tau_rank, int64_t tile_stride, int64_t Q, u64 *tau,
+                               uint32_t *lost, int32_t *flags, int32_t stage, hipStream_t stream)
+{
+    if (Q <= 0) return hipSuccess;
+    if (k_prime > FIRST_KEYS || cap < FIRST_ROWS) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(select_first_kernel, dim3((unsigned)Q), dim3(SF_THREADS), 0, stream, cand, cnt, cap, k_prime, tau_rank, tile_stride, tau, lost,
+                       flags, stage);
     return hipGetLastError();
 }
 
