@@ -103,133 +103,6 @@ __device__ u64 radix_kth(const u64 *__restrict__ c, uint32_t n, uint32_t rank, R
     return kth;
 }
 
-// ---- the best `rank` keys of a list that one wave holds in registers -----------------------------
-// The wanted score is bracketed by halving: a step counts the keys at or above the middle with one compare and one ballot per
-// register, no LDS and no barrier.  It stops as soon as exactly `rank` keys lie above, after about a dozen steps for scores that
-// differ; equal scores at the edge are told apart by the low words in the same way.  Lanes without a key hold zero.
-template <int K>
-__device__ __forceinline__ uint32_t wave_count(const uint32_t (&v)[K], uint32_t least)
-{
-    uint32_t n = 0;
-#pragma unroll
-    for (int i = 0; i < K; ++i) n += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(v[i] >= least));
-    return n;
-}
-// Halves [lo, hi) until the value at lo is reached by at least `rank` and at most `most` of the wave's values, or has no other left
-// beside it.  lo, hi and rank are uniform; on entry n values reach lo, n >= rank, and fewer than rank reach hi; on return n is that of
-// the result.  early, n_early: the smallest count seen on the way that is at least early_rank, and what is reached by it.
-template <int K>
-__device__ __forceinline__ uint32_t wave_bracket(const uint32_t (&v)[K], uint32_t lo, uint32_t hi, uint32_t rank, uint32_t most, uint32_t &n,
-                                                 uint32_t early_rank, uint32_t &early, uint32_t &n_early)
-{
-    early = lo;
-    n_early = n;
-    while (n > most && hi - lo > 1) {
-        const uint32_t mid = lo + (hi - lo) / 2, m = wave_count<K>(v, mid);
-        if (m >= early_rank && m < n_early) {
-            early = mid;
-            n_early = m;
-        }
-        if (m >= rank) {
-            lo = mid;
-            n = m;
-        } else {
-            hi = mid;
-        }
-    }
-    return lo;
-}
-// the largest value of the wave (exchanges without LDS: a step of a shuffle is ten times as long)
-__device__ __forceinline__ uint32_t wave_max(uint32_t v)
-{
-    auto larger = [](uint32_t a, uint32_t b) { return a > b ? a : b; };
-    v = larger(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, false));    // lane ^ 1
-    v = larger(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, false));    // lane ^ 2
-    v = larger(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, false));   // the other quad of the 8
-    v = larger(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, false));   // the other half of the 16
-    const uint32_t a = larger((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16));
-    const uint32_t b = larger((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48));
-    return larger(a, b);
-}
-__device__ __forceinline__ uint32_t wave_min(uint32_t v) { return ~wave_max(~v); }
-
-// The rank-th best of the wave's K * 64 registers, of which n >= rank >= 1 hold keys.  early_rank, early: see select_best.
-template <int K>
-__device__ __forceinline__ u64 wave_kth(const u64 (&key)[K], uint32_t n, uint32_t rank, uint32_t early_rank, u64 &early)
-{
-    uint32_t b[K], least = 0xffffffffu, most = 0u;
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-        b[i] = (uint32_t)(key[i] >> 32);
-        least = key[i] && b[i] < least ? b[i] : least;
-        most = b[i] > most ? b[i] : most;
-    }
-    const uint32_t hi = wave_max(most);
-    // (the best score: 0xffffffff has no value above it, but is no score of a finite key)
-    const uint32_t end = hi == 0xffffffffu ? hi : hi + 1;
-    if (early_rank == 0 || early_rank > rank) early_rank = rank;
-    uint32_t e, n_e, none, n_none;
-    const uint32_t at = wave_bracket<K>(b, wave_min(least), end, rank, rank, n, early_rank, e, n_e);
-    // the keys at the edge: those of the smallest score that reaches `at`
-    uint32_t edge = 0xffffffffu;
-#pragma unroll
-    for (int i = 0; i < K; ++i) edge = b[i] >= at && b[i] < edge ? b[i] : edge;
-    edge = wave_min(edge);
-    uint32_t low[K], cut = 1u;
-#pragma unroll
-    for (int i = 0; i < K; ++i) low[i] = key[i] && b[i] == edge ? (uint32_t)key[i] : 0u;   // (ids are below 2^31 - 1: no key's low word is zero)
-    if (n > rank) {   // equal scores at the edge
-        const uint32_t want = rank - (edge == 0xffffffffu ? 0u : wave_count<K>(b, edge + 1));
-        uint32_t m = wave_count<K>(low, 1u);
-        cut = wave_bracket<K>(low, 1u, 0x80000000u, want, want, m, want, none, n_none);
-    }
-    uint32_t worst = 0xffffffffu;
-#pragma unroll
-    for (int i = 0; i < K; ++i) worst = low[i] >= cut && low[i] < worst ? low[i] : worst;
-    const u64 kth = (u64)edge << 32 | wave_min(worst);
-    early = kth;
-    if (early_rank < rank && n_e <= rank) {
-        // any key between the two ranks serves, the nearer to early_rank the better; this many steps are enough to get near
-        uint32_t from = e, to = end;
-        for (int step = 0; step < 6 && n_e > early_rank + (rank - early_rank) / 4 && to - from > 1; ++step) {
-            const uint32_t mid = from + (to - from) / 2, m = wave_count<K>(b, mid);
-            if (m >= early_rank) {
-                from = mid;
-                n_e = m;
-            } else {
-                to = mid;
-            }
-        }
-        const u64 k = (u64)from << 32;
-        if (k > kth) early = k;
-    }
-    return kth;
-}
-// the `rank` keys from kth on, in any order; f(position, key)
-template <int K, class F>
-__device__ __forceinline__ void wave_compact(const u64 (&key)[K], u64 kth, uint32_t rank, F f)
-{
-    uint32_t base = 0;
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-        const bool keep = key[i] >= kth;   // kth is a key, so zeros never pass
-        const unsigned long long m = __builtin_amdgcn_ballot_w64(keep);
-        const uint32_t at = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-        if (keep && at < rank) f(at, key[i]);
-        base += (uint32_t)__builtin_popcountll(m);
-    }
-}
-template <int K>
-__device__ __forceinline__ void wave_load(u64 (&key)[K], const u64 *__restrict__ c, uint32_t n)
-{
-    const uint32_t lane = threadIdx.x & 63;
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-        const uint32_t at = (uint32_t)i * 64 + lane;
-        key[i] = at < n ? c[at] : 0ull;    // 0 is no key: scores of any value have non-zero keys
-    }
-}
-
 // ---- the best `rank` keys of a list -----------------------------------------------------------
 // The digits of a radix descent are a poor histogram for scores: the top byte of a float is its
 // sign and most of its exponent, so thousands of keys fall into two or three bins and their LDS
@@ -241,7 +114,6 @@ __device__ __forceinline__ void wave_load(u64 (&key)[K], const u64 *__restrict__
 // lists 65 -> 38 us, 2341 lists 227 -> 113 us.  A range that is not positive and finite, or a bin with more keys
 // than SEL_BIN_KEYS (many equal or nearly equal scores), takes the radix descent.
 constexpr int SEL_REGS = 16, SEL_BIN_KEYS = 1024;
-constexpr int WAVE_KEYS = 512;   // keys that one wave selects from
 
 template <int NT>
 struct SelectShared {
@@ -441,23 +313,12 @@ __global__ __launch_bounds__(NT) void select_kernel(u64 *__restrict__ cand, uint
         if (tid == 0) cnt[q * CNT_PITCH] = n;   // (tau is 0 still)
         return;
     }
-    u64 early, kth;
-    // A short list is one wave's work: no LDS, no barriers.
-    if (n <= (uint32_t)WAVE_KEYS) {   // (uniform)
-        if (tid >= 64) return;
-        auto cut = [&](auto size) __attribute__((always_inline)) {
-            constexpr int K = decltype(size)::value;
-            u64 key[K];
-            wave_load<K>(key, c, n);
-            kth = wave_kth<K>(key, n, (uint32_t)k_prime, (uint32_t)tau_rank, early);
-            wave_compact<K>(key, kth, (uint32_t)k_prime, [&](uint32_t at, u64 k) { c[at] = k; });
-        };
-        if (n <= 256) cut(std::integral_constant<int, 4>{});
-        else cut(std::integral_constant<int, WAVE_KEYS / 64>{});
-    } else {
-        kth = select_best<NT>(c, n, (uint32_t)k_prime, sh, out, (uint32_t)tau_rank, early);
-        for (int i = tid; i < k_prime; i += NT) c[i] = out[i];
-    }
+    u64 early;
+    // A short list: less code to fetch, for a kernel that is over in a few microseconds.  81 lists of about 200 keys 7.6 us in the general
+    // form, 7.0 by one wave in registers (bracketing the score with ballots), 5.7.
+    if (n <= (uint32_t)(2 * NT)) select_best<NT, 2>(c, n, (uint32_t)k_prime, sh, out, (uint32_t)tau_rank, early);
+    else select_best<NT>(c, n, (uint32_t)k_prime, sh, out, (uint32_t)tau_rank, early);
+    for (int i = tid; i < k_prime; i += NT) c[i] = out[i];
     if (tid == 0) {
         if (tau_rank > 0) {   // (an admission key is never lowered: what it kept out stays out)
             tau[q] = early > before ? early : before;
@@ -471,7 +332,7 @@ __global__ __launch_bounds__(NT) void select_kernel(u64 *__restrict__ cand, uint
 // block that is left out has no better one (of blocks with that very best the first are taken, whose rows have the lower ids).  So
 // 2 KB of bests and k' x 128 bytes are read per query, and not 128 KB of keys.  A thread has one best and four scores: what bounds it is
 // the chain, and how much code is fetched for it (one wave per query with 8 bests and 32 scores per lane, all unrolled: 17 us for 3 lists).
-//   select_kernel before, now: 3 lists 9.3, , 81 lists , 1024 lists , 2341 lists  us
+// With 128 KB of keys and now: 3 lists 9.5, 9.0 us, 81 lists 12.2, 12.1, 2341 lists 113, 32.
 constexpr int SF_THREADS = 512;
 __global__ __launch_bounds__(SF_THREADS) void select_first_kernel(u64 *__restrict__ cand, uint32_t *__restrict__ cnt, uint32_t cap, int k_prime,
                                                                   int tau_rank, int64_t tile_stride, u64 *__restrict__ tau,
@@ -718,11 +579,7 @@ __global__ __launch_bounds__(RS_THREADS) void rescore_kernel(const u64 *__restri
     const bool stats = out_margin || cert.flags;   // wave-uniform
 
     // the list's length and its first keys travel while |q|^2 is formed (every list has that many slots, or it is the caches')
-    constexpr int K = WAVE_KEYS / 64;
     uint32_t n_list = cnt[q * cnt_pitch];
-    u64 key[K];
-    const bool ahead = wave == 0 && cap >= WAVE_KEYS;
-    if (ahead) wave_load<K>(key, mine, WAVE_KEYS);
     if (stats) query_norm2_part<RS_THREADS>(qv, d, s_q2);
     if (tid < RS_COUNT_MAX) s_rank[tid] = 0;
     // what the check needs at the end travels with the rows
@@ -735,13 +592,8 @@ __global__ __launch_bounds__(RS_THREADS) void rescore_kernel(const u64 *__restri
     if (n > k_prime) {
         n = k_prime;
         u64 none;
-        if (n_list <= WAVE_KEYS && cap >= WAVE_KEYS) {   // one wave's work, see select_kernel
-            if (wave == 0) {
-#pragma unroll
-                for (int i = 0; i < K; ++i) key[i] = i * 64 + lane < (int)n_list ? key[i] : 0ull;
-                const u64 kth = wave_kth<K>(key, n_list, (uint32_t)k_prime, 0, none);
-                wave_compact<K>(key, kth, (uint32_t)k_prime, [&](uint32_t at, u64 k) { list[at] = k; });
-            }
+        if (n_list <= 2 * RS_THREADS) {   // less code to fetch, see select_kernel
+            select_best<RS_THREADS, 2>(mine, n_list, (uint32_t)k_prime, sel, list, 0, none);
         } else {
             select_best<RS_THREADS>(mine, n_list, (uint32_t)k_prime, sel, list, 0, none);
         }
