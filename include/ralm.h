@@ -176,7 +176,8 @@ size_t ralm_workspace_bytes(int64_t Q, const ralm_datastore_t *ds, int32_t k, in
  *   out_margin  optional device fp32 [Q] (may be NULL): exact score of the
  *               rank-k row among the candidates minus the scan score of the
  *               k'-th kept candidate (brought to the same scale under
- *               RALM_METRIC_L2).  A row outside the candidates can belong in
+ *               RALM_METRIC_L2), or minus the score that the last rows had to
+ *               reach to be admitted where that is higher (below).  A row outside the candidates can belong in
  *               the top k only if the scan mis-scored it by at least this
  *               much.  Diagnostic: the library acts on it by itself (above).
  *               +inf when every row was a candidate (N < k').
@@ -187,7 +188,11 @@ size_t ralm_workspace_bytes(int64_t Q, const ralm_datastore_t *ds, int32_t k, in
  *
  * The rows are visited in a fixed strided order, coarse samples first, and a
  * query's candidate list (a fixed number of slots in the workspace) takes only
- * scores that beat the k'-th best of the rows visited before.  Does not
+ * scores that beat a score of the rows visited before: the one of the rank that
+ * the final k'-th best is expected to have in that sample, five standard
+ * deviations and a little more below, never better than a quarter of the way
+ * from rank k to rank k'.  If the order of the rows has it that fewer than k'
+ * rows beat it in the end, the check's margin is taken from it.  Does not
  * synchronise.  If the list of some query overflows (only when the order of
  * the rows is correlated with that stride pattern, e.g. every other 256-row
  * tile holding the best matches), the list keeps what it has, the scan goes
@@ -257,8 +262,8 @@ ralm_status ralm_workspace_counters(const void *workspace, void *stream, ralm_co
  * elements; of a longer ladder (the sequential form) the first
  * RALM_MAX_LADDER_STAGES stages are reported.  Synchronises `stream`.  A
  * diagnostic: with rows in an order that the strided samples represent well a
- * stage that multiplies the rows scanned by g admits about k' (g - 1) scores
- * per query.
+ * stage that multiplies the rows scanned by g admits about r (g - 1) scores
+ * per query, r <= k' the rank of its admission score (ralm_retrieve_topk_ex).
  */
 #define RALM_MAX_LADDER_STAGES 40
 ralm_status ralm_workspace_stage_entries(const void *workspace, void *stream, int32_t *n_stages,
