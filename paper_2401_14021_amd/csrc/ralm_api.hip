@@ -7,12 +7,13 @@
 //   2. the datastore's 256-row tiles are scanned exactly once, in a ladder of stages that
 //      visit them in a progressively finer strided order: stage 0 visits every s0-th tile and
 //      keeps every score (s0 is chosen so that they fit the candidate lists); stage i visits
-//      the tiles at stride s0/g^i that no earlier stage visited.  After each stage the exact
-//      k'-th best key of everything scanned so far becomes the admission key of the next
-//      stage (a valid lower bound on the final k'-th best, because the scanned rows are a
-//      subset of all rows) and each list is cut down to its k' best.  Every stage's rows are
-//      a representative sample, so a stage admits only about k'*(g-1) scores per query.
-//   3. the k' keys left in each list are re-scored from the exact copy and ranked.
+//      the tiles at stride s0/g^i that no earlier stage visited.  After each stage each list is cut
+//      down to the k' best of everything scanned so far, and one of them becomes the admission key of the
+//      next stage: the one at the rank r <= k' that the final k'-th best is expected to have in
+//      that sample, with room for chance (early_rank).  Every stage's rows are
+//      a representative sample, so a stage admits only about r*(g-1) scores per query.
+//   3. the k' keys left in each list are re-scored from the exact copy and ranked, and the result is checked
+//      against what the scan's rounding or an admission key may have kept out.
 #include <hip/hip_runtime.h>
 #include <atomic>
 #include <math.h>

@@ -47,12 +47,12 @@ __device__ __forceinline__ void push_global(const ScanParams &p, int q, u64 key)
 }
 
 // All threads of the workgroup, after a barrier that follows the last append: moves the first n parked
-// entries to the global lists and empties the LDS list.  GROUP (batches of up to 128 queries, one
+// entries to the global lists and empties the LDS list.  GROUP (batches of up to 256 queries, one
 // query tile): the entries of each query are counted in LDS first (`tally`, one word per query): a query's length is then moved once per
 // flush and not once per entry.  Adds to one length are served one after the other wherever they come
 // from (about 13 ns each here), so a stage that admits 3800 scores per query was bound by them.  Q = 8,
 // 1M x 768, k' = 64, refining by 64 at once: whole call 328 -> 271 us.  With more queries an entry of a
-// flush seldom shares its query with another, and the widest tile has no registers to spare.
+// flush seldom shares its query with another.
 template <int NT, bool GROUP>
 __device__ __forceinline__ void flush_parked(const ScanParams &p, const PushList pl, RALM_LDS uint32_t *tally, uint32_t n)
 {
