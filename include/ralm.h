@@ -191,7 +191,8 @@ size_t ralm_workspace_bytes(int64_t Q, const ralm_datastore_t *ds, int32_t k, in
  * scores that beat a score of the rows visited before: the one of the rank that
  * the final k'-th best is expected to have in that sample, five standard
  * deviations and a little more below, never better than a quarter of the way
- * from rank k to rank k'.  If the order of the rows has it that fewer than k'
+ * from rank k to rank k', and never nearer to the score of rank k than what
+ * rounding can do to a score (then it is the k'-th best).  If the order of the rows has it that fewer than k'
  * rows beat it in the end, the check's margin is taken from it.  Does not
  * synchronise.  If the list of some query overflows (only when the order of
  * the rows is correlated with that stride pattern, e.g. every other 256-row

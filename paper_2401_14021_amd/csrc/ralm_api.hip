@@ -10,7 +10,7 @@
 //      the tiles at stride s0/g^i that no earlier stage visited.  After each stage each list is cut
 //      down to the k' best of everything scanned so far, and one of them becomes the admission key of the
 //      next stage: the one at the rank r <= k' that the final k'-th best is expected to have in
-//      that sample, with room for chance (early_rank).  Every stage's rows are
+//      that sample, with room for chance (early_rank), unless it scores about what rank k does (early_gap).  Every stage's rows are
 //      a representative sample, so a stage admits only about r*(g-1) scores per query.
 //   3. the k' keys left in each list are re-scored from the exact copy and ranked, and the result is checked
 //      against what the scan's rounding or an admission key may have kept out.
@@ -293,6 +293,17 @@ int32_t early_rank(int32_t k, int32_t k_prime, int64_t stride)
     return rank < k_prime ? rank : k_prime;
 }
 
+// How far below the score at rank k, as a share of it, an admission key of an early rank has to lie; nearer ones give way to rank k'.
+// Rounding both factors to u moves a score by about 0.6 u |q| |x| / sqrt(d) (root mean square, elements of about the same size), and the check
+// asks for 8 times what it finds: 4.7 u / sqrt(d) of a score whose row points the query's way.  Times five for rows that do not and for
+// queries whose own rounding happens to be large.  What it is for: rows that come many times, one copy behind the other.  1M x 768, us a call
+// with rank k' throughout, no such gap, 12 u and 24 u:
+//   40 copies                      200 queries, k = 10    438, 1436 (29 queries took the exact pass), 388, 388
+//   40 copies with noise of 0.03   200, k = 10            428, 947 (2), 947 (1), 386;  600, k = 20  1106, 1526 (14), 1521 (4), 1005
+//   60 copies with noise of 0.01   600, k = 20            1199, 5790 (131), 1567 (8), 1043
+// It costs 0.3 % of a call (mean of 190 over stores in three orders), 5 % at most: 144 queries, k = 250, 400 000 rows sorted by cluster.
+float early_gap(float u, int32_t d) { return 24.f * u / sqrtf((float)d); }
+
 // ---- scan timing aid ------------------------------------------------------------------------
 constexpr int MAX_PROF = 2048;
 bool g_prof_on = false;
@@ -366,6 +377,8 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
                                reinterpret_cast<uint32_t *>(flags), FLAG_BLOCK_BYTES / 4,
                                reinterpret_cast<uint32_t *>(tau), (int64_t)(pl.off_fb - pl.off_tau) / 4, stream));
 
+    const float u = mma_dt == RALM_F16 ? 1.f / 2048.f : 1.f / 256.f;   // 11 / 8 significant bits
+    const float apart = early_gap(u, ds->d);
     sp.Qs = qs; sp.tau = tau; sp.cand = cand; sp.cnt = cnt;
     // one stage: scan the tiles sp describes, then cut every list down to its k' best
     int32_t stage_no = 0;
@@ -391,9 +404,9 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
         last_expected = expected;
         if (last && cut_in_rescore) return RALM_OK;
         if (sp.scores_only)
-            RALM_HIP(launch_select_first(cand, cnt, pl.cap, pl.k_prime, tau_rank, sp.tile_stride, Q, tau, lost, flags, stage_no++, stream));
+            RALM_HIP(launch_select_first(cand, cnt, pl.cap, k, pl.k_prime, tau_rank, apart, sp.tile_stride, Q, tau, lost, flags, stage_no++, stream));
         else
-            RALM_HIP(launch_select(cand, cnt, pl.cap, pl.k_prime, last ? 0 : tau_rank, Q, tau, lost, flags, stage_no++, expected, stream));
+            RALM_HIP(launch_select(cand, cnt, pl.cap, k, pl.k_prime, last ? 0 : tau_rank, apart, Q, tau, lost, flags, stage_no++, expected, stream));
         return RALM_OK;
     };
 
@@ -435,7 +448,6 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
     cert.cnt_rw = cnt;
     cert.tau_exact = tau;
     cert.fb_list = fb_list;
-    const float u = mma_dt == RALM_F16 ? 1.f / 2048.f : 1.f / 256.f;   // 11 / 8 significant bits
     cert.u_query = u;
     cert.u_rows = (scan == ds->exact && scan_dt == ds->exact_dtype && scan_dt != RALM_F32) ? 0.f : u;
     if (cut_in_rescore)

@@ -103,19 +103,20 @@ struct CertifyParams {
 };
 
 // per query: the list cand[q, 0..cnt[q]) is cut down, in place, to its k' best keys (cnt[q] <- min(cnt[q], k')); the admission key
-// tau[q] is raised to one that at least the best tau_rank <= k' of them reach, to the k'-th best itself if tau_rank = k' (0: it stays).  A list
+// tau[q] is raised to one that at least the best tau_rank <= k' of them reach, to the k'-th best itself if tau_rank = k' or if the other would
+// lie nearer to the score at rank k than `apart` times that (0: it stays).  A list
 // that was sent more than cap keys holds the first cap of them: lost[q] is set and the query
 // counted once in flags[FLAG_LADDER_OVERFLOWS].
 // The lists' lengths before the cut are recorded behind the flag block if stage < MAX_STAGE_SUMS.
 // expected: keys that a list should hold (any number is handled).
-hipError_t launch_select(u64 *cand, uint32_t *cnt, uint32_t cap, int32_t k_prime, int32_t tau_rank, int64_t Q, u64 *tau,
+hipError_t launch_select(u64 *cand, uint32_t *cnt, uint32_t cap, int32_t k, int32_t k_prime, int32_t tau_rank, float apart, int64_t Q, u64 *tau,
                          uint32_t *lost, int32_t *flags, int32_t stage, int64_t expected,
                          hipStream_t stream);
 
 // The same behind a launch that kept every score as scores (ScanParams::scores_only) of every tile_stride-th tile, for k' = FIRST_KEYS at most
 // and at least FIRST_ROWS / 2 rows: the list's area holds FIRST_ROWS scores and the best of every 32 of them.
 constexpr int FIRST_ROWS = 16384, FIRST_KEYS = 64;
-hipError_t launch_select_first(u64 *cand, uint32_t *cnt, uint32_t cap, int32_t k_prime, int32_t tau_rank, int64_t tile_stride, int64_t Q, u64 *tau,
+hipError_t launch_select_first(u64 *cand, uint32_t *cnt, uint32_t cap, int32_t k, int32_t k_prime, int32_t tau_rank, float apart, int64_t tile_stride, int64_t Q, u64 *tau,
                                uint32_t *lost, int32_t *flags, int32_t stage, hipStream_t stream);
 
 // per query: exact scores of the k' best rows of its list, final ranking, top k out;

@@ -124,7 +124,7 @@ struct SelectShared {
     u64 bin_keys[SEL_BIN_KEYS];
     uint32_t lo[NT / 64], hi[NT / 64], total[NT / 64];
     uint32_t bin, rest, in_bin, n_bin, n_out;
-    uint32_t early_bin, early_bits;
+    uint32_t early_bin, early_bits, n_above;
     u64 kth;
 };
 
@@ -179,7 +179,7 @@ __device__ __forceinline__ u64 select_best(const u64 *__restrict__ c, uint32_t n
     }
     for (int i = tid; i < SEL_BINS; i += NT) sh.hist[i] = 0;
     if (tid == 0) {
-        sh.n_bin = sh.n_out = 0;
+        sh.n_bin = sh.n_out = sh.n_above = 0;
         sh.early_bits = 0xffffffffu;
     }
     __syncthreads();
@@ -264,6 +264,25 @@ __device__ __forceinline__ u64 select_best(const u64 *__restrict__ c, uint32_t n
     return kth;
 }
 
+// The admission key that select_best found early, or the k'-th best key if `early` lies too near rank k.  Whoever is not admitted scores
+// less than the key, so the gap between the scores at rank k and at the key is what is left of the check's margin where the sample holds a query's
+// best rows all together (copies of one row have no gap at all).  It has to be `apart` times the score: more than the
+// check asks for (early_gap in ralm_api.hip).  out: the k' best keys; all threads, behind select_best.
+template <int NT>
+__device__ __forceinline__ u64 with_margin(u64 early, u64 kth, const u64 *out, int k, int k_prime, float apart, SelectShared<NT> &sh)
+{
+    if (early == kth) return kth;   // uniform
+    const float at = key_score(early);
+    for (int base = 0; base < k_prime; base += NT) {
+        const int i = base + threadIdx.x;
+        const float s = key_score(out[i < k_prime ? i : 0]);   // (s - apart |s| rises with s)
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(i < k_prime && s > at && s - at >= apart * fabsf(s));
+        if ((threadIdx.x & 63) == 0 && m) atomicAdd(&sh.n_above, (uint32_t)__popcll(m));
+    }
+    __syncthreads();
+    return sh.n_above >= (uint32_t)k ? early : kth;
+}
+
 // What select_kernel and the re-score do with a query's list before they read it: the length that the
 // stage left is recorded, and a list that was sent more keys than it has slots, of which it kept the first
 // `cap`, is marked.  Returns the number of keys in the list.
@@ -285,7 +304,7 @@ __device__ uint32_t list_length(uint32_t n, int64_t q, uint32_t cap, uint32_t *_
 }
 
 // Per query: the list is cut down to its k' best keys in place, and a key of rank tau_rank <= k' among them becomes the admission
-// key of the next scan stage (tau_rank 0: there is none).  A list that was sent more keys than
+// key of the next scan stage (tau_rank 0: there is none; with_margin: or the k'-th best).  A list that was sent more keys than
 // it has slots kept only the first `cap` of them: it is processed as it is (its k'-th best key
 // is still a valid lower bound, the rows behind those keys were all scanned) and the query is
 // marked in `lost`, so that it is answered by the exact pass at the end of the call.
@@ -296,7 +315,7 @@ __device__ uint32_t list_length(uint32_t n, int64_t q, uint32_t cap, uint32_t *_
 // of the result (certify) takes the admission key for the score of the best row that may be missing.
 template <int NT>
 __global__ __launch_bounds__(NT) void select_kernel(u64 *__restrict__ cand, uint32_t *__restrict__ cnt,
-                                                             uint32_t cap, int k_prime, int tau_rank, u64 *__restrict__ tau,
+                                                             uint32_t cap, int k, int k_prime, int tau_rank, float apart, u64 *__restrict__ tau,
                                                              uint32_t *__restrict__ lost, int32_t *__restrict__ flags,
                                                              int stage)
 {
@@ -313,12 +332,13 @@ __global__ __launch_bounds__(NT) void select_kernel(u64 *__restrict__ cand, uint
         if (tid == 0) cnt[q * CNT_PITCH] = n;   // (tau is 0 still)
         return;
     }
-    u64 early;
+    u64 early, kth;
     // A short list: less code to fetch, for a kernel that is over in a few microseconds.  81 lists of about 200 keys 7.6 us in the general
     // form, 7.0 by one wave in registers (bracketing the score with ballots), 5.7.
-    if (n <= (uint32_t)(2 * NT)) select_best<NT, 2>(c, n, (uint32_t)k_prime, sh, out, (uint32_t)tau_rank, early);
-    else select_best<NT>(c, n, (uint32_t)k_prime, sh, out, (uint32_t)tau_rank, early);
+    if (n <= (uint32_t)(2 * NT)) kth = select_best<NT, 2>(c, n, (uint32_t)k_prime, sh, out, (uint32_t)tau_rank, early);
+    else kth = select_best<NT>(c, n, (uint32_t)k_prime, sh, out, (uint32_t)tau_rank, early);
     for (int i = tid; i < k_prime; i += NT) c[i] = out[i];
+    early = with_margin<NT>(early, kth, out, k, k_prime, apart, sh);
     if (tid == 0) {
         if (tau_rank > 0) {   // (an admission key is never lowered: what it kept out stays out)
             tau[q] = early > before ? early : before;
@@ -334,8 +354,8 @@ __global__ __launch_bounds__(NT) void select_kernel(u64 *__restrict__ cand, uint
 // the chain, and how much code is fetched for it (one wave per query with 8 bests and 32 scores per lane, all unrolled: 17 us for 3 lists).
 // With 128 KB of keys and now: 3 lists 9.5, 9.0 us, 81 lists 12.2, 12.1, 2341 lists 113, 32.
 constexpr int SF_THREADS = 512;
-__global__ __launch_bounds__(SF_THREADS) void select_first_kernel(u64 *__restrict__ cand, uint32_t *__restrict__ cnt, uint32_t cap, int k_prime,
-                                                                  int tau_rank, int64_t tile_stride, u64 *__restrict__ tau,
+__global__ __launch_bounds__(SF_THREADS) void select_first_kernel(u64 *__restrict__ cand, uint32_t *__restrict__ cnt, uint32_t cap, int k, int k_prime,
+                                                                  int tau_rank, float apart, int64_t tile_stride, u64 *__restrict__ tau,
                                                                   uint32_t *__restrict__ lost, int32_t *__restrict__ flags, int stage)
 {
     constexpr int PER = FIRST_KEYS * 32 / SF_THREADS;   // scores per thread
@@ -368,8 +388,9 @@ __global__ __launch_bounds__(SF_THREADS) void select_first_kernel(u64 *__restric
         if (i * SF_THREADS + tid < k_prime * 32) s_key[i * SF_THREADS + tid] = (uint32_t)at[i] < n ? make_key(f[i], (int32_t)row) : 0ull;
     }
     __syncthreads();
-    select_best<SF_THREADS, PER>(s_key, (uint32_t)k_prime * 32, (uint32_t)k_prime, sh, s_out, (uint32_t)tau_rank, early);
+    const u64 kth = select_best<SF_THREADS, PER>(s_key, (uint32_t)k_prime * 32, (uint32_t)k_prime, sh, s_out, (uint32_t)tau_rank, early);
     if (tid < k_prime) c[tid] = s_out[tid];
+    early = with_margin<SF_THREADS>(early, kth, s_out, k, k_prime, apart, sh);
     if (tid == 0) {
         tau[q] = early;
         cnt[q * CNT_PITCH] = (uint32_t)k_prime;
@@ -1011,7 +1032,7 @@ __global__ __launch_bounds__(SEL_THREADS) void exact_finish_kernel(const u64 *__
 
 }  // namespace
 
-hipError_t launch_select(u64 *cand, uint32_t *cnt, uint32_t cap, int32_t k_prime, int32_t tau_rank, int64_t Q, u64 *tau,
+hipError_t launch_select(u64 *cand, uint32_t *cnt, uint32_t cap, int32_t k, int32_t k_prime, int32_t tau_rank, float apart, int64_t Q, u64 *tau,
                          uint32_t *lost, int32_t *flags, int32_t stage, int64_t expected, hipStream_t stream)
 {
     if (Q <= 0) return hipSuccess;
@@ -1019,20 +1040,20 @@ hipError_t launch_select(u64 *cand, uint32_t *cnt, uint32_t cap, int32_t k_prime
     // lists that should be short are ranked by small workgroups, eight to a CU instead of two: 2341 lists of
     // about 128 keys 11 us instead of 20 (any length is right in either)
     if (expected <= 512)
-        hipLaunchKernelGGL(select_kernel<256>, dim3((unsigned)Q), dim3(256), smem, stream, cand, cnt, cap, k_prime,
-                           tau_rank, tau, lost, flags, stage);
+        hipLaunchKernelGGL(select_kernel<256>, dim3((unsigned)Q), dim3(256), smem, stream, cand, cnt, cap, k, k_prime,
+                           tau_rank, apart, tau, lost, flags, stage);
     else
         hipLaunchKernelGGL(select_kernel<SEL_THREADS>, dim3((unsigned)Q), dim3(SEL_THREADS), smem, stream, cand, cnt, cap,
-                           k_prime, tau_rank, tau, lost, flags, stage);
+                           k, k_prime, tau_rank, apart, tau, lost, flags, stage);
     return hipGetLastError();
 }
 
-hipError_t launch_select_first(u64 *cand, uint32_t *cnt, uint32_t cap, int32_t k_prime, int32_t tau_rank, int64_t tile_stride, int64_t Q, u64 *tau,
+hipError_t launch_select_first(u64 *cand, uint32_t *cnt, uint32_t cap, int32_t k, int32_t k_prime, int32_t tau_rank, float apart, int64_t tile_stride, int64_t Q, u64 *tau,
                                uint32_t *lost, int32_t *flags, int32_t stage, hipStream_t stream)
 {
     if (Q <= 0) return hipSuccess;
     if (k_prime > FIRST_KEYS || cap < FIRST_ROWS) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(select_first_kernel, dim3((unsigned)Q), dim3(SF_THREADS), 0, stream, cand, cnt, cap, k_prime, tau_rank, tile_stride, tau, lost,
+    hipLaunchKernelGGL(select_first_kernel, dim3((unsigned)Q), dim3(SF_THREADS), 0, stream, cand, cnt, cap, k, k_prime, tau_rank, apart, tile_stride, tau, lost,
                        flags, stage);
     return hipGetLastError();
 }

@@ -73,3 +73,48 @@ def test_the_check_knows_what_was_not_admitted():
     assert sc[:, -1].cpu().tolist() == [216.0] * 4
     m = margin.cpu()
     assert ((m >= 216 - 200) & (m <= 216 - 191)).all(), m
+
+
+@pytest.mark.parametrize("Q", [16, 100, 200, 600])
+@pytest.mark.parametrize("k", [10, 20])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+def test_copies_that_lie_together(dtype, k, Q):
+    """Every row 40 times in a row: the first sample holds a query's best k rows and as many of the same score again.  An admission key among
+    those would leave the check no margin; one of rank k' does, and no query may need the exact pass."""
+    from paper_2401_14021_amd import binding as B, inputs
+    copies = 40
+    X, _ = inputs.clustered_datastore(5000, 128, 1000, seed=7, device="cuda")
+    near = torch.arange(Q, device="cuda") % 4 + 1                # their copies lie in tile 0
+    q = inputs.queries_near_rows(X, near, seed=Q, sigma=0.005)
+    ds = B.Datastore.from_fp32(X.repeat_interleave(copies, 0).contiguous(), dtype)
+    ws = B.alloc_workspace(Q, ds, k)
+    ids, _ = B.ralm_retrieve_topk_ex(q, ds, k, workspace=ws)
+    c = B.ralm_workspace_counters(ws)
+    assert c["exact_pass"] == 0 and c["soft_certified"] == Q, c
+    best = (q.double() @ X.double().T).argmax(dim=1)             # its first k copies
+    assert torch.equal(ids.long(), best[:, None] * copies + torch.arange(k, device="cuda"))
+
+
+@pytest.mark.parametrize("Q", [3, 70, 200, 600])
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+def test_equal_scores_around_the_admission_key(oracle, dtype, Q):
+    """Whole numbers, which every type scores exactly: ranks 1 to 40 of the first sample have one score.  Rows of that score that come
+    later have higher ids, so nothing is in doubt and no query may need the exact pass."""
+    from paper_2401_14021_amd import binding as B
+    k = 20
+    X = torch.zeros(N, d)
+    for c in range(4):
+        X[c * 64:c * 64 + 40, c] = 230.0
+        X[c * 64 + 40:c * 64 + 64, c] = 200.0 - torch.arange(24).float()
+        X[701 * 256 + c * 64:701 * 256 + c * 64 + 8, c] = 230.0
+    q = torch.zeros(Q, d)
+    q[torch.arange(Q), torch.arange(Q) % 4] = 1.0
+    ds = B.Datastore(X.cuda()) if dtype == "f32" else B.Datastore.from_fp32(X.cuda(), torch.bfloat16 if dtype == "bf16" else torch.float16)
+    ws = B.alloc_workspace(Q, ds, k)
+    ids, sc = B.ralm_retrieve_topk_ex(q.cuda(), ds, k, workspace=ws)
+    c = B.ralm_workspace_counters(ws)
+    assert c["exact_pass"] == 0 and c["ladder_overflows"] == 0, c
+    wi, wsc = oracle.retrieve_topk(q[:4].numpy(), X.numpy(), k)
+    want = np.arange(Q) % 4
+    np.testing.assert_array_equal(ids.cpu().numpy(), wi[want])
+    np.testing.assert_array_equal(sc.cpu().numpy(), wsc[want])
