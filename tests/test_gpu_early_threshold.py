@@ -12,7 +12,7 @@ N, d = 200_001, 64
 
 def _rows(levels):
     """Column c of four is query c's: tile 0, which every stage's sample has visited, holds 64 rows of the best scores in it, another
-    tile, which only the last stage visits (a prime number of tiles from the first), 100 rows with scores of ranks 40 to 60, and
+    tile, which only the last stage visits (a prime number of tiles from the first), 59 rows with scores of ranks 40 to 60, and
     five of the best."""
     g = torch.Generator().manual_seed(3)
     X = torch.randint(-1, 2, (N, d), generator=g).float()
@@ -69,7 +69,7 @@ def test_the_check_knows_what_was_not_admitted():
     c = B.ralm_workspace_counters(ws)
     assert c["exact_pass"] == 0 and c["soft_certified"] == 4, c
     # The best: five of 240, then 230, 229, ..: rank 20 scores 216.  The admission key of the last stages is the first sample's rank 31
-    # (score 200) or a few ranks worse, above the other tile's 100 rows; the worst kept of 64 candidates scores 172.
+    # (score 200) or a few ranks worse, above the other tile's 59 rows; the worst kept of 64 candidates scores 172.
     assert sc[:, -1].cpu().tolist() == [216.0] * 4
     m = margin.cpu()
     assert ((m >= 216 - 200) & (m <= 216 - 191)).all(), m
@@ -118,3 +118,40 @@ def test_equal_scores_around_the_admission_key(oracle, dtype, Q):
     want = np.arange(Q) % 4
     np.testing.assert_array_equal(ids.cpu().numpy(), wi[want])
     np.testing.assert_array_equal(sc.cpu().numpy(), wsc[want])
+
+
+@pytest.mark.parametrize("Q", [3, 70, 200, 300])
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+def test_a_row_that_rounding_puts_below_the_admission_key(oracle, dtype, Q):
+    """The check has to queue a query whose rank-k score lies within the rounding of the admission key.  Values near 480 (2270 for fp16), where the scan's
+    type counts by two.  Tile 0, 64 rows per query: scan scores 484 (19 rows), 480, 474 (ranks 21 to 31) and 462 (up to rank 64),
+    every one 0.99 off the exact score, which rounding can be 8 times of in the check's eyes: 7.9.  The admission key is 474, 5 below the exact rank-20 score, the
+    worst kept score 462, 17 below it.  Another tile holds a row of the exact score 479.92, before rank 20, whose eight values are each rounded down by 0.99: its
+    scan score 472 is not admitted."""
+    from paper_2401_14021_amd import binding as B
+    k, width = 20, 128
+    base, n = (1792, 3000) if dtype == "f16" else (0, 300)
+    X = torch.zeros(N, width)
+    v = torch.tensor([484.0] * 19 + [480.0] + [474.0] * 11 + [462.0] * 33)
+    off = torch.where(torch.arange(64) % 2 == 0, 0.99, -0.99)     # (rank 20: -0.99)
+    total = 472 + base + 3 * n                                    # of the other tile's row's five positive values, as scanned
+    low = total // 10 * 2
+    five = [low + 2] * ((total - 5 * low) // 2) + [low] * (5 - (total - 5 * low) // 2)
+    for c in range(4):
+        X[c * 64:c * 64 + 64, 8 * c] = v + base + off
+        X[701 * 256 + c, 8 * c:8 * c + 8] = torch.tensor([x + 0.99 for x in five] + [-(n - 0.99)] * 3)
+    q = torch.zeros(Q, width)
+    for i in range(Q):
+        q[i, i % 4 * 8:i % 4 * 8 + 8] = 2.0 ** (i // 4 % 3)
+    ds = B.Datastore(X.cuda()) if dtype == "f32" else B.Datastore.from_fp32(X.cuda(), torch.bfloat16 if dtype == "bf16" else torch.float16)
+    ws, margin = B.alloc_workspace(Q, ds, k), torch.empty(Q, device="cuda")
+    ids, sc = B.ralm_retrieve_topk_ex(q.cuda(), ds, k, workspace=ws, out_margin=margin)
+    c = B.ralm_workspace_counters(ws)
+    assert c["exact_pass"] == Q and c["ladder_overflows"] == 0 and c["unanswered"] == 0, c
+    scale = 2.0 ** (torch.arange(Q) // 4 % 3)
+    assert torch.allclose(margin.cpu(), 5.01 * scale, rtol=0, atol=0.01)   # 479.01 - 474
+    picked = list(range(min(Q, 12)))
+    wi, wsc = oracle.retrieve_topk(q[picked].numpy(), X.numpy(), k)
+    assert (wi[:, -1] == 701 * 256 + np.arange(len(picked)) % 4).all()
+    np.testing.assert_array_equal(ids.cpu().numpy(), wi[np.arange(Q) % 4])
+    np.testing.assert_array_equal(sc.cpu().numpy()[picked], wsc)
