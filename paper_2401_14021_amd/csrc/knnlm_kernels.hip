@@ -37,10 +37,10 @@ __device__ __forceinline__ double block_join(double x, double *red, F f)
     return t;
 }
 
-// One workgroup per query, a thread for every entry or every second one (up to four from 4096 entries on): what bounds it is the chain of
-// ids, scores and tokens from memory, exp, sort and sums, of which a thread with more entries has more in a row.  1024 entries each
-// for 256 queries: 27 us with 256 threads, 21.5 with 1024.
-template <int KP_THREADS>
+// One workgroup per query, KP_MAX_PER entries per thread at most: what bounds it is the chain of ids, scores and tokens from memory, exp, sort
+// and sums, of which a thread with more entries has more in a row, and with many queries how many of their workgroups a CU holds
+// (launch_knnlm_probs has the line and the times).
+template <int KP_THREADS, int KP_MAX_PER>
 __global__ __launch_bounds__(KP_THREADS) void knnlm_probs_kernel(
     const int32_t *__restrict__ ids, const float *__restrict__ scores, int k, int kp2,
     const int32_t *__restrict__ values, int64_t N, double T, int32_t *__restrict__ tokens,
@@ -50,8 +50,7 @@ __global__ __launch_bounds__(KP_THREADS) void knnlm_probs_kernel(
     double *e = reinterpret_cast<double *>(smem);     // [kp2] weight of the entry at each rank
     u64 *keys = reinterpret_cast<u64 *>(e + kp2);      // [kp2] (token, rank), sorted by token then rank
     constexpr int KP_WAVES = KP_THREADS / 64;
-    constexpr int KP_MAX_PER = KP_THREADS == 1024 ? RALM_MAX_K / KP_THREADS : 2;   // entries per thread
-    static_assert(RALM_MAX_K % 1024 == 0 && (RALM_MAX_K & (RALM_MAX_K - 1)) == 0, "a power of two of at least one entry per thread");
+    static_assert((RALM_MAX_K & (RALM_MAX_K - 1)) == 0, "the entries are padded to a power of two");
     __shared__ double red[KP_WAVES];
     __shared__ double s_p[KP_WAVES];
     __shared__ int32_t s_tok[KP_WAVES];
@@ -180,11 +179,19 @@ hipError_t launch_knnlm_probs(const int32_t *ids, const float *scores, int64_t Q
     int kp2 = 2;
     while (kp2 < k) kp2 <<= 1;
     const size_t smem = (size_t)kp2 * 16;
+    // More than 512 entries: with 512 threads four workgroups fit a CU, with 256 eight.  1024 entries each, us a call with 256, 512 and 1024
+    // threads: 128 queries 16.3, 13.3, 13.3; 256 17.4, 13.3, 14.0; 512 20.7, 17.5, 25.5; 1024 28.0, 28.6, 48.0; 1025 29.7, 31.9, 57.2;
+    // 2048 44.8, 47.2, 92.6; 4000 71, 84, 181.
+    constexpr int64_t KP_FEW_QUERIES = 1024;
+    static_assert(RALM_MAX_K <= 1024, "entries per thread");
     if (kp2 <= 512)
-        hipLaunchKernelGGL(knnlm_probs_kernel<256>, dim3((unsigned)Q), dim3(256), smem, stream, ids, scores, k, kp2,
+        hipLaunchKernelGGL((knnlm_probs_kernel<256, 2>), dim3((unsigned)Q), dim3(256), smem, stream, ids, scores, k, kp2,
+                           values, N, T, tokens, weights, top_token, top_prob);
+    else if (Q <= KP_FEW_QUERIES)
+        hipLaunchKernelGGL((knnlm_probs_kernel<512, 2>), dim3((unsigned)Q), dim3(512), smem, stream, ids, scores, k, kp2,
                            values, N, T, tokens, weights, top_token, top_prob);
     else
-        hipLaunchKernelGGL(knnlm_probs_kernel<1024>, dim3((unsigned)Q), dim3(1024), smem, stream, ids, scores, k, kp2,
+        hipLaunchKernelGGL((knnlm_probs_kernel<256, 4>), dim3((unsigned)Q), dim3(256), smem, stream, ids, scores, k, kp2,
                            values, N, T, tokens, weights, top_token, top_prob);
     return hipGetLastError();
 }
