@@ -720,17 +720,21 @@ __global__ __launch_bounds__(CI_THREADS) void cache_insert_kernel(
             todo &= ~safe;
             int used = 0, taken = 64;      // used: the zone's slot that takes the next insertion
             bool round = false;            // the zone is the ring and has been gone round
-            if (__popcll((long long)todo) > 12) {   // (so few are walked faster than compared)
+            const int n_todo = __popcll((long long)todo);
+            if (n_todo > 12 && (n_todo <= zone_n || len < C || zone_n < C)) {   // (so few are walked faster than compared)
                 u64 repeated = 0, in_zone = 0;
-#pragma unroll 8
-                for (int c = 0; c < 64; ++c) {
-                    const int32_t ec = __builtin_amdgcn_readlane(e, c);
-                    repeated |= __ballot(e == ec) & (~1ull << c);
-                    in_zone |= __ballot(zone == ec) && ec >= 0 ? 1ull << c : 0ull;
+                for (int c0 = 0; c0 < 64 && !(todo & in_zone); c0 += 8) {   // (the walk it is as soon as one is found in the zone)
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const int c = c0 + i;
+                        const int32_t ec = __builtin_amdgcn_readlane(e, c);
+                        repeated |= __ballot(e == ec) & (~1ull << c);
+                        in_zone |= __ballot(zone == ec) && ec >= 0 ? 1ull << c : 0ull;
+                    }
                 }
                 const u64 fresh = todo & ~repeated;
                 const int n_fresh = __popcll((long long)fresh);
-                if (!(todo & in_zone) && (n_fresh <= zone_n || len < C || zone_n < C)) {   // wave-uniform
+                if (!(todo & in_zone)) {   // wave-uniform
                     used = n_fresh < zone_n ? n_fresh : zone_n;
                     const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(fresh >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)fresh, 0u));
                     const bool mine = (fresh >> lane) & 1;

@@ -38,3 +38,27 @@ def test_new_ids_together(oracle, C, n_new):
         got = dc.cpu().numpy()
         for r in range(R):
             assert np.array_equal(got[r, :wl[r]], wi[r, :wl[r]]), r
+
+
+@pytest.mark.parametrize("at", [(0,), (7,), (8,), (31, 40), (63,), (120,), tuple(range(0, 160, 3))])   # places of ids that wait to be evicted
+@pytest.mark.parametrize("C", [16, 40, 63, 64, 65, 100, 500])
+def test_new_ids_and_ids_that_wait_to_be_evicted(oracle, C, at):
+    """Full rings: what is in one of the next 64 slots is a member or not by what was put in before it is asked for."""
+    from paper_2401_14021_amd import binding as B
+    rng = np.random.default_rng(C + len(at) + at[0])
+    R, k, N = 12, 160, 1_000_000
+    off = np.arange(R + 1).astype(np.int64)
+    cache = np.stack([rng.choice(N // 2, size=C, replace=False) for _ in range(R)]).astype(np.int32)
+    heads = rng.integers(0, C, size=R).astype(np.int32)
+    lens = np.full(R, C, dtype=np.int32)
+    truth = np.stack([N // 2 + rng.choice(N // 2, size=k, replace=False) for _ in range(R)]).astype(np.int32)
+    for r in range(R):
+        truth[r, list(at)] = cache[r, (heads[r] + rng.integers(0, min(C, 64), size=len(at))) % C]
+        if r % 3 == 0:
+            truth[r, 70:] = truth[r, rng.integers(0, 70, size=90)]       # few different ones
+    wi, wl, wh = oracle.cache_insert(cache, lens, heads, truth, off, N=N, p=k, n_next=0)
+    dc, dl, dh = (torch.from_numpy(x.copy()).cuda() for x in (cache, lens, heads))
+    B.ralm_cache_insert(dc, dl, dh, torch.from_numpy(truth).cuda(), torch.from_numpy(off).cuda(), N, p=k)
+    np.testing.assert_array_equal(dl.cpu().numpy(), wl)
+    np.testing.assert_array_equal(dh.cpu().numpy(), wh)
+    np.testing.assert_array_equal(dc.cpu().numpy(), wi)
