@@ -290,6 +290,15 @@ ralm_status ralm_scan_routes(int64_t Q, const ralm_datastore_t *ds, int32_t k, i
                              int32_t *n_stages, int32_t *routes);
 
 /*
+ * Whether the first stage of such a call (RALM_SCAN_ALL or
+ * RALM_SCAN_ALL_QUARTERS) leaves bare scores and the best of every 32 rows, of
+ * which its select reads few (*scores_only = 1), or a key per row (0).  Host
+ * only, as ralm_scan_routes.  A diagnostic.
+ */
+ralm_status ralm_first_stage_scores(int64_t Q, const ralm_datastore_t *ds, int32_t k, int32_t k_prime,
+                                    int32_t *scores_only);
+
+/*
  * Build the low-precision scan copy of a datastore: dst[j, c] = round-to-
  * nearest-even(src[j, c]) in dst_dtype (RALM_BF16 or RALM_F16).  src is device
  * fp32 [N, d] with pitch src_stride elements, dst device [N, d] with pitch

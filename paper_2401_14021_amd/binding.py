@@ -69,6 +69,7 @@ def lib() -> ctypes.CDLL:
         L.ralm_workspace_counters.argtypes = [vp, vp, ctypes.POINTER(ralm_counters_t)]
         L.ralm_workspace_stage_entries.argtypes = [vp, vp, ctypes.POINTER(i32), ctypes.POINTER(i64)]
         L.ralm_scan_routes.argtypes = [i64, dsp, i32, i32, ctypes.POINTER(i32), ctypes.POINTER(i32)]
+        L.ralm_first_stage_scores.argtypes = [i64, dsp, i32, i32, ctypes.POINTER(i32)]
         L.ralm_build_scan_copy.argtypes = [vp, i64, vp, i32, i64, i64, i32, vp]
         L.ralm_build_scan_copy_l2.argtypes = [vp, i32, i64, vp, i32, i64, i64, i32, vp]
         L.ralm_cache_lookup.argtypes = [vp, vp, i32, i64, vp, i64, vp, dsp, vp, vp, vp, ctypes.c_size_t, vp]
@@ -101,7 +102,7 @@ def lib() -> ctypes.CDLL:
         L.ralm_profile_enable.restype = None
         L.ralm_profile_scan_ms.argtypes = [ctypes.POINTER(ctypes.c_float), ctypes.POINTER(i32)]
         for name in ("ralm_retrieve_topk", "ralm_retrieve_topk_ex", "ralm_retrieve_topk_seq", "ralm_workspace_overflows",
-                     "ralm_workspace_counters", "ralm_workspace_stage_entries", "ralm_scan_routes",
+                     "ralm_workspace_counters", "ralm_workspace_stage_entries", "ralm_scan_routes", "ralm_first_stage_scores",
                      "ralm_build_scan_copy", "ralm_build_scan_copy_l2", "ralm_cache_lookup", "ralm_cache_lookup_all",
                      "ralm_cache_lookup_static",
                      "ralm_cache_lookup_topk", "ralm_lookup_route", "ralm_verify", "ralm_cache_insert", "ralm_knnlm_probs",
@@ -254,6 +255,13 @@ def ralm_scan_routes(Q: int, ds: Datastore, k: int, k_prime: int = 0) -> list:
     arr = (ctypes.c_int32 * RALM_MAX_LADDER_STAGES)()
     _check(lib().ralm_scan_routes(Q, ctypes.byref(ds.desc), k, k_prime, ctypes.byref(n), arr))
     return [SCAN_ROUTES[arr[i]] for i in range(n.value)]
+
+
+def ralm_first_stage_scores(Q: int, ds: Datastore, k: int, k_prime: int = 0) -> bool:
+    """Whether the first ladder stage of ralm_retrieve_topk_ex leaves scores instead of a key per row (host only)."""
+    out = ctypes.c_int32(0)
+    _check(lib().ralm_first_stage_scores(Q, ctypes.byref(ds.desc), k, k_prime, ctypes.byref(out)))
+    return bool(out.value)
 
 
 def ralm_retrieve_topk(queries: torch.Tensor, datastore: torch.Tensor, k: int

@@ -270,8 +270,12 @@ int64_t ladder_stage(const Plan &pl, int64_t tiles, int s, ScanParams &sp)
         sp.tile_skip = 0;                                   // every multiple of the stride
         sp.n_row_tiles = (tiles + stride - 1) / stride;
         sp.admits = sp.n_row_tiles * SCAN_BM;               // everything
+        // the first of several stages leaves scores, of which its select reads few, where k' is small and the rows are enough blocks of 32
+        sp.scores_only = pl.n_stages > 1 && pl.k_prime <= FIRST_KEYS && sp.n_row_tiles * SCAN_BM <= FIRST_ROWS &&
+                         (sp.n_row_tiles - 1) * SCAN_BM >= FIRST_ROWS / 2;
         return sp.admits;
     }
+    sp.scores_only = 0;
     const int64_t m_max = (tiles + stride - 1) / stride - 1;   // multiples m >= 1 with m*stride < tiles
     const int64_t g = pl.stride[s - 1] / stride;               // ... that no earlier stage visited
     sp.tile_skip = (int32_t)g;
@@ -430,9 +434,6 @@ ralm_status retrieve_impl(const float *queries, int64_t Q, const ralm_datastore_
             if (s > 0) expected = pl.k_prime + (expected - pl.k_prime) * rank_before / pl.k_prime;
             // (with CUs reserved the ladder's last steps are by 2 and admit little)
             rank_before = reserve > 0 ? pl.k_prime : early_rank(k, pl.k_prime, pl.stride[s]);
-            // the first of several stages leaves scores, of which its select reads few, where k' is small and the rows are enough blocks of 32
-            sp.scores_only = s == 0 && pl.n_stages > 1 && pl.k_prime <= FIRST_KEYS && sp.n_row_tiles * SCAN_BM <= FIRST_ROWS &&
-                             (sp.n_row_tiles - 1) * SCAN_BM >= FIRST_ROWS / 2;
             st = run_stage(expected, s + 1 == pl.n_stages, rank_before);
             if (st != RALM_OK) return st;
         }
@@ -540,23 +541,48 @@ ralm_status ralm_workspace_stage_entries(const void *workspace, void *stream, in
     return RALM_OK;
 }
 
-ralm_status ralm_scan_routes(int64_t Q, const ralm_datastore_t *ds, int32_t k, int32_t k_prime, int32_t *n_stages, int32_t *routes)
+namespace {
+
+// the plan and the scan launches' common part of a call with these arguments, for the entry points that report on it
+ralm_status report_plan(int64_t Q, const ralm_datastore_t *ds, int32_t k, int32_t k_prime, int reserve, Plan &pl, ScanParams &sp)
 {
-    if (!n_stages || !routes) return fail(RALM_ERR_NULL, "n_stages/routes is NULL");
     if (Q < 1 || Q > MAX_QUERIES) return fail(RALM_ERR_SHAPE, "Q=%lld out of [1, 2^20]", (long long)Q);
     ralm_status st = check_datastore(ds, true);
     if (st != RALM_OK) return st;
-    Plan pl;
-    const int reserve = g_scan_reserve.load(std::memory_order_relaxed);
     st = make_plan(Q, ds, k, k_prime, pl, reserve > 0);
     if (st != RALM_OK) return st;
-    ScanParams sp = scan_params(ds, Q, pl, reserve);
+    sp = scan_params(ds, Q, pl, reserve);
+    return RALM_OK;
+}
+
+}  // namespace
+
+ralm_status ralm_scan_routes(int64_t Q, const ralm_datastore_t *ds, int32_t k, int32_t k_prime, int32_t *n_stages, int32_t *routes)
+{
+    if (!n_stages || !routes) return fail(RALM_ERR_NULL, "n_stages/routes is NULL");
+    Plan pl;
+    ScanParams sp;
+    const int reserve = g_scan_reserve.load(std::memory_order_relaxed);
+    const ralm_status st = report_plan(Q, ds, k, k_prime, reserve, pl, sp);
+    if (st != RALM_OK) return st;
     for (int i = 0; i < RALM_MAX_LADDER_STAGES; ++i) routes[i] = 0;
     for (int i = 0; i < pl.n_stages; ++i) {
         ladder_stage(pl, (ds->N + SCAN_BM - 1) / SCAN_BM, i, sp);
         if (sp.n_row_tiles > 0) routes[i] = scan_route(sp, scan_cus(reserve));
     }
     *n_stages = pl.n_stages;
+    return RALM_OK;
+}
+
+ralm_status ralm_first_stage_scores(int64_t Q, const ralm_datastore_t *ds, int32_t k, int32_t k_prime, int32_t *scores_only)
+{
+    if (!scores_only) return fail(RALM_ERR_NULL, "scores_only is NULL");
+    Plan pl;
+    ScanParams sp;
+    const ralm_status st = report_plan(Q, ds, k, k_prime, g_scan_reserve.load(std::memory_order_relaxed), pl, sp);
+    if (st != RALM_OK) return st;
+    ladder_stage(pl, (ds->N + SCAN_BM - 1) / SCAN_BM, 0, sp);
+    *scores_only = sp.scores_only;
     return RALM_OK;
 }
 

@@ -223,6 +223,22 @@ def test_scan_routes_with_compute_units_reserved(L):
         b.ralm_scan_reserve_cus(0)
 
 
+# (k = 10 and 32 keep 64 candidates, 33 keeps 128)
+@pytest.mark.parametrize("Q,k,N,k_prime,want", [
+    (81, 10, 1_000_000, 0, True), (1, 32, 100_000, 0, True), (2341, 20, 4_000_000, 0, True), (600, 10, 16_385, 0, True),
+    (81, 33, 1_000_000, 0, False), (81, 10, 1_000_000, 65, False), (81, 10, 1_000_000, 64, True), (8, 10, 16_384, 0, False),
+])
+def test_first_stage_scores(L, Q, k, N, k_prime, want):
+    """Up to 64 candidates and more than one stage."""
+    from paper_2401_14021_amd import binding as b
+    ds = _ds(b, N=N, scan_dtype=1)
+    out = ctypes.c_int32(-1)
+    assert L.ralm_first_stage_scores(Q, ctypes.byref(ds), k, k_prime, ctypes.byref(out)) == 0
+    assert out.value == int(want)
+    assert L.ralm_first_stage_scores(Q, ctypes.byref(ds), k, k_prime, None) == 1
+    assert L.ralm_first_stage_scores(0, ctypes.byref(ds), k, k_prime, ctypes.byref(out)) == 2
+
+
 def _lookup(L, R, C, d, dtype=0, metric=0, Qt=None, k=0):
     from paper_2401_14021_amd import binding as b
     ds = _ds(b, d=d, exact_dtype=dtype, scan=None)
