@@ -132,15 +132,15 @@ struct SelectShared {
 // keys are distinct) in out[0, rank), in any order.  All NT threads of a workgroup; out is in
 // LDS and complete when the function returns; c is not read after that.
 // early: the wanted key, or if 0 < early_rank < rank a better one that at least early_rank of the list reach, as few as the bins tell apart.
-// REGS: keys per thread that are held in registers.
-template <int NT, int REGS = SEL_REGS>
+// REGS: keys per thread that are held in registers.  FITS: n <= REGS * NT, so that the form that walks a longer list in memory is not compiled.
+template <int NT, int REGS = SEL_REGS, bool FITS = false>
 __device__ __forceinline__ u64 select_best(const u64 *__restrict__ c, uint32_t n, uint32_t rank, SelectShared<NT> &sh, u64 *out,
                                            uint32_t early_rank, u64 &early)
 {
     constexpr int SEL_BINS = 2 * NT, SEL_WAVES = NT / 64;
     const bool want_early = early_rank > 0 && early_rank < rank;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const bool in_regs = n <= (uint32_t)(REGS * NT);
+    const bool in_regs = FITS || n <= (uint32_t)(REGS * NT);
     u64 reg[REGS];
     if (in_regs) {
 #pragma unroll
@@ -335,6 +335,7 @@ __global__ __launch_bounds__(NT) void select_kernel(u64 *__restrict__ cand, uint
     u64 early, kth;
     // A short list: less code to fetch, for a kernel that is over in a few microseconds.  81 lists of about 200 keys 7.6 us in the general
     // form, 7.0 by one wave in registers (bracketing the score with ballots), 5.7.
+    // (Not FITS, here and in the re-score: 2200 queries, k' = 128 and 256, over 50 000 x 768 took 543 and 703 us a call so, 522 and 682 as it is.)
     if (n <= (uint32_t)(2 * NT)) kth = select_best<NT, 2>(c, n, (uint32_t)k_prime, sh, out, (uint32_t)tau_rank, early);
     else kth = select_best<NT>(c, n, (uint32_t)k_prime, sh, out, (uint32_t)tau_rank, early);
     for (int i = tid; i < k_prime; i += NT) c[i] = out[i];
@@ -372,7 +373,7 @@ __global__ __launch_bounds__(SF_THREADS) void select_first_kernel(u64 *__restric
     if (tid < nb) s_key[tid] = (u64)best << 32 | (uint32_t)(0x7fffffff - tid);   // distinct, and the first of equal ones the better
     __syncthreads();
     u64 early;
-    select_best<SF_THREADS, 1>(s_key, (uint32_t)nb, (uint32_t)k_prime, sh, s_out, 0, early);
+    select_best<SF_THREADS, 1, true>(s_key, (uint32_t)nb, (uint32_t)k_prime, sh, s_out, 0, early);
     float f[PER];
     int32_t at[PER];
 #pragma unroll
@@ -388,7 +389,7 @@ __global__ __launch_bounds__(SF_THREADS) void select_first_kernel(u64 *__restric
         if (i * SF_THREADS + tid < k_prime * 32) s_key[i * SF_THREADS + tid] = (uint32_t)at[i] < n ? make_key(f[i], (int32_t)row) : 0ull;
     }
     __syncthreads();
-    const u64 kth = select_best<SF_THREADS, PER>(s_key, (uint32_t)k_prime * 32, (uint32_t)k_prime, sh, s_out, (uint32_t)tau_rank, early);
+    const u64 kth = select_best<SF_THREADS, PER, true>(s_key, (uint32_t)k_prime * 32, (uint32_t)k_prime, sh, s_out, (uint32_t)tau_rank, early);
     if (tid < k_prime) c[tid] = s_out[tid];
     early = with_margin<SF_THREADS>(early, kth, s_out, k, k_prime, apart, sh);
     if (tid == 0) {
