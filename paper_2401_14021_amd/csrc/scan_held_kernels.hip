@@ -437,7 +437,9 @@ bool scan_held_takes(const ScanParams &p, int n_cu)
     // A workgroup loads 128 TN queries before its first row: at least 8 tiles each.  (On the safe side for rows that are no whole lines:
     // 120 queries over 400 000 x 392, whose middle stage has 7.8 tiles for each, 128, 117.)
     if (n_tiles < 64 * streams) return false;
-    // Admitted scores interrupt a lone wave.  us per launch by the scores expected per tile of 32 rows: 26: 120, 159; 18: 61, 72; 10 (81
+    // Admitted scores interrupt a lone wave.  p.admits is what the k'-th best of the rows scanned so far would admit: the figures are of launches
+    // that scanned with that key.  Stages scan with a better one now and admit about half as many where the rows' order allows it, so the lines are
+    // on the safe side.  us per launch by such scores per tile of 32 rows: 26: 120, 159; 18: 61, 72; 10 (81
     // queries): 42, 44; 5.7: 578, 565; 4.7: 476, 516; 3.3 (100 queries): 235, 207; 2.3: 337, 294; 1.6: 1357, 1183; 0.8: 1968, 1870.
     // Rows that are no whole lines, in corpus order: 11 a tile (90 queries over 777001 x 392, the first of two such stages in tiles or
     // not) 244, 214 us a round.  There and in stores sorted by cluster the lines are on the safe side: 200 queries whose middle stage is

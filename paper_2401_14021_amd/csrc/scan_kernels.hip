@@ -865,6 +865,10 @@ int scan_route(const ScanParams &p, int n_cu)
     // scores of a tile are counted and stored together, which takes about 20 us a tile of 256 queries whatever their number.  Parked they take
     // time by their number: rounds of 144 neighbour queries over 2M x 1024 (k' = 1024) 1410 us with the line at 2, 1373 at 3, 1370 at
     // 8, 1375 at 16, of 256 over 10M x 1024 (k' = 2048) 6044 at 2, 5988 at 5, and about 90 us more with no counted launches.
+    // Rows whose admitted scores come in bursts, whole calls that the line divides, with it at 2 over with it at 8 (mean, and the one that is best
+    // at 2): up to 256 queries over stores in corpus order 1.067 (128 calls, 0.999), sorted by cluster 1.044 (118, 0.954: 256 queries, k' =
+    // 256, over 1M x 512 417, 437 us), of rows that come 40 to 150 times 1.027 (32, 1.000); more queries in corpus order 1.018 (31, 0.994), sorted by
+    // cluster 0.983 (28, 0.939: 2200, k' = 256, over 130 000 x 384 fp32 943, 1004).  200 queries, k' = 128, over 2M x 768 in corpus order 814, 775.
     if (p.admits >= COUNT_MIN * p.n_row_tiles) return RALM_SCAN_COUNTED;
     return scan_held_takes(p, n_cu) ? RALM_SCAN_HELD : RALM_SCAN_PARKED;
 }
